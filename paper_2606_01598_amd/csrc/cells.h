@@ -4,7 +4,8 @@
 // kernel visits, for each atom, the 3 x 3 x 3 neighbouring cells, or every cell
 // along an axis with fewer than three, so that with the cutoff below half the
 // smallest perpendicular width every pair within the cutoff is seen once under the
-// minimum image.
+// minimum image.  The sort leaves the positions themselves in cell order
+// (CellList::sp), so the candidates of a row of cells are consecutive 16-byte loads.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,6 +29,7 @@ struct CellList {
   int* cellof = nullptr;            // [max_atoms]
   int* slot = nullptr;              // [max_atoms]
   int* sorted = nullptr;            // [max_atoms] atom indices grouped by cell
+  float4* sp = nullptr;             // [max_atoms] the same order: position, atom (bits)
 };
 
 __device__ __forceinline__ void frac(const CellGrid& g, float x, float y, float z, float& s0,
@@ -49,21 +51,43 @@ __device__ __forceinline__ void cell_of(const CellGrid& g, float x, float y, flo
   }
 }
 
-// Minimum-image displacement through fractional coordinates.
+// Minimum-image displacement: the nearest whole lattice vector is found through
+// fractional coordinates and taken off the Cartesian difference itself, which keeps
+// the difference exact for pairs of the same image (going back from fractional
+// coordinates rounds at the cell's size: 3e-6 Angstrom in a 50 Angstrom box).
 __device__ __forceinline__ float3 min_image(const CellGrid& g, float dx, float dy, float dz) {
   float f0, f1, f2;
   frac(g, dx, dy, dz, f0, f1, f2);
-  f0 -= rintf(f0);
-  f1 -= rintf(f1);
-  f2 -= rintf(f2);
-  return make_float3(f0 * g.C[0] + f1 * g.C[3] + f2 * g.C[6],
-                     f0 * g.C[1] + f1 * g.C[4] + f2 * g.C[7],
-                     f0 * g.C[2] + f1 * g.C[5] + f2 * g.C[8]);
+  const float n0 = -rintf(f0), n1 = -rintf(f1), n2 = -rintf(f2);
+  return make_float3(fmaf(n0, g.C[0], fmaf(n1, g.C[3], fmaf(n2, g.C[6], dx))),
+                     fmaf(n0, g.C[1], fmaf(n1, g.C[4], fmaf(n2, g.C[7], dy))),
+                     fmaf(n0, g.C[2], fmaf(n1, g.C[5], fmaf(n2, g.C[8], dz))));
 }
 
 // Neighbour cell number `o` (0 .. min(nc, 3) - 1) along an axis of a cell c.
 __device__ __forceinline__ int neighbour_cell(int c, int o, int nc) {
   return (nc >= 3) ? (c + o - 1 + nc) % nc : o;
+}
+
+// The runs of consecutive cell-ordered atoms that hold the neighbours of cell c: run e
+// (0 .. 17) is segment e % 2 of row (ox, oy) = (e / 6, e / 2 % 3); a row's z cells
+// c_z - 1 .. c_z + 1 are one run, or two where they wrap.  Returns an empty run where
+// there is none (fewer than three cells along an axis: each cell once).
+constexpr int kCellRuns = 18;
+__device__ __forceinline__ int2 cell_run(const CellGrid& g, const int* start, const int (&c)[3],
+                                         int e) {
+  const int ox = e / 6, oy = (e >> 1) % 3, seg = e & 1;
+  if (e >= kCellRuns || ox >= min(g.nc[0], 3) || oy >= min(g.nc[1], 3)) return make_int2(0, 0);
+  const int row = (neighbour_cell(c[0], ox, g.nc[0]) * g.nc[1] + neighbour_cell(c[1], oy, g.nc[1])) *
+                  g.nc[2];
+  const int last = g.nc[2] - 1;
+  int z0 = max(c[2] - 1, 0), z1 = min(c[2] + 1, last);
+  if (g.nc[2] <= 3) { z0 = 0; z1 = last; }
+  if (seg) {
+    if (g.nc[2] <= 3 || (c[2] != 0 && c[2] != last)) return make_int2(0, 0);
+    z0 = z1 = c[2] == 0 ? last : 0;
+  }
+  return make_int2(start[row + z0], start[row + z1 + 1]);
 }
 
 __global__ void k_cell_clear(int* count, int ncell) {
@@ -103,10 +127,77 @@ __global__ void __launch_bounds__(1024) k_cell_scan(const int* count, int* start
   if (t == 1023) start[ncell] = part[1023];
 }
 
-__global__ void k_cell_fill(int n, const int* cellof, const int* slot, const int* start,
-                            int* sorted) {
+__global__ void k_cell_fill(int n, const float* pos, const int* cellof, const int* slot,
+                            const int* start, int* sorted, float4* sp) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) sorted[start[cellof[i]] + slot[i]] = i;
+  if (i >= n) return;
+  const int k = start[cellof[i]] + slot[i];
+  sorted[k] = i;
+  sp[k] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+}
+
+// The whole counting sort in one workgroup, the counters in LDS: up to kSortAtoms atoms
+// and kSortCells cells.  At 4096 atoms the four kernels above take 13 us and four
+// launches, this one 7 us and one; past 8 atoms a thread the one CU is the
+// bound and the four kernels win.
+constexpr int kSortAtoms = 8192, kSortCells = 12288;
+__global__ void __launch_bounds__(1024) k_cell_sort(int n, const float* pos, CellGrid g,
+                                                    int* start, int* sorted, float4* sp) {
+  __shared__ int s_count[kSortCells];
+  __shared__ int s_wave[16];
+  constexpr int U = kSortAtoms / 1024;
+  const int t = threadIdx.x;
+  for (int c = t; c < g.ncell; c += 1024) s_count[c] = 0;
+  float x[U], y[U], z[U];
+  int cell[U], slot[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = t + u * 1024;
+    if (i < n) { x[u] = pos[3 * i]; y[u] = pos[3 * i + 1]; z[u] = pos[3 * i + 2]; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (t + u * 1024 < n) {
+      int c[3];
+      cell_of(g, x[u], y[u], z[u], c);
+      cell[u] = (c[0] * g.nc[1] + c[1]) * g.nc[2] + c[2];
+      slot[u] = atomicAdd(&s_count[cell[u]], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive scan: a segment of cells per thread, wavefront prefix sums, their totals
+  const int seg = (g.ncell + 1023) / 1024;
+  const int c0 = min(t * seg, g.ncell), c1 = min(c0 + seg, g.ncell);
+  int acc = 0;
+  for (int c = c0; c < c1; ++c) acc += s_count[c];
+  int incl = acc;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if ((t & 63) >= o) incl += v;
+  }
+  if ((t & 63) == 63) s_wave[t >> 6] = incl;
+  __syncthreads();
+  int run = incl - acc;
+  for (int w = 0; w < (t >> 6); ++w) run += s_wave[w];
+  for (int c = c0; c < c1; ++c) {
+    const int v = s_count[c];
+    s_count[c] = run;
+    start[c] = run;
+    run += v;
+  }
+  if (t == 1023) start[g.ncell] = run;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = t + u * 1024;
+    if (i < n) {
+      const int k = s_count[cell[u]] + slot[u];
+      sorted[k] = i;
+      sp[k] = make_float4(x[u], y[u], z[u], __int_as_float(i));
+    }
+  }
 }
 
 inline int cell_blocks(int m, int t) { return m > 0 ? (m + t - 1) / t : 1; }
@@ -147,20 +238,26 @@ inline int setup_cells(CellList& cl, const double* C, double rc, int max_atoms) 
   ok(hipMalloc(&cl.cellof, sizeof(int) * m));
   ok(hipMalloc(&cl.slot, sizeof(int) * m));
   ok(hipMalloc(&cl.sorted, sizeof(int) * m));
+  ok(hipMalloc(&cl.sp, sizeof(float4) * m));
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? PME_ENOMEM : PME_EHIP;
   return PME_OK;
 }
 
 inline void free_cells(CellList& cl) {
-  void* ptrs[] = {cl.count, cl.start, cl.cellof, cl.slot, cl.sorted};
+  void* ptrs[] = {cl.count, cl.start, cl.cellof, cl.slot, cl.sorted, cl.sp};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   cl = CellList();
 }
 
-// Cell list of the current positions (4 launches on `s`).
+// Cell list of the current positions (one launch on `s`, or four for many atoms).
 inline hipError_t build_cells(const CellList& cl, hipStream_t s, int n, const float* pos) {
   const CellGrid& g = cl.g;
+  if (n <= kSortAtoms && g.ncell <= kSortCells) {
+    hipLaunchKernelGGL(k_cell_sort, dim3(1), dim3(1024), 0, s, n, pos, g, cl.start, cl.sorted,
+                       cl.sp);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_cell_clear, dim3(cell_blocks(g.ncell, 256)), dim3(256), 0, s, cl.count,
                      g.ncell);
   if (n > 0)
@@ -168,8 +265,8 @@ inline hipError_t build_cells(const CellList& cl, hipStream_t s, int n, const fl
                        cl.count, cl.cellof, cl.slot);
   hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(1024), 0, s, cl.count, cl.start, g.ncell);
   if (n > 0)
-    hipLaunchKernelGGL(k_cell_fill, dim3(cell_blocks(n, 256)), dim3(256), 0, s, n, cl.cellof,
-                       cl.slot, cl.start, cl.sorted);
+    hipLaunchKernelGGL(k_cell_fill, dim3(cell_blocks(n, 256)), dim3(256), 0, s, n, pos,
+                       cl.cellof, cl.slot, cl.start, cl.sorted, cl.sp);
   return hipGetLastError();
 }
 

@@ -3,8 +3,9 @@
 // matrix-vector product is the PME Hessian (pme_backward) plus the real-space
 // dipole tensor.  The model and its conventions are documented in pol.h.
 //
-// Pair kernels give 16 lanes to an atom; the lanes split the atoms of the
-// neighbouring cells and combine their partial sums with wavefront shuffles.
+// Pair kernels give a wavefront to an atom: the lanes test the atoms of the
+// neighbouring cells, compact the pairs within the cutoff into LDS, evaluate them 64 at
+// a time and combine their partial sums with wavefront shuffles.
 // The screened functions follow the recursion of the explicit Ewald sum,
 //     B0 = erfc(a r)/r,  B_l = [(2l-1) B_{l-1} + (2a^2)^l exp(-a^2 r^2)/(a sqrt(pi))] / r^2,
 // and the damped B_l^t keep grad B_l^t = -R B_{l+1}^t, so every gradient has the
@@ -21,8 +22,8 @@
 
 namespace {
 
-constexpr int kLanes = 16;          // lanes per atom in the pair kernels
 constexpr int kPairThreads = 256;
+constexpr int kPairAtoms = kPairThreads / 64;   // one wavefront per atom
 
 enum PairMode { kEnergyGrad = 0, kMuGrad = 1, kMixed = 2, kHvp = 3 };
 
@@ -37,7 +38,7 @@ struct PairArgs {
   const float* vmu;
   CellGrid g;
   const int* start;
-  const int* sorted;
+  const float4* sp;
   float alpha;
   float rc2;
   float A;
@@ -53,125 +54,151 @@ __device__ __forceinline__ float3 ld3(const float* p, int i) {
 }
 __device__ __forceinline__ float dot3(float3 a, float3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 
-__device__ __forceinline__ float lane_sum(float v) {
+__device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
-  for (int o = kLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kLanes);
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
 
+// LDS written by some lanes of a wavefront, read by others of the same one: LDS
+// operations of a wavefront stay in order, only the compiler has to keep them so.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Bound by vector issue: a pair within the cutoff costs about 150 instructions (erfc,
+// two exponentials, the screened functions), a candidate about 35, and at a 10 Angstrom
+// cutoff only one candidate in seven is within it.  So candidates (consecutive loads in
+// cell order) are only tested, and the pairs that pass are queued until 64 lanes of work
+// are there.  Evaluating each pair where it is found, 16 lanes an atom, ran the long
+// body at an eighth of its lanes on one wavefront per SIMD: 67 to 82 us at 4096 ions
+// against 16 to 22 us.
 template <int MODE>
 __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a) {
-  __shared__ double red[kPairThreads / kLanes];
-  const int lane = threadIdx.x % kLanes;
-  const int slot = threadIdx.x / kLanes;
-  const int i = blockIdx.x * (kPairThreads / kLanes) + slot;
-  const bool live = i < a.n;
-  const int ii = live ? i : 0;
-  const float3 pi = ld3(a.pos, ii);
-  const float qi = a.q ? a.q[ii] : 0.0f;
-  const float3 mi = ld3(a.mu, ii);
-  const float ai = a.pol[ii];
+  __shared__ double red[kPairAtoms];
+  __shared__ float4 s_pair[kPairAtoms][128];   // R, neighbour (bits)
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  // wavefronts take atoms in cell order, so that those of a workgroup share candidates
+  const int at = blockIdx.x * kPairAtoms + wave;
+  const bool live = at < a.n;
+  const float4 pi = a.sp[live ? at : 0];
+  const int i = __builtin_amdgcn_readfirstlane(__float_as_int(pi.w));
+  const float qi = a.q ? a.q[i] : 0.0f;
+  const float3 mi = ld3(a.mu, i);
+  const float ai = a.pol[i];
   const float3 vi =
-      (MODE == kMixed || MODE == kHvp) ? ld3(a.vpos, ii) : make_float3(0.f, 0.f, 0.f);
-  int c[3], no[3];
-  cell_of(a.g, pi.x, pi.y, pi.z, c);
-#pragma unroll
-  for (int d = 0; d < 3; ++d) no[d] = a.g.nc[d] < 3 ? a.g.nc[d] : 3;
+      (MODE == kMixed || MODE == kHvp) ? ld3(a.vpos, i) : make_float3(0.f, 0.f, 0.f);
   const float sqpi = 1.7724538509055159f;
   const float t2 = 2.0f * a.alpha * a.alpha;
   float e = 0.f, gx = 0.f, gy = 0.f, gz = 0.f, mx = 0.f, my = 0.f, mz = 0.f, gq = 0.f;
+  float4* list = s_pair[wave];
+
+  auto pair = [&](const float4 ent) {
+    const float3 R = make_float3(ent.x, ent.y, ent.z);
+    const int j = __float_as_int(ent.w);
+    const float r2 = dot3(R, R);
+    const float r = sqrtf(r2), ir = 1.0f / r, ir2 = ir * ir;
+    const float ar = a.alpha * r;
+    const float gexp = expf(-ar * ar) / (a.alpha * sqpi);
+    const float B0 = erfcf(ar) * ir;
+    const float B1 = (B0 + t2 * gexp) * ir2;
+    const float B2 = (3.0f * B1 + t2 * t2 * gexp) * ir2;
+    const float B3 = (5.0f * B2 + t2 * t2 * t2 * gexp) * ir2;
+    float B1t = B1, B2t = B2, B3t = B3;
+    const float aj = a.pol[j];
+    const float pp = ai * aj;
+    if (a.A > 0.0f && pp > 0.0f) {
+      const float au3 = a.A * r2 * r * rsqrtf(pp);
+      const float ex = expf(-au3);
+      const float ir3 = ir2 * ir;
+      B1t = B1 - ex * ir3;
+      B2t = B2 - 3.0f * (1.0f + au3) * ex * ir3 * ir2;
+      B3t = B3 - 15.0f * (1.0f + au3 + 0.6f * au3 * au3) * ex * ir3 * ir2 * ir2;
+    }
+    const float qj = a.q ? a.q[j] : 0.0f;
+    const float3 mj = ld3(a.mu, j);
+    const float mjr = dot3(mj, R);
+    if (MODE == kHvp || MODE == kMixed) {
+      // r column: d/dR of dE/dmu_i (and dE/dq_i) along w = v_i - v_j (grad B0 = -R B1
+      // undamped)
+      const float3 vj = ld3(a.vpos, j);
+      const float3 w = make_float3(vi.x - vj.x, vi.y - vj.y, vi.z - vj.z);
+      const float rw = dot3(R, w), mjw = dot3(mj, w);
+      const float cw = -qj * B1t - mjr * B2t;
+      float cR = qj * rw * B2t - mjw * B2t + rw * mjr * B3t;
+      const float cm = -rw * B2t;
+      float3 vmj = make_float3(0.f, 0.f, 0.f);
+      if (MODE == kHvp) {
+        // (q, mu) columns: the bilinear gradients with charges vq and dipoles vmu
+        const float vqj = a.vq ? a.vq[j] : 0.0f;
+        vmj = ld3(a.vmu, j);
+        const float vmjr = dot3(vmj, R);
+        gq += -qj * B1 * rw + B1t * mjw - mjr * B2t * rw + vqj * B0 + vmjr * B1t;
+        cR += -vqj * B1t - vmjr * B2t;
+      }
+      mx += cw * w.x + cR * R.x + cm * mj.x + B1t * vmj.x;
+      my += cw * w.y + cR * R.y + cm * mj.y + B1t * vmj.y;
+      mz += cw * w.z + cR * R.z + cm * mj.z + B1t * vmj.z;
+      return;
+    }
+    // dE/dmu_i
+    const float cRm = -qj * B1t - mjr * B2t;
+    mx += cRm * R.x + B1t * mj.x;
+    my += cRm * R.y + B1t * mj.y;
+    mz += cRm * R.z + B1t * mj.z;
+    if (MODE == kEnergyGrad) {
+      gq += qj * B0 + mjr * B1t;
+      const float mir = dot3(mi, R), mm = dot3(mi, mj);
+      const float cross = qi * mjr - qj * mir;
+      e += 0.5f * (qi * qj * B0 + cross * B1t + mm * B1t - mir * mjr * B2t);
+      const float cR = -qi * qj * B1 - cross * B2t - mm * B2t + mir * mjr * B3t;
+      gx += cR * R.x + B1t * (qi * mj.x - qj * mi.x) - B2t * (mi.x * mjr + mj.x * mir);
+      gy += cR * R.y + B1t * (qi * mj.y - qj * mi.y) - B2t * (mi.y * mjr + mj.y * mir);
+      gz += cR * R.z + B1t * (qi * mj.z - qj * mi.z) - B2t * (mi.z * mjr + mj.z * mir);
+    }
+  };
+
   if (live) {
-    for (int ox = 0; ox < no[0]; ++ox)
-      for (int oy = 0; oy < no[1]; ++oy)
-        for (int oz = 0; oz < no[2]; ++oz) {
-          const int cx = neighbour_cell(c[0], ox, a.g.nc[0]);
-          const int cy = neighbour_cell(c[1], oy, a.g.nc[1]);
-          const int cz = neighbour_cell(c[2], oz, a.g.nc[2]);
-          const int cell = (cx * a.g.nc[1] + cy) * a.g.nc[2] + cz;
-          const int b0 = a.start[cell], b1 = a.start[cell + 1];
-          for (int k = b0 + lane; k < b1; k += kLanes) {
-            const int j = a.sorted[k];
-            if (j == i) continue;
-            const float3 pj = ld3(a.pos, j);
-            const float3 R = min_image(a.g, pi.x - pj.x, pi.y - pj.y, pi.z - pj.z);
-            const float r2 = dot3(R, R);
-            if (r2 >= a.rc2 || r2 <= 0.0f) continue;
-            const float r = sqrtf(r2), ir = 1.0f / r, ir2 = ir * ir;
-            const float ar = a.alpha * r;
-            const float gexp = expf(-ar * ar) / (a.alpha * sqpi);
-            const float B0 = erfcf(ar) * ir;
-            const float B1 = (B0 + t2 * gexp) * ir2;
-            const float B2 = (3.0f * B1 + t2 * t2 * gexp) * ir2;
-            const float B3 = (5.0f * B2 + t2 * t2 * t2 * gexp) * ir2;
-            float B1t = B1, B2t = B2, B3t = B3;
-            const float aj = a.pol[j];
-            const float pp = ai * aj;
-            if (a.A > 0.0f && pp > 0.0f) {
-              const float au3 = a.A * r2 * r * rsqrtf(pp);
-              const float ex = expf(-au3);
-              const float ir3 = ir2 * ir;
-              B1t = B1 - ex * ir3;
-              B2t = B2 - 3.0f * (1.0f + au3) * ex * ir3 * ir2;
-              B3t = B3 - 15.0f * (1.0f + au3 + 0.6f * au3 * au3) * ex * ir3 * ir2 * ir2;
-            }
-            const float qj = a.q ? a.q[j] : 0.0f;
-            const float3 mj = ld3(a.mu, j);
-            const float mjr = dot3(mj, R);
-            if (MODE == kHvp) {
-              // r column: d/dR of dE/dq_i and dE/dmu_i along w = v_i - v_j
-              // (grad B0 = -R B1 undamped); (q, mu) columns: the bilinear
-              // gradients with charges vq and dipoles vmu
-              const float3 vj = ld3(a.vpos, j);
-              const float3 w = make_float3(vi.x - vj.x, vi.y - vj.y, vi.z - vj.z);
-              const float rw = dot3(R, w), mjw = dot3(mj, w);
-              const float vqj = a.vq ? a.vq[j] : 0.0f;
-              const float3 vmj = ld3(a.vmu, j);
-              const float vmjr = dot3(vmj, R);
-              gq += -qj * B1 * rw + B1t * mjw - mjr * B2t * rw + vqj * B0 + vmjr * B1t;
-              const float cw = -qj * B1t - mjr * B2t;
-              const float cR = qj * rw * B2t - mjw * B2t + rw * mjr * B3t - vqj * B1t -
-                               vmjr * B2t;
-              const float cm = -rw * B2t;
-              mx += cw * w.x + cR * R.x + cm * mj.x + B1t * vmj.x;
-              my += cw * w.y + cR * R.y + cm * mj.y + B1t * vmj.y;
-              mz += cw * w.z + cR * R.z + cm * mj.z + B1t * vmj.z;
-              continue;
-            }
-            if (MODE == kMixed) {
-              const float3 vj = ld3(a.vpos, j);
-              const float3 w = make_float3(vi.x - vj.x, vi.y - vj.y, vi.z - vj.z);
-              const float rw = dot3(R, w), mjw = dot3(mj, w);
-              const float cw = -qj * B1t - mjr * B2t;
-              const float cR = qj * rw * B2t - mjw * B2t + rw * mjr * B3t;
-              const float cm = -rw * B2t;
-              mx += cw * w.x + cR * R.x + cm * mj.x;
-              my += cw * w.y + cR * R.y + cm * mj.y;
-              mz += cw * w.z + cR * R.z + cm * mj.z;
-              continue;
-            }
-            // dE/dmu_i
-            const float cRm = -qj * B1t - mjr * B2t;
-            mx += cRm * R.x + B1t * mj.x;
-            my += cRm * R.y + B1t * mj.y;
-            mz += cRm * R.z + B1t * mj.z;
-            if (MODE == kEnergyGrad) {
-              gq += qj * B0 + mjr * B1t;
-              const float mir = dot3(mi, R), mm = dot3(mi, mj);
-              const float cross = qi * mjr - qj * mir;
-              e += 0.5f * (qi * qj * B0 + cross * B1t + mm * B1t - mir * mjr * B2t);
-              const float cR = -qi * qj * B1 - cross * B2t - mm * B2t + mir * mjr * B3t;
-              gx += cR * R.x + B1t * (qi * mj.x - qj * mi.x) - B2t * (mi.x * mjr + mj.x * mir);
-              gy += cR * R.y + B1t * (qi * mj.y - qj * mi.y) - B2t * (mi.y * mjr + mj.y * mir);
-              gz += cR * R.z + B1t * (qi * mj.z - qj * mi.z) - B2t * (mi.z * mjr + mj.z * mir);
-            }
-          }
+    int c[3];
+    cell_of(a.g, pi.x, pi.y, pi.z, c);
+    const int2 runs = cell_run(a.g, a.start, c, lane);   // lane e holds run e
+    int cnt = 0;
+    for (int s = 0; s < kCellRuns; ++s) {
+      const int k0 = __builtin_amdgcn_readlane(runs.x, s);
+      const int k1 = __builtin_amdgcn_readlane(runs.y, s);
+      for (int b = k0; b < k1; b += 64) {
+        const int k = b + lane;
+        const float4 pj = a.sp[min(k, k1 - 1)];
+        const float3 R = min_image(a.g, pi.x - pj.x, pi.y - pj.y, pi.z - pj.z);
+        const float r2 = dot3(R, R);
+        const bool hit = k < k1 && r2 < a.rc2 && r2 > 0.0f && __float_as_int(pj.w) != i;
+        const unsigned long long m = __ballot(hit);
+        const int below = int(__builtin_amdgcn_mbcnt_hi(
+            uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
+        if (hit) list[cnt + below] = make_float4(R.x, R.y, R.z, pj.w);
+        cnt += __popcll(m);
+        if (cnt >= 64) {   // at most 63 were left, so the list holds at most 127
+          wave_lds_fence();
+          const float4 now = list[lane];
+          const float4 rest = list[64 + lane];
+          wave_lds_fence();
+          cnt -= 64;
+          if (lane < cnt) list[lane] = rest;
+          pair(now);
         }
+      }
+    }
+    wave_lds_fence();
+    if (lane < cnt) pair(list[lane]);
   }
-  mx = lane_sum(mx); my = lane_sum(my); mz = lane_sum(mz);
-  if (MODE == kEnergyGrad || MODE == kHvp) gq = lane_sum(gq);
+  mx = wave_sum(mx); my = wave_sum(my); mz = wave_sum(mz);
+  if (MODE == kEnergyGrad || MODE == kHvp) gq = wave_sum(gq);
   if (MODE == kEnergyGrad) {
-    e = lane_sum(e);
-    gx = lane_sum(gx); gy = lane_sum(gy); gz = lane_sum(gz);
+    e = wave_sum(e);
+    gx = wave_sum(gx); gy = wave_sum(gy); gz = wave_sum(gz);
   }
   if (live && lane == 0) {
     if (a.o_mu) {
@@ -187,11 +214,11 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a) {
     }
   }
   if (MODE == kEnergyGrad && a.epart) {
-    if (lane == 0) red[slot] = live ? double(e) : 0.0;
+    if (lane == 0) red[wave] = live ? double(e) : 0.0;
     __syncthreads();
     if (threadIdx.x == 0) {
       double sum = 0.0;
-      for (int k = 0; k < kPairThreads / kLanes; ++k) sum += red[k];
+      for (int k = 0; k < kPairAtoms; ++k) sum += red[k];
       a.epart[blockIdx.x] = sum;
     }
   }
@@ -355,7 +382,7 @@ PairArgs pair_args(const pol_plan_s* pl, int n, const float* pos, const float* q
   a.n = n; a.pos = pos; a.q = q; a.mu = mu; a.pol = pol;
   a.vpos = nullptr; a.vq = nullptr; a.vmu = nullptr;
   a.g = pl->cells.g;
-  a.start = pl->cells.start; a.sorted = pl->cells.sorted;
+  a.start = pl->cells.start; a.sp = pl->cells.sp;
   a.alpha = float(pl->desc.alpha);
   a.rc2 = float(pl->desc.cutoff * pl->desc.cutoff);
   a.A = float(pl->desc.thole_a);
@@ -364,13 +391,11 @@ PairArgs pair_args(const pol_plan_s* pl, int n, const float* pos, const float* q
   return a;
 }
 
-int pair_blocks(int n) { return blocks_for(n, kPairThreads / kLanes); }
+int pair_blocks(int n) { return blocks_for(n, kPairAtoms); }
 
-// dE_real/dmu only (dipole field of mu and q)
+// dE_real/dmu only (dipole field of mu and q), on the cell list of these positions
 hipError_t real_mu_grad(pol_plan_s* pl, hipStream_t s, int n, const float* pos, const float* q,
                         const float* mu, const float* pol, float* out) {
-  hipError_t e = build_cells(pl->cells, s, n, pos);
-  if (e != hipSuccess) return e;
   PairArgs a = pair_args(pl, n, pos, q, mu, pol);
   a.o_mu = out;
   hipLaunchKernelGGL(k_pair<kMuGrad>, dim3(pair_blocks(n)), dim3(kPairThreads), 0, s, a);
@@ -548,6 +573,8 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
   if (iters) *iters = 0;
   if (resid) *resid = 0.0;
   if (n == 0) return PME_OK;
+  // the positions do not move during the solve: one cell list serves every product
+  if ((e = build_cells(plan->cells, s, n, pos)) != hipSuccess) return pol_hip_fail(e);
   // A v = (pf / a) v + H_pme v + H_real v
   auto matvec = [&](const float* v, float* out) -> int {
     int rr = pme_backward(pme, stream, n, pos, q, nullptr, box, nullptr, nullptr, v, nullptr,
