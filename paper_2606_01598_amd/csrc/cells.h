@@ -28,8 +28,7 @@ struct CellList {
   int* start = nullptr;             // [ncell + 1]
   int* cellof = nullptr;            // [max_atoms]
   int* slot = nullptr;              // [max_atoms]
-  int* sorted = nullptr;            // [max_atoms] atom indices grouped by cell
-  float4* sp = nullptr;             // [max_atoms] the same order: position, atom (bits)
+  float4* sp = nullptr;             // [max_atoms] atoms grouped by cell: position, atom (bits)
 };
 
 __device__ __forceinline__ void frac(const CellGrid& g, float x, float y, float z, float& s0,
@@ -90,6 +89,85 @@ __device__ __forceinline__ int2 cell_run(const CellGrid& g, const int* start, co
   return make_int2(start[row + z0], start[row + z1 + 1]);
 }
 
+// Sum over a wavefront; every lane gets it.
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// LDS written by some lanes of a wavefront, read by others of the same one: LDS
+// operations of a wavefront stay in order, only the compiler has to keep them so.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The pairs of atom i (at pi) within the cutoff, by one whole wavefront: candidates are
+// tested 64 at a time and those within the cutoff queued in `list` (64 + BATCH entries
+// of LDS: R = r_i - r_j, atom j in bits); batch(entries, count) is called with up to
+// BATCH of them.  FLAT numbers the candidates of all runs through, at about 90
+// instructions a round: for cells of a few atoms, whose runs leave most lanes idle.
+template <int BATCH, bool FLAT, class F>
+__device__ __forceinline__ void visit_pairs(const CellGrid& g, const int* start, const float4* sp,
+                                            const float4 pi, int i, float rc2, float4* list,
+                                            F&& batch) {
+  const int lane = threadIdx.x & 63;
+  int c[3];
+  cell_of(g, pi.x, pi.y, pi.z, c);
+  const int2 runs = cell_run(g, start, c, lane);   // lane e holds run e
+  int cnt = 0;
+  auto test = [&](int k, bool in) {
+    const float4 pj = sp[in ? k : 0];
+    const float3 R = min_image(g, pi.x - pj.x, pi.y - pj.y, pi.z - pj.z);
+    const float r2 = R.x * R.x + R.y * R.y + R.z * R.z;
+    const bool hit = in && r2 < rc2 && r2 > 0.0f && __float_as_int(pj.w) != i;
+    const unsigned long long m = __ballot(hit);
+    const int below = int(__builtin_amdgcn_mbcnt_hi(
+        uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
+    if (hit) list[cnt + below] = make_float4(R.x, R.y, R.z, pj.w);
+    cnt += __popcll(m);
+    if (cnt >= BATCH) {
+      wave_lds_fence();
+      int o = 0;
+      for (; cnt - o >= BATCH; o += BATCH) batch(list + o, BATCH);
+      cnt -= o;
+      float4 rest;
+      if (lane < cnt) rest = list[o + lane];
+      wave_lds_fence();
+      if (lane < cnt) list[lane] = rest;
+    }
+  };
+  if constexpr (FLAT) {
+    const int len = runs.y - runs.x;
+    int end = len;   // end of the run in the numbering, then k minus the number in it
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+      const int v = __shfl_up(end, o, 64);
+      if (lane >= o) end += v;
+    }
+    const int total = __builtin_amdgcn_readlane(end, kCellRuns - 1);
+    const int first = end - len, shift = runs.x - first;
+    for (int b = 0; b < total; b += 64) {
+      const int t = b + lane;
+      int k = 0;
+#pragma unroll
+      for (int s = 0; s < kCellRuns; ++s)   // the last run that starts at or before t
+        if (t >= __builtin_amdgcn_readlane(first, s)) k = t + __builtin_amdgcn_readlane(shift, s);
+      test(k, t < total);
+    }
+  } else {
+    for (int s = 0; s < kCellRuns; ++s) {
+      const int k0 = __builtin_amdgcn_readlane(runs.x, s);
+      const int k1 = __builtin_amdgcn_readlane(runs.y, s);
+      for (int b = k0; b < k1; b += 64) test(b + lane, b + lane < k1);
+    }
+  }
+  wave_lds_fence();
+  if (cnt) batch(list, cnt);
+}
+
 __global__ void k_cell_clear(int* count, int ncell) {
   for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < ncell; c += gridDim.x * blockDim.x)
     count[c] = 0;
@@ -128,21 +206,20 @@ __global__ void __launch_bounds__(1024) k_cell_scan(const int* count, int* start
 }
 
 __global__ void k_cell_fill(int n, const float* pos, const int* cellof, const int* slot,
-                            const int* start, int* sorted, float4* sp) {
+                            const int* start, float4* sp) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int k = start[cellof[i]] + slot[i];
-  sorted[k] = i;
-  sp[k] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+  sp[start[cellof[i]] + slot[i]] =
+      make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
 }
 
 // The whole counting sort in one workgroup, the counters in LDS: up to kSortAtoms atoms
 // and kSortCells cells.  At 4096 atoms the four kernels above take 13 us and four
-// launches, this one 7 us and one; past 8 atoms a thread the one CU is the
-// bound and the four kernels win.
+// launches, this one 7 us and one.  The limits keep a thread's atoms in registers and
+// the counters in 48 KB.
 constexpr int kSortAtoms = 8192, kSortCells = 12288;
 __global__ void __launch_bounds__(1024) k_cell_sort(int n, const float* pos, CellGrid g,
-                                                    int* start, int* sorted, float4* sp) {
+                                                    int* start, float4* sp) {
   __shared__ int s_count[kSortCells];
   __shared__ int s_wave[16];
   constexpr int U = kSortAtoms / 1024;
@@ -193,9 +270,7 @@ __global__ void __launch_bounds__(1024) k_cell_sort(int n, const float* pos, Cel
   for (int u = 0; u < U; ++u) {
     const int i = t + u * 1024;
     if (i < n) {
-      const int k = s_count[cell[u]] + slot[u];
-      sorted[k] = i;
-      sp[k] = make_float4(x[u], y[u], z[u], __int_as_float(i));
+      sp[s_count[cell[u]] + slot[u]] = make_float4(x[u], y[u], z[u], __int_as_float(i));
     }
   }
 }
@@ -237,14 +312,13 @@ inline int setup_cells(CellList& cl, const double* C, double rc, int max_atoms) 
   ok(hipMalloc(&cl.start, sizeof(int) * (ncell + 1)));
   ok(hipMalloc(&cl.cellof, sizeof(int) * m));
   ok(hipMalloc(&cl.slot, sizeof(int) * m));
-  ok(hipMalloc(&cl.sorted, sizeof(int) * m));
   ok(hipMalloc(&cl.sp, sizeof(float4) * m));
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? PME_ENOMEM : PME_EHIP;
   return PME_OK;
 }
 
 inline void free_cells(CellList& cl) {
-  void* ptrs[] = {cl.count, cl.start, cl.cellof, cl.slot, cl.sorted, cl.sp};
+  void* ptrs[] = {cl.count, cl.start, cl.cellof, cl.slot, cl.sp};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   cl = CellList();
@@ -254,8 +328,7 @@ inline void free_cells(CellList& cl) {
 inline hipError_t build_cells(const CellList& cl, hipStream_t s, int n, const float* pos) {
   const CellGrid& g = cl.g;
   if (n <= kSortAtoms && g.ncell <= kSortCells) {
-    hipLaunchKernelGGL(k_cell_sort, dim3(1), dim3(1024), 0, s, n, pos, g, cl.start, cl.sorted,
-                       cl.sp);
+    hipLaunchKernelGGL(k_cell_sort, dim3(1), dim3(1024), 0, s, n, pos, g, cl.start, cl.sp);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_cell_clear, dim3(cell_blocks(g.ncell, 256)), dim3(256), 0, s, cl.count,
@@ -266,7 +339,7 @@ inline hipError_t build_cells(const CellList& cl, hipStream_t s, int n, const fl
   hipLaunchKernelGGL(k_cell_scan, dim3(1), dim3(1024), 0, s, cl.count, cl.start, g.ncell);
   if (n > 0)
     hipLaunchKernelGGL(k_cell_fill, dim3(cell_blocks(n, 256)), dim3(256), 0, s, n, pos,
-                       cl.cellof, cl.slot, cl.start, cl.sorted, cl.sp);
+                       cl.cellof, cl.slot, cl.start, cl.sp);
   return hipGetLastError();
 }
 

@@ -1,8 +1,9 @@
 // Learned dipole head: local features, the SiLU MLP forward and backward, the
 // training loss against the polarizable teacher and Adam (definitions in dip.h).
 //
-// Features give 16 lanes to an atom over the cell list of cells.h and combine the
-// lanes' sums with shuffles.  The MLP runs 16 atoms per 64-thread workgroup with
+// Features give a wavefront to an atom over the cell list of cells.h: the pairs within
+// the cutoff are queued, their radial functions are made a pair per lane, and then each
+// lane sums one of the atom's 64 channels over the queued pairs.  The MLP runs 16 atoms per 64-thread workgroup with
 // the weights staged in LDS (transposed, padded rows): a thread owns one hidden
 // unit and loops over the workgroup's atoms.  Parameter gradients are summed per
 // workgroup, then over workgroups in a fixed order.
@@ -23,17 +24,12 @@ constexpr int oW3 = ob2 + HID, ob3 = oW3 + NCH * HID;
 static_assert(ob3 + NCH == NP, "parameter layout");
 static_assert(NCH == NR * NS && NF == 2 * NCH + NS, "feature layout");
 
-constexpr int kLanes = 16;
 constexpr int kFeatThreads = 256;
+constexpr int kFeatAtoms = kFeatThreads / 64;   // one wavefront per atom
+constexpr int kFeatBatch = 32;                  // pairs whose radial functions are held at once
 constexpr int kAtoms = 16;            // atoms per MLP workgroup
 constexpr int kMlpThreads = 64;
 constexpr int HP = HID + 1;           // padded LDS row of 64
-
-__device__ __forceinline__ float lane_sum(float v) {
-#pragma unroll
-  for (int o = kLanes / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kLanes);
-  return v;
-}
 
 struct FeatArgs {
   int n;
@@ -41,103 +37,84 @@ struct FeatArgs {
   const float* q;
   CellGrid g;
   const int* start;
-  const int* sorted;
+  const float4* sp;
   float rc;
   float* feat;
   float* vec;
 };
 
+// Radial functions of one pair, R_k = norm sin((k+1) pi x) env / r, and with dR their
+// r-derivatives; sin and cos of the multiples by the Chebyshev recurrences.
+__device__ __forceinline__ void radial(float r, float ir, float irc, float (&Rk)[NR], float* dR) {
+  const float norm = sqrtf(2.0f * irc), kpi = float(M_PI) * irc;
+  const float x = r * irc, x2 = x * x, x4 = x2 * x2, x5 = x4 * x;
+  const float env = 1.0f - 21.0f * x5 + 35.0f * x5 * x - 15.0f * x5 * x2;
+  const float denv = (-105.0f * x4 + 210.0f * x5 - 105.0f * x5 * x) * irc;
+  float sn, cs;
+  sincospif(x, &sn, &cs);
+  float s_prev = 0.0f, s_cur = sn, c_prev = 1.0f, c_cur = cs;
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    Rk[k] = norm * s_cur * env * ir;
+    if (dR)
+      dR[k] = norm * ((k + 1) * kpi * c_cur * env * ir - s_cur * env * ir * ir + s_cur * ir * denv);
+    const float s_next = 2.0f * cs * s_cur - s_prev;
+    const float c_next = 2.0f * cs * c_cur - c_prev;
+    s_prev = s_cur;
+    s_cur = s_next;
+    c_prev = c_cur;
+    c_cur = c_next;
+  }
+}
+
+// Channel (component, species, k) of a lane: component 0 is the scalar G, 1..3 are V.
+// Bound by latency and issue: at 4096 ions and 5 Angstrom an atom has 110 candidates and
+// 17 pairs.  With 16 lanes an atom the long radial body ran for an eighth of its lanes,
+// and 64 sums a lane were shuffled together at the end; here a pair's radial functions
+// are made once and the sums need no shuffle: 31 -> 9 us.
 __global__ void __launch_bounds__(kFeatThreads) k_features(FeatArgs a) {
-  const int lane = threadIdx.x % kLanes;
-  const int i = blockIdx.x * (kFeatThreads / kLanes) + threadIdx.x / kLanes;
-  const bool live = i < a.n;
-  const int ii = live ? i : 0;
-  const float px = a.pos[3 * ii], py = a.pos[3 * ii + 1], pz = a.pos[3 * ii + 2];
-  // per species s (A: cation neighbours, B: anion neighbours) and radial k
-  float gA[NR], gB[NR], vA[NR][3], vB[NR][3];
+  __shared__ float4 s_pair[kFeatAtoms][64 + kFeatBatch];
+  __shared__ float s_R[kFeatAtoms][kFeatBatch][NR];
+  __shared__ float4 s_w[kFeatAtoms][kFeatBatch][NS];   // (1, q_j u) at the neighbour's species
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int at = blockIdx.x * kFeatAtoms + wave;
+  if (at >= a.n) return;   // no workgroup barrier below
+  const float4 pi = a.sp[at];
+  const int i = __builtin_amdgcn_readfirstlane(__float_as_int(pi.w));
+  const int k = lane & 7, s = (lane >> 3) & 1, comp = lane >> 4;
+  float acc = 0.0f;
+  visit_pairs<kFeatBatch, true>(
+      a.g, a.start, a.sp, pi, i, a.rc * a.rc, s_pair[wave], [&](const float4* l, int nb) {
+        if (lane < nb) {
+          const float4 p = l[lane];
+          const float r = sqrtf(p.x * p.x + p.y * p.y + p.z * p.z), ir = 1.0f / r;
+          float Rk[NR];
+          radial(r, ir, 1.0f / a.rc, Rk, nullptr);
 #pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    gA[k] = gB[k] = 0.0f;
-    vA[k][0] = vA[k][1] = vA[k][2] = vB[k][0] = vB[k][1] = vB[k][2] = 0.0f;
-  }
-  const float rc2 = a.rc * a.rc, irc = 1.0f / a.rc;
-  const float norm = sqrtf(2.0f * irc);
-  if (live) {
-    int c[3], no[3];
-    cell_of(a.g, px, py, pz, c);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) no[d] = a.g.nc[d] < 3 ? a.g.nc[d] : 3;
-    for (int ox = 0; ox < no[0]; ++ox)
-      for (int oy = 0; oy < no[1]; ++oy)
-        for (int oz = 0; oz < no[2]; ++oz) {
-          const int cell = (neighbour_cell(c[0], ox, a.g.nc[0]) * a.g.nc[1] +
-                            neighbour_cell(c[1], oy, a.g.nc[1])) * a.g.nc[2] +
-                           neighbour_cell(c[2], oz, a.g.nc[2]);
-          for (int kk = a.start[cell] + lane; kk < a.start[cell + 1]; kk += kLanes) {
-            const int j = a.sorted[kk];
-            if (j == i) continue;
-            const float3 R = min_image(a.g, px - a.pos[3 * j], py - a.pos[3 * j + 1],
-                                       pz - a.pos[3 * j + 2]);
-            const float r2 = R.x * R.x + R.y * R.y + R.z * R.z;
-            if (r2 >= rc2 || r2 <= 0.0f) continue;
-            const float r = sqrtf(r2), ir = 1.0f / r, x = r * irc;
-            const float x2 = x * x, x5 = x2 * x2 * x;
-            const float env = 1.0f - 21.0f * x5 + 35.0f * x5 * x - 15.0f * x5 * x2;
-            const float pref = norm * ir * env;
-            const float qj = a.q[j];
-            const bool cat = qj > 0.0f;
-            const float ux = R.x * ir, uy = R.y * ir, uz = R.z * ir;
-            // sin((k+1) t) by the Chebyshev recurrence from sin t, cos t
-            float sn, cs;
-            sincosf(float(M_PI) * x, &sn, &cs);
-            float s_prev = 0.0f, s_cur = sn;
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-              const float Rk = pref * s_cur;
-              const float qR = qj * Rk;
-              if (cat) {
-                gA[k] += Rk;
-                vA[k][0] += qR * ux; vA[k][1] += qR * uy; vA[k][2] += qR * uz;
-              } else {
-                gB[k] += Rk;
-                vB[k][0] += qR * ux; vB[k][1] += qR * uy; vB[k][2] += qR * uz;
-              }
-              const float s_next = 2.0f * cs * s_cur - s_prev;
-              s_prev = s_cur;
-              s_cur = s_next;
-            }
-          }
+          for (int m = 0; m < NR; ++m) s_R[wave][lane][m] = Rk[m];
+          const float qj = a.q[__float_as_int(p.w)];
+          const float4 w = make_float4(1.0f, qj * p.x * ir, qj * p.y * ir, qj * p.z * ir);
+          const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          s_w[wave][lane][0] = qj > 0.0f ? w : none;
+          s_w[wave][lane][1] = qj > 0.0f ? none : w;
         }
+        wave_lds_fence();
+        const float* R = &s_R[wave][0][k];
+        const float* w = reinterpret_cast<const float*>(&s_w[wave][0][s]) + comp;
+        for (int m = 0; m < nb; ++m) acc = fmaf(R[NR * m], w[4 * NS * m], acc);
+        wave_lds_fence();
+      });
+  float v2 = acc * acc;   // |V|^2 of (species, k): the sum over the three components
+  v2 = __shfl(v2, 16 + (lane & 15), 64) + __shfl(v2, 32 + (lane & 15), 64) +
+       __shfl(v2, 48 + (lane & 15), 64);
+  float* f = a.feat + size_t(i) * NF;
+  if (comp == 0) {
+    f[lane] = acc;
+    f[NCH + lane] = v2;
+  } else {
+    a.vec[size_t(i) * NCH * 3 + 3 * (lane & 15) + comp - 1] = acc;
   }
-#pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    gA[k] = lane_sum(gA[k]);
-    gB[k] = lane_sum(gB[k]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      vA[k][d] = lane_sum(vA[k][d]);
-      vB[k][d] = lane_sum(vB[k][d]);
-    }
-  }
-  if (live && lane == 0) {
-    float* f = a.feat + size_t(i) * NF;
-    float* v = a.vec + size_t(i) * NCH * 3;
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      f[k] = gA[k];
-      f[NR + k] = gB[k];
-      f[NCH + k] = vA[k][0] * vA[k][0] + vA[k][1] * vA[k][1] + vA[k][2] * vA[k][2];
-      f[NCH + NR + k] = vB[k][0] * vB[k][0] + vB[k][1] * vB[k][1] + vB[k][2] * vB[k][2];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        v[3 * k + d] = vA[k][d];
-        v[3 * (NR + k) + d] = vB[k][d];
-      }
-    }
-    const float qi = a.q[i];
-    f[2 * NCH] = qi > 0.0f ? 1.0f : 0.0f;
-    f[2 * NCH + 1] = qi > 0.0f ? 0.0f : 1.0f;
-  }
+  if (lane < NS) f[2 * NCH + lane] = (a.q[i] > 0.0f) == (lane == 0) ? 1.0f : 0.0f;
 }
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + expf(-z)); }
@@ -376,7 +353,7 @@ struct VjpArgs {
   const float* q;
   CellGrid g;
   const int* start;
-  const int* sorted;
+  const float4* sp;
   float rc;
   const float* fbar;   // [n][64] feature cotangents
   const float* base;   // [n][3] added to the output, or NULL
@@ -385,10 +362,18 @@ struct VjpArgs {
 
 // d/dR of the features of the centre atom of a pair (R = r_c - r_o, neighbour o
 // with charge qo) contracted with the cotangents cg[k], cv[k][3] of the neighbour's
-// species: sum_k cg R_k' u + qo [R_k' (cv.u) u + R_k / r (cv - (cv.u) u)].
-__device__ __forceinline__ float3 pair_vjp(const float* cg, const float* cv, float qo, float ux,
-                                           float uy, float uz, const float (&Rk)[NR],
-                                           const float (&dR)[NR], float ir) {
+// species: sum_k cg R_k' u + qo [R_k' (cv.u) u + R_k / r (cv - (cv.u) u)].  c points at
+// 16-byte aligned cg; cv follows `to_v` floats later.
+__device__ __forceinline__ float3 pair_vjp(const float* c, int to_v, float qo, float ux, float uy,
+                                           float uz, const float (&Rk)[NR], const float (&dR)[NR],
+                                           float ir) {
+  float cg[NR], cv[3 * NR];
+#pragma unroll
+  for (int k = 0; k < NR; k += 4)
+    *reinterpret_cast<float4*>(cg + k) = *reinterpret_cast<const float4*>(c + k);
+#pragma unroll
+  for (int k = 0; k < 3 * NR; k += 4)
+    *reinterpret_cast<float4*>(cv + k) = *reinterpret_cast<const float4*>(c + to_v + k);
   float fx = 0.0f, fy = 0.0f, fz = 0.0f;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
@@ -404,94 +389,49 @@ __device__ __forceinline__ float3 pair_vjp(const float* cg, const float* cv, flo
 }
 
 // g_i = sum_j [d/dr_i of the features of i, with i's cotangents] + [d/dr_i of the
-// features of j, with j's cotangents]: the pair (i, j) is visited from i only, so
-// no atomics are needed.  16 lanes per atom as in k_features.
+// features of j, with j's cotangents]: the pair (i, j) is visited from i only, so no
+// atomics are needed.  A wavefront per atom, a queued pair per lane (52 -> 10 us at 4096
+// ions against 16 lanes an atom with the pairs evaluated where they are found).
 __global__ void __launch_bounds__(kFeatThreads) k_features_vjp(VjpArgs a) {
-  __shared__ float s_f[kFeatThreads / kLanes][4 * NCH];
-  const int lane = threadIdx.x % kLanes;
-  const int slot = threadIdx.x / kLanes;
-  const int i = blockIdx.x * (kFeatThreads / kLanes) + slot;
-  const bool live = i < a.n;
-  const int ii = live ? i : 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) s_f[slot][lane + kLanes * k] = a.fbar[size_t(ii) * 4 * NCH + lane + kLanes * k];
-  __syncthreads();
-  const float px = a.pos[3 * ii], py = a.pos[3 * ii + 1], pz = a.pos[3 * ii + 2];
-  const float qi = a.q[ii];
+  __shared__ float4 s_pair[kFeatAtoms][128];
+  __shared__ __attribute__((aligned(16))) float s_f[kFeatAtoms][4 * NCH];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int at = blockIdx.x * kFeatAtoms + wave;
+  if (at >= a.n) return;   // no workgroup barrier below
+  const float4 pi = a.sp[at];
+  const int i = __builtin_amdgcn_readfirstlane(__float_as_int(pi.w));
+  const float* fi = s_f[wave];
+  s_f[wave][lane] = a.fbar[size_t(i) * 4 * NCH + lane];
+  wave_lds_fence();
+  const float qi = a.q[i];
   const int si = qi > 0.0f ? 0 : 1;
-  const float rc2 = a.rc * a.rc, irc = 1.0f / a.rc;
-  const float norm = sqrtf(2.0f * irc);
-  const float kpi = float(M_PI) * irc;
   float gx = 0.0f, gy = 0.0f, gz = 0.0f;
-  if (live) {
-    int c[3], no[3];
-    cell_of(a.g, px, py, pz, c);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) no[d] = a.g.nc[d] < 3 ? a.g.nc[d] : 3;
-    for (int ox = 0; ox < no[0]; ++ox)
-      for (int oy = 0; oy < no[1]; ++oy)
-        for (int oz = 0; oz < no[2]; ++oz) {
-          const int cell = (neighbour_cell(c[0], ox, a.g.nc[0]) * a.g.nc[1] +
-                            neighbour_cell(c[1], oy, a.g.nc[1])) * a.g.nc[2] +
-                           neighbour_cell(c[2], oz, a.g.nc[2]);
-          for (int kk = a.start[cell] + lane; kk < a.start[cell + 1]; kk += kLanes) {
-            const int j = a.sorted[kk];
-            if (j == i) continue;
-            const float3 R = min_image(a.g, px - a.pos[3 * j], py - a.pos[3 * j + 1],
-                                       pz - a.pos[3 * j + 2]);
-            const float r2 = R.x * R.x + R.y * R.y + R.z * R.z;
-            if (r2 >= rc2 || r2 <= 0.0f) continue;
-            const float r = sqrtf(r2), ir = 1.0f / r, x = r * irc;
-            const float x2 = x * x, x4 = x2 * x2, x5 = x4 * x;
-            const float env = 1.0f - 21.0f * x5 + 35.0f * x5 * x - 15.0f * x5 * x2;
-            const float denv = (-105.0f * x4 + 210.0f * x5 - 105.0f * x5 * x) * irc;
-            const float ux = R.x * ir, uy = R.y * ir, uz = R.z * ir;
-            // R_k = norm sin(k pi x) env / r and its r-derivative, sin and cos of
-            // (k+1) pi x by the Chebyshev recurrences
-            float sn, cs;
-            sincosf(float(M_PI) * x, &sn, &cs);
-            float Rk[NR], dR[NR];
-            float s_prev = 0.0f, s_cur = sn, c_prev = 1.0f, c_cur = cs;
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-              Rk[k] = norm * s_cur * env * ir;
-              dR[k] = norm * ((k + 1) * kpi * c_cur * env * ir - s_cur * env * ir * ir +
-                              s_cur * ir * denv);
-              const float s_next = 2.0f * cs * s_cur - s_prev;
-              const float c_next = 2.0f * cs * c_cur - c_prev;
-              s_prev = s_cur;
-              s_cur = s_next;
-              c_prev = c_cur;
-              c_cur = c_next;
-            }
-            const float qj = a.q[j];
-            const int sj = qj > 0.0f ? 0 : 1;
-            // features of i (neighbour j of species sj), R_ij = R
-            const float* fi = s_f[slot];
-            const float3 f1 = pair_vjp(fi + sj * NR, fi + NCH + 3 * sj * NR, qj, ux, uy, uz, Rk,
-                                       dR, ir);
-            // features of j (neighbour i of species si), R_ji = -R
-            const float* fj = a.fbar + size_t(j) * 4 * NCH;
-            const float3 f2 = pair_vjp(fj + si * NR, fj + NCH + 3 * si * NR, qi, -ux, -uy, -uz,
-                                       Rk, dR, ir);
-            gx += f1.x - f2.x;
-            gy += f1.y - f2.y;
-            gz += f1.z - f2.z;
-          }
-        }
-  }
-  gx = lane_sum(gx);
-  gy = lane_sum(gy);
-  gz = lane_sum(gz);
-  if (live && lane == 0) {
-    if (a.base) {
-      gx += a.base[3 * i];
-      gy += a.base[3 * i + 1];
-      gz += a.base[3 * i + 2];
-    }
-    a.g_pos[3 * i] = gx;
-    a.g_pos[3 * i + 1] = gy;
-    a.g_pos[3 * i + 2] = gz;
+  visit_pairs<64, true>(
+      a.g, a.start, a.sp, pi, i, a.rc * a.rc, s_pair[wave], [&](const float4* l, int nb) {
+        if (lane >= nb) return;
+        const float4 p = l[lane];
+        const int j = __float_as_int(p.w);
+        const float r = sqrtf(p.x * p.x + p.y * p.y + p.z * p.z), ir = 1.0f / r;
+        const float ux = p.x * ir, uy = p.y * ir, uz = p.z * ir;
+        float Rk[NR], dR[NR];
+        radial(r, ir, 1.0f / a.rc, Rk, dR);
+        const float qj = a.q[j];
+        const int sj = qj > 0.0f ? 0 : 1;
+        // features of i (neighbour j of species sj), R_ij = R; then features of j
+        // (neighbour i of species si), R_ji = -R
+        const float3 f1 = pair_vjp(fi + sj * NR, NCH + 2 * sj * NR, qj, ux, uy, uz, Rk, dR, ir);
+        const float3 f2 = pair_vjp(a.fbar + size_t(j) * 4 * NCH + si * NR, NCH + 2 * si * NR, qi,
+                                   -ux, -uy, -uz, Rk, dR, ir);
+        gx += f1.x - f2.x;
+        gy += f1.y - f2.y;
+        gz += f1.z - f2.z;
+      });
+  gx = wave_sum(gx);
+  gy = wave_sum(gy);
+  gz = wave_sum(gz);
+  if (lane < 3) {
+    const float g = lane == 0 ? gx : (lane == 1 ? gy : gz);
+    a.g_pos[3 * i + lane] = a.base ? g + a.base[3 * i + lane] : g;
   }
 }
 
@@ -511,12 +451,6 @@ constexpr int kGradBlocks = 512;      // cap on the workgroups of the parameter 
 __device__ __forceinline__ float d2silu(float z) {
   const float s = 1.0f / (1.0f + expf(-z));
   return s * (1.0f - s) * (2.0f + z * (1.0f - 2.0f * s));
-}
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
 }
 
 // rows [a0, a0 + na) of a [n][W] array into LDS rows of stride LD (zeros past na
@@ -721,7 +655,7 @@ struct FeatJvpArgs {
   const float* q;
   CellGrid g;
   const int* start;
-  const int* sorted;
+  const float4* sp;
   float rc;
   const float* vec;    // [n][16][3] features of dip_features
   const float* v;      // [n][3] position tangent
@@ -729,116 +663,68 @@ struct FeatJvpArgs {
   float* vec_dot;      // [n][16][3]
 };
 
-// Directional derivative of the features along v; 16 lanes per atom as in
-// k_features.  Pair R = r_i - r_j, w = v_i - v_j, u = R/r, r_dot = u . w:
+// Directional derivative of the features along v, laid out as k_features (39 -> 11 us at
+// 4096 ions).  Pair R = r_i - r_j, w = v_i - v_j, u = R/r, r_dot = u . w:
 //   G_dot += R_k' r_dot,  V_dot += q_j [R_k' r_dot u + R_k/r (w - r_dot u)].
 __global__ void __launch_bounds__(kFeatThreads) k_features_jvp(FeatJvpArgs a) {
-  const int lane = threadIdx.x % kLanes;
-  const int i = blockIdx.x * (kFeatThreads / kLanes) + threadIdx.x / kLanes;
-  const bool live = i < a.n;
-  const int ii = live ? i : 0;
-  const float px = a.pos[3 * ii], py = a.pos[3 * ii + 1], pz = a.pos[3 * ii + 2];
-  const float vix = a.v[3 * ii], viy = a.v[3 * ii + 1], viz = a.v[3 * ii + 2];
-  float gA[NR], gB[NR], vA[NR][3], vB[NR][3];
+  __shared__ float4 s_pair[kFeatAtoms][64 + kFeatBatch];
+  __shared__ float s_R[kFeatAtoms][kFeatBatch][2 * NR];         // R_k' r_dot, R_k / r
+  __shared__ float4 s_w[kFeatAtoms][kFeatBatch][2 * NS];        // their factors by species
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int at = blockIdx.x * kFeatAtoms + wave;
+  if (at >= a.n) return;   // no workgroup barrier below
+  const float4 pi = a.sp[at];
+  const int i = __builtin_amdgcn_readfirstlane(__float_as_int(pi.w));
+  const float vix = a.v[3 * i], viy = a.v[3 * i + 1], viz = a.v[3 * i + 2];
+  const int k = lane & 7, s = (lane >> 3) & 1, comp = lane >> 4;
+  float acc = 0.0f;
+  visit_pairs<kFeatBatch, true>(
+      a.g, a.start, a.sp, pi, i, a.rc * a.rc, s_pair[wave], [&](const float4* l, int nb) {
+        if (lane < nb) {
+          const float4 p = l[lane];
+          const int j = __float_as_int(p.w);
+          const float r = sqrtf(p.x * p.x + p.y * p.y + p.z * p.z), ir = 1.0f / r;
+          const float ux = p.x * ir, uy = p.y * ir, uz = p.z * ir;
+          const float wx = vix - a.v[3 * j], wy = viy - a.v[3 * j + 1], wz = viz - a.v[3 * j + 2];
+          const float rd = ux * wx + uy * wy + uz * wz;
+          float Rk[NR], dR[NR];
+          radial(r, ir, 1.0f / a.rc, Rk, dR);
 #pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    gA[k] = gB[k] = 0.0f;
-    vA[k][0] = vA[k][1] = vA[k][2] = vB[k][0] = vB[k][1] = vB[k][2] = 0.0f;
-  }
-  const float rc2 = a.rc * a.rc, irc = 1.0f / a.rc;
-  const float norm = sqrtf(2.0f * irc);
-  const float kpi = float(M_PI) * irc;
-  if (live) {
-    int c[3], no[3];
-    cell_of(a.g, px, py, pz, c);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) no[d] = a.g.nc[d] < 3 ? a.g.nc[d] : 3;
-    for (int ox = 0; ox < no[0]; ++ox)
-      for (int oy = 0; oy < no[1]; ++oy)
-        for (int oz = 0; oz < no[2]; ++oz) {
-          const int cell = (neighbour_cell(c[0], ox, a.g.nc[0]) * a.g.nc[1] +
-                            neighbour_cell(c[1], oy, a.g.nc[1])) * a.g.nc[2] +
-                           neighbour_cell(c[2], oz, a.g.nc[2]);
-          for (int kk = a.start[cell] + lane; kk < a.start[cell + 1]; kk += kLanes) {
-            const int j = a.sorted[kk];
-            if (j == i) continue;
-            const float3 R = min_image(a.g, px - a.pos[3 * j], py - a.pos[3 * j + 1],
-                                       pz - a.pos[3 * j + 2]);
-            const float r2 = R.x * R.x + R.y * R.y + R.z * R.z;
-            if (r2 >= rc2 || r2 <= 0.0f) continue;
-            const float r = sqrtf(r2), ir = 1.0f / r, x = r * irc;
-            const float x2 = x * x, x4 = x2 * x2, x5 = x4 * x;
-            const float env = 1.0f - 21.0f * x5 + 35.0f * x5 * x - 15.0f * x5 * x2;
-            const float denv = (-105.0f * x4 + 210.0f * x5 - 105.0f * x5 * x) * irc;
-            const float ux = R.x * ir, uy = R.y * ir, uz = R.z * ir;
-            const float wx = vix - a.v[3 * j], wy = viy - a.v[3 * j + 1],
-                        wz = viz - a.v[3 * j + 2];
-            const float rd = ux * wx + uy * wy + uz * wz;
-            const float px_ = wx - rd * ux, py_ = wy - rd * uy, pz_ = wz - rd * uz;
-            const float qj = a.q[j];
-            const bool cat = qj > 0.0f;
-            float sn, cs;
-            sincosf(float(M_PI) * x, &sn, &cs);
-            float s_prev = 0.0f, s_cur = sn, c_prev = 1.0f, c_cur = cs;
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-              const float Rk = norm * s_cur * env * ir;
-              const float dR = norm * ((k + 1) * kpi * c_cur * env * ir - s_cur * env * ir * ir +
-                                       s_cur * ir * denv);
-              const float gd = dR * rd;
-              const float au = qj * gd, ap = qj * Rk * ir;
-              if (cat) {
-                gA[k] += gd;
-                vA[k][0] += au * ux + ap * px_;
-                vA[k][1] += au * uy + ap * py_;
-                vA[k][2] += au * uz + ap * pz_;
-              } else {
-                gB[k] += gd;
-                vB[k][0] += au * ux + ap * px_;
-                vB[k][1] += au * uy + ap * py_;
-                vB[k][2] += au * uz + ap * pz_;
-              }
-              const float s_next = 2.0f * cs * s_cur - s_prev;
-              const float c_next = 2.0f * cs * c_cur - c_prev;
-              s_prev = s_cur;
-              s_cur = s_next;
-              c_prev = c_cur;
-              c_cur = c_next;
-            }
+          for (int m = 0; m < NR; ++m) {
+            s_R[wave][lane][m] = dR[m] * rd;
+            s_R[wave][lane][NR + m] = Rk[m] * ir;
           }
+          const float qj = a.q[j];
+          const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          const float4 w0 = make_float4(1.0f, qj * ux, qj * uy, qj * uz);
+          const float4 w1 = make_float4(0.0f, qj * (wx - rd * ux), qj * (wy - rd * uy),
+                                        qj * (wz - rd * uz));
+          s_w[wave][lane][0] = qj > 0.0f ? w0 : none;
+          s_w[wave][lane][1] = qj > 0.0f ? none : w0;
+          s_w[wave][lane][2] = qj > 0.0f ? w1 : none;
+          s_w[wave][lane][3] = qj > 0.0f ? none : w1;
         }
+        wave_lds_fence();
+        const float* R = &s_R[wave][0][k];
+        const float* w = reinterpret_cast<const float*>(&s_w[wave][0][s]) + comp;
+        for (int m = 0; m < nb; ++m)
+          acc = fmaf(R[2 * NR * m], w[8 * NS * m],
+                     fmaf(R[2 * NR * m + NR], w[8 * NS * m + 4 * NS], acc));
+        wave_lds_fence();
+      });
+  // d|V|^2 = 2 V . V_dot of (species, k)
+  float vd = 0.0f;
+  if (comp) vd = a.vec[size_t(i) * NCH * 3 + 3 * (lane & 15) + comp - 1] * acc;
+  vd = __shfl(vd, 16 + (lane & 15), 64) + __shfl(vd, 32 + (lane & 15), 64) +
+       __shfl(vd, 48 + (lane & 15), 64);
+  float* f = a.feat_dot + size_t(i) * NF;
+  if (comp == 0) {
+    f[lane] = acc;
+    f[NCH + lane] = 2.0f * vd;
+  } else {
+    a.vec_dot[size_t(i) * NCH * 3 + 3 * (lane & 15) + comp - 1] = acc;
   }
-#pragma unroll
-  for (int k = 0; k < NR; ++k) {
-    gA[k] = lane_sum(gA[k]);
-    gB[k] = lane_sum(gB[k]);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      vA[k][d] = lane_sum(vA[k][d]);
-      vB[k][d] = lane_sum(vB[k][d]);
-    }
-  }
-  if (live && lane == 0) {
-    float* f = a.feat_dot + size_t(i) * NF;
-    float* vd = a.vec_dot + size_t(i) * NCH * 3;
-    const float* V = a.vec + size_t(i) * NCH * 3;
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      f[k] = gA[k];
-      f[NR + k] = gB[k];
-      f[NCH + k] = 2.0f * (V[3 * k] * vA[k][0] + V[3 * k + 1] * vA[k][1] + V[3 * k + 2] * vA[k][2]);
-      const float* W = V + 3 * NR;
-      f[NCH + NR + k] =
-          2.0f * (W[3 * k] * vB[k][0] + W[3 * k + 1] * vB[k][1] + W[3 * k + 2] * vB[k][2]);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        vd[3 * k + d] = vA[k][d];
-        vd[3 * (NR + k) + d] = vB[k][d];
-      }
-    }
-    f[2 * NCH] = 0.0f;
-    f[2 * NCH + 1] = 0.0f;
-  }
+  if (lane < NS) f[2 * NCH + lane] = 0.0f;
 }
 
 // LDS of the dual dipole network: the weights once per workgroup, and per tile
@@ -1186,9 +1072,9 @@ int dip_features(dip_plan_t plan, void* stream, int32_t n, const float* pos, con
   if (e != hipSuccess) return dip_fail(e);
   FeatArgs a;
   a.n = n; a.pos = pos; a.q = q; a.g = plan->cells.g;
-  a.start = plan->cells.start; a.sorted = plan->cells.sorted;
+  a.start = plan->cells.start; a.sp = plan->cells.sp;
   a.rc = float(plan->desc.cutoff); a.feat = feat; a.vec = vec;
-  const int per = kFeatThreads / kLanes;
+  const int per = kFeatAtoms;
   hipLaunchKernelGGL(k_features, dim3((n + per - 1) / per), dim3(kFeatThreads), 0, s, a);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
@@ -1244,9 +1130,9 @@ int dip_position_vjp(dip_plan_t plan, void* stream, int32_t n, const float* para
   }
   VjpArgs a;
   a.n = n; a.pos = pos; a.q = q; a.g = plan->cells.g;
-  a.start = plan->cells.start; a.sorted = plan->cells.sorted;
+  a.start = plan->cells.start; a.sp = plan->cells.sp;
   a.rc = float(plan->desc.cutoff); a.fbar = plan->fbar; a.base = base; a.g_pos = g_pos;
-  const int per = kFeatThreads / kLanes;
+  const int per = kFeatAtoms;
   hipLaunchKernelGGL(k_features_vjp, dim3((n + per - 1) / per), dim3(kFeatThreads), 0, s, a);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
@@ -1263,10 +1149,10 @@ int dip_features_jvp(dip_plan_t plan, void* stream, int32_t n, const float* pos,
   if (e != hipSuccess) return dip_fail(e);
   FeatJvpArgs a;
   a.n = n; a.pos = pos; a.q = q; a.g = plan->cells.g;
-  a.start = plan->cells.start; a.sorted = plan->cells.sorted;
+  a.start = plan->cells.start; a.sp = plan->cells.sp;
   a.rc = float(plan->desc.cutoff); a.vec = vec; a.v = v;
   a.feat_dot = feat_dot; a.vec_dot = vec_dot;
-  const int per = kFeatThreads / kLanes;
+  const int per = kFeatAtoms;
   hipLaunchKernelGGL(k_features_jvp, dim3((n + per - 1) / per), dim3(kFeatThreads), 0, s, a);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);

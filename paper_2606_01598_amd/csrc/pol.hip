@@ -54,20 +54,6 @@ __device__ __forceinline__ float3 ld3(const float* p, int i) {
 }
 __device__ __forceinline__ float dot3(float3 a, float3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// LDS written by some lanes of a wavefront, read by others of the same one: LDS
-// operations of a wavefront stay in order, only the compiler has to keep them so.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Bound by vector issue: a pair within the cutoff costs about 150 instructions (erfc,
 // two exponentials, the screened functions), a candidate about 35, and at a 10 Angstrom
 // cutoff only one candidate in seven is within it.  So candidates (consecutive loads in
@@ -161,39 +147,9 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a) {
     }
   };
 
-  if (live) {
-    int c[3];
-    cell_of(a.g, pi.x, pi.y, pi.z, c);
-    const int2 runs = cell_run(a.g, a.start, c, lane);   // lane e holds run e
-    int cnt = 0;
-    for (int s = 0; s < kCellRuns; ++s) {
-      const int k0 = __builtin_amdgcn_readlane(runs.x, s);
-      const int k1 = __builtin_amdgcn_readlane(runs.y, s);
-      for (int b = k0; b < k1; b += 64) {
-        const int k = b + lane;
-        const float4 pj = a.sp[min(k, k1 - 1)];
-        const float3 R = min_image(a.g, pi.x - pj.x, pi.y - pj.y, pi.z - pj.z);
-        const float r2 = dot3(R, R);
-        const bool hit = k < k1 && r2 < a.rc2 && r2 > 0.0f && __float_as_int(pj.w) != i;
-        const unsigned long long m = __ballot(hit);
-        const int below = int(__builtin_amdgcn_mbcnt_hi(
-            uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));
-        if (hit) list[cnt + below] = make_float4(R.x, R.y, R.z, pj.w);
-        cnt += __popcll(m);
-        if (cnt >= 64) {   // at most 63 were left, so the list holds at most 127
-          wave_lds_fence();
-          const float4 now = list[lane];
-          const float4 rest = list[64 + lane];
-          wave_lds_fence();
-          cnt -= 64;
-          if (lane < cnt) list[lane] = rest;
-          pair(now);
-        }
-      }
-    }
-    wave_lds_fence();
-    if (lane < cnt) pair(list[lane]);
-  }
+  if (live)
+    visit_pairs<64, false>(a.g, a.start, a.sp, pi, i, a.rc2, list,
+                           [&](const float4* l, int nb) { if (lane < nb) pair(l[lane]); });
   mx = wave_sum(mx); my = wave_sum(my); mz = wave_sum(mz);
   if (MODE == kEnergyGrad || MODE == kHvp) gq = wave_sum(gq);
   if (MODE == kEnergyGrad) {

@@ -1,5 +1,5 @@
-"""Edges of the wavefront-per-atom pair kernels and of the cell list they read,
-against the FP64 oracle: one to four cells along an axis (and mixed), atoms with no
+"""Edges of the wavefront-per-atom pair and feature kernels and of the cell list they
+read, against the FP64 oracle: one to four cells along an axis (and mixed), atoms with no
 neighbour and with more than the 128 pairs a wavefront queues, positions outside the
 cell, and both cell sorts (one workgroup, or four launches).
 
@@ -11,8 +11,9 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import dev, f32, host, rms_rel
-from oracle import pol as opol
+import synth
+from gpu_util import RMS_REL_TOL, dev, f32, host, rms_rel
+from oracle import dip as odip, heads as oheads, pol as opol
 
 pytestmark = pytest.mark.gpu
 TOL = 5e-5
@@ -71,3 +72,28 @@ def test_pair_kernels(name):
             "dE_dmu": rms_rel(host(out["dE_dmu"]), gm), "mixed": rms_rel(host(mixed), ref)}
     print(name, {k: f"{w:.2e}" for k, w in errs.items()}, flush=True)
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_feature_kernels(name):
+    from paper_2606_01598_amd.dip import DipPlan
+    box, rc, pos, shift, q, _, _, rng = _case(name)
+    n = len(q)
+    t = lambda a: torch.tensor(a, dtype=torch.float32, device=dev())   # noqa: E731
+    v, u = rng.normal(0, 1, (n, 3)), rng.normal(0, 1, (n, 3))
+    theta = f32(synth.mlp_init(5, last_scale=1.0))
+    plan = DipPlan(box, n, cutoff=rc)
+    feat, vec = plan.features(t(pos), t(q))
+    fd, vd = plan.features_jvp(t(pos), t(q), vec, t(v))
+    base = rng.normal(0, 1, (n, 3))
+    g = plan.position_vjp(t(theta), t(pos), t(q), feat, vec, t(u), base=t(base))
+    x = f32(pos) - shift
+    rf, rv = odip.features(x, f32(q), box, rc)
+    rfd, rvd = oheads.features_jvp(x, f32(q), box, rc, f32(v))
+    rg = odip.position_vjp(theta, x, f32(q), box, rc, f32(u))
+    errs = {"feat": rms_rel(host(feat), rf), "vec": rms_rel(host(vec), rv),
+            "feat_dot": rms_rel(host(fd), rfd), "vec_dot": rms_rel(host(vd), rvd)}
+    eg = rms_rel(host(g) - f32(base), rg)
+    print(name, {k: f"{w:.2e}" for k, w in errs.items()}, f"vjp {eg:.2e}", flush=True)
+    assert max(errs.values()) <= TOL, errs
+    assert eg <= RMS_REL_TOL
