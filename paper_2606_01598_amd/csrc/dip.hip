@@ -3,9 +3,8 @@
 //
 // Features give a wavefront to an atom over the cell list of cells.h: the pairs within
 // the cutoff are queued, their radial functions are made a pair per lane, and then each
-// lane sums one of the atom's 64 channels over the queued pairs.  The MLP runs 16 atoms per 64-thread workgroup with
-// the weights staged in LDS (transposed, padded rows): a thread owns one hidden
-// unit and loops over the workgroup's atoms.  Parameter gradients are summed per
+// lane sums one of the atom's 64 channels over the queued pairs.  The networks run 16
+// atoms per workgroup in fp32 matrix instructions.  Parameter gradients are summed per
 // workgroup, then over workgroups in a fixed order.
 #include <math.h>
 #include <stdio.h>
@@ -27,9 +26,6 @@ static_assert(NCH == NR * NS && NF == 2 * NCH + NS, "feature layout");
 constexpr int kFeatThreads = 256;
 constexpr int kFeatAtoms = kFeatThreads / 64;   // one wavefront per atom
 constexpr int kFeatBatch = 32;                  // pairs whose radial functions are held at once
-constexpr int kAtoms = 16;            // atoms per MLP workgroup
-constexpr int kMlpThreads = 64;
-constexpr int HP = HID + 1;           // padded LDS row of 64
 
 struct FeatArgs {
   int n;
@@ -123,228 +119,458 @@ __device__ __forceinline__ float dsilu(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// LDS of one MLP workgroup
-struct MlpLds {
-  float W1T[NF][HP];     // W1T[k][o] = W1[o][k]
-  float W2T[HID][HP];    // W2T[k][o] = W2[o][k]
-  float W3[NCH][HP];
-  float b1[HID], b2[HID], b3[NCH];
-  float x[kAtoms][NF + 1];
-  float z1[kAtoms][HP], h1[kAtoms][HP];
-  float z2[kAtoms][HP], h2[kAtoms][HP];
-  float w[kAtoms][NCH + 1];
-  float V[kAtoms][NCH * 3 + 1];
+__device__ __forceinline__ float d2silu(float z) {
+  const float s = 1.0f / (1.0f + expf(-z));
+  return s * (1.0f - s) * (2.0f + z * (1.0f - 2.0f * s));
+}
+
+// ---- the networks on the matrix cores -------------------------------------------
+//
+// One workgroup of four wavefronts runs 16 atoms.  Every layer is out^T = W in^T in
+// 16 x 16 x 4 fp32 matrix instructions: wavefront w makes hidden units 16 w .. 16 w + 15
+// of the 16 atoms, lane l = 16 g + a holding units 4 g + r (r = 0..3) of atom a, and the
+// next layer contracts them in that same order (k = 16 T + 4 g + r in step (T, r)), so
+// that activations pass through LDS as they lie and the weights come straight from
+// memory, one value a lane and step.  Bound by latency: a layer is at most 16 dependent
+// matrix instructions of 32 cycles.  One wavefront of 64 hidden units per workgroup with
+// the weights staged through LDS took 36 to 63 us a kernel at 4096 atoms; these take 5
+// to 8 us, the parameter gradient of the dual network 16 us.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kNetThreads = 256;
+constexpr int HS = HID + 4;           // LDS row of hidden units: 16-byte rows, no conflicts
+constexpr int CS = NCH + 4;
+
+__device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+struct NetLane {
+  int l16, g, w;
+  __device__ __forceinline__ NetLane()
+      : l16(threadIdx.x & 15), g((threadIdx.x >> 4) & 3),
+        w(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {}
 };
 
-// Stage the weights and the workgroup's inputs, run the network; leaves z1, h1,
-// z2, h2 and w in LDS.
-__device__ void mlp_eval(MlpLds& L, const float* P, const float* feat, const float* vec, int a0,
-                         int na) {
-  const int t = threadIdx.x;
-  for (int e = t; e < HID * NF; e += kMlpThreads) {
-    const int o = e / NF, k = e - o * NF;
-    L.W1T[k][o] = P[oW1 + e];
-  }
-  for (int e = t; e < HID * HID; e += kMlpThreads) {
-    const int o = e / HID, k = e - o * HID;
-    L.W2T[k][o] = P[oW2 + e];
-  }
-  for (int e = t; e < NCH * HID; e += kMlpThreads) {
-    const int c = e / HID, k = e - c * HID;
-    L.W3[c][k] = P[oW3 + e];
-  }
-  L.b1[t] = P[ob1 + t];
-  L.b2[t] = P[ob2 + t];
-  if (t < NCH) L.b3[t] = P[ob3 + t];
-  for (int e = t; e < kAtoms * NF; e += kMlpThreads) {
-    const int a = e / NF, k = e - a * NF;
-    L.x[a][k] = (a < na) ? feat[size_t(a0 + a) * NF + k] : 0.0f;
-  }
-  for (int e = t; e < kAtoms * NCH * 3; e += kMlpThreads) {
-    const int a = e / (NCH * 3), k = e - a * NCH * 3;
-    L.V[a][k] = (a < na) ? vec[size_t(a0 + a) * NCH * 3 + k] : 0.0f;
-  }
-  __syncthreads();
-  // layer 1: thread t is hidden unit t
-  for (int a = 0; a < kAtoms; ++a) {
-    float z = L.b1[t];
-#pragma unroll
-    for (int k = 0; k < NF; ++k) z += L.W1T[k][t] * L.x[a][k];
-    L.z1[a][t] = z;
-    L.h1[a][t] = silu(z);
-  }
-  __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float z = L.b2[t];
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) z += L.W2T[k][t] * L.h1[a][k];
-    L.z2[a][t] = z;
-    L.h2[a][t] = silu(z);
-  }
-  __syncthreads();
-  // layer 3: 16 atoms x 16 outputs, four per thread
-  for (int e = t; e < kAtoms * NCH; e += kMlpThreads) {
-    const int a = e / NCH, c = e - a * NCH;
-    float z = L.b3[c];
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) z += L.W3[c][k] * L.h2[a][k];
-    L.w[a][c] = z;
-  }
-  __syncthreads();
+__device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f}; }
+
+// f(z) of the four units a lane holds
+template <class F>
+__device__ __forceinline__ f32x4 map4(f32x4 z, F f) {
+  return f32x4{f(z[0]), f(z[1]), f(z[2]), f(z[3])};
 }
 
-__global__ void __launch_bounds__(kMlpThreads) k_mlp_forward(int n, const float* P,
+// The inputs of atom a0 + l16 as the second operand of layer 1 (zeros past na or for a
+// NULL array): k = 16 T + 4 g + r, then k = 32 + g.
+struct NetIn {
+  float v[9];
+  __device__ __forceinline__ void load(const NetLane& L, const float* feat, int a0, int na) {
+    const bool in = feat && L.l16 < na;
+    const float* f = feat + size_t(a0 + L.l16) * NF;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = in ? f[16 * (k >> 2) + 4 * L.g + (k & 3)] : 0.0f;
+    v[8] = in && L.g < NF - 32 ? f[32 + L.g] : 0.0f;
+  }
+};
+
+// Layer 1 weights of the lane's row (hidden unit 16 w + l16) in the same order
+struct NetW1 {
+  float v[9];
+  __device__ __forceinline__ void load(const NetLane& L, const float* W) {
+    const float* f = W + (16 * L.w + L.l16) * NF;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = f[16 * (k >> 2) + 4 * L.g + (k & 3)];
+    v[8] = L.g < NF - 32 ? f[32 + L.g] : 0.0f;
+  }
+};
+
+__device__ __forceinline__ f32x4 layer1(const NetW1& W, const NetIn& x, f32x4 acc) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) acc = mma(W.v[k], x.v[k], acc);
+  return acc;
+}
+
+__device__ __forceinline__ f32x4 bias4(const NetLane& L, const float* b) {
+  const float* f = b + 16 * L.w + 4 * L.g;
+  return f32x4{f[0], f[1], f[2], f[3]};
+}
+
+// the lane's four units of its atom into a [16][HS] LDS matrix
+__device__ __forceinline__ void put_units(const NetLane& L, float (*m)[HS], f32x4 v) {
+  *reinterpret_cast<f32x4*>(&m[L.l16][16 * L.w + 4 * L.g]) = v;
+}
+
+// sum over the 64 units of m: acc += W m^T with the weights in w4 (k = 16 T + 4 g + r)
+__device__ __forceinline__ f32x4 contract64(const NetLane& L, const float (&w4)[16],
+                                            const float (*m)[HS], f32x4 acc) {
+#pragma unroll
+  for (int T = 0; T < 4; ++T) {
+    const f32x4 h = *reinterpret_cast<const f32x4*>(&m[L.l16][16 * T + 4 * L.g]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc = mma(w4[4 * T + r], h[r], acc);
+  }
+  return acc;
+}
+
+// Partial results of the four wavefronts (16 rows 4 g + r of atom l16 each) added up;
+// every wavefront gets the sum.  Two barriers; `part` is free after the second.
+__device__ __forceinline__ f32x4 sum_waves(const NetLane& L, float (*part)[16][CS], f32x4 v) {
+  *reinterpret_cast<f32x4*>(&part[L.w][L.l16][4 * L.g]) = v;
+  __syncthreads();
+  f32x4 s = zero4();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) s += *reinterpret_cast<const f32x4*>(&part[w][L.l16][4 * L.g]);
+  __syncthreads();
+  return s;
+}
+
+// Weights of the dipole head a lane feeds forward, loaded at once
+struct NetWeights {
+  NetW1 w1;
+  float w2[16], w3[4];
+  f32x4 b1, b2, b3;
+  __device__ __forceinline__ void load(const NetLane& L, const float* P) {
+    w1.load(L, P + oW1);
+    const float* r2 = P + oW2 + (16 * L.w + L.l16) * HID;
+    const float* r3 = P + oW3 + L.l16 * HID + 16 * L.w;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) w2[k] = r2[16 * (k >> 2) + 4 * L.g + (k & 3)];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w3[r] = r3[4 * L.g + r];
+    b1 = bias4(L, P + ob1);
+    b2 = bias4(L, P + ob2);
+    b3 = f32x4{P[ob3 + 4 * L.g], P[ob3 + 4 * L.g + 1], P[ob3 + 4 * L.g + 2], P[ob3 + 4 * L.g + 3]};
+  }
+};
+
+struct NetLds {
+  float h1[16][HS];
+  float part[4][16][CS];
+};
+template <bool DUAL>
+struct NetLdsT : NetLds {
+  float h1d[DUAL ? 16 : 1][HS];
+};
+
+// What the forward pass leaves in registers: pre-activations, activations and the
+// output weights w (channels 4 g + r of atom l16, in every wavefront); with DUAL their
+// tangents along feat_dot.
+template <bool DUAL>
+struct NetState {
+  f32x4 z1, z2, h2, w;
+  f32x4 z1d, z2d, h2d, wd;
+};
+
+template <bool DUAL>
+__device__ __forceinline__ void net_forward(const NetLane& L, const NetWeights& W, const NetIn& x,
+                                            const NetIn& xd, NetLdsT<DUAL>& m,
+                                            NetState<DUAL>& s) {
+  s.z1 = layer1(W.w1, x, W.b1);
+  put_units(L, m.h1, map4(s.z1, silu));
+  if constexpr (DUAL) {
+    s.z1d = layer1(W.w1, xd, zero4());
+    put_units(L, m.h1d, map4(s.z1, dsilu) * s.z1d);
+  }
+  __syncthreads();
+  s.z2 = contract64(L, W.w2, m.h1, W.b2);
+  s.h2 = map4(s.z2, silu);
+  f32x4 w = zero4(), wd = zero4();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) w = mma(W.w3[r], s.h2[r], w);
+  if constexpr (DUAL) {
+    s.z2d = contract64(L, W.w2, m.h1d, zero4());
+    s.h2d = map4(s.z2, dsilu) * s.z2d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) wd = mma(W.w3[r], s.h2d[r], wd);
+  }
+  s.w = sum_waves(L, m.part, w) + W.b3;
+  if constexpr (DUAL) s.wd = sum_waves(L, m.part, wd);
+}
+
+// Component d of the vector channels 4 g + r of atom a0 + l16 (zeros past na)
+__device__ __forceinline__ f32x4 channels(const NetLane& L, const float* vec, int a0, int na,
+                                          int d) {
+  f32x4 v = zero4();
+  if (vec && L.l16 < na) {
+    const float* f = vec + size_t(a0 + L.l16) * NCH * 3 + 12 * L.g + d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = f[3 * r];
+  }
+  return v;
+}
+__device__ __forceinline__ float sum_groups(float v) {   // over g, the four 16-lane groups
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
+__device__ __forceinline__ float dot4(f32x4 a, f32x4 b) {
+  return a[0] * b[0] + a[1] * b[1] + a[2] * b[2] + a[3] * b[3];
+}
+__device__ __forceinline__ float of3(const float* p, size_t k) { return p ? p[k] : 0.0f; }
+
+// mu = sum_c w_c V_c and with DUAL mu_dot = sum_c (wd_c V_c + w_c Vd_c); 16 atoms per
+// workgroup, component d by wavefront d.
+template <bool DUAL>
+__global__ void __launch_bounds__(kNetThreads) k_mlp_forward(int n, const float* P,
                                                              const float* feat, const float* vec,
-                                                             float* mu) {
-  __shared__ MlpLds L;
-  const int a0 = blockIdx.x * kAtoms;
-  const int na = min(kAtoms, n - a0);
-  mlp_eval(L, P, feat, vec, a0, na);
-  const int t = threadIdx.x;
-  if (t < 3 * kAtoms) {
-    const int a = t / 3, d = t - 3 * a;
-    if (a < na) {
-      float m = 0.0f;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) m += L.w[a][c] * L.V[a][3 * c + d];
-      mu[size_t(a0 + a) * 3 + d] = m;
-    }
+                                                             const float* feat_dot,
+                                                             const float* vec_dot, float* mu,
+                                                             float* mud) {
+  __shared__ __attribute__((aligned(16))) NetLdsT<DUAL> m;
+  const NetLane L;
+  const int a0 = blockIdx.x * 16, na = min(16, n - a0);
+  NetWeights W;
+  NetIn x, xd;
+  x.load(L, feat, a0, na);
+  if constexpr (DUAL) xd.load(L, feat_dot, a0, na);
+  W.load(L, P);
+  const int d = min(L.w, 2);
+  const f32x4 V = channels(L, vec, a0, na, d);
+  f32x4 Vd = zero4();
+  if constexpr (DUAL) Vd = channels(L, vec_dot, a0, na, d);
+  NetState<DUAL> s;
+  net_forward<DUAL>(L, W, x, xd, m, s);
+  const float v = sum_groups(dot4(s.w, V));
+  float vd = 0.0f;
+  if constexpr (DUAL) vd = sum_groups(dot4(s.wd, V) + dot4(s.w, Vd));
+  if (L.w < 3 && L.g == 0 && L.l16 < na) {
+    const size_t k = size_t(a0 + L.l16) * 3 + d;
+    if (mu) mu[k] = v;
+    if (DUAL && mud) mud[k] = vd;
   }
 }
 
-// Per-workgroup parameter gradient partials (part[block][NP]).
-__global__ void __launch_bounds__(kMlpThreads) k_mlp_backward(int n, const float* P,
-                                                              const float* feat, const float* vec,
-                                                              const float* g0, const float* g1,
-                                                              const float* g2, float* part) {
-  __shared__ MlpLds L;
-  __shared__ float gw[kAtoms][NCH + 1];
-  __shared__ float gz2[kAtoms][HP];
-  __shared__ float gz1[kAtoms][HP];
-  const int a0 = blockIdx.x * kAtoms;
-  const int na = min(kAtoms, n - a0);
-  mlp_eval(L, P, feat, vec, a0, na);
-  const int t = threadIdx.x;
-  // dL/dw_c = dL/dmu . V_c
-  for (int e = t; e < kAtoms * NCH; e += kMlpThreads) {
-    const int a = e / NCH, c = e - a * NCH;
-    float s = 0.0f;
-    if (a < na) {
+// The transposed products of the backward passes, weights loaded at once: W3 for
+// gh2 = W3^T gw (units 16 w + l16, channels 4 g + r), W2 for gh1 = W2^T gz2.
+struct NetBack {
+  float w3[4], w2[16];
+  __device__ __forceinline__ void load(const NetLane& L, const float* P) {
+    const int u = 16 * L.w + L.l16;
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const size_t k = size_t(a0 + a) * 3 + d;
-        const float g = (g0 ? g0[k] : 0.0f) + (g1 ? g1[k] : 0.0f) + (g2 ? g2[k] : 0.0f);
-        s += g * L.V[a][3 * c + d];
-      }
-    }
-    gw[a][c] = s;
-  }
-  __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float s = 0.0f;
+    for (int r = 0; r < 4; ++r) w3[r] = P[oW3 + (4 * L.g + r) * HID + u];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) s += L.W3[c][t] * gw[a][c];
-    gz2[a][t] = s * dsilu(L.z2[a][t]);
+    for (int k = 0; k < 16; ++k) w2[k] = P[oW2 + (16 * (k >> 2) + 4 * L.g + (k & 3)) * HID + u];
   }
-  __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float s = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) s += L.W2T[t][k] * gz2[a][k];   // W2[k][t]
-    gz1[a][t] = s * dsilu(L.z1[a][t]);
+};
+
+// Layer 1 transposed over the wavefront's own 16 units: its share of dL/dx_k for the
+// inputs 16 kt + 4 g + r (the species one-hot does not move)
+struct NetInBack {
+  float w[2][4];
+  __device__ __forceinline__ void load(const NetLane& L, const float* W1) {
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[kt][r] = W1[(16 * L.w + 4 * L.g + r) * NF + 16 * kt + L.l16];
   }
-  __syncthreads();
-  float* out = part + size_t(blockIdx.x) * NP;
-  // thread t owns row t of W1, W2 and b1, b2, column t of W3, and b3[t] (t < 16)
-  for (int k = 0; k < NF; ++k) {
-    float s = 0.0f;
-    for (int a = 0; a < kAtoms; ++a) s += gz1[a][t] * L.x[a][k];
-    out[oW1 + t * NF + k] = s;
+  __device__ __forceinline__ f32x4 run(int kt, f32x4 gz) const {
+    f32x4 acc = zero4();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) acc = mma(w[kt][r], gz[r], acc);
+    return acc;
   }
-  for (int k = 0; k < HID; ++k) {
-    float s = 0.0f;
-    for (int a = 0; a < kAtoms; ++a) s += gz2[a][t] * L.h1[a][k];
-    out[oW2 + t * HID + k] = s;
-  }
-  for (int c = 0; c < NCH; ++c) {
-    float s = 0.0f;
-    for (int a = 0; a < kAtoms; ++a) s += gw[a][c] * L.h2[a][t];
-    out[oW3 + c * HID + t] = s;
-  }
-  float sb1 = 0.0f, sb2 = 0.0f;
-  for (int a = 0; a < kAtoms; ++a) {
-    sb1 += gz1[a][t];
-    sb2 += gz2[a][t];
-  }
-  out[ob1 + t] = sb1;
-  out[ob2 + t] = sb2;
-  if (t < NCH) {
-    float s = 0.0f;
-    for (int a = 0; a < kAtoms; ++a) s += gw[a][t];
-    out[ob3 + t] = s;
-  }
-}
+};
 
 // Feature cotangents of the position vector-Jacobian product for dL/dmu = u:
 // fbar[i] = [dL/dG_i (16) | dL/dV_i (16 x 3)], with dL/dw_c = u . V_c run back through
 // the network to its inputs and dL/dV_c = w_c u + 2 (dL/dx_{16+c}) V_c.
-__global__ void __launch_bounds__(kMlpThreads) k_mlp_input_grad(int n, const float* P,
+__global__ void __launch_bounds__(kNetThreads) k_mlp_input_grad(int n, const float* P,
                                                                 const float* feat,
                                                                 const float* vec, const float* u,
                                                                 float* fbar) {
-  __shared__ MlpLds L;
-  __shared__ float gw[kAtoms][NCH + 1];
-  __shared__ float gz2[kAtoms][HP];   // later the input gradient (first 2 NCH inputs)
-  __shared__ float gz1[kAtoms][HP];
-  const int a0 = blockIdx.x * kAtoms;
-  const int na = min(kAtoms, n - a0);
-  mlp_eval(L, P, feat, vec, a0, na);
-  const int t = threadIdx.x;
-  for (int e = t; e < kAtoms * NCH; e += kMlpThreads) {
-    const int a = e / NCH, c = e - a * NCH;
-    float s = 0.0f;
-    if (a < na)
+  __shared__ __attribute__((aligned(16))) NetLdsT<false> m;
+  const NetLane L;
+  const int a0 = blockIdx.x * 16, na = min(16, n - a0);
+  NetWeights W;
+  NetBack B;
+  NetInBack I;
+  NetIn x;
+  x.load(L, feat, a0, na);
+  W.load(L, P);
+  B.load(L, P);
+  I.load(L, P + oW1);
+  f32x4 V[3], gw = zero4();
+  float uu[3];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) s += u[size_t(a0 + a) * 3 + d] * L.V[a][3 * c + d];
-    gw[a][c] = s;
+  for (int d = 0; d < 3; ++d) {
+    V[d] = channels(L, vec, a0, na, d);
+    uu[d] = L.l16 < na ? u[size_t(a0 + L.l16) * 3 + d] : 0.0f;
+    gw += uu[d] * V[d];
   }
-  __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float s = 0.0f;
+  NetState<false> s;
+  net_forward<false>(L, W, x, x, m, s);
+  f32x4 g = zero4();
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) s += L.W3[c][t] * gw[a][c];
-    gz2[a][t] = s * dsilu(L.z2[a][t]);
-  }
+  for (int r = 0; r < 4; ++r) g = mma(B.w3[r], gw[r], g);
+  put_units(L, m.h1, g * map4(s.z2, dsilu));   // h1 was last read before sum_waves' barriers
   __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float s = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) s += L.W2T[t][k] * gz2[a][k];   // W2[k][t]
-    gz1[a][t] = s * dsilu(L.z1[a][t]);
+  g = contract64(L, B.w2, m.h1, zero4()) * map4(s.z1, dsilu);
+  const f32x4 gG = sum_waves(L, m.part, I.run(0, g));
+  const f32x4 gS = sum_waves(L, m.part, I.run(1, g));
+  // wavefront w writes channel 4 g + w
+  if (L.l16 < na) {
+    float* f = fbar + size_t(a0 + L.l16) * 4 * NCH;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r == L.w) {
+        const int c = 4 * L.g + r;
+        f[c] = gG[r];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) f[NCH + 3 * c + d] = s.w[r] * uu[d] + 2.0f * gS[r] * V[d][r];
+      }
   }
-  __syncthreads();
-  // dL/dx_k = sum_o gz1[o] W1[o][k] for the inputs G and |V|^2 (the species one-hot
-  // does not move)
-  for (int e = t; e < kAtoms * 2 * NCH; e += kMlpThreads) {
-    const int a = e / (2 * NCH), k = e - a * 2 * NCH;
-    float s = 0.0f;
-#pragma unroll 8
-    for (int o = 0; o < HID; ++o) s += gz1[a][o] * L.W1T[k][o];
-    gz2[a][k] = s;
+}
+
+// sum_a A[a][row] B[a][col] over the 16 atoms: rows 16 rt + l16 of an LDS matrix (its
+// stride S) against b(atom, t) = B[4 g + t][col of the lane]
+template <int S, class Bf>
+__device__ __forceinline__ f32x4 outer16(const NetLane& L, const float (*A)[S], int row0, Bf b,
+                                         f32x4 acc) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) acc = mma(A[4 * L.g + t][row0 + L.l16], b(4 * L.g + t), acc);
+  return acc;
+}
+
+// Outer products of hidden-unit cotangents gz (LDS, the wavefront's rows 16 w ..) with
+// the 34 inputs, into three tiles of 16 columns
+__device__ __forceinline__ void outer_inputs(const NetLane& L, const float (*gz)[HS],
+                                             const float* feat, int a0, int na, f32x4 (&acc)[3]) {
+  if (!feat) return;
+#pragma unroll
+  for (int T = 0; T < 3; ++T) {
+    const int k = 16 * T + L.l16;
+    acc[T] = outer16<HS>(L, gz, 16 * L.w,
+                         [&](int a) { return k < NF && a < na ? feat[size_t(a0 + a) * NF + k] : 0.0f; },
+                         acc[T]);
   }
-  __syncthreads();
-  for (int e = t; e < kAtoms * 4 * NCH; e += kMlpThreads) {
-    const int a = e / (4 * NCH), k = e - a * 4 * NCH;
-    if (a >= na) continue;
-    float v;
-    if (k < NCH) {
-      v = gz2[a][k];
-    } else {
-      const int c = (k - NCH) / 3, d = (k - NCH) - 3 * c;
-      v = L.w[a][c] * u[size_t(a0 + a) * 3 + d] + 2.0f * gz2[a][NCH + c] * L.V[a][3 * c + d];
+}
+
+// the lane's rows 16 w + 4 g + r, columns 16 T + l16 < cols of a row-major array
+template <int T>
+__device__ __forceinline__ void put_rows(const NetLane& L, float* out, int cols,
+                                         const f32x4 (&acc)[T]) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int k = 16 * t + L.l16;
+    if (k < cols)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(16 * L.w + 4 * L.g + r) * cols + k] = acc[t][r];
+  }
+}
+// sums over the atoms of the lane's units (lanes of one group), written by its first lane
+__device__ __forceinline__ void put_sums(const NetLane& L, float* out, f32x4 v) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) v[r] += __shfl_xor(v[r], o, 16);
+    if (L.l16 == 0) out[4 * L.g + r] = v[r];
+  }
+}
+
+template <bool DUAL>
+struct GradLds : NetLdsT<DUAL> {
+  float h2[16][HS], gz1[16][HS], gz2[16][HS];
+  float gw[16][CS];
+  float h2d[DUAL ? 16 : 1][HS], gz1d[DUAL ? 16 : 1][HS], gz2d[DUAL ? 16 : 1][HS];
+  float gwd[DUAL ? 16 : 1][CS];
+};
+
+// Dipole-head parameter gradient.  Cotangents on w: gw_c = (g0 + g1 + g2) . V_c, and
+// with DUAL + u . Vd_c on w and gwd_c = u . V_c on wd, run back through the primal and
+// the tangent activations (silu'' couples them).  The workgroup walks the 16-atom tiles
+// blockIdx.x, + gridDim.x, ..; the weight gradients are outer products over its atoms,
+// kept in matrix accumulators and written once to the workgroup's partial row.
+template <bool DUAL>
+__global__ void __launch_bounds__(kNetThreads) k_mlp_backward(
+    int n, const float* P, const float* feat, const float* vec, const float* feat_dot,
+    const float* vec_dot, const float* g0, const float* g1, const float* g2, const float* u,
+    float* part) {
+  __shared__ __attribute__((aligned(16))) GradLds<DUAL> m;
+  const NetLane L;
+  NetWeights W;
+  NetBack B;
+  W.load(L, P);
+  B.load(L, P);
+  f32x4 aW1[3], aW2[4], aW3[1], ab1 = zero4(), ab2 = zero4(), ab3 = zero4();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) aW2[t] = zero4();
+#pragma unroll
+  for (int t = 0; t < 3; ++t) aW1[t] = zero4();
+  aW3[0] = zero4();
+  const int tiles = (n + 15) / 16;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int a0 = tile * 16, na = min(16, n - a0);
+    NetIn x, xd;
+    x.load(L, feat, a0, na);
+    if constexpr (DUAL) xd.load(L, feat_dot, a0, na);
+    f32x4 gw = zero4(), gwd = zero4();
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const f32x4 V = channels(L, vec, a0, na, d);
+      const size_t k = size_t(a0 + L.l16) * 3 + d;
+      const bool in = L.l16 < na;
+      gw += (in ? of3(g0, k) + of3(g1, k) + of3(g2, k) : 0.0f) * V;
+      if constexpr (DUAL) {
+        const float ud = in ? of3(u, k) : 0.0f;
+        gw += ud * channels(L, vec_dot, a0, na, d);
+        gwd += ud * V;
+      }
     }
-    fbar[size_t(a0 + a) * 4 * NCH + k] = v;
+    __syncthreads();   // the previous tile's outer products are done with the LDS
+    NetState<DUAL> s;
+    net_forward<DUAL>(L, W, x, xd, m, s);
+    put_units(L, m.h2, s.h2);
+    if constexpr (DUAL) put_units(L, m.h2d, s.h2d);
+    if (L.w == 0) {
+      *reinterpret_cast<f32x4*>(&m.gw[L.l16][4 * L.g]) = gw;
+      if constexpr (DUAL) *reinterpret_cast<f32x4*>(&m.gwd[L.l16][4 * L.g]) = gwd;
+      ab3 += gw;
+    }
+    f32x4 g = zero4(), gd = zero4();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) g = mma(B.w3[r], gw[r], g);
+    f32x4 ds = map4(s.z2, dsilu);
+    f32x4 gz2 = g * ds;
+    if constexpr (DUAL) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) gd = mma(B.w3[r], gwd[r], gd);
+      gz2 += gd * map4(s.z2, d2silu) * s.z2d;
+      put_units(L, m.gz2d, gd * ds);
+    }
+    put_units(L, m.gz2, gz2);
+    ab2 += gz2;
+    __syncthreads();
+    g = contract64(L, B.w2, m.gz2, zero4());
+    ds = map4(s.z1, dsilu);
+    f32x4 gz1 = g * ds;
+    if constexpr (DUAL) {
+      gd = contract64(L, B.w2, m.gz2d, zero4());
+      gz1 += gd * map4(s.z1, d2silu) * s.z1d;
+      put_units(L, m.gz1d, gd * ds);
+    }
+    put_units(L, m.gz1, gz1);
+    ab1 += gz1;
+    __syncthreads();
+    outer_inputs(L, m.gz1, feat, a0, na, aW1);
+#pragma unroll
+    for (int T = 0; T < 4; ++T)
+      aW2[T] = outer16<HS>(L, m.gz2, 16 * L.w, [&](int a) { return m.h1[a][16 * T + L.l16]; }, aW2[T]);
+    aW3[0] = outer16<CS>(L, m.gw, 0, [&](int a) { return m.h2[a][16 * L.w + L.l16]; }, aW3[0]);
+    if constexpr (DUAL) {
+      outer_inputs(L, m.gz1d, feat_dot, a0, na, aW1);
+#pragma unroll
+      for (int T = 0; T < 4; ++T)
+        aW2[T] = outer16<HS>(L, m.gz2d, 16 * L.w, [&](int a) { return m.h1d[a][16 * T + L.l16]; },
+                             aW2[T]);
+      aW3[0] = outer16<CS>(L, m.gwd, 0, [&](int a) { return m.h2d[a][16 * L.w + L.l16]; }, aW3[0]);
+    }
   }
+  float* out = part + size_t(blockIdx.x) * NP;
+  put_rows(L, out + oW1, NF, aW1);
+  put_rows(L, out + oW2, HID, aW2);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) out[oW3 + (4 * L.g + r) * HID + 16 * L.w + L.l16] = aW3[0][r];
+  put_sums(L, out + ob1 + 16 * L.w, ab1);
+  put_sums(L, out + ob2 + 16 * L.w, ab2);
+  if (L.w == 0) put_sums(L, out + ob3, ab3);
 }
 
 struct VjpArgs {
@@ -435,80 +661,48 @@ __global__ void __launch_bounds__(kFeatThreads) k_features_vjp(VjpArgs a) {
   }
 }
 
-// ---- Charge head, feature tangents and the dual (forward-mode) networks ----
+// ---- Charge head ------------------------------------------------------------------
 //
-// The charge head c_i = w2 . silu(W1 x_i + b1) runs 16 atoms per 64-thread
-// workgroup with a thread per hidden unit; the output sums over the hidden units
-// are wavefront butterflies (every lane ends with the same bits).  Centring uses
-// means from k_means, one workgroup reducing in a fixed order in FP64.
+// c_i = w2 . silu(W1 x_i + b1) on the same tiles: layer 1 by matrix instructions, the
+// output sum over the units of a lane, its group and the four wavefronts.
 
 constexpr int NQP = DIP_NQPARAM;
 constexpr int oQW1 = 0, oQb1 = HID * NF, oQw2 = oQb1 + HID;
 static_assert(oQw2 + HID == NQP, "charge head layout");
-constexpr int kAtomsD = 8;            // atoms per tile of the dual dipole network
-constexpr int kGradBlocks = 512;      // cap on the workgroups of the parameter gradients
+constexpr int kGradBlocks = 256;      // cap on the workgroups of the parameter gradients
 
-__device__ __forceinline__ float d2silu(float z) {
-  const float s = 1.0f / (1.0f + expf(-z));
-  return s * (1.0f - s) * (2.0f + z * (1.0f - 2.0f * s));
-}
-
-// rows [a0, a0 + na) of a [n][W] array into LDS rows of stride LD (zeros past na
-// or for a NULL source)
-template <int ROWS, int W, int LD>
-__device__ __forceinline__ void stage_rows(float (&dst)[ROWS][LD], const float* src, int a0,
-                                           int na) {
-  for (int e = threadIdx.x; e < ROWS * W; e += kMlpThreads) {
-    const int a = e / W, k = e - a * W;
-    dst[a][k] = (src && a < na) ? src[size_t(a0 + a) * W + k] : 0.0f;
-  }
-}
-
-struct QLds {
-  float W1T[NF][HP];     // W1T[k][o] = W1q[o][k]
-  float b1[HID], w2[HID];
-  float x[kAtoms][NF + 1];
-  float xd[kAtoms][NF + 1];
-  float s[kAtoms][HP];
-  float gx[kAtoms][2 * NCH + 1];
-};
-
-__device__ void q_stage_weights(QLds& L, const float* P) {
-  const int t = threadIdx.x;
-  for (int e = t; e < HID * NF; e += kMlpThreads) {
-    const int o = e / NF, k = e - o * NF;
-    L.W1T[k][o] = P[oQW1 + e];
-  }
-  L.b1[t] = P[oQb1 + t];
-  L.w2[t] = P[oQw2 + t];
-}
-
-// c and its tangent c_dot along feat_dot (uncentred), one 16-atom tile per workgroup
-__global__ void __launch_bounds__(kMlpThreads) k_qhead_forward(int n, const float* P,
+// c and its tangent c_dot along feat_dot (uncentred), and their sums over the tile's
+// atoms into csum[2 blockIdx.x ..] (FP64; k_qcentre adds them up)
+__global__ void __launch_bounds__(kNetThreads) k_qhead_forward(int n, const float* P,
                                                                const float* feat,
                                                                const float* feat_dot, float* c,
-                                                               float* cd) {
-  __shared__ QLds L;
-  const int a0 = blockIdx.x * kAtoms;
-  const int na = min(kAtoms, n - a0);
-  const int t = threadIdx.x;
-  q_stage_weights(L, P);
-  stage_rows<kAtoms, NF, NF + 1>(L.x, feat, a0, na);
-  stage_rows<kAtoms, NF, NF + 1>(L.xd, feat_dot, a0, na);
+                                                               float* cd, double* csum) {
+  __shared__ float part[2][4][16];
+  const NetLane L;
+  const int a0 = blockIdx.x * 16, na = min(16, n - a0);
+  NetW1 W;
+  NetIn x, xd;
+  x.load(L, feat, a0, na);
+  xd.load(L, feat_dot, a0, na);
+  W.load(L, P + oQW1);
+  const f32x4 w2 = bias4(L, P + oQw2);
+  const f32x4 z = layer1(W, x, bias4(L, P + oQb1)), zd = layer1(W, xd, zero4());
+  const float s = sum_groups(dot4(w2, map4(z, silu)));
+  const float sd = sum_groups(dot4(w2, map4(z, dsilu) * zd));
+  if (L.g == 0) {
+    part[0][L.w][L.l16] = s;
+    part[1][L.w][L.l16] = sd;
+  }
   __syncthreads();
-  for (int a = 0; a < kAtoms; ++a) {
-    float z = L.b1[t], zd = 0.0f;
+  if (threadIdx.x < 32) {   // lanes 0..15: c of atom l16, lanes 16..31: c_dot
+    const int which = threadIdx.x >> 4;
+    const float* p = part[which][0] + L.l16;
+    const float v = (p[0] + p[16]) + (p[32] + p[48]);
+    if (L.l16 < na) (which ? cd : c)[a0 + L.l16] = v;
+    double t = L.l16 < na ? double(v) : 0.0;
 #pragma unroll
-    for (int k = 0; k < NF; ++k) {
-      z += L.W1T[k][t] * L.x[a][k];
-      zd += L.W1T[k][t] * L.xd[a][k];
-    }
-    const float s = wave_sum(L.w2[t] * silu(z));
-    const float sd = wave_sum(L.w2[t] * dsilu(z) * zd);
-    if (t == 0 && a < na) {
-      c[a0 + a] = s;
-      cd[a0 + a] = sd;
-    }
+    for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 16);
+    if (L.l16 == 0) csum[2 * blockIdx.x + which] = t;
   }
 }
 
@@ -537,10 +731,29 @@ __global__ void __launch_bounds__(1024) k_means(int n, const float* a0, const fl
   }
 }
 
-// q = z + c - mean c; q_dot = c_dot - mean c_dot (either output may be NULL)
-__global__ void k_qcentre(int n, const float* z, const float* c, const float* cd,
-                          const double* mean, float* q, float* qd) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// q = z + c - mean c; q_dot = c_dot - mean c_dot (either output may be NULL).  Every
+// workgroup adds up the tiles' sums, in the same order.
+__global__ void __launch_bounds__(256) k_qcentre(int n, const float* z, const float* c,
+                                                 const float* cd, const double* csum, float* q,
+                                                 float* qd) {
+  __shared__ double red[2][4];
+  const int t = threadIdx.x;
+  double s[2] = {0.0, 0.0};
+  for (int k = t; k < (n + 15) / 16; k += 256) {
+    s[0] += csum[2 * k];
+    s[1] += csum[2 * k + 1];
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s[m] += __shfl_xor(s[m], o, 64);
+    if ((t & 63) == 0) red[m][t >> 6] = s[m];
+  }
+  __syncthreads();
+  double mean[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) mean[m] = ((red[m][0] + red[m][1]) + (red[m][2] + red[m][3])) / n;
+  const int i = blockIdx.x * 256 + t;
   if (i >= n) return;
   if (q) q[i] = z[i] + (c[i] - float(mean[0]));
   if (qd) qd[i] = cd[i] - float(mean[1]);
@@ -550,55 +763,47 @@ __global__ void k_qcentre(int n, const float* z, const float* c, const float* cd
 // mean[1]): dL/dx = sum_o (g - mean) w2_o silu'(z_o) W1q[o][:], mapped to
 // fbar = [dL/dG (16) | dL/dV (16 x 3)] with dL/dV_c = 2 (dL/dx_{16+c}) V_c; added
 // to fbar when `accumulate`.
-__global__ void __launch_bounds__(kMlpThreads) k_qhead_input_grad(int n, const float* P,
+__global__ void __launch_bounds__(kNetThreads) k_qhead_input_grad(int n, const float* P,
                                                                   const float* feat,
                                                                   const float* vec,
                                                                   const float* g,
                                                                   const double* mean,
                                                                   float* fbar, int accumulate) {
-  __shared__ QLds L;
-  const int a0 = blockIdx.x * kAtoms;
-  const int na = min(kAtoms, n - a0);
-  const int t = threadIdx.x;
-  q_stage_weights(L, P);
-  stage_rows<kAtoms, NF, NF + 1>(L.x, feat, a0, na);
-  __syncthreads();
-  const float gm = float(mean[1]);
-  for (int a = 0; a < kAtoms; ++a) {
-    float z = L.b1[t];
+  __shared__ __attribute__((aligned(16))) float part[4][16][CS];
+  const NetLane L;
+  const int a0 = blockIdx.x * 16, na = min(16, n - a0);
+  NetW1 W;
+  NetInBack I;
+  NetIn x;
+  x.load(L, feat, a0, na);
+  W.load(L, P + oQW1);
+  I.load(L, P + oQW1);
+  const float ga = L.l16 < na ? g[a0 + L.l16] - float(mean[1]) : 0.0f;
+  const f32x4 z = layer1(W, x, bias4(L, P + oQb1));
+  const f32x4 gz = ga * bias4(L, P + oQw2) * map4(z, dsilu);
+  const f32x4 gG = sum_waves(L, part, I.run(0, gz));
+  const f32x4 gS = sum_waves(L, part, I.run(1, gz));
+  if (L.l16 < na) {
+    float* f = fbar + size_t(a0 + L.l16) * 4 * NCH;
+    const float* V = vec + size_t(a0 + L.l16) * NCH * 3;
 #pragma unroll
-    for (int k = 0; k < NF; ++k) z += L.W1T[k][t] * L.x[a][k];
-    const float ga = a < na ? g[a0 + a] - gm : 0.0f;
-    L.s[a][t] = ga * L.w2[t] * dsilu(z);
-  }
-  __syncthreads();
-  for (int e = t; e < kAtoms * 2 * NCH; e += kMlpThreads) {
-    const int a = e / (2 * NCH), k = e - a * 2 * NCH;
-    float s = 0.0f;
-#pragma unroll 8
-    for (int o = 0; o < HID; ++o) s += L.s[a][o] * L.W1T[k][o];
-    L.gx[a][k] = s;
-  }
-  __syncthreads();
-  for (int e = t; e < kAtoms * 4 * NCH; e += kMlpThreads) {
-    const int a = e / (4 * NCH), k = e - a * 4 * NCH;
-    if (a >= na) continue;
-    float v;
-    if (k < NCH) {
-      v = L.gx[a][k];
-    } else {
-      const int c = (k - NCH) / 3, d = (k - NCH) - 3 * c;
-      v = 2.0f * L.gx[a][NCH + c] * vec[size_t(a0 + a) * NCH * 3 + 3 * c + d];
-    }
-    float* f = fbar + size_t(a0 + a) * 4 * NCH + k;
-    *f = accumulate ? *f + v : v;
+    for (int r = 0; r < 4; ++r)
+      if (r == L.w) {
+        const int c = 4 * L.g + r;
+        f[c] = accumulate ? f[c] + gG[r] : gG[r];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const int k = NCH + 3 * c + d;
+          const float v = 2.0f * gS[r] * V[3 * c + d];
+          f[k] = accumulate ? f[k] + v : v;
+        }
+      }
   }
 }
 
 // Charge-head parameter gradient from cotangents (g_q0 + g_q1 - mean[0]) on c and
-// (cq - mean[1]) on c_dot; the workgroup walks tiles blockIdx.x, + gridDim.x, ...
-// and keeps its thread's row of W1q, b1q[t] and w2q[t] in registers.
-__global__ void __launch_bounds__(kMlpThreads) k_qhead_backward(int n, const float* P,
+// (cq - mean[1]) on c_dot; tiles and partial rows as in k_mlp_backward.
+__global__ void __launch_bounds__(kNetThreads) k_qhead_backward(int n, const float* P,
                                                                 const float* feat,
                                                                 const float* feat_dot,
                                                                 const float* g_q0,
@@ -606,47 +811,39 @@ __global__ void __launch_bounds__(kMlpThreads) k_qhead_backward(int n, const flo
                                                                 const float* cq,
                                                                 const double* mean,
                                                                 float* part) {
-  __shared__ QLds L;
-  const int t = threadIdx.x;
-  q_stage_weights(L, P);
+  __shared__ __attribute__((aligned(16))) float gzs[16][HS], gzds[16][HS];
+  const NetLane L;
+  NetW1 W;
+  W.load(L, P + oQW1);
+  const f32x4 b1 = bias4(L, P + oQb1), w2 = bias4(L, P + oQw2);
   const float m0 = float(mean[0]), m1 = float(mean[1]);
-  float aW[NF];
-#pragma unroll
-  for (int k = 0; k < NF; ++k) aW[k] = 0.0f;
-  float ab = 0.0f, aw2 = 0.0f;
-  const int tiles = (n + kAtoms - 1) / kAtoms;
+  f32x4 aW[3] = {zero4(), zero4(), zero4()}, ab = zero4(), aw2 = zero4();
+  const int tiles = (n + 15) / 16;
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int a0 = tile * kAtoms;
-    const int na = min(kAtoms, n - a0);
-    __syncthreads();   // the previous tile's reads of x, xd are done
-    stage_rows<kAtoms, NF, NF + 1>(L.x, feat, a0, na);
-    stage_rows<kAtoms, NF, NF + 1>(L.xd, feat_dot, a0, na);
+    const int a0 = tile * 16, na = min(16, n - a0);
+    NetIn x, xd;
+    x.load(L, feat, a0, na);
+    xd.load(L, feat_dot, a0, na);
+    const size_t i = size_t(a0 + L.l16);
+    const bool in = L.l16 < na;
+    const float gc = in ? of3(g_q0, i) + of3(g_q1, i) - m0 : 0.0f;
+    const float gcd = in ? of3(cq, i) - m1 : 0.0f;
+    const f32x4 z = layer1(W, x, b1), zd = layer1(W, xd, zero4());
+    const f32x4 ds = map4(z, dsilu);
+    aw2 += gc * map4(z, silu) + gcd * ds * zd;
+    const f32x4 gz = gc * w2 * ds + gcd * w2 * map4(z, d2silu) * zd;
+    ab += gz;
+    __syncthreads();   // the previous tile's outer products are done with the LDS
+    put_units(L, gzs, gz);
+    put_units(L, gzds, gcd * w2 * ds);
     __syncthreads();
-    for (int a = 0; a < na; ++a) {
-      float z = L.b1[t], zd = 0.0f;
-#pragma unroll
-      for (int k = 0; k < NF; ++k) {
-        z += L.W1T[k][t] * L.x[a][k];
-        zd += L.W1T[k][t] * L.xd[a][k];
-      }
-      const size_t i = size_t(a0 + a);
-      const float gc = (g_q0 ? g_q0[i] : 0.0f) + (g_q1 ? g_q1[i] : 0.0f) - m0;
-      const float gcd = (cq ? cq[i] : 0.0f) - m1;
-      const float ds = dsilu(z);
-      aw2 += gc * silu(z) + gcd * ds * zd;
-      const float gh = gc * L.w2[t], ghd = gcd * L.w2[t];
-      const float gz = gh * ds + ghd * d2silu(z) * zd;
-      const float gzd = ghd * ds;
-      ab += gz;
-#pragma unroll
-      for (int k = 0; k < NF; ++k) aW[k] += gz * L.x[a][k] + gzd * L.xd[a][k];
-    }
+    outer_inputs(L, gzs, feat, a0, na, aW);
+    outer_inputs(L, gzds, feat_dot, a0, na, aW);
   }
   float* out = part + size_t(blockIdx.x) * NQP;
-#pragma unroll
-  for (int k = 0; k < NF; ++k) out[oQW1 + t * NF + k] = aW[k];
-  out[oQb1 + t] = ab;
-  out[oQw2 + t] = aw2;
+  put_rows(L, out + oQW1, NF, aW);
+  put_sums(L, out + oQb1 + 16 * L.w, ab);
+  put_sums(L, out + oQw2 + 16 * L.w, aw2);
 }
 
 struct FeatJvpArgs {
@@ -727,223 +924,26 @@ __global__ void __launch_bounds__(kFeatThreads) k_features_jvp(FeatJvpArgs a) {
   if (lane < NS) f[2 * NCH + lane] = 0.0f;
 }
 
-// LDS of the dual dipole network: the weights once per workgroup, and per tile
-// the primal and tangent activations of kAtomsD atoms
-struct DualLds {
-  float W1T[NF][HP];
-  float W2T[HID][HP];
-  float W3[NCH][HP];
-  float b1[HID], b2[HID], b3[NCH];
-  float x[kAtomsD][NF + 1], xd[kAtomsD][NF + 1];
-  float z1[kAtomsD][HP], z1d[kAtomsD][HP], h1[kAtomsD][HP], h1d[kAtomsD][HP];
-  float z2[kAtomsD][HP], z2d[kAtomsD][HP], h2[kAtomsD][HP], h2d[kAtomsD][HP];
-  float w[kAtomsD][NCH + 1], wd[kAtomsD][NCH + 1];
-  float V[kAtomsD][NCH * 3 + 1], Vd[kAtomsD][NCH * 3 + 1];
-};
-
-__device__ void dual_stage_weights(DualLds& L, const float* P) {
-  const int t = threadIdx.x;
-  for (int e = t; e < HID * NF; e += kMlpThreads) {
-    const int o = e / NF, k = e - o * NF;
-    L.W1T[k][o] = P[oW1 + e];
-  }
-  for (int e = t; e < HID * HID; e += kMlpThreads) {
-    const int o = e / HID, k = e - o * HID;
-    L.W2T[k][o] = P[oW2 + e];
-  }
-  for (int e = t; e < NCH * HID; e += kMlpThreads) {
-    const int c = e / HID, k = e - c * HID;
-    L.W3[c][k] = P[oW3 + e];
-  }
-  L.b1[t] = P[ob1 + t];
-  L.b2[t] = P[ob2 + t];
-  if (t < NCH) L.b3[t] = P[ob3 + t];
-}
-
-// One tile through the network in forward mode (weights already staged); leaves
-// every activation and its tangent in LDS.
-__device__ void dual_eval(DualLds& L, const float* feat, const float* vec, const float* feat_dot,
-                          const float* vec_dot, int a0, int na) {
-  const int t = threadIdx.x;
-  stage_rows<kAtomsD, NF, NF + 1>(L.x, feat, a0, na);
-  stage_rows<kAtomsD, NF, NF + 1>(L.xd, feat_dot, a0, na);
-  stage_rows<kAtomsD, NCH * 3, NCH * 3 + 1>(L.V, vec, a0, na);
-  stage_rows<kAtomsD, NCH * 3, NCH * 3 + 1>(L.Vd, vec_dot, a0, na);
-  __syncthreads();
-  for (int a = 0; a < kAtomsD; ++a) {
-    float z = L.b1[t], zd = 0.0f;
-#pragma unroll
-    for (int k = 0; k < NF; ++k) {
-      z += L.W1T[k][t] * L.x[a][k];
-      zd += L.W1T[k][t] * L.xd[a][k];
-    }
-    L.z1[a][t] = z;
-    L.z1d[a][t] = zd;
-    L.h1[a][t] = silu(z);
-    L.h1d[a][t] = dsilu(z) * zd;
-  }
-  __syncthreads();
-  for (int a = 0; a < kAtomsD; ++a) {
-    float z = L.b2[t], zd = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) {
-      z += L.W2T[k][t] * L.h1[a][k];
-      zd += L.W2T[k][t] * L.h1d[a][k];
-    }
-    L.z2[a][t] = z;
-    L.z2d[a][t] = zd;
-    L.h2[a][t] = silu(z);
-    L.h2d[a][t] = dsilu(z) * zd;
-  }
-  __syncthreads();
-  for (int e = t; e < kAtomsD * NCH; e += kMlpThreads) {
-    const int a = e / NCH, c = e - a * NCH;
-    float z = L.b3[c], zd = 0.0f;
-#pragma unroll 8
-    for (int k = 0; k < HID; ++k) {
-      z += L.W3[c][k] * L.h2[a][k];
-      zd += L.W3[c][k] * L.h2d[a][k];
-    }
-    L.w[a][c] = z;
-    L.wd[a][c] = zd;
-  }
-  __syncthreads();
-}
-
-// mu = sum_c w_c V_c and mu_dot = sum_c (wd_c V_c + w_c Vd_c), one tile per workgroup
-__global__ void __launch_bounds__(kMlpThreads) k_mlp_jvp_forward(int n, const float* P,
-                                                                 const float* feat,
-                                                                 const float* vec,
-                                                                 const float* feat_dot,
-                                                                 const float* vec_dot, float* mu,
-                                                                 float* mud) {
-  __shared__ DualLds L;
-  const int a0 = blockIdx.x * kAtomsD;
-  const int na = min(kAtomsD, n - a0);
-  dual_stage_weights(L, P);
-  dual_eval(L, feat, vec, feat_dot, vec_dot, a0, na);
-  const int t = threadIdx.x;
-  if (t < 3 * kAtomsD) {
-    const int a = t / 3, d = t - 3 * a;
-    if (a < na) {
-      float m = 0.0f, md = 0.0f;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        m += L.w[a][c] * L.V[a][3 * c + d];
-        md += L.wd[a][c] * L.V[a][3 * c + d] + L.w[a][c] * L.Vd[a][3 * c + d];
-      }
-      if (mu) mu[size_t(a0 + a) * 3 + d] = m;
-      if (mud) mud[size_t(a0 + a) * 3 + d] = md;
-    }
-  }
-}
-
-// Dipole-head parameter gradient through the dual network: cotangents
-// gw_c = (g_mu0 + g_mu1) . V_c + u . Vd_c on w and gwd_c = u . V_c on wd, run back
-// through both the primal and the tangent activations (silu'' couples them).  The
-// workgroup walks tiles blockIdx.x, + gridDim.x, ...; thread t keeps row t of W1
-// and W2, column t of W3 and its biases in registers and writes them once to its
-// partial row.
-__global__ void __launch_bounds__(kMlpThreads) k_mlp_jvp_backward(
-    int n, const float* P, const float* feat, const float* vec, const float* feat_dot,
-    const float* vec_dot, const float* g_mu0, const float* g_mu1, const float* u, float* part) {
-  __shared__ DualLds L;
-  __shared__ float gw[kAtomsD][NCH + 1], gwd[kAtomsD][NCH + 1];
-  __shared__ float gz2[kAtomsD][HP], gz2d[kAtomsD][HP];
-  __shared__ float gz1[kAtomsD][HP], gz1d[kAtomsD][HP];
-  const int t = threadIdx.x;
-  dual_stage_weights(L, P);
-  float aW1[NF], aW2[HID], aW3[NCH];
-#pragma unroll
-  for (int k = 0; k < NF; ++k) aW1[k] = 0.0f;
-#pragma unroll
-  for (int k = 0; k < HID; ++k) aW2[k] = 0.0f;
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) aW3[c] = 0.0f;
-  float ab1 = 0.0f, ab2 = 0.0f, ab3 = 0.0f;
-  const int tiles = (n + kAtomsD - 1) / kAtomsD;
-  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
-    const int a0 = tile * kAtomsD;
-    const int na = min(kAtomsD, n - a0);
-    __syncthreads();   // the previous tile is done with the LDS
-    dual_eval(L, feat, vec, feat_dot, vec_dot, a0, na);
-    for (int e = t; e < kAtomsD * NCH; e += kMlpThreads) {
-      const int a = e / NCH, c = e - a * NCH;
-      float s = 0.0f, sd = 0.0f;
-      if (a < na) {
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const size_t k = size_t(a0 + a) * 3 + d;
-          const float g = (g_mu0 ? g_mu0[k] : 0.0f) + (g_mu1 ? g_mu1[k] : 0.0f);
-          const float uk = u ? u[k] : 0.0f;
-          s += g * L.V[a][3 * c + d] + uk * L.Vd[a][3 * c + d];
-          sd += uk * L.V[a][3 * c + d];
-        }
-      }
-      gw[a][c] = s;
-      gwd[a][c] = sd;
-    }
-    __syncthreads();
-    for (int a = 0; a < kAtomsD; ++a) {
-      float s = 0.0f, sd = 0.0f;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        s += L.W3[c][t] * gw[a][c];
-        sd += L.W3[c][t] * gwd[a][c];
-      }
-      const float z = L.z2[a][t];
-      const float ds = dsilu(z);
-      gz2[a][t] = s * ds + sd * d2silu(z) * L.z2d[a][t];
-      gz2d[a][t] = sd * ds;
-    }
-    __syncthreads();
-    for (int a = 0; a < kAtomsD; ++a) {
-      float s = 0.0f, sd = 0.0f;
-#pragma unroll 8
-      for (int k = 0; k < HID; ++k) {
-        s += L.W2T[t][k] * gz2[a][k];      // W2[k][t]
-        sd += L.W2T[t][k] * gz2d[a][k];
-      }
-      const float z = L.z1[a][t];
-      const float ds = dsilu(z);
-      gz1[a][t] = s * ds + sd * d2silu(z) * L.z1d[a][t];
-      gz1d[a][t] = sd * ds;
-    }
-    __syncthreads();
-    for (int a = 0; a < kAtomsD; ++a) {
-      const float g1 = gz1[a][t], g1d = gz1d[a][t];
-      const float g2 = gz2[a][t], g2d = gz2d[a][t];
-#pragma unroll
-      for (int k = 0; k < NF; ++k) aW1[k] += g1 * L.x[a][k] + g1d * L.xd[a][k];
-#pragma unroll
-      for (int k = 0; k < HID; ++k) aW2[k] += g2 * L.h1[a][k] + g2d * L.h1d[a][k];
-      const float h = L.h2[a][t], hd = L.h2d[a][t];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) aW3[c] += gw[a][c] * h + gwd[a][c] * hd;
-      ab1 += g1;
-      ab2 += g2;
-      if (t < NCH) ab3 += gw[a][t];
-    }
-  }
-  float* out = part + size_t(blockIdx.x) * NP;
-#pragma unroll
-  for (int k = 0; k < NF; ++k) out[oW1 + t * NF + k] = aW1[k];
-#pragma unroll
-  for (int k = 0; k < HID; ++k) out[oW2 + t * HID + k] = aW2[k];
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) out[oW3 + c * HID + t] = aW3[c];
-  out[ob1 + t] = ab1;
-  out[ob2 + t] = ab2;
-  if (t < NCH) out[ob3 + t] = ab3;
-}
-
-// g[p] = sum over nb partial rows of width `width` in row order
-__global__ void k_rows_reduce(int nb, int width, const float* part, float* g) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= width) return;
+// g[p] = sum over nb partial rows of width `width`, in a fixed order: 32 columns and 8
+// groups of rows per workgroup.  A thread per column alone left 30 workgroups walking
+// 512 rows each (91 us for the 7440 parameters; now 4 us).
+__global__ void __launch_bounds__(256) k_rows_reduce(int nb, int width, const float* part,
+                                                     float* g) {
+  __shared__ float s_part[8][32];
+  const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int p = blockIdx.x * 32 + col;
   float s = 0.0f;
-  for (int b = 0; b < nb; ++b) s += part[size_t(b) * width + p];
-  g[p] = s;
+  if (p < width)
+#pragma unroll 8
+    for (int b = grp; b < nb; b += 8) s += part[size_t(b) * width + p];
+  s_part[grp][col] = s;
+  __syncthreads();
+  if (grp == 0 && p < width) {
+    float t = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t += s_part[k][col];
+    g[p] = t;
+  }
 }
 
 __global__ void __launch_bounds__(1024) k_loss(int n, const double* Us, const double* Ut,
@@ -998,25 +998,38 @@ int dip_fail(hipError_t e) {
   return PME_EHIP;
 }
 
-inline int mlp_blocks(int n) { return n > 0 ? (n + kAtoms - 1) / kAtoms : 1; }
+inline int mlp_blocks(int n) { return n > 0 ? (n + 15) / 16 : 1; }
+inline int grad_blocks(int n) { return mlp_blocks(n) < kGradBlocks ? mlp_blocks(n) : kGradBlocks; }
+
+// add up nb partial rows
+void launch_reduce(hipStream_t s, int nb, int width, const float* part, float* g) {
+  hipLaunchKernelGGL(k_rows_reduce, dim3((width + 31) / 32), dim3(256), 0, s, nb, width, part, g);
+}
 
 }  // namespace
-
-inline int grad_blocks(int n, int per) {
-  const int tiles = n > 0 ? (n + per - 1) / per : 1;
-  return tiles < kGradBlocks ? tiles : kGradBlocks;
-}
 
 struct dip_plan_s {
   dip_desc_t desc;
   CellList cells;
-  float* part = nullptr;     // [mlp blocks][NP]
+  float* part = nullptr;     // [grad_blocks(max_atoms)][NP] dipole-head partials
+  float* qpart = nullptr;    // [grad_blocks(max_atoms)][NQP] charge-head partials
   float* fbar = nullptr;     // [max_atoms][64] feature cotangents (position VJP)
-  float* dpart = nullptr;    // [grad_blocks(max_atoms, kAtomsD)][NP] dual-network partials
-  float* qpart = nullptr;    // [grad_blocks(max_atoms, kAtoms)][NQP] charge-head partials
   float* qbuf = nullptr;     // [2][max_atoms] charge-head outputs c, c_dot
+  double* csum = nullptr;    // [mlp_blocks(max_atoms)][2] their sums per tile
   double* means = nullptr;   // [2]
 };
+
+namespace {
+
+void dip_free(dip_plan_s* pl) {
+  free_cells(pl->cells);
+  void* ptrs[] = {pl->part, pl->qpart, pl->fbar, pl->qbuf, pl->csum, pl->means};
+  for (void* q : ptrs)
+    if (q) (void)hipFree(q);
+  delete pl;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -1029,23 +1042,18 @@ int dip_plan_create(const dip_desc_t* desc, dip_plan_t* out) {
   pl->desc = *desc;
   int rc = setup_cells(pl->cells, desc->box, desc->cutoff, desc->max_atoms);
   hipError_t e = hipSuccess;
-  if (rc == PME_OK)
-    e = hipMalloc(&pl->part, sizeof(float) * size_t(mlp_blocks(desc->max_atoms)) * NP);
-  if (rc == PME_OK && e == hipSuccess)
-    e = hipMalloc(&pl->fbar, sizeof(float) * size_t(desc->max_atoms) * 4 * NCH);
-  if (rc == PME_OK && e == hipSuccess)
-    e = hipMalloc(&pl->dpart, sizeof(float) * size_t(grad_blocks(desc->max_atoms, kAtomsD)) * NP);
-  if (rc == PME_OK && e == hipSuccess)
-    e = hipMalloc(&pl->qpart, sizeof(float) * size_t(grad_blocks(desc->max_atoms, kAtoms)) * NQP);
-  if (rc == PME_OK && e == hipSuccess)
-    e = hipMalloc(&pl->qbuf, sizeof(float) * 2 * size_t(desc->max_atoms));
-  if (rc == PME_OK && e == hipSuccess) e = hipMalloc(&pl->means, sizeof(double) * 2);
+  if (rc == PME_OK) {
+    const size_t n = size_t(desc->max_atoms), nb = size_t(grad_blocks(desc->max_atoms));
+    auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
+    ok(hipMalloc(&pl->part, sizeof(float) * nb * NP));
+    ok(hipMalloc(&pl->qpart, sizeof(float) * nb * NQP));
+    ok(hipMalloc(&pl->fbar, sizeof(float) * n * 4 * NCH));
+    ok(hipMalloc(&pl->qbuf, sizeof(float) * 2 * n));
+    ok(hipMalloc(&pl->csum, sizeof(double) * 2 * mlp_blocks(desc->max_atoms)));
+    ok(hipMalloc(&pl->means, sizeof(double) * 2));
+  }
   if (rc != PME_OK || e != hipSuccess) {
-    free_cells(pl->cells);
-    void* ptrs[] = {pl->part, pl->fbar, pl->dpart, pl->qpart, pl->qbuf, pl->means};
-    for (void* q : ptrs)
-      if (q) (void)hipFree(q);
-    delete pl;
+    dip_free(pl);
     return rc != PME_OK ? rc : (e == hipErrorOutOfMemory ? PME_ENOMEM : dip_fail(e));
   }
   *out = pl;
@@ -1055,11 +1063,7 @@ int dip_plan_create(const dip_desc_t* desc, dip_plan_t* out) {
 void dip_plan_destroy(dip_plan_t plan) {
   if (!plan) return;
   (void)hipDeviceSynchronize();
-  free_cells(plan->cells);
-  void* ptrs[] = {plan->part, plan->fbar, plan->dpart, plan->qpart, plan->qbuf, plan->means};
-  for (void* q : ptrs)
-    if (q) (void)hipFree(q);
-  delete plan;
+  dip_free(plan);
 }
 
 int dip_features(dip_plan_t plan, void* stream, int32_t n, const float* pos, const float* q,
@@ -1086,8 +1090,8 @@ int dip_forward(dip_plan_t plan, void* stream, int32_t n, const float* params, c
     return PME_EINVAL;
   if (n == 0) return PME_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_mlp_forward, dim3(mlp_blocks(n)), dim3(kMlpThreads), 0, s, n, params,
-                     feat, vec, mu);
+  hipLaunchKernelGGL(k_mlp_forward<false>, dim3(mlp_blocks(n)), dim3(kNetThreads), 0, s, n,
+                     params, feat, vec, nullptr, nullptr, mu, nullptr);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
 }
@@ -1099,12 +1103,11 @@ int dip_backward(dip_plan_t plan, void* stream, int32_t n, const float* params, 
       (n > 0 && (!params || !feat || !vec)))
     return PME_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int nb = n > 0 ? mlp_blocks(n) : 0;
+  const int nb = n > 0 ? grad_blocks(n) : 0;
   if (n > 0)
-    hipLaunchKernelGGL(k_mlp_backward, dim3(nb), dim3(kMlpThreads), 0, s, n, params, feat, vec,
-                       g_mu0, g_mu1, g_mu2, plan->part);
-  hipLaunchKernelGGL(k_rows_reduce, dim3((NP + 255) / 256), dim3(256), 0, s, nb, NP, plan->part,
-                     g_params);
+    hipLaunchKernelGGL(k_mlp_backward<false>, dim3(nb), dim3(kNetThreads), 0, s, n, params, feat,
+                       vec, nullptr, nullptr, g_mu0, g_mu1, g_mu2, nullptr, plan->part);
+  launch_reduce(s, nb, NP, plan->part, g_params);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
 }
@@ -1121,11 +1124,11 @@ int dip_position_vjp(dip_plan_t plan, void* stream, int32_t n, const float* para
   hipError_t e = build_cells(plan->cells, s, n, pos);
   if (e != hipSuccess) return dip_fail(e);
   if (u)
-    hipLaunchKernelGGL(k_mlp_input_grad, dim3(mlp_blocks(n)), dim3(kMlpThreads), 0, s, n, params,
+    hipLaunchKernelGGL(k_mlp_input_grad, dim3(mlp_blocks(n)), dim3(kNetThreads), 0, s, n, params,
                        feat, vec, u, plan->fbar);
   if (c) {
     hipLaunchKernelGGL(k_means, dim3(1), dim3(1024), 0, s, n, nullptr, nullptr, c, plan->means);
-    hipLaunchKernelGGL(k_qhead_input_grad, dim3(mlp_blocks(n)), dim3(kMlpThreads), 0, s, n,
+    hipLaunchKernelGGL(k_qhead_input_grad, dim3(mlp_blocks(n)), dim3(kNetThreads), 0, s, n,
                        qparams, feat, vec, c, plan->means, plan->fbar, u ? 1 : 0);
   }
   VjpArgs a;
@@ -1167,10 +1170,9 @@ int dip_charges(dip_plan_t plan, void* stream, int32_t n, const float* qparams, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   float* c = plan->qbuf;
   float* cd = plan->qbuf + plan->desc.max_atoms;
-  hipLaunchKernelGGL(k_qhead_forward, dim3(mlp_blocks(n)), dim3(kMlpThreads), 0, s, n, qparams,
-                     feat, feat_dot, c, cd);
-  hipLaunchKernelGGL(k_means, dim3(1), dim3(1024), 0, s, n, c, nullptr, cd, plan->means);
-  hipLaunchKernelGGL(k_qcentre, dim3((n + 255) / 256), dim3(256), 0, s, n, z, c, cd, plan->means,
+  hipLaunchKernelGGL(k_qhead_forward, dim3(mlp_blocks(n)), dim3(kNetThreads), 0, s, n, qparams,
+                     feat, feat_dot, c, cd, plan->csum);
+  hipLaunchKernelGGL(k_qcentre, dim3((n + 255) / 256), dim3(256), 0, s, n, z, c, cd, plan->csum,
                      q, q_dot);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
@@ -1184,8 +1186,8 @@ int dip_forward_jvp(dip_plan_t plan, void* stream, int32_t n, const float* param
     return PME_EINVAL;
   if (n == 0) return PME_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_mlp_jvp_forward, dim3((n + kAtomsD - 1) / kAtomsD), dim3(kMlpThreads), 0,
-                     s, n, params, feat, vec, feat_dot, vec_dot, mu, mu_dot);
+  hipLaunchKernelGGL(k_mlp_forward<true>, dim3(mlp_blocks(n)), dim3(kNetThreads), 0, s, n, params,
+                     feat, vec, feat_dot, vec_dot, mu, mu_dot);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
 }
@@ -1199,23 +1201,20 @@ int dip_backward_jvp(dip_plan_t plan, void* stream, int32_t n, const float* para
       (g_params && !params) || (g_qparams && !qparams) || (n > 0 && (!feat || !vec)))
     return PME_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const int nb = n > 0 ? grad_blocks(n) : 0;
   if (g_params) {
-    const int nb = grad_blocks(n, kAtomsD);
     if (n > 0)
-      hipLaunchKernelGGL(k_mlp_jvp_backward, dim3(nb), dim3(kMlpThreads), 0, s, n, params, feat,
-                         vec, feat_dot, vec_dot, g_mu0, g_mu1, u, plan->dpart);
-    hipLaunchKernelGGL(k_rows_reduce, dim3((NP + 255) / 256), dim3(256), 0, s, n > 0 ? nb : 0,
-                       NP, plan->dpart, g_params);
+      hipLaunchKernelGGL(k_mlp_backward<true>, dim3(nb), dim3(kNetThreads), 0, s, n, params, feat,
+                         vec, feat_dot, vec_dot, g_mu0, g_mu1, nullptr, u, plan->part);
+    launch_reduce(s, nb, NP, plan->part, g_params);
   }
   if (g_qparams) {
-    const int nb = grad_blocks(n, kAtoms);
     if (n > 0) {
       hipLaunchKernelGGL(k_means, dim3(1), dim3(1024), 0, s, n, g_q0, g_q1, c, plan->means);
-      hipLaunchKernelGGL(k_qhead_backward, dim3(nb), dim3(kMlpThreads), 0, s, n, qparams, feat,
+      hipLaunchKernelGGL(k_qhead_backward, dim3(nb), dim3(kNetThreads), 0, s, n, qparams, feat,
                          feat_dot, g_q0, g_q1, c, plan->means, plan->qpart);
     }
-    hipLaunchKernelGGL(k_rows_reduce, dim3((NQP + 255) / 256), dim3(256), 0, s, n > 0 ? nb : 0,
-                       NQP, plan->qpart, g_qparams);
+    launch_reduce(s, nb, NQP, plan->qpart, g_qparams);
   }
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? PME_OK : dip_fail(e);
