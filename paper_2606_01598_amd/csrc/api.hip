@@ -714,6 +714,26 @@ int forward_impl(pme_plan_t plan, void* stream, int32_t n, const float* pos, con
 
 }  // namespace
 
+int pme::dipole_response(pme_plan_s* plan, hipStream_t s, int n, const float* pos, const float* v,
+                         const double* box, float* out) {
+  if (n > plan->max_atoms) return PME_ECAPACITY;
+  DevPlan d = plan->d;
+  d.phi = d.rho;   // the potential replaces its density, as the tangent potential does
+  pme::KTimer& tm = plan->timer;
+  hipError_t e;
+  const int set = plan->set;
+  plan->set ^= 1;
+  if ((e = pme::launch_bin(d, s, set, n, pos, nullptr, v, box, nullptr, nullptr, nullptr, false,
+                           false, tm.next(PME_K_BIN))) != hipSuccess)
+    return hip_fail(e);
+  if ((e = spread_convolve(d, s, set, false, box, d.phi, false, tm)) != hipSuccess)
+    return hip_fail(e);
+  if ((e = pme::launch_gather(d, s, set, n, pos, nullptr, v, box, nullptr, nullptr, nullptr, out,
+                              0, tm.next(PME_K_GATHER))) != hipSuccess)
+    return hip_fail(e);
+  return PME_OK;
+}
+
 extern "C" {
 
 int pme_forward(pme_plan_t plan, void* stream, int32_t n, const float* pos, const float* q,

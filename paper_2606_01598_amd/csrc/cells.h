@@ -22,8 +22,25 @@ struct CellGrid {
   int ncell;
 };
 
+// Several device arrays out of one allocation (each is a call into the driver): take()
+// the sizes, allocate(), then ask for the addresses.
+struct Carve {
+  size_t bytes = 0;
+  char* base = nullptr;
+  template <class T>
+  size_t take(size_t count) {
+    const size_t at = bytes;
+    bytes += (sizeof(T) * count + 255) / 256 * 256;
+    return at;
+  }
+  hipError_t allocate() { return hipMalloc(reinterpret_cast<void**>(&base), bytes ? bytes : 256); }
+  template <class T>
+  T* at(size_t offset) const { return reinterpret_cast<T*>(base + offset); }
+};
+
 struct CellList {
   CellGrid g;
+  char* base = nullptr;             // the allocation that holds the arrays
   int* count = nullptr;             // [ncell]
   int* start = nullptr;             // [ncell + 1]
   int* cellof = nullptr;            // [max_atoms]
@@ -305,22 +322,24 @@ inline int setup_cells(CellList& cl, const double* C, double rc, int max_atoms) 
   }
   cl.g.ncell = int(ncell);
   for (int k = 0; k < 9; ++k) { cl.g.C[k] = float(C[k]); cl.g.Ci[k] = float(Ci[k]); }
-  const size_t m = size_t(max_atoms);
-  hipError_t e = hipSuccess;
-  auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
-  ok(hipMalloc(&cl.count, sizeof(int) * ncell));
-  ok(hipMalloc(&cl.start, sizeof(int) * (ncell + 1)));
-  ok(hipMalloc(&cl.cellof, sizeof(int) * m));
-  ok(hipMalloc(&cl.slot, sizeof(int) * m));
-  ok(hipMalloc(&cl.sp, sizeof(float4) * m));
+  const size_t m = size_t(max_atoms), c = size_t(ncell);
+  Carve all;
+  const size_t at_sp = all.take<float4>(m), at_count = all.take<int>(c),
+               at_start = all.take<int>(c + 1), at_cellof = all.take<int>(m),
+               at_slot = all.take<int>(m);
+  const hipError_t e = all.allocate();
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? PME_ENOMEM : PME_EHIP;
+  cl.base = all.base;
+  cl.sp = all.at<float4>(at_sp);
+  cl.count = all.at<int>(at_count);
+  cl.start = all.at<int>(at_start);
+  cl.cellof = all.at<int>(at_cellof);
+  cl.slot = all.at<int>(at_slot);
   return PME_OK;
 }
 
 inline void free_cells(CellList& cl) {
-  void* ptrs[] = {cl.count, cl.start, cl.cellof, cl.slot, cl.sp};
-  for (void* p : ptrs)
-    if (p) (void)hipFree(p);
+  if (cl.base) (void)hipFree(cl.base);
   cl = CellList();
 }
 

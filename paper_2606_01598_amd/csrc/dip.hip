@@ -1011,6 +1011,7 @@ void launch_reduce(hipStream_t s, int nb, int width, const float* part, float* g
 struct dip_plan_s {
   dip_desc_t desc;
   CellList cells;
+  char* base = nullptr;      // the allocation that holds the arrays
   float* part = nullptr;     // [grad_blocks(max_atoms)][NP] dipole-head partials
   float* qpart = nullptr;    // [grad_blocks(max_atoms)][NQP] charge-head partials
   float* fbar = nullptr;     // [max_atoms][64] feature cotangents (position VJP)
@@ -1023,9 +1024,7 @@ namespace {
 
 void dip_free(dip_plan_s* pl) {
   free_cells(pl->cells);
-  void* ptrs[] = {pl->part, pl->qpart, pl->fbar, pl->qbuf, pl->csum, pl->means};
-  for (void* q : ptrs)
-    if (q) (void)hipFree(q);
+  if (pl->base) (void)hipFree(pl->base);
   delete pl;
 }
 
@@ -1044,13 +1043,20 @@ int dip_plan_create(const dip_desc_t* desc, dip_plan_t* out) {
   hipError_t e = hipSuccess;
   if (rc == PME_OK) {
     const size_t n = size_t(desc->max_atoms), nb = size_t(grad_blocks(desc->max_atoms));
-    auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
-    ok(hipMalloc(&pl->part, sizeof(float) * nb * NP));
-    ok(hipMalloc(&pl->qpart, sizeof(float) * nb * NQP));
-    ok(hipMalloc(&pl->fbar, sizeof(float) * n * 4 * NCH));
-    ok(hipMalloc(&pl->qbuf, sizeof(float) * 2 * n));
-    ok(hipMalloc(&pl->csum, sizeof(double) * 2 * mlp_blocks(desc->max_atoms)));
-    ok(hipMalloc(&pl->means, sizeof(double) * 2));
+    Carve all;
+    const size_t at_part = all.take<float>(nb * NP), at_qpart = all.take<float>(nb * NQP),
+                 at_fbar = all.take<float>(n * 4 * NCH), at_qbuf = all.take<float>(2 * n),
+                 at_csum = all.take<double>(2 * size_t(mlp_blocks(desc->max_atoms))),
+                 at_means = all.take<double>(2);
+    if ((e = all.allocate()) == hipSuccess) {
+      pl->base = all.base;
+      pl->part = all.at<float>(at_part);
+      pl->qpart = all.at<float>(at_qpart);
+      pl->fbar = all.at<float>(at_fbar);
+      pl->qbuf = all.at<float>(at_qbuf);
+      pl->csum = all.at<double>(at_csum);
+      pl->means = all.at<double>(at_means);
+    }
   }
   if (rc != PME_OK || e != hipSuccess) {
     dip_free(pl);

@@ -7,6 +7,8 @@
 
 #include <vector>
 
+struct pme_plan_s;
+
 namespace pme {
 
 constexpr int kMaxStages = 16;
@@ -332,5 +334,11 @@ hipError_t launch_gather_hvp(const DevPlan& d, hipStream_t s, int set, int n, co
                              const float* v_pos, const float* v_q, const float* v_mu,
                              float* g_pos, float* g_q, float* g_mu, const LaunchEvents* ev,
                              const GatherForward* fwd = nullptr);
+
+// out = (d2E^lr / dmu dmu) v (api.hip): the gradient in mu of the dipoles v alone, since
+// E^lr is quadratic in them.  One forward of four coefficients an atom, which leaves the
+// plan's kept potential as it is; a PME_* code.
+int dipole_response(pme_plan_s* plan, hipStream_t s, int n, const float* pos, const float* v,
+                    const double* box, float* out);
 
 }  // namespace pme

@@ -46,7 +46,14 @@ struct PairArgs {
   float* o_pos;      // dE/dr
   float* o_q;        // dE/dq (or the q row of the Hessian product)
   float* o_mu;       // dE/dmu (or the mixed block, or the mu row)
-  double* epart;     // [blocks] energy partials
+  // added to the outputs (the long-range part; may be the outputs themselves) and, to
+  // o_mu, the polarization term (pf / a) p_mu; NULL = nothing
+  const float* b_pos;
+  const float* b_q;
+  const float* b_mu;
+  const float* p_mu;
+  double* epart;     // [blocks] energy partials, with p_mu including |mu|^2 / (2 a); or
+                     // (kMuGrad) partials of mu . o_mu
 };
 
 __device__ __forceinline__ float3 ld3(const float* p, int i) {
@@ -156,21 +163,31 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a) {
     e = wave_sum(e);
     gx = wave_sum(gx); gy = wave_sum(gy); gz = wave_sum(gz);
   }
+  double part = double(e);
   if (live && lane == 0) {
+    auto add = [](const float* b, int k, float v) { return b ? b[k] + v : v; };
     if (a.o_mu) {
-      a.o_mu[3 * i] = a.pf * mx;
-      a.o_mu[3 * i + 1] = a.pf * my;
-      a.o_mu[3 * i + 2] = a.pf * mz;
+      float o[3] = {add(a.b_mu, 3 * i, a.pf * mx), add(a.b_mu, 3 * i + 1, a.pf * my),
+                    add(a.b_mu, 3 * i + 2, a.pf * mz)};
+      if (a.p_mu)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) o[d] += a.pf * a.p_mu[3 * i + d] / ai;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) a.o_mu[3 * i + d] = o[d];
+      if (MODE == kMuGrad) part = double(mi.x) * o[0] + double(mi.y) * o[1] + double(mi.z) * o[2];
     }
-    if ((MODE == kEnergyGrad || MODE == kHvp) && a.o_q) a.o_q[i] = a.pf * gq;
+    if (MODE == kEnergyGrad && a.p_mu)
+      part += (double(mi.x) * mi.x + double(mi.y) * mi.y + double(mi.z) * mi.z) / (2.0 * double(ai));
+    if ((MODE == kEnergyGrad || MODE == kHvp) && a.o_q) a.o_q[i] = add(a.b_q, i, a.pf * gq);
     if (MODE == kEnergyGrad && a.o_pos) {
-      a.o_pos[3 * i] = a.pf * gx;
-      a.o_pos[3 * i + 1] = a.pf * gy;
-      a.o_pos[3 * i + 2] = a.pf * gz;
+      const float o[3] = {add(a.b_pos, 3 * i, a.pf * gx), add(a.b_pos, 3 * i + 1, a.pf * gy),
+                          add(a.b_pos, 3 * i + 2, a.pf * gz)};
+#pragma unroll
+      for (int d = 0; d < 3; ++d) a.o_pos[3 * i + d] = o[d];
     }
   }
-  if (MODE == kEnergyGrad && a.epart) {
-    if (lane == 0) red[wave] = live ? double(e) : 0.0;
+  if ((MODE == kEnergyGrad || MODE == kMuGrad) && a.epart) {
+    if (lane == 0) red[wave] = live ? part : 0.0;
     __syncthreads();
     if (threadIdx.x == 0) {
       double sum = 0.0;
@@ -180,127 +197,123 @@ __global__ void __launch_bounds__(kPairThreads) k_pair(PairArgs a) {
   }
 }
 
-// energy = pf * sum of block partials (one workgroup)
-__global__ void __launch_bounds__(256) k_energy_sum(const double* part, int nb, double pf,
-                                                    double* energy) {
-  __shared__ double red[256];
+// Sum of n doubles (stride `by`) by a workgroup of 256, in a fixed order; every thread
+// gets it.  `red` holds 4 values and is free after the call.
+__device__ __forceinline__ double sum256(const double* p, int n, int by, double* red) {
   double s = 0.0;
-  for (int k = threadIdx.x; k < nb; k += 256) s += part[k];
-  red[threadIdx.x] = s;
+  for (int k = threadIdx.x; k < n; k += 256) s += p[size_t(by) * k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) energy[0] = pf * red[0];
+  s = (red[0] + red[1]) + (red[2] + red[3]);
+  __syncthreads();
+  return s;
+}
+
+// energy = pf * sum of block partials, plus the three long-range terms (one workgroup)
+__global__ void __launch_bounds__(256) k_energy_sum(const double* part, int nb, double pf,
+                                                    const double* e_lr, double* energy) {
+  __shared__ double red[4];
+  const double s = sum256(part, nb, 1, red);
+  if (threadIdx.x == 0) energy[0] = (e_lr ? e_lr[0] + e_lr[1] + e_lr[2] : 0.0) + pf * s;
 }
 
 // ---- PCG vector kernels (length m = 3n) ----
+//
+// Dot products are FP64 partials per workgroup, added up in the same order by every
+// workgroup of the kernel that needs them: an iteration is the product (its pair kernel
+// leaves the partials of p . A p) and two launches, where single-workgroup dot products,
+// a copy of the scalars and the vector sums took six (25 us of an iteration at 4096
+// ions, now 10).  Grids are at most kPcgBlocks workgroups, so the partials stay few.
+constexpr int kPcgBlocks = 64;
 
-// Two dot products a.b and c.d in FP64 (one workgroup), into out[0], out[1].
-__global__ void __launch_bounds__(1024) k_dot2(int m, const float* a, const float* b,
-                                               const float* c, const float* d, double* out) {
-  __shared__ double r0[1024], r1[1024];
-  double s0 = 0.0, s1 = 0.0;
-  for (int k = threadIdx.x; k < m; k += 1024) {
-    s0 += double(a[k]) * b[k];
-    s1 += double(c[k]) * d[k];
+struct PcgResidual {   // in host memory: a workgroup's z . z and the step it belongs to
+  double zz;
+  unsigned long long step;
+};
+
+// block sums of (a, b) into part[2 blk ..], and b to the host with its step number
+__device__ __forceinline__ void pcg_partials(double a, double b, double* part, PcgResidual* host,
+                                             unsigned long long step, double* red) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a += __shfl_xor(a, o, 64);
+    b += __shfl_xor(b, o, 64);
   }
-  r0[threadIdx.x] = s0;
-  r1[threadIdx.x] = s1;
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * (threadIdx.x >> 6)] = a;
+    red[2 * (threadIdx.x >> 6) + 1] = b;
+  }
   __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (threadIdx.x < o) {
-      r0[threadIdx.x] += r0[threadIdx.x + o];
-      r1[threadIdx.x] += r1[threadIdx.x + o];
+  if (threadIdx.x == 0) {
+    const double sa = (red[0] + red[2]) + (red[4] + red[6]);
+    const double sb = (red[1] + red[3]) + (red[5] + red[7]);
+    part[2 * blockIdx.x] = sa;
+    part[2 * blockIdx.x + 1] = sb;
+    if (host) {
+      PcgResidual* h = host + blockIdx.x;
+      *reinterpret_cast<volatile double*>(&h->zz) = sb;
+      __threadfence_system();
+      *reinterpret_cast<volatile unsigned long long*>(&h->step) = step;
     }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) { out[0] = r0[0]; out[1] = r1[0]; }
 }
 
-// Av = (pf / a) v + g1 + g2
-__global__ void k_matvec_sum(int m, float pf, const float* pol, const float* v, const float* g1,
-                             const float* g2, float* Av) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < m) Av[k] = pf * v[k] / pol[k / 3] + g1[k] + g2[k];
-}
-
-// r = -(g1 + g2) - (warm ? Ax : 0); x = warm ? x : 0; z = (a / pf) r; p = z
-__global__ void k_pcg_start(int m, float pf, const float* pol, const float* g1, const float* g2,
-                            const float* Ax, float* x, float* r, float* z, float* p, int warm) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= m) return;
-  float rk = -(g1[k] + g2[k]);
-  if (warm) rk -= Ax[k];
-  else x[k] = 0.0f;
-  const float zk = pol[k / 3] / pf * rk;
-  r[k] = rk;
-  z[k] = zk;
-  p[k] = zk;
-}
-
-// scal: [0] r.z  [1] z.z  [2] p.Ap  [3] (unused)  [4] new r.z  [5] new z.z
-// alpha = r.z / p.Ap; x += alpha p; r -= alpha Ap; z = (a / pf) r
-__global__ void k_pcg_step(int m, float pf, const float* pol, const double* scal, const float* p,
-                           const float* Ap, float* x, float* r, float* z) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= m) return;
-  const double pap = scal[2];
-  const float al = pap != 0.0 ? float(scal[0] / pap) : 0.0f;
-  x[k] += al * p[k];
-  const float rk = r[k] - al * Ap[k];
-  r[k] = rk;
-  z[k] = pol[k / 3] / pf * rk;
-}
-
-// beta = new r.z / r.z; p = z + beta p
-__global__ void k_pcg_dir(int m, const double* scal, const float* z, float* p) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= m) return;
-  const float be = scal[0] != 0.0 ? float(scal[4] / scal[0]) : 0.0f;
-  p[k] = z[k] + be * p[k];
-}
-
-// dU_dpos = g_pos + h_pos; dU_dmu = g_mu + h_mu + (pf / a) mu (each output optional)
-__global__ void k_model_grads(int n, float pf, const float* pol, const float* mu,
-                              const float* gp, const float* hp, const float* gm, const float* hm,
-                              float* dpos, float* dmu) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= 3 * n) return;
-  if (dpos) dpos[k] = gp[k] + hp[k];
-  if (dmu) dmu[k] = gm[k] + hm[k] + (mu ? pf * mu[k] / pol[k / 3] : 0.0f);
-}
-
-// dU_dq = g_q + h_q
-__global__ void k_add(int m, const float* a, const float* b, float* out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < m) out[k] = a[k] + b[k];
-}
-
-// energy = e_lr[0] + e_lr[1] + e_lr[2] + e_real + pf sum |mu|^2 / (2 a) (one workgroup)
-__global__ void __launch_bounds__(256) k_model_energy(int n, double pf, const float* pol,
-                                                      const float* mu, const double* e_lr,
-                                                      const double* e_real, double* energy) {
-  __shared__ double red[256];
-  double s = 0.0;
-  if (mu)
-    for (int i = threadIdx.x; i < n; i += 256) {
-      const double m2 = double(mu[3 * i]) * mu[3 * i] + double(mu[3 * i + 1]) * mu[3 * i + 1] +
-                        double(mu[3 * i + 2]) * mu[3 * i + 2];
-      s += m2 / (2.0 * double(pol[i]));
-    }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
+// r = -g - (warm ? Ax : 0); x = warm ? x : 0; z = (a / pf) r; p = z; partials of r.z, z.z
+__global__ void __launch_bounds__(256) k_pcg_start(int m, float pf, const float* pol,
+                                                   const float* g, const float* Ax, float* x,
+                                                   float* r, float* z, float* p, int warm,
+                                                   double* part, PcgResidual* host,
+                                                   unsigned long long step) {
+  __shared__ double red[8];
+  double rz = 0.0, zz = 0.0;
+  for (int k = blockIdx.x * 256 + threadIdx.x; k < m; k += gridDim.x * 256) {
+    float rk = -g[k];
+    if (warm) rk -= Ax[k];
+    else x[k] = 0.0f;
+    const float zk = pol[k / 3] / pf * rk;
+    r[k] = rk;
+    z[k] = zk;
+    p[k] = zk;
+    rz += double(rk) * zk;
+    zz += double(zk) * zk;
   }
-  if (threadIdx.x == 0) energy[0] = e_lr[0] + e_lr[1] + e_lr[2] + e_real[0] + pf * red[0];
+  pcg_partials(rz, zz, part, host, step, red);
 }
 
-__global__ void k_copy_scal(double* scal) {
-  if (threadIdx.x == 0) { scal[0] = scal[4]; scal[1] = scal[5]; }
+// alpha = r.z / p.Ap; x += alpha p; r -= alpha Ap; z = (a / pf) r; partials of the new
+// r.z and z.z (old: npart workgroups' partials of the old ones; pap: npap of p . Ap)
+__global__ void __launch_bounds__(256) k_pcg_step(int m, float pf, const float* pol,
+                                                  const double* old, int npart,
+                                                  const double* pap, int npap, const float* p,
+                                                  const float* Ap, float* x, float* r, float* z,
+                                                  double* part, PcgResidual* host,
+                                                  unsigned long long step) {
+  __shared__ double red[8];
+  const double rz0 = sum256(old, npart, 2, red), pAp = sum256(pap, npap, 1, red);
+  const float al = pAp != 0.0 ? float(rz0 / pAp) : 0.0f;
+  double rz = 0.0, zz = 0.0;
+  for (int k = blockIdx.x * 256 + threadIdx.x; k < m; k += gridDim.x * 256) {
+    x[k] += al * p[k];
+    const float rk = r[k] - al * Ap[k];
+    const float zk = pol[k / 3] / pf * rk;
+    r[k] = rk;
+    z[k] = zk;
+    rz += double(rk) * zk;
+    zz += double(zk) * zk;
+  }
+  pcg_partials(rz, zz, part, host, step, red);
+}
+
+// beta = new r.z / old r.z; p = z + beta p
+__global__ void __launch_bounds__(256) k_pcg_dir(int m, const double* old, const double* now,
+                                                 int npart, const float* z, float* p) {
+  __shared__ double red[4];
+  const double rz0 = sum256(old, npart, 2, red), rz = sum256(now, npart, 2, red);
+  const float be = rz0 != 0.0 ? float(rz / rz0) : 0.0f;
+  for (int k = blockIdx.x * 256 + threadIdx.x; k < m; k += gridDim.x * 256)
+    p[k] = z[k] + be * p[k];
 }
 
 }  // namespace
@@ -308,9 +321,12 @@ __global__ void k_copy_scal(double* scal) {
 struct pol_plan_s {
   pol_desc_t desc;
   CellList cells;
-  double* epart = nullptr;
-  double* scal = nullptr;
-  float* vec = nullptr;      // 8 work vectors of 3 max_atoms floats
+  char* base = nullptr;      // the allocation that holds the arrays
+  double* epart = nullptr;   // [pair_blocks(max_atoms)]
+  double* scal = nullptr;    // [0..2] long-range energy terms; from 8: PCG partials
+  float* vec = nullptr;      // 6 work vectors of 3 max_atoms floats
+  PcgResidual* host = nullptr;        // [kPcgBlocks] pinned, written by the device
+  unsigned long long steps = 0;       // PCG steps launched (their numbers are never reused)
 };
 
 namespace {
@@ -324,9 +340,8 @@ int pol_hip_fail(hipError_t e) {
 
 void pol_free(pol_plan_s* p) {
   free_cells(p->cells);
-  void* ptrs[] = {p->epart, p->scal, p->vec};
-  for (void* q : ptrs)
-    if (q) (void)hipFree(q);
+  if (p->base) (void)hipFree(p->base);
+  if (p->host) (void)hipHostFree(p->host);
   delete p;
 }
 
@@ -344,18 +359,52 @@ PairArgs pair_args(const pol_plan_s* pl, int n, const float* pos, const float* q
   a.A = float(pl->desc.thole_a);
   a.pf = float(pl->desc.prefactor);
   a.o_pos = nullptr; a.o_q = nullptr; a.o_mu = nullptr; a.epart = nullptr;
+  a.b_pos = nullptr; a.b_q = nullptr; a.b_mu = nullptr; a.p_mu = nullptr;
   return a;
 }
 
 int pair_blocks(int n) { return blocks_for(n, kPairAtoms); }
 
-// dE_real/dmu only (dipole field of mu and q), on the cell list of these positions
+// base + dE_real/dmu (dipole field of mu and q) on the cell list of these positions;
+// with p_mu also the polarization term and, in plan->epart, the partials of mu . out
 hipError_t real_mu_grad(pol_plan_s* pl, hipStream_t s, int n, const float* pos, const float* q,
-                        const float* mu, const float* pol, float* out) {
+                        const float* mu, const float* pol, const float* base, const float* p_mu,
+                        float* out) {
   PairArgs a = pair_args(pl, n, pos, q, mu, pol);
   a.o_mu = out;
+  a.b_mu = base;
+  a.p_mu = p_mu;
+  a.epart = p_mu ? pl->epart : nullptr;
   hipLaunchKernelGGL(k_pair<kMuGrad>, dim3(pair_blocks(n)), dim3(kPairThreads), 0, s, a);
   return hipGetLastError();
+}
+
+// Wait for every workgroup's residual of PCG step `step` and add them up.  The device
+// writes them to host memory as the step ends, so the wait costs no copy and no wake-up
+// (about 15 us an iteration); a stream that has ended without them, or is not running
+// (being captured), is an error.
+int wait_residual(pol_plan_s* pl, hipStream_t s, int nb, unsigned long long step, double& zz) {
+  auto arrived = [&](int& k) {
+    while (k < nb && *static_cast<volatile unsigned long long*>(&pl->host[k].step) == step) ++k;
+    return k == nb;
+  };
+  int k = 0;
+  for (unsigned spin = 1; !arrived(k); ++spin) {
+    __builtin_ia32_pause();
+    if (spin % 4096 == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipErrorNotReady) {
+        (void)hipGetLastError();   // not an error of the launches that follow
+        continue;
+      }
+      if (e != hipSuccess) return pol_hip_fail(e);
+      if (!arrived(k)) return pol_hip_fail(hipErrorUnknown);
+    }
+  }
+  __atomic_thread_fence(__ATOMIC_ACQUIRE);
+  zz = 0.0;
+  for (int b = 0; b < nb; ++b) zz += *static_cast<volatile double*>(&pl->host[b].zz);
+  return PME_OK;
 }
 
 bool check_common(const pol_plan_s* pl, int n, const float* pos, const float* pol) {
@@ -383,11 +432,19 @@ int pol_plan_create(const pol_desc_t* desc, pol_plan_t* out) {
     return rc0;
   }
   const size_t m = size_t(desc->max_atoms);
-  hipError_t e = hipSuccess;
-  auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
-  ok(hipMalloc(&pl->epart, sizeof(double) * pair_blocks(int(m))));
-  ok(hipMalloc(&pl->scal, sizeof(double) * 8));
-  ok(hipMalloc(&pl->vec, sizeof(float) * 8 * 3 * m));
+  Carve all;
+  const size_t at_epart = all.take<double>(size_t(pair_blocks(int(m)))),
+               at_scal = all.take<double>(8 + 4 * kPcgBlocks), at_vec = all.take<float>(6 * 3 * m);
+  hipError_t e = all.allocate();
+  if (e == hipSuccess) {
+    pl->base = all.base;
+    pl->epart = all.at<double>(at_epart);
+    pl->scal = all.at<double>(at_scal);
+    pl->vec = all.at<float>(at_vec);
+    e = hipHostMalloc(reinterpret_cast<void**>(&pl->host), sizeof(PcgResidual) * kPcgBlocks,
+                      hipHostMallocCoherent);
+  }
+  if (e == hipSuccess) memset(pl->host, 0, sizeof(PcgResidual) * kPcgBlocks);
   if (e != hipSuccess) {
     pol_free(pl);
     return e == hipErrorOutOfMemory ? PME_ENOMEM : pol_hip_fail(e);
@@ -414,16 +471,11 @@ int pol_real(pol_plan_t plan, void* stream, int32_t n, const float* pos, const f
   a.o_q = dE_dq;
   a.o_mu = dE_dmu;
   a.epart = energy ? plan->epart : nullptr;
-  const int nb = pair_blocks(n);
+  const int nb = n > 0 ? pair_blocks(n) : 0;
   if (n > 0) hipLaunchKernelGGL(k_pair<kEnergyGrad>, dim3(nb), dim3(kPairThreads), 0, s, a);
-  if (energy) {
-    if (n > 0)
-      hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(256), 0, s, plan->epart, nb,
-                         plan->desc.prefactor, energy);
-    else
-      hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(256), 0, s, plan->epart, 0,
-                         plan->desc.prefactor, energy);
-  }
+  if (energy)
+    hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(256), 0, s, plan->epart, nb,
+                       plan->desc.prefactor, nullptr, energy);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : pol_hip_fail(e);
 }
@@ -448,31 +500,24 @@ int pol_model(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const fl
               double* energy, float* dU_dpos, float* dU_dq, float* dU_dmu) {
   if (!check_common(plan, n, pos, pol) || !pme || !box) return PME_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t stride = size_t(3) * plan->desc.max_atoms;
-  float* gp = plan->vec + 4 * stride;     // PME gradients
-  float* gm = plan->vec + 5 * stride;
-  float* hp = plan->vec + 6 * stride;     // real-space gradients
-  float* hm = plan->vec + 7 * stride;
-  float* gq = plan->vec;                  // charge gradients (PME, real space)
-  float* hq = plan->vec + stride;
-  double* e_lr = plan->scal;              // [0..2]
-  double* e_re = plan->scal + 3;
-  int rc = pme_forward(pme, stream, n, pos, q, mu, box, energy ? e_lr : nullptr,
-                       dU_dpos ? gp : nullptr, dU_dq ? gq : nullptr, dU_dmu ? gm : nullptr);
+  // the long-range gradients go straight into the outputs, to which the pair kernel adds
+  // the real-space part and the polarization term
+  int rc = pme_forward(pme, stream, n, pos, q, mu, box, energy ? plan->scal : nullptr, dU_dpos,
+                       dU_dq, dU_dmu);
   if (rc != PME_OK) return rc;
-  if ((rc = pol_real(plan, stream, n, pos, q, mu, pol, energy ? e_re : nullptr,
-                     dU_dpos ? hp : nullptr, dU_dq ? hq : nullptr,
-                     dU_dmu ? hm : nullptr)) != PME_OK)
-    return rc;
-  if (n > 0 && (dU_dpos || dU_dmu))
-    hipLaunchKernelGGL(k_model_grads, dim3(blocks_for(3 * n, 256)), dim3(256), 0, s, n,
-                       float(plan->desc.prefactor), pol, mu, gp, hp, gm, hm, dU_dpos, dU_dmu);
-  if (n > 0 && dU_dq)
-    hipLaunchKernelGGL(k_add, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, gq, hq, dU_dq);
+  hipError_t e = build_cells(plan->cells, s, n, pos);
+  if (e != hipSuccess) return pol_hip_fail(e);
+  PairArgs a = pair_args(plan, n, pos, q, mu, pol);
+  a.o_pos = dU_dpos; a.o_q = dU_dq; a.o_mu = dU_dmu;
+  a.b_pos = dU_dpos; a.b_q = dU_dq; a.b_mu = dU_dmu;
+  a.p_mu = mu;
+  a.epart = energy ? plan->epart : nullptr;
+  const int nb = n > 0 ? pair_blocks(n) : 0;
+  if (n > 0) hipLaunchKernelGGL(k_pair<kEnergyGrad>, dim3(nb), dim3(kPairThreads), 0, s, a);
   if (energy)
-    hipLaunchKernelGGL(k_model_energy, dim3(1), dim3(256), 0, s, n, plan->desc.prefactor, pol,
-                       mu, e_lr, e_re, energy);
-  hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(256), 0, s, plan->epart, nb,
+                       plan->desc.prefactor, plan->scal, energy);
+  e = hipGetLastError();
   return e == hipSuccess ? PME_OK : pol_hip_fail(e);
 }
 
@@ -483,24 +528,16 @@ int pol_model_hvp(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, cons
   if (!check_common(plan, n, pos, pol) || !pme || !box || !g_q || !g_mu) return PME_EINVAL;
   if (n == 0) return PME_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t stride = size_t(3) * plan->desc.max_atoms;
-  float* lq = plan->vec;                  // PME rows
-  float* lm = plan->vec + 4 * stride;
-  float* rq = plan->vec + stride;         // real-space rows
-  float* rm = plan->vec + 5 * stride;
-  int rc = pme_backward(pme, stream, n, pos, q, mu, box, v_pos, v_q, v_mu, nullptr, lq, lm);
+  int rc = pme_backward(pme, stream, n, pos, q, mu, box, v_pos, v_q, v_mu, nullptr, g_q, g_mu);
   if (rc != PME_OK) return rc;
   hipError_t e = build_cells(plan->cells, s, n, pos);
   if (e != hipSuccess) return pol_hip_fail(e);
   PairArgs a = pair_args(plan, n, pos, q, mu, pol);
   a.vpos = v_pos; a.vq = v_q; a.vmu = v_mu;
-  a.o_q = rq;
-  a.o_mu = rm;
+  a.o_q = g_q; a.o_mu = g_mu;
+  a.b_q = g_q; a.b_mu = g_mu;
+  a.p_mu = v_mu;   // the polarization term adds (pf / a) v_mu
   hipLaunchKernelGGL(k_pair<kHvp>, dim3(pair_blocks(n)), dim3(kPairThreads), 0, s, a);
-  // mu row: the polarization term adds (pf / a) v_mu (k_model_grads with mu = v_mu)
-  hipLaunchKernelGGL(k_model_grads, dim3(blocks_for(3 * n, 256)), dim3(256), 0, s, n,
-                     float(plan->desc.prefactor), pol, v_mu, lm, rm, lm, rm, nullptr, g_mu);
-  hipLaunchKernelGGL(k_add, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, lq, rq, g_q);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : pol_hip_fail(e);
 }
@@ -519,11 +556,12 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
   float* z = r + stride;
   float* p = z + stride;
   float* Ap = p + stride;
-  double* scal = plan->scal;
+  double* part[2] = {plan->scal + 8, plan->scal + 8 + 2 * kPcgBlocks};
   const float pf = float(plan->desc.prefactor);
   const bool warm = (plan->desc.flags & POL_F_WARM_START) != 0;
   const bool fixed = (plan->desc.flags & POL_F_FIXED_ITERS) != 0;
-  const int vb = blocks_for(m, 256);
+  int vb = blocks_for(m, 256);
+  if (vb > kPcgBlocks) vb = kPcgBlocks;
   int rc;
   hipError_t e;
   if (iters) *iters = 0;
@@ -531,15 +569,11 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
   if (n == 0) return PME_OK;
   // the positions do not move during the solve: one cell list serves every product
   if ((e = build_cells(plan->cells, s, n, pos)) != hipSuccess) return pol_hip_fail(e);
-  // A v = (pf / a) v + H_pme v + H_real v
+  // A v = (pf / a) v + H_pme v + H_real v, and the partials of v . A v
   auto matvec = [&](const float* v, float* out) -> int {
-    int rr = pme_backward(pme, stream, n, pos, q, nullptr, box, nullptr, nullptr, v, nullptr,
-                          nullptr, g1);
+    const int rr = pme::dipole_response(pme, s, n, pos, v, box, g1);
     if (rr != PME_OK) return rr;
-    hipError_t he = real_mu_grad(plan, s, n, pos, nullptr, v, pol, g2);
-    if (he != hipSuccess) return pol_hip_fail(he);
-    hipLaunchKernelGGL(k_matvec_sum, dim3(vb), dim3(256), 0, s, m, pf, pol, v, g1, g2, out);
-    he = hipGetLastError();
+    const hipError_t he = real_mu_grad(plan, s, n, pos, nullptr, v, pol, g1, v, out);
     return he == hipSuccess ? PME_OK : pol_hip_fail(he);
   };
   if (warm && (rc = matvec(mu, Ap)) != PME_OK) return rc;
@@ -547,35 +581,35 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
   if ((rc = pme_forward(pme, stream, n, pos, q, nullptr, box, nullptr, nullptr, nullptr, g1)) !=
       PME_OK)
     return rc;
-  if ((e = real_mu_grad(plan, s, n, pos, q, nullptr, pol, g2)) != hipSuccess)
+  if ((e = real_mu_grad(plan, s, n, pos, q, nullptr, pol, g1, nullptr, g2)) != hipSuccess)
     return pol_hip_fail(e);
-  hipLaunchKernelGGL(k_pcg_start, dim3(vb), dim3(256), 0, s, m, pf, pol, g1, g2, Ap, mu, r, z, p,
-                     warm ? 1 : 0);
-  hipLaunchKernelGGL(k_dot2, dim3(1), dim3(1024), 0, s, m, r, z, z, z, scal);
+  // with a fixed count (capturable) the residual does not go to the host
+  PcgResidual* host = fixed ? nullptr : plan->host;
+  hipLaunchKernelGGL(k_pcg_start, dim3(vb), dim3(256), 0, s, m, pf, pol, g2, Ap, mu, r, z, p,
+                     warm ? 1 : 0, part[0], host, ++plan->steps);
+  if ((e = hipGetLastError()) != hipSuccess) return pol_hip_fail(e);
   int it = 0;
   double rms = 0.0;
   for (;;) {
     if (fixed) {
-      // no host round trip: exactly max_iter iterations (capturable)
+      // no host round trip: exactly max_iter iterations
       if (it >= max_iter) {
         rms = -1.0;
         break;
       }
     } else {
-      double h[2];
-      if ((e = hipMemcpyAsync(h, scal, sizeof(h), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-          (e = hipStreamSynchronize(s)) != hipSuccess)
-        return pol_hip_fail(e);
-      rms = sqrt(fmax(h[1], 0.0) / double(m));
+      double zz;
+      if ((rc = wait_residual(plan, s, vb, plan->steps, zz)) != PME_OK) return rc;
+      rms = sqrt(fmax(zz, 0.0) / double(m));
       if (!isfinite(rms)) return PME_ENONFINITE;
       if (rms < tol || it >= max_iter) break;
     }
+    const double* old = part[it & 1];
+    double* now = part[(it & 1) ^ 1];
     if ((rc = matvec(p, Ap)) != PME_OK) return rc;
-    hipLaunchKernelGGL(k_dot2, dim3(1), dim3(1024), 0, s, m, p, Ap, p, p, scal + 2);
-    hipLaunchKernelGGL(k_pcg_step, dim3(vb), dim3(256), 0, s, m, pf, pol, scal, p, Ap, mu, r, z);
-    hipLaunchKernelGGL(k_dot2, dim3(1), dim3(1024), 0, s, m, r, z, z, z, scal + 4);
-    hipLaunchKernelGGL(k_pcg_dir, dim3(vb), dim3(256), 0, s, m, scal, z, p);
-    hipLaunchKernelGGL(k_copy_scal, dim3(1), dim3(64), 0, s, scal);
+    hipLaunchKernelGGL(k_pcg_step, dim3(vb), dim3(256), 0, s, m, pf, pol, old, vb, plan->epart,
+                       pair_blocks(n), p, Ap, mu, r, z, now, host, ++plan->steps);
+    hipLaunchKernelGGL(k_pcg_dir, dim3(vb), dim3(256), 0, s, m, old, now, vb, z, p);
     if ((e = hipGetLastError()) != hipSuccess) return pol_hip_fail(e);
     ++it;
   }
