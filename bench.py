@@ -73,8 +73,9 @@ BAND_STEP_SPREAD = "k_spread_band<6, 1, true>"
 
 
 # The transform kinds of a pencil-layout plan (a y-z plane of the half spectrum too
-# large for LDS): each spans two launches (the z pass and a y pass)
-PENCIL_SYMBOL = {"fft_r2c": "k_fftz_r2c+k_ffty", "fft_c2r": "k_ffty+k_fftz_c2r"}
+# large for LDS): the first and last span two launches each (the z pass and a y pass)
+PENCIL_SYMBOL = {"fft_r2c": "k_pencil_r2c<true>+k_pencil_y<true>", "fft_x": "k_pencil_x<true, 0>",
+                 "fft_c2r": "k_pencil_y<true>+k_pencil_c2r<true>"}
 SLAB_LDS_MAX = 160 * 1024 - 2048     # kSlabLdsMax of the library
 
 

@@ -344,41 +344,24 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
         d.band_lds = size_t(bytes_of(rows));
       }
     }
-    // pencil passes: about 1024 complex points per workgroup
-    int pairs = (1024 + d.N[2] - 1) / d.N[2];
-    if (pairs > 32) pairs = 32;
-    d.rows_per_block = 2 * pairs;
-    const int nmax = d.N[0] > d.N[1] ? d.N[0] : d.N[1];
-    const int kt0 = nmax <= 64 ? 16 : (nmax <= 160 ? 24 : 4);
-    int kt = desc.fft_lines > 0 ? desc.fft_lines : kt0;
-    // the pencil y pass holds no g table: on meshes above 160 points it takes twice
-    // the x pass's default lines (64-byte segments of its strided lines); on smaller
-    // meshes, and with lines given in the descriptor, the x pass's
-    int kty = desc.fft_lines > 0 ? desc.fft_lines : 2 * kt0;
-    // LDS of a line workgroup within 56 KB: twiddles, two line buffers and (x pass)
-    // the kt N_x table of g and the deconvolution factors:
-    // 8 N + kt (16 (N + 1) + 4 N) + 4 (N + kt) bytes
-    // (optimal influence: 12 (N + kt) more bytes of aliasing weights)
-    const int extra = d.opt ? 3 * (nmax + 1) / 2 : 0;
-    const int lds_cap = (7000 - nmax - (nmax + 1) / 2 - extra) /
-                        (2 * (nmax + 1) + (nmax + 1) / 2 + 2 + (d.opt ? 2 : 0));
-    if (kt > lds_cap) kt = lds_cap;
-    if (kt < 1) kt = 1;
-    if (kt > d.H) kt = d.H;
-    // the y pass: twiddles and two line buffers within the same 56 KB
-    const int ycap = (7000 - nmax) / (2 * (nmax + 1));
-    if (kty > ycap) kty = ycap;
-    if (kty < 1) kty = 1;
-    if (kty > d.H) kty = d.H;
-    // equal chunks of the H columns (no mostly-empty last chunk)
-    const int nchunk = (d.H + kt - 1) / kt;
-    kt = (d.H + nchunk - 1) / nchunk;
-    d.ktile = kt;
-    if (nmax <= 160 || desc.fft_lines > 0) {
-      d.ytile = kt;
+    if (!d.slab) {
+      pme::pencil_lines(d);
     } else {
-      const int nchunk_y = (d.H + kty - 1) / kty;
-      d.ytile = (d.H + nchunk_y - 1) / nchunk_y;
+      const int nmax = d.N[0] > d.N[1] ? d.N[0] : d.N[1];
+      int kt = desc.fft_lines > 0 ? desc.fft_lines : (nmax <= 64 ? 16 : (nmax <= 160 ? 24 : 4));
+      // LDS of a line workgroup within 56 KB: twiddles, two line buffers, the kt N_x table
+      // of g and the deconvolution factors:
+      // 8 N + kt (16 (N + 1) + 4 N) + 4 (N + kt) bytes
+      // (optimal influence: 12 (N + kt) more bytes of aliasing weights)
+      const int extra = d.opt ? 3 * (nmax + 1) / 2 : 0;
+      const int lds_cap = (7000 - nmax - (nmax + 1) / 2 - extra) /
+                          (2 * (nmax + 1) + (nmax + 1) / 2 + 2 + (d.opt ? 2 : 0));
+      if (kt > lds_cap) kt = lds_cap;
+      if (kt < 1) kt = 1;
+      if (kt > d.H) kt = d.H;
+      // equal chunks of the H columns (no mostly-empty last chunk)
+      const int nchunk = (d.H + kt - 1) / kt;
+      d.ktile = (d.H + nchunk - 1) / nchunk;
     }
   }
   nbins_out = nbins;
@@ -526,16 +509,16 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
   // meshes the strided line traffic bounds it and the table's extra bytes cost more
   // than the arithmetic they save, except for the optimal influence function
   const size_t xblocks = size_t(pme::fftx_blocks(d));
-  const bool gtables = d.opt || xblocks <= 1024;
+  const bool gtables = d.opt || (d.slab && xblocks <= 1024);
   d.gcache = nullptr;
   d.gkey = nullptr;
   if (gtables) {
     ok(dev_alloc(&d.gcache, xblocks * d.N[0] * d.ktile, by));
     ok(dev_alloc(&d.gkey, 9 * xblocks, by));
   }
-  ok(dev_alloc(&d.rho, size_t(M), by));
+  ok(dev_alloc(&d.rho, pme::mesh_floats(d), by));
   ok(dev_alloc(&d.spec, size_t(d.N[0]) * d.N[1] * d.H, by));
-  ok(dev_alloc(&d.phi, size_t(M), by));
+  ok(dev_alloc(&d.phi, pme::mesh_floats(d), by));
   ok(dev_alloc(&d.epart, size_t(pme::fftx_blocks(d)), by));
   ok(dev_alloc(&d.spart, size_t(4 * pme::bin_blocks(desc->max_atoms)), by));
   ok(dev_alloc(&d.vpart, size_t(6 * pme::fftx_blocks(d) + 9 * d.nt[0] * d.nt[1] * d.nt[2]), by));
@@ -603,7 +586,7 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
       ok(dev_alloc(&t.cmax_fwd[k], 1, by));
     }
     ok(dev_alloc(&t.rec, (size_t(t.ovf_base) + size_t(desc->max_atoms)) * 16, by));
-    ok(dev_alloc(&t.rho, size_t(M), by));
+    ok(dev_alloc(&t.rho, pme::mesh_floats(d), by));
     ok(dev_alloc(&t.spec, size_t(d.N[0]) * d.N[1] * d.H, by));
     // the cotangent chain's x passes keep their own g tables: the two chains' passes
     // run at the same time
@@ -624,6 +607,7 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
     ok(hipEventCreateWithFlags(&pl->binned, hipEventDisableTiming));
   }
   if (d.slab) ok(pme::enable_slab_lds(d.slab_lds));
+  else ok(pme::enable_pencil_lds());
   if (d.band) ok(pme::enable_band_lds());
   ok(pme::enable_spread_lds());
   ok(pme::enable_gather_lds());
@@ -1234,6 +1218,7 @@ int scratch_address(unsigned char** out) {
     if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess) return hip_fail(e);
     if (!p) return PME_EHIP;
     if ((e = pme::enable_slab_lds(pme::kSlabLdsMax)) != hipSuccess) return hip_fail(e);
+    if ((e = pme::enable_pencil_lds()) != hipSuccess) return hip_fail(e);
     if ((e = pme::enable_band_lds()) != hipSuccess) return hip_fail(e);
     if ((e = pme::enable_spread_lds()) != hipSuccess) return hip_fail(e);
     if ((e = pme::enable_gather_lds()) != hipSuccess) return hip_fail(e);
@@ -1309,7 +1294,7 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
     o_dc[a] = take(sizeof(float) * size_t(d.N[a]));
   }
   const size_t o_rho = take(sizeof(float) * size_t(M));
-  const size_t o_phi = take(sizeof(float) * size_t(M));
+  (void)take(sizeof(float) * size_t(M));
   const size_t o_spec = take(sizeof(float2) * size_t(d.N[0]) * d.N[1] * d.H);
   const size_t o_epart = take(sizeof(double) * size_t(pme::fftx_blocks(d)));
   const size_t o_spart = take(sizeof(double) * 4 * size_t(pme::bin_blocks(dd.max_atoms)));
@@ -1340,7 +1325,9 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
     ta.dc[a] = d.deconv[a];
   }
   d.rho = reinterpret_cast<float*>(base + o_rho);
-  d.phi = reinterpret_cast<float*>(base + o_phi);
+  // the potential takes the density's place; the room after it makes twice the mesh,
+  // enough for the spectrum that lies there in the pencil layout
+  d.phi = d.rho;
   d.spec = reinterpret_cast<float2*>(base + o_spec);
   d.epart = reinterpret_cast<double*>(base + o_epart);
   d.spart = reinterpret_cast<double*>(base + o_spart);

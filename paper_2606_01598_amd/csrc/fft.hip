@@ -4,14 +4,14 @@
 // k-space form of the reciprocal energy (Eq. energy_recip):
 //     E_recip = (1/2V) sum_n rho phi = (1/2V) sum_k g(k) |rho~(k)|^2.
 //
-// LDS-staged passes over the half spectrum spec[x][y][kz], kz < N_z/2+1.  When a
-// y-z plane of the half spectrum fits in LDS (slab mode) there are three:
+// LDS-staged passes over the half spectrum spec[x][y][kz], kz < N_z/2+1, when a
+// y-z plane of the half spectrum fits in LDS (slab mode; otherwise the five passes of
+// pencil.hip):
 //   slab fwd  one x-plane per workgroup: z R2C (two real rows packed into one
 //             complex pencil) then y FFT, in LDS
 //   x         fused forward FFT along x, x g(k), energy partial, inverse FFT along x
 //   slab inv  y inverse FFT then z C2R (two Hermitian rows unpacked into one
 //             complex pencil), in LDS
-// Otherwise five pencil passes: z R2C, y fwd, x fused, y inv, z C2R.
 // Each 1D transform is a mixed-radix (2, 3, 4, 5, 6, 8, 10) Stockham autosort over
 // LDS ping-pong buffers; twiddles come from a per-axis table staged into LDS.
 //
@@ -23,6 +23,7 @@
 
 #include "../../include/pme.h"
 #include "fft_radix.h"
+#include "influence.h"
 #include "kernels.h"
 #include "pme_common.h"
 #include "plane_spread.h"
@@ -96,100 +97,6 @@ __device__ __forceinline__ void staged_copy(int total, Ld ld, St st) {
       const int e = e0 + u * blockDim.x;
       if (e < total) st(e, v[u]);
     }
-  }
-}
-
-struct ZArgs {
-  AxisPlan ax;
-  const float2* tw;
-  int rows;        // N_x N_y
-  int H;
-  int rp;          // rows per block (even)
-  FastDiv nd;      // division by N_z
-  const float* src;
-  float2* spec;
-  float* dst;
-};
-
-// z pass, real to complex
-__global__ void __launch_bounds__(kFFTThreads) k_fftz_r2c(ZArgs a) {
-  extern __shared__ float2 sm[];
-  const int N = a.ax.N, H = a.H;
-  float2* tw = sm;
-  float2* X = tw + N;
-  float2* Y = X + (a.rp / 2) * N;
-  const int r0 = blockIdx.x * a.rp;
-  Twiddles<kFFTThreads> twr;
-  twr.load(a.tw, N);
-  const int np = a.rp / 2;
-  staged_copy<16, float2>(
-      np * N,
-      [&](int e) {
-        const int c = int(fdiv(uint32_t(e), a.nd)), m = e - c * N;
-        const int ra = r0 + 2 * c, rb = ra + 1;
-        return make_float2(ra < a.rows ? a.src[size_t(ra) * N + m] : 0.0f,
-                           rb < a.rows ? a.src[size_t(rb) * N + m] : 0.0f);
-      },
-      [&](int e, float2 v) { X[e] = v; });
-  twr.store(tw, N);
-  __syncthreads();
-  const float2* Z = lds_fft(X, Y, np, N, a.ax, tw, -1.0f);
-  for (int e = threadIdx.x; e < a.rp * H; e += blockDim.x) {
-    const int rr = e / H, k = e - rr * H;
-    const int row = r0 + rr;
-    if (row >= a.rows) continue;
-    const int c = rr >> 1;
-    const float2 zk = Z[c * N + k];
-    const float2 zn = Z[c * N + (k ? N - k : 0)];
-    float2 v;
-    if ((rr & 1) == 0) v = make_float2(0.5f * (zk.x + zn.x), 0.5f * (zk.y - zn.y));
-    else v = make_float2(0.5f * (zk.y + zn.y), -0.5f * (zk.x - zn.x));
-    a.spec[size_t(row) * H + k] = v;
-  }
-}
-
-// z pass, complex to real
-__global__ void __launch_bounds__(kFFTThreads) k_fftz_c2r(ZArgs a) {
-  extern __shared__ float2 sm[];
-  const int N = a.ax.N, H = a.H;
-  float2* tw = sm;
-  float2* S = tw + N;
-  float2* X = S + a.rp * H;
-  float2* Y = X + (a.rp / 2) * N;
-  const int r0 = blockIdx.x * a.rp;
-  Twiddles<kFFTThreads> twr;
-  twr.load(a.tw, N);
-  const int nvalid = min(a.rp, a.rows - r0) * H;
-  staged_copy<16, float2>(
-      a.rp * H, [&](int e) { return e < nvalid ? a.spec[size_t(r0) * H + e] : make_float2(0.f, 0.f); },
-      [&](int e, float2 v) { S[e] = v; });
-  twr.store(tw, N);
-  __syncthreads();
-  const int np = a.rp / 2;
-  const bool even = (N & 1) == 0;
-  for (int e = threadIdx.x; e < np * N; e += blockDim.x) {
-    const int c = e / N, m = e - c * N;
-    float2 A, B;
-    if (m < H) {
-      A = S[(2 * c) * H + m];
-      B = S[(2 * c + 1) * H + m];
-    } else {
-      A = S[(2 * c) * H + N - m];
-      B = S[(2 * c + 1) * H + N - m];
-      A.y = -A.y;
-      B.y = -B.y;
-    }
-    if (m == 0 || (even && m == N / 2)) { A.y = 0.0f; B.y = 0.0f; }
-    X[e] = make_float2(A.x - B.y, A.y + B.x);
-  }
-  __syncthreads();
-  const float2* Z = lds_fft(X, Y, np, N, a.ax, tw, +1.0f);
-  for (int e = threadIdx.x; e < np * N; e += blockDim.x) {
-    const int c = e / N, m = e - c * N;
-    const int ra = r0 + 2 * c, rb = ra + 1;
-    const float2 z = Z[e];
-    if (ra < a.rows) a.dst[size_t(ra) * N + m] = z.x;
-    if (rb < a.rows) a.dst[size_t(rb) * N + m] = z.y;
   }
 }
 
@@ -444,49 +351,6 @@ __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const int x) {
   }
 }
 
-struct YArgs {
-  AxisPlan ax;
-  const float2* tw;
-  int Ny, H, kt;
-  FastDiv ktd;
-  float2* spec;
-  float sign;
-};
-
-// y pass: block = (x, tile of kz columns)
-__global__ void __launch_bounds__(kFFTThreads) k_ffty(YArgs a) {
-  extern __shared__ float2 sm[];
-  const int N = a.ax.N, H = a.H, kt = a.kt;
-  const int ps = N + 1;
-  float2* tw = sm;
-  float2* X = tw + N;
-  float2* Y = X + kt * ps;
-  const int ntk = (H + kt - 1) / kt;
-  const int x = blockIdx.x / ntk, kz0 = (blockIdx.x - x * ntk) * kt;
-  Twiddles<kFFTThreads> twr;
-  twr.load(a.tw, N);
-  float2* base = a.spec + size_t(x) * a.Ny * H;
-  staged_copy<16, float2>(
-      N * kt,
-      [&](int e) {
-        const int yy = int(fdiv(uint32_t(e), a.ktd)), l = e - yy * kt;
-        const int kz = kz0 + l;
-        return (kz < H) ? base[size_t(yy) * H + kz] : make_float2(0.f, 0.f);
-      },
-      [&](int e, float2 v) {
-        const int yy = int(fdiv(uint32_t(e), a.ktd)), l = e - yy * kt;
-        X[l * ps + yy] = v;
-      });
-  twr.store(tw, N);
-  __syncthreads();
-  const float2* Z = lds_fft(X, Y, kt, ps, a.ax, tw, a.sign);
-  for (int e = threadIdx.x; e < N * kt; e += blockDim.x) {
-    const int yy = e / kt, l = e - yy * kt;
-    const int kz = kz0 + l;
-    if (kz < H) base[size_t(yy) * H + kz] = Z[l * ps + yy];
-  }
-}
-
 struct XArgs {
   AxisPlan ax;
   AxisPlan axi;    // the same radices in reverse order (inverse transform)
@@ -512,8 +376,6 @@ struct XArgs {
   float* gcache;
   double* gkey;
 };
-
-__device__ __forceinline__ int signed_freq(int k, int N) { return (k >= (N + 1) / 2) ? k - N : k; }
 
 // x pass fused with the influence function: forward FFT along x of kt half-spectrum
 // lines (fixed y, consecutive kz), x g(k) (with the energy partial), inverse FFT.
@@ -1201,60 +1063,23 @@ hipError_t launch_convolve(const DevPlan& d, hipStream_t s, const double* box, f
                            bool energy, KTimer* tm, double* vpart, bool from_spec) {
   hipError_t err;
   if (from_spec && !d.slab) return hipErrorInvalidValue;
+  if (!d.slab) return launch_pencil(d, s, box, out, energy, tm, vpart);
   XArgs x = make_x_args(d, box, energy);
   x.vpart = vpart;
   const size_t xsh = x_lds(d);
-  // timed kinds: a kind spanning two launches records its start with the first
-  // and its stop with the second
   const LaunchEvents* er = (tm && !from_spec) ? tm->next(PME_K_FFT_R2C) : nullptr;
   const LaunchEvents* ex = tm ? tm->next(PME_K_FFT_X) : nullptr;
   const LaunchEvents* ei = tm ? tm->next(PME_K_FFT_C2R) : nullptr;
-  LaunchEvents er0, er1, ei0, ei1;
-  if (er) { er0.start = er->start; er1.stop = er->stop; }
-  if (ei) { ei0.start = ei->start; ei1.stop = ei->stop; }
-
-  if (d.slab) {
-    const SlabArgs sa = make_slab_args(d, out);
-    if (!from_spec) {
-      launch_k(er, k_slab_fwd, dim3(d.N[0]), dim3(kSlabThreads), d.slab_lds, s, sa);
-      if ((err = hipGetLastError()) != hipSuccess) return err;
-    }
-    if (vpart) launch_k(ex, k_fftx_fused<1>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
-    else if (d.opt) launch_k(ex, k_fftx_fused<2>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
-    else launch_k(ex, k_fftx_fused<0>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
+  const SlabArgs sa = make_slab_args(d, out);
+  if (!from_spec) {
+    launch_k(er, k_slab_fwd, dim3(d.N[0]), dim3(kSlabThreads), d.slab_lds, s, sa);
     if ((err = hipGetLastError()) != hipSuccess) return err;
-    launch_k(ei, k_slab_inv, dim3(d.N[0]), dim3(kSlabThreads), d.slab_lds, s, sa);
-    return hipGetLastError();
   }
-
-  const int rows = d.N[0] * d.N[1];
-  ZArgs z;
-  z.ax = d.ax[2]; z.tw = d.twiddle[2]; z.rows = rows; z.H = d.H; z.rp = d.rows_per_block;
-  z.src = d.rho; z.spec = d.spec; z.dst = out;
-  z.nd = make_fast_div(d.N[2]);
-  const int zb = fftz_blocks(d);
-  const size_t zsh_f = sizeof(float2) * (d.N[2] + d.rows_per_block * d.N[2]);
-  YArgs y;
-  y.ax = d.ax[1]; y.tw = d.twiddle[1]; y.Ny = d.N[1]; y.H = d.H; y.kt = d.ytile; y.spec = d.spec;
-  y.ktd = make_fast_div(d.ytile);
-  const size_t ysh = sizeof(float2) * (d.N[1] + 2 * d.ytile * (d.N[1] + 1));
-
-  launch_k(er ? &er0 : nullptr, k_fftz_r2c, dim3(zb), dim3(kFFTThreads), zsh_f, s, z);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  y.sign = -1.0f;
-  launch_k(er ? &er1 : nullptr, k_ffty, dim3(ffty_blocks(d)), dim3(kFFTThreads), ysh, s, y);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-
   if (vpart) launch_k(ex, k_fftx_fused<1>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
   else if (d.opt) launch_k(ex, k_fftx_fused<2>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
   else launch_k(ex, k_fftx_fused<0>, dim3(fftx_blocks(d)), dim3(kFFTThreads), xsh, s, x);
   if ((err = hipGetLastError()) != hipSuccess) return err;
-
-  y.sign = +1.0f;
-  launch_k(ei ? &ei0 : nullptr, k_ffty, dim3(ffty_blocks(d)), dim3(kFFTThreads), ysh, s, y);
-  if ((err = hipGetLastError()) != hipSuccess) return err;
-  const size_t zsh_i = sizeof(float2) * (d.N[2] + d.rows_per_block * d.H + d.rows_per_block * d.N[2]);
-  launch_k(ei ? &ei1 : nullptr, k_fftz_c2r, dim3(zb), dim3(kFFTThreads), zsh_i, s, z);
+  launch_k(ei, k_slab_inv, dim3(d.N[0]), dim3(kSlabThreads), d.slab_lds, s, sa);
   return hipGetLastError();
 }
 

@@ -5,7 +5,7 @@
 // N = prod R_s.  Stage s (Ns = product of the earlier radices) takes inputs
 // in[j + r N/R], multiplies them by the twiddles w_N^{r k step}, k = j mod Ns,
 // applies an R-point DFT and writes out[(j / Ns) Ns R + k + r Ns].  The R-point DFTs
-// are done in registers: 2, 3, 4 and 5 directly, 6, 8 and 10 as R1 x R2
+// are done in registers: 2, 3, 4 and 5 directly, the larger ones as R1 x R2
 // Cooley-Tukey splits with compile-time internal twiddles.  Fewer, larger stages
 // mean fewer LDS round trips and workgroup barriers per transform.
 #pragma once
@@ -200,9 +200,24 @@ template <>
 struct Dft<8> : DftSplit<2, 4> {};
 template <>
 struct Dft<10> : DftSplit<2, 5> {};
+template <>
+struct Dft<9> : DftSplit<3, 3> {};
+template <>
+struct Dft<12> : DftSplit<3, 4> {};
+template <>
+struct Dft<15> : DftSplit<3, 5> {};
+template <>
+struct Dft<16> : DftSplit<4, 4> {};
+template <>
+struct Dft<18> : DftSplit<3, 6> {};
+template <>
+struct Dft<20> : DftSplit<4, 5> {};
 
 // Radices a stage may use, in the order the planner prefers at equal stage count.
 constexpr int kRadices[] = {10, 8, 6, 5, 4, 3, 2};
+
+// All of them, for the two-stage transforms N = R0 R1 (two_stage).
+constexpr int kWideRadices[] = {20, 18, 16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2};
 
 // One radix-R Stockham butterfly (see the header comment) reading its inputs through
 // ld(index in the pencil) and writing through st(index, value); the twiddle table
@@ -254,6 +269,82 @@ __host__ __device__ __forceinline__ void with_radix(int R, F&& f) {
     case 10: f(std::integral_constant<int, 10>{}); break;
     default: break;
   }
+}
+
+// The same for the stages of two_stage.
+template <class F>
+__host__ __device__ __forceinline__ void with_wide_radix(int R, F&& f) {
+  switch (R) {
+    case 9: f(std::integral_constant<int, 9>{}); break;
+    case 12: f(std::integral_constant<int, 12>{}); break;
+    case 15: f(std::integral_constant<int, 15>{}); break;
+    case 16: f(std::integral_constant<int, 16>{}); break;
+    case 18: f(std::integral_constant<int, 18>{}); break;
+    case 20: f(std::integral_constant<int, 20>{}); break;
+    default: with_radix(R, f); break;
+  }
+}
+
+// ---- N = R0 R1 in two stages with one LDS exchange ------------------------------
+//
+// Stage 0 of butterfly j < R1 takes x[j + r R1] and leaves its R0 results in row j of
+// an R1 x R0 array; stage 1 of butterfly j < R0 takes column j, with the twiddles
+// w_N^{r j}, and makes X[j + r R0].  Rows are padded by one value, so that neither the
+// row writes nor the column reads meet in an LDS bank.
+struct TwoStage {
+  int R0, R1;   // R0 >= R1; 0: N is not such a product
+};
+
+// Values of the larger array: R1 padded rows of R0, or (a transform with the radices in
+// reverse) R0 of R1.
+__host__ __device__ constexpr int two_stage_words(int R0, int R1) {
+  return R0 * R1 + (R0 > R1 ? R0 : R1);
+}
+
+template <int R0, class LD>
+__host__ __device__ __forceinline__ void two_stage_first(LD&& ld, float2* __restrict__ rows, int j,
+                                                         int R1, float s) {
+  float2 v[R0];
+#pragma unroll
+  for (int r = 0; r < R0; ++r) v[r] = ld(j + r * R1);
+  Dft<R0>::run(v, s);
+#pragma unroll
+  for (int r = 0; r < R0; ++r) rows[j * (R0 + 1) + r] = v[r];
+}
+
+// column j with its twiddles (tw[t] = e^{-2 pi i t / N})
+template <int R1>
+__host__ __device__ __forceinline__ void two_stage_column(const float2* __restrict__ rows,
+                                                          float2 (&v)[R1], int j, int R0,
+                                                          const float2* __restrict__ tw, float s) {
+#pragma unroll
+  for (int r = 0; r < R1; ++r) v[r] = rows[r * (R0 + 1) + j];
+#pragma unroll
+  for (int r = 1; r < R1; ++r) {
+    float2 w = tw[r * j];
+    w.y *= -s;
+    v[r] = c_mul(v[r], w);
+  }
+}
+
+template <int R1, class ST>
+__host__ __device__ __forceinline__ void two_stage_second(const float2* __restrict__ rows, ST&& st,
+                                                          int j, int R0,
+                                                          const float2* __restrict__ tw, float s) {
+  float2 v[R1];
+  two_stage_column<R1>(rows, v, j, R0, tw, s);
+  Dft<R1>::run(v, s);
+#pragma unroll
+  for (int r = 0; r < R1; ++r) st(j + r * R0, v[r]);
+}
+
+// Host: the product with the smallest R0 (the fewest registers), R0 >= R1.
+inline TwoStage two_stage(int N) {
+  TwoStage t{0, 0};
+  for (int a : kWideRadices)
+    for (int b : kWideRadices)
+      if (a >= b && a * b == N && (t.R0 == 0 || a < t.R0)) t = TwoStage{a, b};
+  return t;
 }
 
 // Last forward stage, x g(k) and first inverse stage of one butterfly, in registers.

@@ -65,6 +65,8 @@ struct AxisPlan {          // 1D mixed-radix FFT of length N
 constexpr int kFFTThreads = 256;    // pencil-pass workgroup
 constexpr int kSlabThreads = 1024;  // slab-pass workgroup (one x-plane)
 constexpr int kSlabLdsMax = 160 * 1024 - 2048;
+constexpr int kLineLdsTwo = 52 * 1024;         // two-stage pencil workgroup: three per CU
+constexpr int kLineLdsGeneral = 144 * 1024;    // general pencil workgroup (8 lines of 1024)
 constexpr int kFusedMap = 4096;     // item -> bin map slots of a fused spread-slab workgroup
 constexpr int kFusedSlotsPerThread = 4;   // scanned slots per thread and round
 constexpr int kFusedHits = 2 * kFusedSlotsPerThread * kSlabThreads;   // its hit list (two rounds)
@@ -122,9 +124,10 @@ struct DevPlan {
   int band_rows;
   int band_nscan;          // bins a band may scan
   size_t band_lds;         // its dynamic LDS bytes
-  int rows_per_block;      // z-pass rows per block (even)
-  int ktile;               // half-spectrum z columns per x-pass block
-  int ytile;               // half-spectrum z columns per y-pass block (pencil layout)
+  int ktile;               // lines per x-pass block: half-spectrum z columns (slab layout),
+                           // or lines of kz blocks (pencil layout, 8 or 16)
+  int ylines;              // lines per y-pass block (pencil layout, 8 or 16)
+  int zpairs;              // pairs of rows per z-pass block (pencil layout)
   // meshes
   float* rho;              // [M] density (also the tangent density / its potential)
   float2* spec;            // [N_x N_y H]
@@ -246,11 +249,20 @@ hipError_t launch_gather_batch(const GatherBatch& t, hipStream_t s, int set, boo
 // Upload `count` bytes of host data to a new device array.
 hipError_t upload(void** dst, const void* src, size_t bytes);
 
-inline int fftx_blocks(const DevPlan& d) { return d.N[1] * ((d.H + d.ktile - 1) / d.ktile); }
-inline int ffty_blocks(const DevPlan& d) { return d.N[0] * ((d.H + d.ytile - 1) / d.ytile); }
-inline int fftz_blocks(const DevPlan& d) {
-  const int rows = d.N[0] * d.N[1];
-  return (rows + d.rows_per_block - 1) / d.rows_per_block;
+// Workgroups of `lines` lines over n planes of a half spectrum in kz blocks of 8 (the
+// last block narrower: more planes in a workgroup)
+inline int line_blocks(int H, int n, int lines) {
+  const int full = lines / 8, last = H % 8 ? lines / (H % 8) : 1;
+  return (H / 8) * ((n + full - 1) / full) + (H % 8 ? (n + last - 1) / last : 0);
+}
+inline int fftx_blocks(const DevPlan& d) {
+  return d.slab ? d.N[1] * ((d.H + d.ktile - 1) / d.ktile) : line_blocks(d.H, d.N[1], d.ktile);
+}
+// Floats of an array that holds a potential: the mesh, and in the pencil layout the
+// spectrum that lies there before it (a value or two more a row)
+inline size_t mesh_floats(const DevPlan& d) {
+  const size_t rows = size_t(d.N[0]) * d.N[1], row = size_t(d.N[2]);
+  return rows * (d.slab || row > 2 * size_t(d.H) ? row : 2 * size_t(d.H));
 }
 inline int bin_blocks(int n) { return n > 0 ? (n + 255) / 256 : 1; }
 
@@ -287,6 +299,12 @@ hipError_t launch_gather_quad(const DevPlan& d, hipStream_t s, int set, int n, c
 hipError_t launch_convolve(const DevPlan& d, hipStream_t s, const double* box, float* out,
                            bool energy, KTimer* tm, double* vpart = nullptr,
                            bool from_spec = false);
+// The same on meshes whose planes exceed LDS (pencil.hip).
+hipError_t launch_pencil(const DevPlan& d, hipStream_t s, const double* box, float* out,
+                         bool energy, KTimer* tm, double* vpart);
+// Their lines per workgroup (ktile, ylines, zpairs) from the mesh.
+void pencil_lines(DevPlan& d);
+hipError_t enable_pencil_lds();
 // Spread fused with the forward slab transform (d.fused): writes d.spec directly.
 // from: the binned records and fixed-point scale to read instead of d's own (the
 // forward density of pme_step from the cotangent binning: tangent records, which
