@@ -190,8 +190,9 @@ int check_desc(const pme_desc_t& desc) {
 
 // Geometry of a plan (host only, nothing allocated): mesh and order, atom bins and
 // their capacity, spread and gather tiles, spread staging, FFT layout.  `nbins`
-// receives the number of atom bins.  PME_EMESH when no tile or FFT layout fits.
-int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
+// receives the number of atom bins.  PME_EMESH when no tile or FFT layout fits.  cubes:
+// cubic atom bins whatever the spread (the smaller workspace of pme_forward_noalloc).
+int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cubes = false) {
   const int p = desc.order;
   for (int a = 0; a < 3; ++a) d.N[a] = desc.mesh[a];
   d.H = d.N[2] / 2 + 1;
@@ -201,11 +202,9 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
   d.opt = (desc.flags & PME_F_OPT_INFLUENCE) != 0;
   const long M = long(d.N[0]) * d.N[1] * d.N[2];
 
-  // bins of B cells and mesh tiles of T = k B cells: by default tiles near
-  // 8 x 8 x 16 that divide the mesh (pick_dividing_tile); a target the descriptor
-  // sets is rounded to the first bin size that divides N, as are axes with no
-  // dividing tile
-  long nbins = 1;
+  // mesh tiles of T = k B points: by default tiles near 8 x 8 x 16 that divide the mesh
+  // (pick_dividing_tile); a target the descriptor sets is rounded to the first B that
+  // divides N, as are axes with no dividing tile
   int target[3] = {8, 8, 16};
   const bool given = desc.tile[0] > 0 || desc.tile[1] > 0 || desc.tile[2] > 0;
   for (int a = 0; a < 3; ++a)
@@ -218,11 +217,14 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
       if (k > d.N[a] / d.B[a]) k = d.N[a] / d.B[a];
       d.T[a] = k * d.B[a];
     }
-    d.nb[a] = d.N[a] / d.B[a];
-    nbins *= d.nb[a];
   }
+  // plane and band spreads need N >= p + B on every axis
+  bool roomy = true;
+  for (int a = 0; a < 3; ++a)
+    if (d.N[a] < p + d.B[a]) roomy = false;
   // shrink tiles until the spread tile, the scanned bin range, the gather's own
   // bins and its LDS field region fit their bounds
+  for (int a = 0; a < 3; ++a) d.nb[a] = d.N[a] / d.B[a];
   for (;;) {
     long range = 1, own = 1, region = 2;
     for (int a = 0; a < 3; ++a) {
@@ -245,6 +247,22 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
     d.T[big] -= d.B[big];
   }
   for (int a = 0; a < 3; ++a) d.nt[a] = (d.N[a] + d.T[a] - 1) / d.T[a];
+  // Where planes or bands are spread, the atom bins are 1 x B_y x T_z mesh cells instead:
+  // every atom of the p bin layers a plane takes reaches it, and a plane has few bins to
+  // count (100^3: 600 of 1 x 5 x 20 with 1920 atoms, all wanted, instead of 800 of
+  // 5 x 5 x 5 with 3200).  The tile spread, whose tiles test a halo in z as well, keeps
+  // cubes.
+  const bool spread_planes = roomy && p <= 7 && !(desc.flags & PME_F_SEPARATE_SPREAD);
+  const bool planes = spread_planes && !cubes;
+  if (planes) {
+    d.B[0] = 1;
+    if (d.N[2] % d.T[2] == 0) d.B[2] = d.T[2];
+  }
+  long nbins = 1;
+  for (int a = 0; a < 3; ++a) {
+    d.nb[a] = d.N[a] / d.B[a];
+    nbins *= d.nb[a];
+  }
   {
     // spread staging: records per round such that five workgroups share a CU's
     // 160 KiB of LDS (all tiles of a 100^3 mesh resident at once; 1 KiB per
@@ -267,7 +285,9 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
   }
   {
     const double per_bin = double(desc.max_atoms) * d.B[0] * d.B[1] * d.B[2] / double(M);
-    long cap = long(ceil(2.0 * per_bin)) + 8;
+    // records per bin: twice the mean and 8, and four times the mean for bins one cell
+    // wide (a crystal fills one plane in three or four of its spacing)
+    long cap = long(ceil((planes ? 4.0 : 2.0) * per_bin)) + 8;
     if (cap > 64) cap = 64;
     d.cap = int(cap);
   }
@@ -283,65 +303,47 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out) {
     d.slab = slab_bytes <= pme::kSlabLdsMax;
     d.slab_lds = size_t(slab_bytes);
     // spread fused with the forward slab transform: the padded plane (64-bit words)
-    // after the first transform buffer, which also holds the bin scan, the item map
-    // and the hit list while atoms are added; the second buffer overlaps the plane.
-    // Every axis needs N >= p + B (a plane's anchors then lie in at most
-    // (p - 1) / B + 2 bin layers and a padded row or column has one periodic image).
+    // after the first transform buffer, which also holds the listed records while atoms
+    // are added; the second buffer overlaps the plane.  Every axis needs N >= p + B (a
+    // padded row or column has one periodic image).
     d.fused = false;
-    if (d.slab && !(desc.flags & PME_F_SEPARATE_SPREAD) && p <= 7) {
-      bool ok = true;
-      for (int a = 0; a < 3; ++a)
-        if (d.N[a] < p + d.B[a]) ok = false;
-      long layers = (p - 1) / d.B[0] + 2;
-      if (layers > d.nb[0]) layers = d.nb[0];
-      const long nscan = layers * d.nb[1] * d.nb[2];
-      const long arrays = 8 * (nscan + 2) + 2L * pme::kFusedMap + 4L * pme::kFusedHits;
+    if (d.slab && spread_planes) {
+      const long arrays = 4L * pme::kFusedMap;
       const long abuf = buf > (arrays + 7) / 8 ? buf : (arrays + 7) / 8;
       const long pl = long(d.N[1] + p - 1) * (d.N[2] + p - 1);
       const long bytes = 8 * (d.N[1] + d.N[2] + abuf + (pl > buf ? pl : buf));
-      if (ok && nscan < 65535 && bytes <= pme::kSlabLdsMax) {
+      if (bytes <= pme::kSlabLdsMax) {
         d.fused = true;
         d.fused_lds = size_t(bytes);
         d.fused_abuf = int(abuf);
-        d.fused_nscan = int(nscan);
       }
     }
     // band spread where the plane spread is not fused with the transform: the most
-    // rows per band (at most 64) whose band, scan arrays, item map and hit list fit
-    // the slab LDS limit, then bands of equal height; worth it from 8 rows.  When
-    // that grid is four or more rounds of workgroups deep, bands sized for two
-    // workgroups per CU instead (one's latency phases overlap the other's adds)
+    // rows per band (at most 64) whose band and listed records fit the slab LDS limit,
+    // then bands of equal height, rounded up to whole bins where they still fit (a band
+    // then lists fewer atoms that miss it); worth it from 8 rows.  When that grid is four
+    // or more rounds of workgroups deep, bands sized for two workgroups per CU instead
+    // (one's latency phases overlap the other's adds)
     d.band = false;
-    if (!d.fused && !(desc.flags & PME_F_SEPARATE_SPREAD) && p <= 7) {
-      bool ok = true;
-      for (int a = 0; a < 3; ++a)
-        if (d.N[a] < p + d.B[a]) ok = false;
+    if (!d.fused && spread_planes) {
       const long PZ = d.N[2] + p - 1;
-      const long lx = std::min<long>(d.nb[0], (p - 1) / d.B[0] + 2);
-      auto scan_of = [&](long rows) {
-        return lx * std::min<long>(d.nb[1], (rows + p - 2) / d.B[1] + 2) * d.nb[2];
-      };
-      auto bytes_of = [&](long rows) {
-        return 8 * rows * PZ + 8 * (scan_of(rows) + 2) + 2L * pme::kFusedMap +
-               4L * pme::kBandHits;
-      };
       auto fit_rows = [&](long budget) {
-        for (long rows = std::min(d.N[1], 64); rows >= 1; --rows)
-          if (scan_of(rows) < 65535 && bytes_of(rows) <= budget) return rows;
-        return 0L;
+        const long rows = (budget - 4L * pme::kFusedMap) / (8 * PZ);
+        return std::min<long>(rows, std::min(d.N[1], 64));
       };
       long fit = fit_rows(pme::kSlabLdsMax);
-      if (fit && d.N[0] * ((d.N[1] + fit - 1) / fit) >= 4L * pme::kNumCUs) {
+      if (fit > 0 && d.N[0] * ((d.N[1] + fit - 1) / fit) >= 4L * pme::kNumCUs) {
         const long fit2 = fit_rows(pme::kBandLdsPair);
         if (fit2 >= std::min(d.N[1], 8)) fit = fit2;
       }
-      if (ok && fit >= std::min(d.N[1], 8)) {
+      if (fit >= std::min(d.N[1], 8)) {
         const long nband = (d.N[1] + fit - 1) / fit;
-        const long rows = (d.N[1] + nband - 1) / nband;
+        long rows = (d.N[1] + nband - 1) / nband;
+        const long whole = (rows + d.B[1] - 1) / d.B[1] * d.B[1];
+        if (whole <= fit && whole * (nband - 1) < d.N[1]) rows = whole;
         d.band = true;
         d.band_rows = int(rows);
-        d.band_nscan = int(scan_of(rows));
-        d.band_lds = size_t(bytes_of(rows));
+        d.band_lds = size_t(8 * rows * PZ + 4L * pme::kFusedMap);
       }
     }
     if (!d.slab) {
@@ -1273,7 +1275,7 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
   memset(&d, 0, sizeof(d));
   long nbins = 0;
   {
-    const int gc = plan_geometry(dd, d, nbins);
+    const int gc = plan_geometry(dd, d, nbins, true);
     if (gc != PME_OK) return gc;
   }
   const long M = long(d.N[0]) * d.N[1] * d.N[2];

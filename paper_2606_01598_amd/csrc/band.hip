@@ -23,6 +23,7 @@
 //
 // TREC: the density from the tangent records (q and mu; q and J mu are formed here,
 // with the same expressions as the forward binning), so that pme_step bins once.
+#include "fft_radix.h"
 #include "kernels.h"
 #include "pme_common.h"
 #include "plane_spread.h"
@@ -41,9 +42,8 @@ struct BandArgs {
   int PZ;                  // padded row length N_z + p - 1
   int rows;                // rows per band (the last band of a plane may have fewer)
   int nband;               // bands per plane
-  int nscan_max;           // bins a band may scan
-  int map_cap;             // slots of the item -> bin map
-  int hits_cap;            // entries of the hit list (>= kFusedSlotsPerThread blockDim)
+  int map_cap;             // records listed at a time
+  FastDiv nbz;             // division by nb[2]
   float* rho;
 };
 
@@ -65,7 +65,8 @@ __device__ __forceinline__ void bin_run(int first, int len, int N, int B, int nb
 }
 
 template <int P, int DEG, bool TREC>
-__global__ void __launch_bounds__(kSlabThreads) k_spread_band(BandArgs a, const double* box) {
+__global__ void __launch_bounds__(kSlabThreads) __attribute__((amdgpu_waves_per_eu(8)))
+k_spread_band(BandArgs a, const double* box) {
   static_assert(!TREC || DEG == 1, "tangent records serve the forward density");
   constexpr int lo = (P - 1) / 2;
   extern __shared__ unsigned long long band[];
@@ -76,13 +77,9 @@ __global__ void __launch_bounds__(kSlabThreads) k_spread_band(BandArgs a, const 
   const int Y0 = (item - X * a.nband) * a.rows;
   const int Ny = a.N[1], Nz = a.N[2];
   const int nrows = min(a.rows, Ny - Y0);
-  // LDS: the band | bin offsets and bins of the scan | item map | hit list
-  int* s_off = reinterpret_cast<int*>(band + size_t(a.rows) * a.PZ);
-  int* s_bin = s_off + a.nscan_max + 2;
-  uint16_t* s_map = reinterpret_cast<uint16_t*>(s_bin + a.nscan_max + 2);
-  int* s_hits = reinterpret_cast<int*>(s_map + a.map_cap);
+  // LDS: the band | listed records
+  uint32_t* s_rec = reinterpret_cast<uint32_t*>(band + size_t(a.rows) * a.PZ);
   __shared__ float s_J[(DEG == 2 || TREC) ? 9 : 1];
-  __shared__ int s_nh;
   __shared__ float s_cw[4 * P * P];           // whole-number spline pieces (x weights)
   __shared__ int s_wsum[kSlabThreads / 64];   // per-wavefront sums of the scan
   constexpr int kTab = spline_offset(P);
@@ -99,18 +96,7 @@ __global__ void __launch_bounds__(kSlabThreads) k_spread_band(BandArgs a, const 
   bin_run(X + lo - P + 1, P, a.N[0], a.B[0], a.nb[0], kx0, nlx);
   bin_run(Y0 + lo - P + 1, nrows + P - 1, Ny, a.B[1], a.nb[1], ky0, nly);
   const int nbz = a.nb[2];
-  const int nyz = nly * nbz;
-  const int nscan = nlx * nyz;                // <= a.nscan_max (host guarantees)
-  load_slot_counts(
-      nscan,
-      [&](int e) {
-        const int li = e / nyz;
-        const int r = e - li * nyz;
-        const int yi = r / nbz;
-        return (((kx0 + li) % a.nb[0]) * a.nb[1] + (ky0 + yi) % a.nb[1]) * nbz + (r - yi * nbz);
-      },
-      a.count, a.cap, a.ovf_count, s_off, s_bin);
-  if (tid == 0) s_nh = 0;
+  const int nscan = nlx * nly * nbz;
   // the fixed-point unit of the tile spread (the same bound and the same scale)
   constexpr float kWhole3 = float(spline_norm(P)) * float(spline_norm(P)) * float(spline_norm(P));
   float scale = 1.0f;
@@ -120,12 +106,7 @@ __global__ void __launch_bounds__(kSlabThreads) k_spread_band(BandArgs a, const 
   }
   const int bvol = nrows * a.PZ;
   for (int e = tid; e < bvol; e += nthr) band[e] = 0ull;
-  __syncthreads();
-  int total;
-  const bool mapped = scan_slot_counts(nscan, s_off, s_wsum, s_map, a.map_cap, total);
-  auto record_of = [&](int it) {
-    return scanned_record(it, mapped, nscan, s_off, s_bin, s_map, a.cap, a.ovf_base);
-  };
+  // the first barrier of for_each_slot separates this from the adds
   // the first stencil row of an anchor relative to the band (mod N_y)
   auto row_rel = [&](int by) {
     int t = by - lo - Y0;
@@ -134,67 +115,47 @@ __global__ void __launch_bounds__(kSlabThreads) k_spread_band(BandArgs a, const 
     t -= (t >= Ny) ? Ny : 0;
     return t;
   };
-  // one atom: its footprint in the plane, in the band's rows (stencil row iy of an atom
-  // anchored at b_y lies on mesh row b_y - lo + iy)
+  // its footprint in the plane, in the band's rows (stencil row iy of an atom anchored at
+  // b_y lies on mesh row b_y - lo + iy)
   auto add_atom = [&](size_t ri) {
-    add_atom_plane<P, DEG, TREC>(a.rec, ri, s_J, s_cw, X, a.N[0], scale, band, a.PZ,
-                                 [&](int by, int iy) {
-                                   const int rr = row_rel(by) + iy;
-                                   return rr - ((rr >= Ny) ? Ny : 0);
-                                 },
-                                 nrows);
+    add_atom_plane<P, DEG, TREC>(
+        a.rec, ri, s_J, s_cw, X, a.N[0], scale, band, a.PZ,
+        [&](int by) {
+          const int t = row_rel(by);
+          return t < nrows || t + P - 1 >= Ny;
+        },
+        [&](int by, int iy) {
+          const int rr = row_rel(by) + iy;
+          return rr - ((rr >= Ny) ? Ny : 0);
+        },
+        nrows);
   };
-
-  // rounds of kFusedSlotsPerThread scanned slots per thread (their anchor words
-  // loaded together): the atoms whose stencil covers the plane and the band are
-  // listed; the list is drained (one atom per thread) when another round might not
-  // fit and after the last round
-  constexpr int U = kFusedSlotsPerThread;
-  for (int r0 = 0; r0 < total; r0 += U * nthr) {
-    size_t ri[U];
-    int pk[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int it = r0 + u * nthr + tid;
-      ri[u] = (it < total) ? record_of(it) : size_t(0);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      pk[u] = (r0 + u * nthr + tid < total) ? __float_as_int(a.rec[ri[u] * kRecWords + 3]) : -1;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bool hit = false;
-      if (pk[u] >= 0) {
-        int d = X - (pk[u] & 1023) + lo;
-        d += (d < 0) ? a.N[0] : 0;
-        d -= (d >= a.N[0]) ? a.N[0] : 0;
-        const int t = row_rel((pk[u] >> 10) & 1023);
-        hit = d < P && (t < nrows || t + P - 1 >= Ny);
-      }
-      const int k = wave_compact(hit, &s_nh);
-      if (hit) s_hits[k] = int(ri[u]);
-    }
-    __syncthreads();
-    const int nh = s_nh;
-    __syncthreads();   // every thread has read the count before it changes
-    if (nh + U * nthr > a.hits_cap || r0 + U * nthr >= total) {
-      for (int e = tid; e < nh; e += nthr) add_atom(size_t(uint32_t(s_hits[e])));
-      if (tid == 0) s_nh = 0;
-      __syncthreads();
-    }
-  }
-  // write-back: each row's extra columns folded into their periodic images
+  for_each_slot(
+      nscan,
+      [&](int e) {
+        // layer li fastest (the counters lie x fastest), then z bin kz, then y bin yi
+        const int r = e / nlx, li = e - r * nlx;
+        const int yi = int(fdiv(uint32_t(r), a.nbz)), kz = r - yi * nbz;
+        int kx = kx0 + li, ky = ky0 + yi;
+        kx -= (kx >= a.nb[0]) ? a.nb[0] : 0;
+        ky -= (ky >= a.nb[1]) ? a.nb[1] : 0;
+        return make_int2((kx * a.nb[1] + ky) * nbz + kz, count_index(kx, ky, kz, a.nb));
+      },
+      a.count, a.cap, a.ovf_count, a.ovf_base, s_rec, a.map_cap, s_wsum, add_atom);
+  __syncthreads();
+  // write-back, a row per wavefront: the row's extra columns folded into their periodic
+  // images
   const double inv_scale = 1.0 / (double(scale) * double(kWhole3));
   float* out = a.rho + (size_t(X) * Ny + Y0) * Nz;
-  const int nout = nrows * Nz;
-  for (int e = tid; e < nout; e += nthr) {
-    const int rr = e / Nz, z = e - rr * Nz;
+  for (int rr = tid >> 6; rr < nrows; rr += nthr >> 6) {
     const unsigned long long* row = band + size_t(rr) * a.PZ;
-    const int pz = z + lo;
-    unsigned long long acc = row[pz];
-    if (pz + Nz < a.PZ) acc += row[pz + Nz];
-    if (pz >= Nz) acc += row[pz - Nz];
-    out[e] = from_fixed((long long)acc, inv_scale);
+    for (int z = tid & 63; z < Nz; z += 64) {
+      const int pz = z + lo;
+      unsigned long long acc = row[pz];
+      if (pz + Nz < a.PZ) acc += row[pz + Nz];
+      if (pz >= Nz) acc += row[pz - Nz];
+      out[size_t(rr) * Nz + z] = from_fixed((long long)acc, inv_scale);
+    }
   }
 }
 
@@ -215,9 +176,8 @@ hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tan
   a.PZ = d.N[2] + d.p - 1;
   a.rows = d.band_rows;
   a.nband = (d.N[1] + d.band_rows - 1) / d.band_rows;
-  a.nscan_max = d.band_nscan;
   a.map_cap = kFusedMap;
-  a.hits_cap = kBandHits;
+  a.nbz = make_fast_div(d.nb[2]);
   a.rho = d.rho;
   const dim3 g(d.N[0] * a.nband), b(kSlabThreads);
   const size_t sh = d.band_lds;

@@ -809,9 +809,7 @@ struct SpreadSlabArgs {
   long long ovf_base;      // record index of the overflow list
   int PY, PZ;              // padded plane: N_y + p - 1 rows of N_z + p - 1 words
   int abuf;                // float2 words before the plane (the transform's first buffer)
-  int nscan_max;           // bins a plane may scan
-  int map_cap;             // slots of the item -> bin map
-  int hits_cap;            // entries of the hit list (>= 2 kFusedSlotsPerThread blockDim)
+  int map_cap;             // records listed at a time
 };
 
 // TREC: the records are tangent records (q, mu, v_q, v_r, v_mu) and the density is
@@ -826,19 +824,15 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   const int tid = threadIdx.x;
   const int nthr = int(blockDim.x);
   const int Ny = a.N[1], Nz = a.N[2];
-  // LDS: twiddles | first transform buffer, which holds the scan, map and hit list
-  // while atoms are added | the padded plane, later the second transform buffer
+  // LDS: twiddles | first transform buffer, which holds the listed records while atoms
+  // are added | the padded plane, later the second transform buffer
   float2* twz = sm;
   float2* twy = twz + Nz;
   float2* A = twy + Ny;
   unsigned long long* plane = reinterpret_cast<unsigned long long*>(A + a.abuf);
   float2* B = reinterpret_cast<float2*>(plane);
-  int* s_off = reinterpret_cast<int*>(A);
-  int* s_bin = s_off + a.nscan_max + 2;
-  uint16_t* s_map = reinterpret_cast<uint16_t*>(s_bin + a.nscan_max + 2);
-  int* s_hits = reinterpret_cast<int*>(s_map + a.map_cap);
+  uint32_t* s_rec = reinterpret_cast<uint32_t*>(A);
   __shared__ float s_J[(DEG == 2 || TREC) ? 9 : 1];
-  __shared__ int s_nh;
   __shared__ float s_cw[4 * P * P];           // whole-number spline pieces (x weights)
   __shared__ int s_wsum[kSlabThreads / 64];   // per-wavefront sums of the scan
   Twiddles<kSlabThreads> tz, ty;
@@ -861,15 +855,7 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   else nl = (k1 < k0) ? a.nb[0] - k0 + k1 + 1 : a.nb[0];
   nl = min(nl, a.nb[0]);
   const int nyz = a.nb[1] * a.nb[2];
-  const int nscan = nl * nyz;                 // <= a.nscan_max (host guarantees)
-  load_slot_counts(
-      nscan,
-      [&](int e) {
-        const int li = e / nyz;
-        return ((k0 + li) % a.nb[0]) * nyz + (e - li * nyz);
-      },
-      a.count, a.cap, a.ovf_count, s_off, s_bin);
-  if (tid == 0) s_nh = 0;
+  const int nscan = nl * nyz;
   // the fixed-point unit of the tile spread (the same bound and the same scale)
   constexpr float kWhole3 = float(spline_norm(P)) * float(spline_norm(P)) * float(spline_norm(P));
   float scale = 1.0f;
@@ -879,56 +865,24 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   }
   const int pvol = a.PY * a.PZ;
   for (int e = tid; e < pvol; e += nthr) plane[e] = 0ull;
+  // the first barrier of for_each_slot separates this from the adds.  One atom: its
+  // footprint in the padded plane (stencil row iy of an atom anchored at b_y in padded
+  // row b_y + iy)
+  for_each_slot(
+      nscan,
+      [&](int e) {
+        // layer li fastest (the counters lie x fastest), then the y-z bin
+        const int r = e / nl, li = e - r * nl;
+        int kx = k0 + li;
+        kx -= (kx >= a.nb[0]) ? a.nb[0] : 0;
+        return make_int2(kx * nyz + r, r * a.nb[0] + kx);
+      },
+      a.count, a.cap, a.ovf_count, a.ovf_base, s_rec, a.map_cap, s_wsum, [&](size_t ri) {
+        add_atom_plane<P, DEG, TREC>(
+            a.rec, ri, s_J, s_cw, X, a.N[0], scale, plane, a.PZ, [](int) { return true; },
+            [](int by, int iy) { return by + iy; }, 0x7fffffff);
+      });
   __syncthreads();
-  int total;
-  const bool mapped = scan_slot_counts(nscan, s_off, s_wsum, s_map, a.map_cap, total);
-  auto record_of = [&](int item) {
-    return scanned_record(item, mapped, nscan, s_off, s_bin, s_map, a.cap, a.ovf_base);
-  };
-  // one atom: its footprint in the padded plane (stencil row iy of an atom anchored at
-  // b_y in padded row b_y + iy)
-  auto add_atom = [&](size_t ri) {
-    add_atom_plane<P, DEG, TREC>(a.rec, ri, s_J, s_cw, X, a.N[0], scale, plane, a.PZ,
-                                 [](int by, int iy) { return by + iy; }, 0x7fffffff);
-  };
-
-  // rounds of kSlotsPerThread scanned slots per thread (their anchor words loaded
-  // together): the atoms whose stencil covers the plane are listed; the list is
-  // drained (one atom per thread) when another round might not fit and after the
-  // last round
-  constexpr int U = kFusedSlotsPerThread;
-  for (int r0 = 0; r0 < total; r0 += U * nthr) {
-    size_t ri[U];
-    int pk[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int item = r0 + u * nthr + tid;
-      ri[u] = (item < total) ? record_of(item) : size_t(0);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      pk[u] = (r0 + u * nthr + tid < total) ? __float_as_int(a.rec[ri[u] * kRecWords + 3]) : -1;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      bool hit = false;
-      if (pk[u] >= 0) {
-        int d = X - (pk[u] & 1023) + lo;
-        d += (d < 0) ? a.N[0] : 0;
-        d -= (d >= a.N[0]) ? a.N[0] : 0;
-        hit = d < P;
-      }
-      const int k = wave_compact(hit, &s_nh);
-      if (hit) s_hits[k] = int(ri[u]);
-    }
-    __syncthreads();
-    const int nh = s_nh;
-    __syncthreads();   // every thread has read the count before it changes
-    if (nh + U * nthr > a.hits_cap || r0 + U * nthr >= total) {
-      for (int e = tid; e < nh; e += nthr) add_atom(size_t(uint32_t(s_hits[e])));
-      if (tid == 0) s_nh = 0;
-      __syncthreads();
-    }
-  }
   // the extra columns, then the extra rows, added into their periodic images: mesh
   // point (y, z) sits at padded (y + lo, z + lo), and padded column c < lo is column
   // c + N_z, column c >= lo + N_z is c - N_z (rows alike).  Each image word takes one
@@ -1099,9 +1053,7 @@ hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tan
   a.PY = d.N[1] + d.p - 1;
   a.PZ = d.N[2] + d.p - 1;
   a.abuf = d.fused_abuf;
-  a.nscan_max = d.fused_nscan;
   a.map_cap = kFusedMap;
-  a.hits_cap = kFusedHits;
   const dim3 g(d.N[0]), b(kSlabThreads);
   const size_t sh = d.fused_lds;
 #define PME_F(P)                                                                   \

@@ -156,14 +156,14 @@ __device__ __forceinline__ FastDiv make_fastdiv(int d) {
 }
 
 // One tile of either gather.
-//  1. One round trip: every thread loads the record of one slot of the tile's own
-//     bins speculatively (slot e is slot e mod cap of own bin e / cap; it is used only
-//     if it is occupied), the own-bin counts, the overflow count and the field
-//     region(s) over the tile plus the stencil halo.
-//  2. Rounds of up to 256 slots: occupied slots are compacted into an LDS queue
-//     (the next round's records are loaded meanwhile) and the queue is processed
-//     with p lanes per atom.
-//  3. Overflow records whose anchor lies in the tile, the same way.
+//  1. The counts of the tile's own bins (one per thread) are scanned while the tables of
+//     the field region are made, and the records of the first kGatherQueue atoms listed.
+//  2. Those records are loaded into the queue together with the field region(s) over the
+//     tile plus the stencil halo, and processed with p lanes per atom; further windows of
+//     atoms follow.  (Loading every slot of the bins at once saves the wait for the
+//     counts but reads several times the records: 1M ions on 320^3, Hessian-vector
+//     product, 385 us so and 353 this way.)
+//  3. Overflow records whose anchor lies in the tile, compacted into the queue.
 // Queue entries: the anchor header and, forward: q, mu, atom; Hessian-vector
 // product: q, mu, v_q, v_r, v_mu, atom (the tangent record carries them).
 
@@ -211,6 +211,8 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
   __shared__ int s_atom[R4 ? 1 : kGatherQueue];      // forward
   __shared__ float4 s_sa[VIR ? kGatherQueue : 1];    // VIR: unwrapped fractional position
   __shared__ int s_n;
+  __shared__ int s_ws[4];                   // per-wavefront sums of the scan
+  __shared__ int s_list[kGatherQueue];      // records of the queued window
   __shared__ float s_coef[4 * P * P];       // pieces of N_P and their derivatives
   constexpr int lo = (P - 1) / 2;
   constexpr int APW = 64 / P;
@@ -243,23 +245,16 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     nbo[ax] = T[ax] / a.B[ax];
     kb0[ax] = t0[ax] / a.B[ax];
   }
-  const int nown = nbo[0] * nbo[1] * nbo[2];
-  const int cap = a.cap;
-  const int nslot = nown * cap;
-  auto own_bin = [&](int j) {
-    const int kz = j % nbo[2], ky = (j / nbo[2]) % nbo[1], kx = j / (nbo[1] * nbo[2]);
-    return ((kb0[0] + kx) * a.nb[1] + kb0[1] + ky) * a.nb[2] + kb0[2] + kz;
-  };
-  auto slot_rec = [&](int e) {
-    const int j = e / cap;
-    return load_rec<R4>(a.rec, size_t(own_bin(j)) * cap + (e - j * cap));
-  };
-  // 1. records of the first 256 slots, their bins' counts and the field region in
-  // flight together (nslot >= cap > 0: a tile holds whole bins; slots past the end
-  // load the last one again and are not used)
-  int ec = min(tid, nslot - 1);
-  RecRegs<R4> cur = slot_rec(ec);
-  int cnt = a.count[own_bin(ec / cap)];
+  const int nown = nbo[0] * nbo[1] * nbo[2];   // at most 256 (one per thread)
+  // 1. the atoms of the tile's bin tid (none past the last bin)
+  int bcnt = 0, bfirst = 0;
+  if (tid < nown) {
+    // x fastest, as the counters lie
+    const int kx = kb0[0] + tid % nbo[0], ky = kb0[1] + tid / nbo[0] % nbo[1];
+    const int kz = kb0[2] + tid / (nbo[0] * nbo[1]);
+    bcnt = min(a.count[count_index(kx, ky, kz, a.nb)], a.cap);
+    bfirst = ((kx * a.nb[1] + ky) * a.nb[2] + kz) * a.cap;
+  }
   const int novf = *a.ovf_count;
   const int EV = E[0] * E[1] * E[2];
   // global offsets of the region's rows (ex, ey) and wrapped z coordinates, made
@@ -279,7 +274,33 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     }
     for (int z = tid; z < E[2]; z += blockDim.x) s_zo[z] = wrap(t0[2] - lo + z, a.N[2]);
   }
+  const int lane = tid & 63, wave = tid >> 6;
+  // the atoms numbered by a scan of the bins' counts
+  int bend = bcnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(bend, o, 64);
+    if (lane >= o) bend += v;
+  }
+  if (lane == 63) s_ws[wave] = bend;
   __syncthreads();
+  int natom = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    bend += w < wave ? s_ws[w] : 0;
+    natom += s_ws[w];
+  }
+  // the records of atoms w0 .. w0 + kGatherQueue - 1 into s_list
+  auto list_window = [&](int w0) {
+    const int off = bend - bcnt - w0;
+    for (int k = max(0, -off); k < min(bcnt, kGatherQueue - off); ++k) s_list[off + k] = bfirst + k;
+  };
+  list_window(0);
+  __syncthreads();
+  // those of the first window and the field region in flight together
+  const int first = min(natom, kGatherQueue);
+  RecRegs<R4> cur;
+  if (tid < first) cur = load_rec<R4>(a.rec, uint32_t(s_list[tid]));
   {
     const FastDiv d2 = make_fastdiv(E[2]);
     constexpr int U = 16;   // loads kept in flight per thread
@@ -323,7 +344,6 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
       vg[k] = 0.0f;
     }
   }
-  const int lane = tid & 63, wave = tid >> 6;
   const int gslot = lane / P, ix = lane - gslot * P;
 
   auto put = [&](int k, const RecRegs<R4>& r) {
@@ -337,12 +357,6 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
       s_atom[k] = __float_as_int(r.sa.w);
       if constexpr (VIR) s_sa[k] = r.sa;
     }
-  };
-  // compacted index of a valid record (-1 otherwise); the first kGatherQueue are queued
-  auto enqueue = [&](bool valid, const RecRegs<R4>& r) {
-    const int k = wave_compact(valid, &s_n);
-    if (valid && k < kGatherQueue) put(k, r);
-    return k;
   };
   auto process = [&](int nq) {
     for (int b0 = 0; b0 < nq; b0 += 4 * APW) {
@@ -708,12 +722,37 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     }
   };
 
-  // 2. rounds of 256 own-bin slots, then of 256 overflow records (those anchored in
-  // the tile are owned); one round is compacted into the queue while the previous
-  // one has been processed, so that no record registers live across the stencil work
-  // the queue of a round in chunks of kGatherQueue: chunks after the first reload
-  // their records (record index ri) from global memory
-  auto drain = [&](int k, uint32_t ri) {
+  // 2. windows of the tile's atoms
+  if (tid < first) put(tid, cur);
+  __syncthreads();
+  process(first);
+  for (int w0 = kGatherQueue; w0 < natom; w0 += kGatherQueue) {
+    const int n = min(natom - w0, kGatherQueue);
+    list_window(w0);   // the queue holds the last window, the list is free
+    __syncthreads();
+    if (tid < n) put(tid, load_rec<R4>(a.rec, uint32_t(s_list[tid])));
+    __syncthreads();
+    process(n);
+  }
+  // 3. rounds of 256 overflow records, those anchored in the tile compacted into the
+  // queue in chunks of kGatherQueue (chunks after the first are loaded again)
+  for (int o0 = 0; o0 < novf; o0 += 256) {
+    __syncthreads();   // the queue has been read
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    bool valid = false;
+    RecRegs<R4> rec;
+    const uint32_t ri = uint32_t(a.ovf_base + o0 + tid);
+    if (o0 + tid < novf) {
+      rec = load_rec<R4>(a.rec, ri);
+      const int pk = __float_as_int(rec.h.w);
+      const int b0 = pk & 1023, b1 = (pk >> 10) & 1023, b2 = (pk >> 20) & 1023;
+      valid = b0 >= t0[0] && b0 < t0[0] + T[0] && b1 >= t0[1] && b1 < t0[1] + T[1] &&
+              b2 >= t0[2] && b2 < t0[2] + T[2];
+    }
+    const int k = wave_compact(valid, &s_n);
+    if (valid && k < kGatherQueue) put(k, rec);
+    __syncthreads();
     const int nv = s_n;
     process(min(nv, kGatherQueue));
     for (int c0 = kGatherQueue; c0 < nv; c0 += kGatherQueue) {
@@ -722,40 +761,6 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
       __syncthreads();
       process(min(kGatherQueue, nv - c0));
     }
-  };
-  int kq = enqueue(tid < nslot && ec % cap < cnt, cur);
-  uint32_t rq = uint32_t(own_bin(ec / cap) * cap + (ec - (ec / cap) * cap));
-  __syncthreads();
-  const int nrs = (nslot + 255) >> 8;
-  const int nr = nrs + ((novf + 255) >> 8);
-  for (int r = 0;;) {
-    drain(kq, rq);
-    if (++r >= nr) break;
-    __syncthreads();   // the queue has been read
-    if (tid == 0) s_n = 0;
-    bool valid = false;
-    RecRegs<R4> rec;
-    if (r < nrs) {
-      const int e = r * 256 + tid;
-      ec = min(e, nslot - 1);
-      rec = slot_rec(ec);
-      cnt = a.count[own_bin(ec / cap)];
-      valid = e < nslot && ec % cap < cnt;
-      rq = uint32_t(own_bin(ec / cap) * cap + (ec - (ec / cap) * cap));
-    } else {
-      const int o = (r - nrs) * 256 + tid;
-      if (o < novf) {
-        rq = uint32_t(a.ovf_base + o);
-        rec = load_rec<R4>(a.rec, rq);
-        const int pk = __float_as_int(rec.h.w);
-        const int b0 = pk & 1023, b1 = (pk >> 10) & 1023, b2 = (pk >> 20) & 1023;
-        valid = b0 >= t0[0] && b0 < t0[0] + T[0] && b1 >= t0[1] && b1 < t0[1] + T[1] &&
-                b2 >= t0[2] && b2 < t0[2] + T[2];
-      }
-    }
-    __syncthreads();   // s_n is cleared
-    kq = enqueue(valid, rec);
-    __syncthreads();
   }
   if constexpr (VIR) {
     __shared__ double vred[16 * 9];

@@ -67,10 +67,7 @@ constexpr int kSlabThreads = 1024;  // slab-pass workgroup (one x-plane)
 constexpr int kSlabLdsMax = 160 * 1024 - 2048;
 constexpr int kLineLdsTwo = 52 * 1024;         // two-stage pencil workgroup: three per CU
 constexpr int kLineLdsGeneral = 144 * 1024;    // general pencil workgroup (8 lines of 1024)
-constexpr int kFusedMap = 4096;     // item -> bin map slots of a fused spread-slab workgroup
-constexpr int kFusedSlotsPerThread = 4;   // scanned slots per thread and round
-constexpr int kFusedHits = 2 * kFusedSlotsPerThread * kSlabThreads;   // its hit list (two rounds)
-constexpr int kBandHits = kFusedSlotsPerThread * kSlabThreads;       // band spread's (one round)
+constexpr int kFusedMap = 4096;     // records a plane or band spread workgroup lists at a time
 constexpr int kBandLdsPair = 78 * 1024;   // band workgroup's LDS budget, two per CU
 constexpr int kNumCUs = 256;               // compute units of the MI355X
 
@@ -117,12 +114,10 @@ struct DevPlan {
   bool fused;
   size_t fused_lds;        // its dynamic LDS bytes
   int fused_abuf;          // float2 words before the plane
-  int fused_nscan;         // bins a plane may scan
   // band spread (meshes without the fused plane spread): one workgroup per band of
   // band_rows y-rows of an x-plane, the band in LDS (band_rows x (N_z + p - 1) words)
   bool band;
   int band_rows;
-  int band_nscan;          // bins a band may scan
   size_t band_lds;         // its dynamic LDS bytes
   int ktile;               // lines per x-pass block: half-spectrum z columns (slab layout),
                            // or lines of kz blocks (pencil layout, 8 or 16)

@@ -1,10 +1,9 @@
 // Pieces shared by the x-plane spreads (Sec. 2.3.2, Eq. charge_dipole_assign): the
 // plane spread fused with the slab transform (fft.hip, k_spread_slab) and the band
-// spread (band.hip, k_spread_band).  A workgroup of either scans the slot counts of
-// the bins whose atoms can reach its plane (or band), maps scanned slots to records,
-// and adds each reaching atom's p x p footprint in its x-plane into 64-bit
-// fixed-point LDS words with the tile spread's expressions, so that every word equals
-// the tile spread's.
+// spread (band.hip, k_spread_band).  A workgroup of either lists the records of the
+// bins whose atoms can reach its plane (or band) and adds each reaching atom's p x p
+// footprint in its x-plane into 64-bit fixed-point LDS words with the tile spread's
+// expressions, so that every word equals the tile spread's.
 #pragma once
 
 #include "kernels.h"
@@ -12,97 +11,93 @@
 
 namespace pme {
 
-// The slot counts of the scanned bins into s_off and the bins into s_bin (bin_of(e) is
-// the e-th scanned bin); entry nscan is the overflow list (pseudo-bin -1).
-template <class BinOf>
-__device__ __forceinline__ void load_slot_counts(int nscan, BinOf bin_of, const int* count,
-                                                 int cap, const int* ovf_count, int* s_off,
-                                                 int* s_bin) {
-  for (int e = threadIdx.x; e < nscan; e += blockDim.x) {
-    const int bin = bin_of(e);
-    s_bin[e] = bin;
-    s_off[e] = min(count[bin], cap);
-  }
-  if (threadIdx.x == 0) {
-    s_bin[nscan] = -1;
-    s_off[nscan] = *ovf_count;
-  }
-}
-
-// After a barrier that follows load_slot_counts: the exclusive scan of s_off[0..nscan]
-// in place over the workgroup (consecutive segments per thread, wavefront prefix sums,
-// then the wavefronts' totals; s_off[nscan + 1] is the total), then the item -> bin
-// map when the total fits it.  Ends with a barrier; returns whether the map was made.
-__device__ __forceinline__ bool scan_slot_counts(int nscan, int* s_off, int* s_wsum,
-                                                 uint16_t* s_map, int map_cap, int& total) {
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  {
-    const int len = nscan + 1;
-    const int seg = (len + nthr - 1) / nthr;
-    const int s0 = min(tid * seg, len), s1 = min(s0 + seg, len);
-    int acc = 0;
-    for (int e = s0; e < s1; ++e) acc += s_off[e];
-    const int lane = tid & 63, wave = tid >> 6;
-    int incl = acc;
+// body(record index) for every record of the scanned bins (bin_of(e) is the e-th of nscan:
+// its number and its counter's) and of the overflow list, by a whole workgroup of up to 1024 threads.  The slots
+// are numbered by a scan of the bins' counts and their records listed in LDS (s_rec, map_cap
+// of them at a time); a lane takes slots far from its neighbours', so that lanes do not
+// add to the same mesh points at once.  Bins are one mesh cell wide in x, so that apart
+// from the overflow list (and bands' edge rows) every listed record is wanted: testing
+// the anchors of wider bins, compacting the hits and scanning an item map took more
+// instructions than adding the atoms.  s_wsum: one int per wavefront.
+template <class BinOf, class Body>
+__device__ __forceinline__ void for_each_slot(int nscan, BinOf bin_of, const int* count, int cap,
+                                              const int* ovf_count, long long ovf_base,
+                                              uint32_t* s_rec, int map_cap, int* s_wsum,
+                                              Body body) {
+  const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6;
+  const int nwave = nthr >> 6;
+  const int novf = *ovf_count;
+  for (int w0 = 0;; w0 += map_cap) {   // windows of map_cap slots
+    int total = 0;
+    for (int r0 = 0; r0 < nscan; r0 += nthr) {
+      const int e = r0 + tid;
+      int c = 0, base = 0;
+      if (e < nscan) {
+        const int2 bin = bin_of(e);   // its record block and its counter
+        c = min(count[bin.y], cap);
+        base = bin.x * cap;
+      }
+      int incl = c;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+      }
+      if (lane == 63) s_wsum[wave] = incl;
+      __syncthreads();
+      int before = 0, all = 0;
+      for (int w = 0; w < nwave; ++w) {
+        const int v = s_wsum[w];
+        before += w < wave ? v : 0;
+        all += v;
+      }
+      const int off = total + before + incl - c - w0;
+      for (int k = max(0, -off); k < min(c, map_cap - off); ++k) s_rec[off + k] = uint32_t(base + k);
+      total += all;
+      __syncthreads();   // s_wsum has been read
     }
-    if (lane == 63) s_wsum[wave] = incl;
+    {
+      const int off = total - w0;
+      for (int k = max(0, -off) + tid; k < min(novf, map_cap - off); k += nthr)
+        s_rec[off + k] = uint32_t(ovf_base + k);
+      total += novf;
+    }
     __syncthreads();
-    int before = 0;
-    for (int w = 0; w < wave; ++w) before += s_wsum[w];
-    int run = before + incl - acc;
-    for (int e = s0; e < s1; ++e) { const int v = s_off[e]; s_off[e] = run; run += v; }
-    if (tid == nthr - 1) s_off[len] = before + incl;
-  }
-  __syncthreads();
-  total = s_off[nscan + 1];
-  const bool mapped = total <= map_cap;
-  if (mapped)
-    for (int e = tid; e <= nscan; e += nthr)
-      for (int k = s_off[e]; k < s_off[e + 1]; ++k) s_map[k] = uint16_t(e);
-  __syncthreads();
-  return mapped;
-}
-
-// Record index of scanned slot `it`: the bin is the last one whose offset is <= it.
-__device__ __forceinline__ size_t scanned_record(int it, bool mapped, int nscan, const int* s_off,
-                                                 const int* s_bin, const uint16_t* s_map, int cap,
-                                                 long long ovf_base) {
-  int lb = 0;
-  if (mapped) {
-    lb = s_map[it];
-  } else {
-    int hb = nscan;
-    while (lb < hb) {
-      const int mid = (lb + hb + 1) >> 1;
-      if (s_off[mid] <= it) lb = mid; else hb = mid - 1;
+    const int n = min(total - w0, map_cap);
+    const int rows = (n + 63) >> 6;
+    for (int r = wave; r < rows; r += nwave) {
+      const int slot = lane * rows + r;
+      if (slot < n) body(size_t(s_rec[slot]));
     }
+    if (w0 + map_cap >= total) break;
+    __syncthreads();   // s_rec has been read
   }
-  const int bin = s_bin[lb];
-  const int slot = it - s_off[lb];
-  return (bin >= 0) ? size_t(bin) * cap + slot : size_t(ovf_base) + slot;
 }
 
-// One atom's footprint in x-plane X: record ri's weights and coefficients with the tile
-// spread's arithmetic, and its P x P words added at row rows(b_y, iy) (skipped from
+// One atom's footprint in x-plane X (nothing when its stencil misses the plane): record
+// ri's weights and coefficients with the tile spread's arithmetic, and its P x P words added at row rows(b_y, iy) (skipped from
 // row_limit on) and padded column b_z + iz of `plane` (rows of PZ words).  DEG 1 takes the
 // forward coefficients from a forward record, or with TREC forms q and J mu from a
 // tangent record; DEG 2 forms the ten tangent coefficients.  s_J holds J (DEG 2 or
-// TREC), s_cw the whole-number spline pieces, scale the fixed-point unit.
-template <int P, int DEG, bool TREC, class Rows>
+// TREC), s_cw the whole-number spline pieces, scale the fixed-point unit; reaches(b_y):
+// whether any of its rows is wanted.
+template <int P, int DEG, bool TREC, class Reaches, class Rows>
 __device__ __forceinline__ void add_atom_plane(const float* rec, size_t ri, const float* s_J,
                                                const float* s_cw, int X, int Nx, float scale,
-                                               unsigned long long* plane, int PZ, Rows rows,
-                                               int row_limit) {
+                                               unsigned long long* plane, int PZ,
+                                               Reaches reaches, Rows rows, int row_limit) {
   static_assert(!TREC || DEG == 1, "tangent records serve the forward density");
   constexpr int NC = (DEG == 1) ? 4 : 10;
   constexpr int D = (DEG == 1) ? 1 : 2;       // highest weight derivative needed
   constexpr int lo = (P - 1) / 2;
   const float4* r = reinterpret_cast<const float4*>(rec + ri * kRecWords);
   const float4 h = r[0];
+  const int pk = __float_as_int(h.w);
+  const int by = (pk >> 10) & 1023, bz = (pk >> 20) & 1023;
+  int ix = X - (pk & 1023) + lo;
+  ix += (ix < 0) ? Nx : 0;
+  ix -= (ix >= Nx) ? Nx : 0;
+  if (ix >= P || !reaches(by)) return;
   const float4 c0v = r[1];
   float co[NC];
   if constexpr (DEG == 2) {
@@ -122,11 +117,6 @@ __device__ __forceinline__ void add_atom_plane(const float* rec, size_t ri, cons
   } else {
     co[0] = c0v.x; co[1] = c0v.y; co[2] = c0v.z; co[3] = c0v.w;
   }
-  const int pk = __float_as_int(h.w);
-  const int by = (pk >> 10) & 1023, bz = (pk >> 20) & 1023;
-  int ix = X - (pk & 1023) + lo;
-  ix += (ix < 0) ? Nx : 0;
-  ix -= (ix >= Nx) ? Nx : 0;
   // this plane's x weights (whole-number, times the fixed-point unit): the column ix
   // of spline_weights_whole, with the same Horner steps
   float x[D + 1];

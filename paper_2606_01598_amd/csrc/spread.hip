@@ -129,8 +129,9 @@ __device__ __forceinline__ void bin_body(const BinArgs& a, const int blk) {
       atomicOr(a.status, 1);
     } else {
       // the slot is reserved first: the coefficients are formed while it returns
-      const int bin = ((base[0] / a.B[0]) * a.nb[1] + base[1] / a.B[1]) * a.nb[2] + base[2] / a.B[2];
-      const int slot = atomicAdd(&a.count[bin], 1);
+      const int kx = base[0] / a.B[0], ky = base[1] / a.B[1], kz = base[2] / a.B[2];
+      const int bin = (kx * a.nb[1] + ky) * a.nb[2] + kz;
+      const int slot = atomicAdd(&a.count[count_index(kx, ky, kz, a.nb)], 1);
       float J[3][3];
       jacobian(c, a.N, J);
       const float3 d = jmul(J, mu);
@@ -426,7 +427,7 @@ __device__ __forceinline__ void spread_body(const SpreadArgs& a, const int tile_
     const int bz = wrapn(kmin[2] + kz, a.nb[2]);
     const int bin = (bx * a.nb[1] + by) * a.nb[2] + bz;
     s_bin[e] = bin;
-    s_off[e] = min(a.count[bin], a.cap);
+    s_off[e] = min(a.count[count_index(bx, by, bz, a.nb)], a.cap);
   }
   if (tid == 0) {
     s_bin[nbr] = -1;                          // pseudo-bin: the overflow list

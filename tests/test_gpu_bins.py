@@ -1,0 +1,58 @@
+"""The bins of the plane spreads (one cell wide in x) and the counted front end of the
+gather where they can go wrong: an ionic crystal that fills every third x-plane, so that
+bins pass their capacity and records overflow; a box whose atoms all lie in one tile of
+the gather (many windows of its queue, and one window with a single atom more than the
+queue holds); and a pair of atoms.  Against
+the FP64 oracle, with the bounds of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_util import (E_REL_TOL, RMS_REL_TOL, host, oracle_forward, oracle_hvp, rel, rms_rel,
+                      to_dev)
+
+pytestmark = pytest.mark.gpu
+
+
+def _frame(kind, diag):
+    rng = np.random.default_rng(sum(map(ord, kind)))
+    diag = np.asarray(diag, dtype=float)
+    if kind == "layered":
+        g = np.stack(np.meshgrid(np.arange(0, diag[0], 3.0), np.arange(0, diag[1], 1.5),
+                                 np.arange(0, diag[2], 1.5), indexing="ij"), -1).reshape(-1, 3)
+        pos = g + rng.uniform(0.0, 0.2, g.shape)
+    else:
+        n = {"two": 2, "queue": 129, "tile": 700}[kind]
+        pos = rng.uniform(0.5, 4.5, (n, 3))
+    n = len(pos)
+    q = rng.normal(0.0, 1.0, n)
+    q -= q.mean()
+    return synth.Frame(pos=pos, q=q, mu=rng.normal(0.0, 0.1, (n, 3)), box=np.diag(diag))
+
+
+@pytest.mark.parametrize("kind,mesh,spread", [
+    ("layered", (30, 32, 32), "fused"), ("layered", (24, 30, 45), "fused"),
+    ("layered", (24, 128, 125), "band"), ("queue", (32, 32, 32), "fused"),
+    ("tile", (32, 27, 25), "fused"), ("tile", (20, 135, 128), "band"),
+    ("two", (16, 16, 16), "fused")])
+def test_crowded_bins_and_tiles(kind, mesh, spread):
+    from paper_2606_01598_amd.pme import Plan
+    f = _frame(kind, mesh)
+    print(f"case: {kind} n={f.n} mesh={mesh}", flush=True)
+    alpha = 0.35
+    plan = Plan(mesh, 6, alpha, max_atoms=f.n)
+    assert plan.spread_kind == spread
+    pos, q, mu, box = to_dev(f)
+    v = synth.random_cotangents(f.n, 5, scale_r=0.1)
+    ref = oracle_forward(f, mesh, 6, alpha, 1.0, with_q=True, with_mu=True)
+    href = oracle_hvp(f, mesh, 6, alpha, v)
+    vd = [torch.tensor(np.asarray(x), dtype=torch.float32, device=pos.device) for x in v]
+    out = plan.forward(pos, q, mu, box)
+    g = plan.backward(pos, q, mu, box, *vd)
+    plan.status()
+    assert rel(host(out["energy"]).sum(), ref.energy) <= E_REL_TOL
+    for k in ("dE_dpos", "dE_dq", "dE_dmu"):
+        assert rms_rel(host(out[k]), getattr(ref, k)) <= RMS_REL_TOL, k
+    for k, want in zip(("g_pos", "g_q", "g_mu"), href):
+        assert rms_rel(host(g[k]), want) <= RMS_REL_TOL, k
