@@ -816,12 +816,32 @@ int pme_step(pme_plan_t plan, void* stream, int32_t n, const float* pos, const f
   hipError_t e;
   mark_phi(plan, false);
   if (d.fused || d.band) {
-    // One binning for both densities and the gather: the cotangent binning (its
-    // records carry q and mu; it also forms the forward coefficients' largest sum and
-    // the self-term sums) on the second stream, then the cotangent chain there; the
-    // forward plane or band spread reads the same records once they are written.
+    // One binning for both densities and the gather: the cotangent binning (its records
+    // carry q and mu; it also forms the forward coefficients' largest sum and the
+    // self-term sums).
     const int tset = plan->tset;
     plan->tset ^= 1;
+    // On slab meshes the two chains then share their launches on the caller's stream
+    // (launch_spread_slab_pair and the like).  Not while the launch timer is armed for one
+    // of their kernels: a kind is one launch there.
+    const pme::GatherForward fwd{energy, dE_dpos, dE_dq, dE_dmu, pme::bin_blocks(n)};
+    if (d.slab && (tm.capturing || tm.kind < PME_K_SPREAD || tm.kind > PME_K_FFT_C2R)) {
+      if ((e = pme::launch_bin(dt, s, tset, n, pos, q, mu, box, v_pos, v_q, v_mu, true,
+                               energy != nullptr, tm.next(PME_K_BIN_TANGENT), true)) != hipSuccess)
+        return hip_fail(e);
+      e = d.fused ? pme::launch_spread_slab_pair(d, dt, s, tset, box)
+                  : pme::launch_spread_band_pair(d, dt, s, tset, box);
+      if (e != hipSuccess) return hip_fail(e);
+      if ((e = pme::launch_convolve_pair(d, dt, s, box, energy != nullptr, d.fused)) != hipSuccess)
+        return hip_fail(e);
+      if ((e = pme::launch_gather_hvp(dt, s, tset, n, pos, q, mu, box, v_pos, v_q, v_mu, g_pos,
+                                      g_q, g_mu, tm.next(PME_K_GATHER_HVP), &fwd)) != hipSuccess)
+        return hip_fail(e);
+      mark_phi(plan, true);
+      return PME_OK;
+    }
+    // Otherwise the binning and the cotangent chain on the second stream; the forward
+    // plane or band spread reads the records once they are written.
     if ((e = hipEventRecord(plan->fork, s)) != hipSuccess) return hip_fail(e);
     if ((e = hipStreamWaitEvent(s2, plan->fork, 0)) != hipSuccess) return hip_fail(e);
     if ((e = pme::launch_bin(dt, s2, tset, n, pos, q, mu, box, v_pos, v_q, v_mu, true,
@@ -840,7 +860,6 @@ int pme_step(pme_plan_t plan, void* stream, int32_t n, const float* pos, const f
       return hip_fail(e);
     if ((e = hipEventRecord(plan->join, s2)) != hipSuccess) return hip_fail(e);
     if ((e = hipStreamWaitEvent(s, plan->join, 0)) != hipSuccess) return hip_fail(e);
-    const pme::GatherForward fwd{energy, dE_dpos, dE_dq, dE_dmu, pme::bin_blocks(n)};
     if ((e = pme::launch_gather_hvp(dt, s, tset, n, pos, q, mu, box, v_pos, v_q, v_mu, g_pos,
                                     g_q, g_mu, tm.next(PME_K_GATHER_HVP), &fwd)) != hipSuccess)
       return hip_fail(e);

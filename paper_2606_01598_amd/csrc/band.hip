@@ -65,14 +65,13 @@ __device__ __forceinline__ void bin_run(int first, int len, int N, int B, int nb
 }
 
 template <int P, int DEG, bool TREC>
-__global__ void __launch_bounds__(kSlabThreads) __attribute__((amdgpu_waves_per_eu(8)))
-k_spread_band(BandArgs a, const double* box) {
+__device__ __forceinline__ void spread_band_body(const BandArgs& a, const unsigned* cmax,
+                                                 float* rho, const int item, const double* box) {
   static_assert(!TREC || DEG == 1, "tangent records serve the forward density");
   constexpr int lo = (P - 1) / 2;
   extern __shared__ unsigned long long band[];
   const int tid = threadIdx.x;
   const int nthr = int(blockDim.x);
-  const int item = xcd_item(blockIdx.x, gridDim.x);
   const int X = item / a.nband;
   const int Y0 = (item - X * a.nband) * a.rows;
   const int Ny = a.N[1], Nz = a.N[2];
@@ -101,7 +100,7 @@ k_spread_band(BandArgs a, const double* box) {
   constexpr float kWhole3 = float(spline_norm(P)) * float(spline_norm(P)) * float(spline_norm(P));
   float scale = 1.0f;
   {
-    const float cm = __uint_as_float(*a.cmax);
+    const float cm = __uint_as_float(*cmax);
     if (cm > 0.0f && isfinite(cm)) scale = ldexpf(1.0f, 31 - (ilogbf(8.0f * cm * kWhole3) + 1));
   }
   const int bvol = nrows * a.PZ;
@@ -146,7 +145,7 @@ k_spread_band(BandArgs a, const double* box) {
   // write-back, a row per wavefront: the row's extra columns folded into their periodic
   // images
   const double inv_scale = 1.0 / (double(scale) * double(kWhole3));
-  float* out = a.rho + (size_t(X) * Ny + Y0) * Nz;
+  float* out = rho + (size_t(X) * Ny + Y0) * Nz;
   for (int rr = tid >> 6; rr < nrows; rr += nthr >> 6) {
     const unsigned long long* row = band + size_t(rr) * a.PZ;
     for (int z = tid & 63; z < Nz; z += 64) {
@@ -159,19 +158,33 @@ k_spread_band(BandArgs a, const double* box) {
   }
 }
 
+template <int P, int DEG, bool TREC>
+__global__ void __launch_bounds__(kSlabThreads) __attribute__((amdgpu_waves_per_eu(8)))
+k_spread_band(BandArgs a, const double* box) {
+  spread_band_body<P, DEG, TREC>(a, a.cmax, a.rho, xcd_item(blockIdx.x, gridDim.x), box);
+}
+
+// Both densities of a step from the one binning's (tangent) records: even items the
+// density's bands, odd ones the tangent density's
+template <int P>
+__global__ void __launch_bounds__(kSlabThreads) __attribute__((amdgpu_waves_per_eu(8)))
+k_spread_band_pair(BandArgs a, const unsigned* cmax1, float* rho1, const double* box) {
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  if (item & 1) spread_band_body<P, 2, false>(a, cmax1, rho1, item >> 1, box);
+  else spread_band_body<P, 1, true>(a, a.cmax, a.rho, item >> 1, box);
+}
+
 }  // namespace
 
-hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tangent,
-                              const double* box, const LaunchEvents* ev, const RecordSource* from) {
-  if (!d.band || (from && (tangent || !from->d || !from->cmax))) return hipErrorInvalidValue;
+namespace {
+
+BandArgs make_band_args(const DevPlan& d, const DevPlan& r, int set, const unsigned* cmax) {
   BandArgs a;
   for (int k = 0; k < 3; ++k) { a.N[k] = d.N[k]; a.B[k] = d.B[k]; a.nb[k] = d.nb[k]; }
   // the bins (same geometry in both views of a plan) and the scale
-  const DevPlan& r = from ? *from->d : d;
-  const int rs = from ? from->set : set;
   a.cap = r.cap;
-  a.count = r.count[rs]; a.ovf_count = r.ovf_count[rs];
-  a.cmax = from ? from->cmax : d.cmax[set];
+  a.count = r.count[set]; a.ovf_count = r.ovf_count[set];
+  a.cmax = cmax;
   a.rec = r.rec; a.ovf_base = r.ovf_base;
   a.PZ = d.N[2] + d.p - 1;
   a.rows = d.band_rows;
@@ -179,6 +192,16 @@ hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tan
   a.map_cap = kFusedMap;
   a.nbz = make_fast_div(d.nb[2]);
   a.rho = d.rho;
+  return a;
+}
+
+}  // namespace
+
+hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tangent,
+                              const double* box, const LaunchEvents* ev, const RecordSource* from) {
+  if (!d.band || (from && (tangent || !from->d || !from->cmax))) return hipErrorInvalidValue;
+  const BandArgs a = from ? make_band_args(d, *from->d, from->set, from->cmax)
+                          : make_band_args(d, d, set, d.cmax[set]);
   const dim3 g(d.N[0] * a.nband), b(kSlabThreads);
   const size_t sh = d.band_lds;
 #define PME_B(P)                                                              \
@@ -195,12 +218,31 @@ hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tan
   return hipGetLastError();
 }
 
+hipError_t launch_spread_band_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s, int tset,
+                                   const double* box) {
+  if (!d.band) return hipErrorInvalidValue;
+  const BandArgs a = make_band_args(d, dt, tset, dt.cmax_fwd[tset]);
+  const dim3 g(2 * d.N[0] * a.nband), b(kSlabThreads);
+#define PME_B(P)                                                                          \
+  case P:                                                                                 \
+    hipLaunchKernelGGL(k_spread_band_pair<P>, g, b, d.band_lds, s, a, dt.cmax[tset], dt.rho, \
+                       box);                                                              \
+    break;
+  switch (d.p) {
+    PME_B(1) PME_B(2) PME_B(3) PME_B(4) PME_B(5) PME_B(6) PME_B(7)
+    default: return hipErrorInvalidValue;
+  }
+#undef PME_B
+  return hipGetLastError();
+}
+
 hipError_t enable_band_lds() {
   const void* fns[] = {
 #define PME_B(P)                                                   \
   reinterpret_cast<const void*>(k_spread_band<P, 1, false>),       \
       reinterpret_cast<const void*>(k_spread_band<P, 1, true>),    \
-      reinterpret_cast<const void*>(k_spread_band<P, 2, false>),
+      reinterpret_cast<const void*>(k_spread_band<P, 2, false>),   \
+      reinterpret_cast<const void*>(k_spread_band_pair<P>),
       PME_B(1) PME_B(2) PME_B(3) PME_B(4) PME_B(5) PME_B(6) PME_B(7)
 #undef PME_B
   };

@@ -131,7 +131,8 @@ __device__ __forceinline__ void slab_layout(const SlabArgs& a, float2* sm, float
 // (stored to twz and twy before the first barrier); A and B hold max(npairs N_z,
 // H (N_y + 1)) complex values each.
 template <class Src>
-__device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, const int x, const Src& src,
+__device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, float2* spec, const int x,
+                                             const Src& src,
                                              const Twiddles<kSlabThreads>& tz,
                                              const Twiddles<kSlabThreads>& ty, float2* twz,
                                              float2* twy, float2* A, float2* B) {
@@ -197,7 +198,7 @@ __device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, const int x, con
     }
   }
   __syncthreads();
-  float2* dst = a.spec + size_t(x) * Ny * H;
+  float2* dst = spec + size_t(x) * Ny * H;
   const int ny = a.ay.nst;
   if (ny >= 2 && H * a.ay.st[ny - 1].NR <= int(blockDim.x)) {
     // last y stage writes the spectrum rows itself (kz fastest across lanes)
@@ -224,7 +225,8 @@ __device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, const int x, con
   }
 }
 
-__device__ __forceinline__ void slab_fwd_body(const SlabArgs& a, const int x) {
+__device__ __forceinline__ void slab_fwd_body(const SlabArgs& a, const float* real, float2* spec,
+                                              const int x) {
   extern __shared__ float2 sm[];
   float2 *twz, *twy, *A, *B;
   slab_layout(a, sm, twz, twy, A, B);
@@ -232,15 +234,16 @@ __device__ __forceinline__ void slab_fwd_body(const SlabArgs& a, const int x) {
   tz.load(a.twz, a.az.N);
   ty.load(a.twy, a.ay.N);
   const int Nz = a.az.N;
-  const float* src = a.src + size_t(x) * a.ay.N * Nz;
-  slab_fwd_run(a, x, [&](int y, int z) { return src[size_t(y) * Nz + z]; }, tz, ty, twz, twy, A, B);
+  const float* src = real + size_t(x) * a.ay.N * Nz;
+  slab_fwd_run(a, spec, x, [&](int y, int z) { return src[size_t(y) * Nz + z]; }, tz, ty, twz, twy, A, B);
 }
 
 // inverse slab: spec[x] -> y inverse FFT -> z C2R -> out[x].  The first y stage reads
 // from global memory (when one round covers it); the first z stage packs two
 // Hermitian rows into one complex pencil as it reads:
 //   P[m] = X_2c[m] + i X_2c+1[m], X[m] = conj X[N-m] for m >= H.
-__device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const int x) {
+__device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const float2* spec, float* real,
+                                              const int x) {
   extern __shared__ float2 sm[];
   const int Ny = a.ay.N, Nz = a.az.N, H = a.H;
   const int npairs = (Ny + 1) / 2;
@@ -250,7 +253,7 @@ __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const int x) {
   tz.load(a.twz, Nz);
   ty.load(a.twy, Ny);
   const int ps = Ny + 1;
-  const float2* src = a.spec + size_t(x) * Ny * H;
+  const float2* src = spec + size_t(x) * Ny * H;
   const FFTStage& y0 = a.ay.st[0];
   float2* R;
   if (H * y0.NR <= int(blockDim.x)) {
@@ -316,7 +319,7 @@ __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const int x) {
     }
   }
   __syncthreads();
-  float* dst = a.dst + size_t(x) * Ny * Nz;
+  float* dst = real + size_t(x) * Ny * Nz;
   const int nz = a.az.nst;
   if (nz >= 2 && npairs * a.az.st[nz - 1].NR <= int(blockDim.x)) {
     // last z stage writes the two real rows of its pencil itself
@@ -351,6 +354,13 @@ __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const int x) {
   }
 }
 
+// The spectrum an x pass works on, with the g cache of its workgroups
+struct XField {
+  float2* spec;
+  float* gcache;   // the per-workgroup cache of g and its keys (DevPlan::gcache, gkey; may
+  double* gkey;    // be null)
+};
+
 struct XArgs {
   AxisPlan ax;
   AxisPlan axi;    // the same radices in reverse order (inverse transform)
@@ -358,7 +368,7 @@ struct XArgs {
   int N[3];
   int H, kt;
   FastDiv ktd;
-  float2* spec;
+  XField f;
   const double* box;
   const float* dcx;
   const float* dcy;
@@ -372,9 +382,6 @@ struct XArgs {
   const float* alx;
   const float* aly;
   const float* alz;
-  // the per-workgroup cache of g and its keys (DevPlan::gcache, gkey; may be null)
-  float* gcache;
-  double* gkey;
 };
 
 // x pass fused with the influence function: forward FFT along x of kt half-spectrum
@@ -390,8 +397,8 @@ struct XArgs {
 // MODE 0: the influence function of Eq. influence; 1: the same, also forming the
 // cell-gradient partials; 2: the optimal influence function (aliasing sums).
 template <int MODE = 0>
-__device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const double* box,
-                                          double* epart) {
+__device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const int blk,
+                                          const double* box, double* epart) {
   extern __shared__ float2 sm[];
   __shared__ double red[8];
   const int Nx = a.N[0], Ny = a.N[1], Nz = a.N[2], H = a.H, kt = a.kt;
@@ -435,7 +442,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const d
   // the workgroup's cached g table, loaded before the lines whether or not its key
   // matches (the decision waits for the key; the loads need not)
   const int KN = Nx * kt;
-  float* gblk = a.gcache ? a.gcache + size_t(blk) * KN : nullptr;
+  float* gblk = f.gcache ? f.gcache + size_t(blk) * KN : nullptr;
   constexpr int GU = 14;   // Nx kt <= GU blockDim (the plan bounds kt (Nx + 1) by 3500)
   float gv[GU];
   if (gblk) {
@@ -463,7 +470,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const d
   Twiddles<kFFTThreads> twr;
   twr.load(a.tw, Nx);
   const size_t xstride = size_t(Ny) * H;
-  float2* base = a.spec + size_t(y) * H;
+  float2* base = f.spec + size_t(y) * H;
   // g of the workgroup's points into LDS (issued while the line loads are in flight)
   auto gtable = [&]() {
     const Cell c = cell_from_box(box);
@@ -546,7 +553,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const d
   auto gfill = [&]() {
     bool cached = gblk != nullptr;
     if (cached) {
-      const double* key = a.gkey + size_t(blk) * 9;
+      const double* key = f.gkey + size_t(blk) * 9;
 #pragma unroll
       for (int k = 0; k < 9; ++k) cached = cached && key[k] == box[k];
     }
@@ -561,7 +568,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const d
       }
     } else {
       gtable();
-      if (gblk && threadIdx.x < 9) a.gkey[size_t(blk) * 9 + threadIdx.x] = box[threadIdx.x];
+      if (gblk && threadIdx.x < 9) f.gkey[size_t(blk) * 9 + threadIdx.x] = box[threadIdx.x];
     }
   };
   const int last = a.ax.nst - 1;
@@ -741,16 +748,42 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const int blk, const d
 
 
 __global__ void __launch_bounds__(kSlabThreads) k_slab_fwd(SlabArgs a) {
-  slab_fwd_body(a, blockIdx.x);
+  slab_fwd_body(a, a.src, a.spec, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(kSlabThreads) k_slab_inv(SlabArgs a) {
-  slab_inv_body(a, blockIdx.x);
+  slab_inv_body(a, a.spec, a.dst, blockIdx.x);
 }
 
 template <int MODE>
 __global__ void __launch_bounds__(kFFTThreads) k_fftx_fused(XArgs a) {
-  fftx_body<MODE>(a, xcd_item(blockIdx.x, gridDim.x), a.box, a.epart);
+  fftx_body<MODE>(a, a.f, xcd_item(blockIdx.x, gridDim.x), a.box, a.epart);
+}
+
+// The passes of a step's two chains (density and tangent density) in one launch: even
+// items are the first chain's, odd ones the second's, so that what both read (records,
+// tables, the influence function's points) is asked for by neighbours on one XCD.
+// Against two streams a step has five launches and no events between them, and as many
+// workgroups in flight (32,000 ions on 100^3: 107 us a step on two streams, 76 so;
+// captured steps of 8,000 on 64^3: 65 and 53).
+__global__ void __launch_bounds__(kSlabThreads) k_slab_fwd_pair(SlabArgs a, const float* src1,
+                                                                float2* spec1) {
+  const bool t = blockIdx.x & 1;
+  slab_fwd_body(a, t ? src1 : a.src, t ? spec1 : a.spec, blockIdx.x >> 1);
+}
+
+__global__ void __launch_bounds__(kSlabThreads) k_slab_inv_pair(SlabArgs a, const float2* spec1,
+                                                                float* dst1) {
+  const bool t = blockIdx.x & 1;
+  slab_inv_body(a, t ? spec1 : a.spec, t ? dst1 : a.dst, blockIdx.x >> 1);
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(kFFTThreads) k_fftx_pair(XArgs a, XField f1) {
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  const bool t = item & 1;
+  const XField f{t ? f1.spec : a.f.spec, t ? f1.gcache : a.f.gcache, t ? f1.gkey : a.f.gkey};
+  fftx_body<MODE>(a, f, item >> 1, a.box, t ? nullptr : a.epart);
 }
 
 // Batched passes: work item (box, x-plane) or (box, x-pass workgroup); per-box
@@ -759,7 +792,7 @@ __global__ void __launch_bounds__(kSlabThreads) k_slab_fwd_batch(const SlabArgs*
                                                                  const int2* items, int n) {
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
-    slab_fwd_body(args[w.x], w.y);
+    slab_fwd_body(args[w.x], args[w.x].src, args[w.x].spec, w.y);
     __syncthreads();
   }
 }
@@ -768,7 +801,7 @@ __global__ void __launch_bounds__(kSlabThreads) k_slab_inv_batch(const SlabArgs*
                                                                  const int2* items, int n) {
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
-    slab_inv_body(args[w.x], w.y);
+    slab_inv_body(args[w.x], args[w.x].spec, args[w.x].dst, w.y);
     __syncthreads();
   }
 }
@@ -779,7 +812,7 @@ __global__ void __launch_bounds__(kFFTThreads) k_fftx_batch(const XArgs* args, c
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
     const XArgs& a = args[w.x];
-    fftx_body<MODE>(a, w.y, box + 9 * w.x, energy ? a.epart : nullptr);
+    fftx_body<MODE>(a, a.f, w.y, box + 9 * w.x, energy ? a.epart : nullptr);
     __syncthreads();
   }
 }
@@ -816,8 +849,8 @@ struct SpreadSlabArgs {
 // the forward one (DEG 1): its coefficients q, J mu are formed from them as the
 // forward binning forms them.
 template <int P, int DEG, bool TREC>
-__device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const int X,
-                                                 const double* box) {
+__device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const unsigned* cmax,
+                                                 float2* spec, const int X, const double* box) {
   static_assert(!TREC || DEG == 1, "tangent records serve the forward density");
   constexpr int lo = (P - 1) / 2;
   extern __shared__ float2 sm[];
@@ -860,7 +893,7 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   constexpr float kWhole3 = float(spline_norm(P)) * float(spline_norm(P)) * float(spline_norm(P));
   float scale = 1.0f;
   {
-    const float cm = __uint_as_float(*a.cmax);
+    const float cm = __uint_as_float(*cmax);
     if (cm > 0.0f && isfinite(cm)) scale = ldexpf(1.0f, 31 - (ilogbf(8.0f * cm * kWhole3) + 1));
   }
   const int pvol = a.PY * a.PZ;
@@ -909,12 +942,23 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   auto value = [&](int y, int z) {
     return from_fixed((long long)plane[(y + lo) * a.PZ + z + lo], inv_scale);
   };
-  slab_fwd_run(a.sl, X, value, tz, ty, twz, twy, A, B);
+  slab_fwd_run(a.sl, spec, X, value, tz, ty, twz, twy, A, B);
 }
 
 template <int P, int DEG, bool TREC>
 __global__ void __launch_bounds__(kSlabThreads) k_spread_slab(SpreadSlabArgs a, const double* box) {
-  spread_slab_body<P, DEG, TREC>(a, xcd_item(blockIdx.x, gridDim.x), box);
+  spread_slab_body<P, DEG, TREC>(a, a.cmax, a.sl.spec, xcd_item(blockIdx.x, gridDim.x), box);
+}
+
+// Both densities of a step from the one binning's (tangent) records, a plane each
+template <int P>
+__global__ void __launch_bounds__(kSlabThreads) k_spread_slab_pair(SpreadSlabArgs a,
+                                                                   const unsigned* cmax1,
+                                                                   float2* spec1,
+                                                                   const double* box) {
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  if (item & 1) spread_slab_body<P, 2, false>(a, cmax1, spec1, item >> 1, box);
+  else spread_slab_body<P, 1, true>(a, a.cmax, a.sl.spec, item >> 1, box);
 }
 
 }  // namespace
@@ -926,13 +970,13 @@ XArgs make_x_args(const DevPlan& d, const double* box, bool energy) {
   x.ax = d.ax[0]; x.tw = d.twiddle[0];
   reverse_plan(d.ax[0], x.axi);
   for (int k = 0; k < 3; ++k) x.N[k] = d.N[k];
-  x.H = d.H; x.kt = d.ktile; x.ktd = make_fast_div(d.ktile); x.spec = d.spec; x.box = box;
+  x.H = d.H; x.kt = d.ktile; x.ktd = make_fast_div(d.ktile); x.box = box;
+  x.f = XField{d.spec, d.gcache, d.gkey};
   x.dcx = d.deconv[0]; x.dcy = d.deconv[1]; x.dcz = d.deconv[2];
   x.alpha = d.alpha;
   x.epart = energy ? d.epart : nullptr;
   x.vpart = nullptr;
   x.alx = d.alias[0]; x.aly = d.alias[1]; x.alz = d.alias[2];
-  x.gcache = d.gcache; x.gkey = d.gkey;
   return x;
 }
 
@@ -1037,23 +1081,53 @@ hipError_t launch_convolve(const DevPlan& d, hipStream_t s, const double* box, f
   return hipGetLastError();
 }
 
-hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tangent,
-                              const double* box, const LaunchEvents* ev, const RecordSource* from) {
-  if (!d.fused || (from && (tangent || !from->d || !from->cmax))) return hipErrorInvalidValue;
+hipError_t launch_convolve_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s,
+                                const double* box, bool energy, bool from_spec) {
+  if (!d.slab) return hipErrorInvalidValue;
+  const SlabArgs sa = make_slab_args(d, d.phi);
+  const XArgs x = make_x_args(d, box, energy);
+  const XField x1{dt.spec, dt.gcache, dt.gkey};
+  const dim3 gs(2 * d.N[0]), gx(2 * fftx_blocks(d));
+  hipError_t err;
+  if (!from_spec) {
+    hipLaunchKernelGGL(k_slab_fwd_pair, gs, dim3(kSlabThreads), d.slab_lds, s, sa, dt.rho, dt.spec);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  }
+  if (d.opt)
+    hipLaunchKernelGGL(k_fftx_pair<2>, gx, dim3(kFFTThreads), x_lds(d), s, x, x1);
+  else
+    hipLaunchKernelGGL(k_fftx_pair<0>, gx, dim3(kFFTThreads), x_lds(d), s, x, x1);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  hipLaunchKernelGGL(k_slab_inv_pair, gs, dim3(kSlabThreads), d.slab_lds, s, sa, dt.spec, dt.rho);
+  return hipGetLastError();
+}
+
+namespace {
+
+SpreadSlabArgs make_spread_slab_args(const DevPlan& d, const DevPlan& r, int set,
+                                     const unsigned* cmax) {
   SpreadSlabArgs a;
   a.sl = make_slab_args(d, nullptr);
   for (int k = 0; k < 3; ++k) { a.N[k] = d.N[k]; a.B[k] = d.B[k]; a.nb[k] = d.nb[k]; }
   // the bins (same geometry in both views of a plan) and the scale
-  const DevPlan& r = from ? *from->d : d;
-  const int rs = from ? from->set : set;
   a.cap = r.cap;
-  a.count = r.count[rs]; a.ovf_count = r.ovf_count[rs];
-  a.cmax = from ? from->cmax : d.cmax[set];
+  a.count = r.count[set]; a.ovf_count = r.ovf_count[set];
+  a.cmax = cmax;
   a.rec = r.rec; a.ovf_base = r.ovf_base;
   a.PY = d.N[1] + d.p - 1;
   a.PZ = d.N[2] + d.p - 1;
   a.abuf = d.fused_abuf;
   a.map_cap = kFusedMap;
+  return a;
+}
+
+}  // namespace
+
+hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tangent,
+                              const double* box, const LaunchEvents* ev, const RecordSource* from) {
+  if (!d.fused || (from && (tangent || !from->d || !from->cmax))) return hipErrorInvalidValue;
+  const SpreadSlabArgs a = from ? make_spread_slab_args(d, *from->d, from->set, from->cmax)
+                                : make_spread_slab_args(d, d, set, d.cmax[set]);
   const dim3 g(d.N[0]), b(kSlabThreads);
   const size_t sh = d.fused_lds;
 #define PME_F(P)                                                                   \
@@ -1061,6 +1135,24 @@ hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tan
     if (tangent) launch_k(ev, k_spread_slab<P, 2, false>, g, b, sh, s, a, box);     \
     else if (from) launch_k(ev, k_spread_slab<P, 1, true>, g, b, sh, s, a, box);    \
     else launch_k(ev, k_spread_slab<P, 1, false>, g, b, sh, s, a, box);             \
+    break;
+  switch (d.p) {
+    PME_F(1) PME_F(2) PME_F(3) PME_F(4) PME_F(5) PME_F(6) PME_F(7)
+    default: return hipErrorInvalidValue;
+  }
+#undef PME_F
+  return hipGetLastError();
+}
+
+hipError_t launch_spread_slab_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s, int tset,
+                                   const double* box) {
+  if (!d.fused) return hipErrorInvalidValue;
+  const SpreadSlabArgs a = make_spread_slab_args(d, dt, tset, dt.cmax_fwd[tset]);
+  const dim3 g(2 * d.N[0]), b(kSlabThreads);
+#define PME_F(P)                                                                            \
+  case P:                                                                                   \
+    hipLaunchKernelGGL(k_spread_slab_pair<P>, g, b, d.fused_lds, s, a, dt.cmax[tset], dt.spec, \
+                       box);                                                                \
     break;
   switch (d.p) {
     PME_F(1) PME_F(2) PME_F(3) PME_F(4) PME_F(5) PME_F(6) PME_F(7)
@@ -1078,10 +1170,13 @@ hipError_t enable_slab_lds(size_t bytes) {
                        reinterpret_cast<const void*>(k_slab_inv),
                        reinterpret_cast<const void*>(k_slab_fwd_batch),
                        reinterpret_cast<const void*>(k_slab_inv_batch),
+                       reinterpret_cast<const void*>(k_slab_fwd_pair),
+                       reinterpret_cast<const void*>(k_slab_inv_pair),
 #define PME_F(P)                                                   \
   reinterpret_cast<const void*>(k_spread_slab<P, 1, false>),       \
       reinterpret_cast<const void*>(k_spread_slab<P, 1, true>),    \
-      reinterpret_cast<const void*>(k_spread_slab<P, 2, false>),
+      reinterpret_cast<const void*>(k_spread_slab<P, 2, false>),   \
+      reinterpret_cast<const void*>(k_spread_slab_pair<P>),
                        PME_F(1) PME_F(2) PME_F(3) PME_F(4) PME_F(5) PME_F(6) PME_F(7)
 #undef PME_F
   };

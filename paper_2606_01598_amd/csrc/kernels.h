@@ -317,6 +317,16 @@ hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tan
 hipError_t launch_spread_band(const DevPlan& d, hipStream_t s, int set, bool tangent,
                               const double* box, const LaunchEvents* ev,
                               const RecordSource* from = nullptr);
+// Both densities of a step from the tangent records of dt's binning tset: into the two
+// views' spectra (fused) or meshes (band)
+hipError_t launch_spread_slab_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s, int tset,
+                                   const double* box);
+hipError_t launch_spread_band_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s, int tset,
+                                   const double* box);
+// Both potentials of a step on a slab plan: d's into d.phi, dt's into dt.rho, from the
+// spectra (from_spec) or the meshes
+hipError_t launch_convolve_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s,
+                                const double* box, bool energy, bool from_spec);
 hipError_t enable_band_lds();
 // Raise the dynamic LDS limit of the spread (kBigLds) and gather (kGatherLds) kernels.
 hipError_t enable_spread_lds();
