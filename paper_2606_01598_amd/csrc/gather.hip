@@ -136,16 +136,37 @@ __device__ __forceinline__ void st3(float* p, int i, float3 v) {
   if (p) { p[3 * i] = v.x; p[3 * i + 1] = v.y; p[3 * i + 2] = v.z; }
 }
 
-// Sum over the P consecutive lanes of a group; the total lands on the group's first lane.
+// Sums over the P consecutive lanes of an atom, in every lane of the group (each starts
+// with its own term): pairs or triples, then their sums.  The lanes take from each other
+// round the group, so no lane has to be masked: P = 6 costs three exchanges and adds.
 template <int P>
-__device__ __forceinline__ float group_sum(float v, int ix) {
-#pragma unroll
-  for (int off = 1; off < P; off <<= 1) {
-    const float o = __shfl_down(v, off, 64);
-    if (ix + off < P) v += o;
+struct LaneGroup {
+  int first;    // byte address of the group's first lane
+  int at[4];    // of the lanes this one takes from
+
+  static constexpr int kPair = P == 6 || P == 7 ? 3 : (P == 4 || P == 5 ? 2 : 0);
+
+  __device__ __forceinline__ LaneGroup(int lane, int ix) {
+    first = 4 * (lane - ix);
+    auto turn = [&](int k) { return first + 4 * (ix + k < P ? ix + k : ix + k - P); };
+    at[0] = turn(kPair);
+    at[1] = turn(1 % P);
+    at[2] = turn(2 % P);
+    at[3] = turn(P - 1);
   }
-  return v;
-}
+  static __device__ __forceinline__ float take(int addr, float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(v)));
+  }
+  __device__ __forceinline__ float sum(float t) const {
+    if constexpr (P == 1) return t;
+    float u = t;
+    if constexpr (kPair > 0) u += take(at[0], t);
+    float r = u + take(at[1], u);
+    if constexpr (P == 3 || P == 6 || P == 7) r += take(at[2], u);
+    if constexpr (P == 5 || P == 7) r += take(at[3], t);   // the lane left over
+    return r;
+  }
+};
 
 // ceil(2^32 / d) as 0xffffffff / d + 1 (a 32-bit division; d = 1 passes through)
 __device__ __forceinline__ FastDiv make_fastdiv(int d) {
@@ -163,6 +184,12 @@ __device__ __forceinline__ FastDiv make_fastdiv(int d) {
 //     atoms follow.  (Loading every slot of the bins at once saves the wait for the
 //     counts but reads several times the records: 1M ions on 320^3, Hessian-vector
 //     product, 385 us so and 353 this way.)
+// Bound by vector issue, with the LDS reads of the stencils half as long beside it: what
+// a pass saves in instructions it gains, unless it pays for them in LDS.  (Sums round the
+// group without masks, outputs by different lanes and the cell by one wavefront: 1M ions,
+// forward 280 -> 235 us, Hessian-vector product 356 -> 344; 32,000 on 100^3 13.4 -> 12.4
+// and 18.1 -> 16.4.  The y and z weights of an atom made once and taken from its lanes:
+// 298 and 391.)
 //  3. Overflow records whose anchor lies in the tile, compacted into the queue.
 // Queue entries: the anchor header and, forward: q, mu, atom; Hessian-vector
 // product: q, mu, v_q, v_r, v_mu, atom (the tangent record carries them).
@@ -214,6 +241,7 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
   __shared__ int s_ws[4];                   // per-wavefront sums of the scan
   __shared__ int s_list[kGatherQueue];      // records of the queued window
   __shared__ float s_coef[4 * P * P];       // pieces of N_P and their derivatives
+  __shared__ float s_cell[VIR ? 19 : 10];   // J, 1 / V (and C^-1)
   constexpr int lo = (P - 1) / 2;
   constexpr int APW = 64 / P;
   const int tid = threadIdx.x;
@@ -222,8 +250,7 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
   // no barrier waits for it
   static_assert(4 * P * P <= 256, "one coefficient per thread");
   const float coef = tid < 4 * P * P ? c_spline.coef[spline_offset(P) + tid] : 0.0f;
-  const Cell c = cell_from_box(a.box);
-  if (tile == 0 && a.energy) finalize_energy(a, c);
+  if (tile == 0 && a.energy) finalize_energy(a, cell_from_box(a.box));
   int t0[3], T[3], E[3];
   {
     int t = tile;
@@ -255,13 +282,29 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     bcnt = min(a.count[count_index(kx, ky, kz, a.nb)], a.cap);
     bfirst = ((kx * a.nb[1] + ky) * a.nb[2] + kz) * a.cap;
   }
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the cell's constants, by one wavefront while the counts are on their way (100 double
+  // precision operations that the four of them would all make)
+  if (wave == 3) {
+    const Cell c = cell_from_box(a.box);
+    float J[3][3];
+    jacobian(c, a.N, J);
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 9; ++k) s_cell[k] = J[k / 3][k % 3];
+      s_cell[9] = float(1.0 / c.vol);
+      if constexpr (VIR)
+#pragma unroll
+        for (int k = 0; k < 9; ++k) s_cell[10 + k] = float(c.inv[k]);
+    }
+  }
   const int novf = *a.ovf_count;
   const int EV = E[0] * E[1] * E[2];
-  // global offsets of the region's rows (ex, ey) and wrapped z coordinates, made
+  // byte offsets of the region's rows (ex, ey) and wrapped z coordinates, made
   // once, after the field region in LDS: a region element then costs two LDS reads
   const int nrow = E[0] * E[1];
-  int* s_row = reinterpret_cast<int*>(sm + (HVP ? 2 : 1) * EV);
-  int* s_zo = s_row + nrow;
+  uint32_t* s_row = reinterpret_cast<uint32_t*>(sm + (HVP ? 2 : 1) * EV);
+  uint32_t* s_zo = s_row + nrow;
   {
     const bool small = (a.N[0] < P) || (a.N[1] < P) || (a.N[2] < P);
     auto wrap = [&](int m, int N) {
@@ -270,11 +313,11 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     const FastDiv d1 = make_fastdiv(E[1]);
     for (int r = tid; r < nrow; r += blockDim.x) {
       const int ex = int(fdiv(uint32_t(r), d1)), ey = r - ex * E[1];
-      s_row[r] = (wrap(t0[0] - lo + ex, a.N[0]) * a.N[1] + wrap(t0[1] - lo + ey, a.N[1])) * a.N[2];
+      s_row[r] = 4u * uint32_t(
+          (wrap(t0[0] - lo + ex, a.N[0]) * a.N[1] + wrap(t0[1] - lo + ey, a.N[1])) * a.N[2]);
     }
-    for (int z = tid; z < E[2]; z += blockDim.x) s_zo[z] = wrap(t0[2] - lo + z, a.N[2]);
+    for (int z = tid; z < E[2]; z += blockDim.x) s_zo[z] = 4u * uint32_t(wrap(t0[2] - lo + z, a.N[2]));
   }
-  const int lane = tid & 63, wave = tid >> 6;
   // the atoms numbered by a scan of the bins' counts
   int bend = bcnt;
 #pragma unroll
@@ -297,55 +340,6 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
   };
   list_window(0);
   __syncthreads();
-  // those of the first window and the field region in flight together
-  const int first = min(natom, kGatherQueue);
-  RecRegs<R4> cur;
-  if (tid < first) cur = load_rec<R4>(a.rec, uint32_t(s_list[tid]));
-  {
-    const FastDiv d2 = make_fastdiv(E[2]);
-    constexpr int U = 16;   // loads kept in flight per thread
-    for (int e0 = tid; e0 < EV; e0 += U * blockDim.x) {
-      float vphi[U], vpsi[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + u * blockDim.x;
-        const int ec = min(e, EV - 1);
-        const int r = int(fdiv(uint32_t(ec), d2));
-        const uint32_t g = uint32_t(s_row[r] + s_zo[ec - r * E[2]]);
-        vphi[u] = a.phi[g];
-        if (HVP) vpsi[u] = a.psi[g];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + u * blockDim.x;
-        if (e < EV) {
-          sm[e] = vphi[u];
-          if (HVP) sm[EV + e] = vpsi[u];
-        }
-      }
-    }
-  }
-  if (tid < 4 * P * P) s_coef[tid] = coef;
-  // cell and prefactor constants are uniform: kept in scalar registers
-  float J[3][3];
-  jacobian(c, a.N, J);
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) J[i][j] = uniform(J[i][j]);
-  const float iv = uniform(float(1.0 / c.vol));
-  const float pf = a.pf, cq = a.cq, cm = a.cm;
-  // VIR: C^-1 in float and the per-thread sums of the atoms this thread finishes
-  float ci[9], vg[9];
-  if constexpr (VIR) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      ci[k] = float(c.inv[k]);
-      vg[k] = 0.0f;
-    }
-  }
-  const int gslot = lane / P, ix = lane - gslot * P;
-
   auto put = [&](int k, const RecRegs<R4>& r) {
     s_h[k] = r.h;
     if constexpr (R4) {
@@ -358,6 +352,67 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
       if constexpr (VIR) s_sa[k] = r.sa;
     }
   };
+  // those of the first window and the field region in flight together
+  const int first = min(natom, kGatherQueue);
+  RecRegs<R4> cur;
+  if (tid < first) cur = load_rec<R4>(a.rec, uint32_t(s_list[tid]));
+  {
+    const FastDiv d2 = make_fastdiv(E[2]);
+    constexpr int U = 16;   // loads kept in flight per thread
+    for (int b0 = 0; b0 < EV; b0 += U * 256) {
+      float vphi[U], vpsi[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // past the end the last element again: cheaper than leaving the loads out
+        const int ec = min(b0 + u * 256 + tid, EV - 1);
+        const int r = int(fdiv(uint32_t(ec), d2));
+        const uint32_t g = s_row[r] + s_zo[ec - r * E[2]];
+        vphi[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.phi) + g);
+        if (HVP) vpsi[u] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.psi) + g);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = b0 + u * 256 + tid;
+        if (e < EV) {
+          sm[e] = vphi[u];
+          if (HVP) sm[EV + e] = vpsi[u];
+        }
+      }
+    }
+  }
+  if (tid < 4 * P * P) s_coef[tid] = coef;
+  if (tid < first) put(tid, cur);
+  __syncthreads();   // the queue, the region and the constants
+  // cell and prefactor constants are uniform: kept in scalar registers
+  float J[3][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) J[i][j] = uniform(s_cell[3 * i + j]);
+  const float iv = uniform(s_cell[9]);
+  const float pf = a.pf, cq = a.cq, cm = a.cm;
+  // VIR: C^-1 in float and the per-thread sums of the atoms this thread finishes
+  float ci[9], vg[9];
+  if constexpr (VIR) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      ci[k] = s_cell[10 + k];
+      vg[k] = 0.0f;
+    }
+  }
+  const int gslot = lane / P, ix = lane - gslot * P;
+  const LaneGroup<P> group(lane, ix);
+
+  // An output vector of an atom, J^T g / V less its self term: prefactor (J^T g / V - c u)
+  auto store_vec = [&](float* out, int i, const float (&g)[3], float c, float3 u) {
+    if (!out) return;
+    const float3 t = jtmul(J, make_float3(g[0], g[1], g[2]));
+    st3(out, i, make_float3(pf * (t.x * iv - c * u.x), pf * (t.y * iv - c * u.y),
+                            pf * (t.z * iv - c * u.z)));
+  };
+  // Every lane of an atom holds its sums: with four lanes or more each of its output
+  // vectors has a lane of its own
+  constexpr bool kSplit = P >= 4;
   auto process = [&](int nq) {
     for (int b0 = 0; b0 < nq; b0 += 4 * APW) {
       const int slot = b0 + wave * APW + gslot;
@@ -373,6 +428,7 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
           const int pk = __float_as_int(h.w);
           const int lx = (pk & 1023) - t0[0] + ix;
           const int yb = ((pk >> 10) & 1023) - t0[1], zb = ((pk >> 20) & 1023) - t0[2];
+          // y weights are made per row (fewer live registers), z weights once
           float wz[4][P], wx[4];
           spline_weights<P, 3>(h.z, wz);
           weight_at_lds<P, 3>(s_coef, ix, h.x, wx);
@@ -422,14 +478,14 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
             op[c] = v;
           }
         }
-        oq = group_sum<P>(oq, ix);
+        oq = group.sum(oq);
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
-          og[x] = group_sum<P>(og[x], ix);
-          op[x] = group_sum<P>(op[x], ix);
+          og[x] = group.sum(og[x]);
+          op[x] = group.sum(op[x]);
         }
 #pragma unroll
-        for (int m = 0; m < 6; ++m) oh[m] = group_sum<P>(oh[m], ix);
+        for (int m = 0; m < 6; ++m) oh[m] = group.sum(oh[m]);
         if (active && ix == 0) {
           const int i = __float_as_int(s_v2[slot].w);
           const float q = s_qm[slot].x;
@@ -519,28 +575,33 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
           op[1] = q * S010 + S110 * d.x + S020 * d.y + S011 * d.z;
           op[2] = q * S001 + S101 * d.x + S011 * d.y + S002 * d.z;
         }
-        oq = group_sum<P>(oq, ix);
+        oq = group.sum(oq);
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
-          og[x] = group_sum<P>(og[x], ix);
-          op[x] = group_sum<P>(op[x], ix);
+          og[x] = group.sum(og[x]);
+          op[x] = group.sum(op[x]);
         }
-        if (active && ix == 0) {
+        if (active && ix < (kSplit ? 3 : 1)) {
           const int i = s_atom[slot];
           const float4 qmv = s_qm[slot];
           const float q = qmv.x;
-          const float3 mu = make_float3(qmv.y, qmv.z, qmv.w);
-          if (a.o_q) a.o_q[i] = pf * (oq * iv - cq * q);
-          if (a.o_mu) {
-            const float3 g = jtmul(J, make_float3(og[0], og[1], og[2]));
-            st3(a.o_mu, i, make_float3(pf * (g.x * iv - cm * mu.x), pf * (g.y * iv - cm * mu.y),
-                                       pf * (g.z * iv - cm * mu.z)));
+          const float3 mu = make_float3(qmv.y, qmv.z, qmv.w), none = make_float3(0.f, 0.f, 0.f);
+          if (kSplit) {
+            // lane 0: position, 1: dipole, 2: charge
+            float g[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) g[x] = ix == 0 ? op[x] : og[x];
+            if (ix == 2) {
+              if (a.o_q) a.o_q[i] = pf * (oq * iv - cq * q);
+            } else {
+              store_vec(ix == 0 ? a.o_pos : a.o_mu, i, g, ix == 0 ? 0.0f : cm, mu);
+            }
+          } else {
+            if (a.o_q) a.o_q[i] = pf * (oq * iv - cq * q);
+            store_vec(a.o_mu, i, og, cm, mu);
+            store_vec(a.o_pos, i, op, 0.0f, none);
           }
-          if (a.o_pos) {
-            const float3 g = jtmul(J, make_float3(op[0], op[1], op[2]));
-            st3(a.o_pos, i, make_float3(pf * iv * g.x, pf * iv * g.y, pf * iv * g.z));
-          }
-          if constexpr (VIR) {
+          if (VIR && ix == 0) {
             // unwrapped fractional position (from the caller's position, by the
             // binning) and the dipole times C^-1
             const float4 sa = s_sa[slot];
@@ -573,7 +634,6 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
             const int pk = __float_as_int(h.w);
             const int lx = (pk & 1023) - t0[0] + ix;
             const int yb = ((pk >> 10) & 1023) - t0[1], zb = ((pk >> 20) & 1023) - t0[2];
-            // y weights are made per row (fewer live registers), z weights once
             float wz[4][P], wx[4];
             spline_weights<P, 3>(h.z, wz);
             weight_at_lds<P, 3>(s_coef, ix, h.x, wx);
@@ -674,47 +734,46 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
             }
           }
         }
-        oq = group_sum<P>(oq, ix);
+        oq = group.sum(oq);
 #pragma unroll
         for (int x = 0; x < 3; ++x) {
-          om[x] = group_sum<P>(om[x], ix);
-          op[x] = group_sum<P>(op[x], ix);
+          om[x] = group.sum(om[x]);
+          op[x] = group.sum(op[x]);
         }
         if (dual) {
-          fq = group_sum<P>(fq, ix);
+          fq = group.sum(fq);
 #pragma unroll
           for (int x = 0; x < 3; ++x) {
-            fm[x] = group_sum<P>(fm[x], ix);
-            fp[x] = group_sum<P>(fp[x], ix);
+            fm[x] = group.sum(fm[x]);
+            fp[x] = group.sum(fp[x]);
           }
         }
-        if (active && ix == 0) {
+        if (active && ix < (kSplit ? 4 : 1)) {
           const float4 qm = s_qm[slot], e1 = s_v1[slot], e2 = s_v2[slot];
           const int i = __float_as_int(e2.w);
-          const float q = qm.x, vq = e1.x;
-          const float3 mu = make_float3(qm.y, qm.z, qm.w);
-          const float3 vm = make_float3(e2.x, e2.y, e2.z);
-          if (a.o_q) a.o_q[i] = pf * (oq * iv - cq * vq);
-          if (a.o_mu) {
-            const float3 g = jtmul(J, make_float3(om[0], om[1], om[2]));
-            st3(a.o_mu, i, make_float3(pf * (g.x * iv - cm * vm.x), pf * (g.y * iv - cm * vm.y),
-                                       pf * (g.z * iv - cm * vm.z)));
-          }
-          if (a.o_pos) {
-            const float3 g = jtmul(J, make_float3(op[0], op[1], op[2]));
-            st3(a.o_pos, i, make_float3(pf * iv * g.x, pf * iv * g.y, pf * iv * g.z));
-          }
-          if (dual) {
-            // gradient of E^lr from the same phi sums
-            if (a.f_q) a.f_q[i] = pf * (fq * iv - cq * q);
-            if (a.f_mu) {
-              const float3 g = jtmul(J, make_float3(fm[0], fm[1], fm[2]));
-              st3(a.f_mu, i, make_float3(pf * (g.x * iv - cm * mu.x), pf * (g.y * iv - cm * mu.y),
-                                         pf * (g.z * iv - cm * mu.z)));
-            }
-            if (a.f_pos) {
-              const float3 g = jtmul(J, make_float3(fp[0], fp[1], fp[2]));
-              st3(a.f_pos, i, make_float3(pf * iv * g.x, pf * iv * g.y, pf * iv * g.z));
+          const float3 mu = make_float3(qm.y, qm.z, qm.w), vm = make_float3(e2.x, e2.y, e2.z);
+          const float3 none = make_float3(0.f, 0.f, 0.f);
+          if (kSplit) {
+            // lane 0: position, 1: dipole, and with the forward outputs (the gradient of
+            // E^lr from the same phi sums) 2 and 3: theirs; the charges by lanes 2 and 3
+            const bool at_pos = !(ix & 1), fwd = dual && ix >= 2;
+            float g[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+              g[x] = fwd ? (at_pos ? fp[x] : fm[x]) : (at_pos ? op[x] : om[x]);
+            float* out = fwd ? (at_pos ? a.f_pos : a.f_mu) : (at_pos ? a.o_pos : a.o_mu);
+            const float3 u = fwd ? mu : vm;
+            if (fwd || ix < 2) store_vec(out, i, g, at_pos ? 0.0f : cm, u);
+            if (ix == 2 && a.o_q) a.o_q[i] = pf * (oq * iv - cq * e1.x);
+            if (dual && ix == 3 && a.f_q) a.f_q[i] = pf * (fq * iv - cq * qm.x);
+          } else {
+            if (a.o_q) a.o_q[i] = pf * (oq * iv - cq * e1.x);
+            store_vec(a.o_mu, i, om, cm, vm);
+            store_vec(a.o_pos, i, op, 0.0f, none);
+            if (dual) {
+              if (a.f_q) a.f_q[i] = pf * (fq * iv - cq * qm.x);
+              store_vec(a.f_mu, i, fm, cm, mu);
+              store_vec(a.f_pos, i, fp, 0.0f, none);
             }
           }
         }
@@ -723,13 +782,11 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
   };
 
   // 2. windows of the tile's atoms
-  if (tid < first) put(tid, cur);
-  __syncthreads();
   process(first);
   for (int w0 = kGatherQueue; w0 < natom; w0 += kGatherQueue) {
     const int n = min(natom - w0, kGatherQueue);
     list_window(w0);   // the queue holds the last window, the list is free
-    __syncthreads();
+    __syncthreads();   // the list; the queue has been read
     if (tid < n) put(tid, load_rec<R4>(a.rec, uint32_t(s_list[tid])));
     __syncthreads();
     process(n);

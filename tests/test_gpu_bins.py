@@ -56,3 +56,28 @@ def test_crowded_bins_and_tiles(kind, mesh, spread):
         assert rms_rel(host(out[k]), getattr(ref, k)) <= RMS_REL_TOL, k
     for k, want in zip(("g_pos", "g_q", "g_mu"), href):
         assert rms_rel(host(g[k]), want) <= RMS_REL_TOL, k
+
+
+@pytest.mark.parametrize("p", [2, 3, 4, 5, 6, 7])
+def test_gather_orders(p):
+    """Both gathers and the step's for every number of lanes an atom has (with four and
+    more its output vectors are stored by different lanes), some outputs left out."""
+    from paper_2606_01598_amd.pme import Plan
+    f = synth.molten_box(90, 40 + p, L=13.0)
+    mesh, alpha = (16, 20, 18), 0.4
+    v = synth.random_cotangents(f.n, p, scale_r=0.2, scale_mu=0.5)
+    ref = oracle_forward(f, mesh, p, alpha, 1.0, with_q=True, with_mu=True)
+    href = oracle_hvp(f, mesh, p, alpha, v)
+    plan = Plan(mesh, p, alpha, max_atoms=f.n, concurrent=True)
+    args = to_dev(f)
+    vd = [torch.tensor(np.asarray(x), dtype=torch.float32, device=args[0].device) for x in v]
+    want = {"dE_dpos": ref.dE_dpos, "dE_dq": ref.dE_dq, "dE_dmu": ref.dE_dmu,
+            "g_pos": href[0], "g_q": href[1], "g_mu": href[2]}
+    both = plan.step(*args, *vd)
+    apart = {**plan.forward(*args), **plan.backward(*args, *vd)}
+    less = plan.backward(*args, *vd, g_pos=False, g_q=False)
+    plan.status()
+    assert sorted(less) == ["g_mu"] and torch.equal(less["g_mu"], apart["g_mu"])
+    for k, w in want.items():
+        assert rms_rel(host(both[k]), w) <= RMS_REL_TOL, ("step", k)
+        assert rms_rel(host(apart[k]), w) <= RMS_REL_TOL, k
