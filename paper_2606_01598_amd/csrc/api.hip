@@ -1045,7 +1045,9 @@ int batch_forward(pme_batch_s* b, hipStream_t s, const pme::BatchIO& io) {
   if ((e = pme::launch_clear_batch(b->sp, s)) != hipSuccess) return hip_fail(e);
   if ((e = pme::launch_bin_batch(b->sp, s, 0, false, io, io.energy != nullptr)) != hipSuccess)
     return hip_fail(e);
-  if ((e = pme::launch_spread_batch(b->sp, s, 0, false, io.box)) != hipSuccess) return hip_fail(e);
+  e = b->ff.fused ? pme::launch_spread_slab_batch(b->ff, s, 0, false, io.box)
+                  : pme::launch_spread_batch(b->sp, s, 0, false, io.box);
+  if (e != hipSuccess) return hip_fail(e);
   if ((e = pme::launch_convolve_batch(b->ff, s, io.box, true, io.energy != nullptr)) !=
       hipSuccess)
     return hip_fail(e);
@@ -1059,7 +1061,9 @@ int batch_backward(pme_batch_s* b, hipStream_t s, int set, const pme::BatchIO& i
   hipError_t e;
   if ((e = pme::launch_bin_batch(b->sp, s, set, true, io, false)) != hipSuccess)
     return hip_fail(e);
-  if ((e = pme::launch_spread_batch(b->sp, s, set, true, io.box)) != hipSuccess) return hip_fail(e);
+  e = b->ff.fused ? pme::launch_spread_slab_batch(b->ff, s, set, true, io.box)
+                  : pme::launch_spread_batch(b->sp, s, set, true, io.box);
+  if (e != hipSuccess) return hip_fail(e);
   if ((e = pme::launch_convolve_batch(b->ff, s, io.box, false, false)) != hipSuccess)
     return hip_fail(e);
   if ((e = pme::launch_gather_batch(b->ga, s, set, true, io)) != hipSuccess) return hip_fail(e);

@@ -19,6 +19,7 @@
 // Nyquist bins of a non-orthogonal cell use the mean of g over the bin and its
 // Hermitian partner, which makes the half-spectrum product equal the real part of
 // the full complex product (the real-to-complex semantics).
+#include <algorithm>
 #include <vector>
 
 #include "../../include/pme.h"
@@ -61,10 +62,10 @@ __device__ __forceinline__ float2* lds_fft(float2* x, float2* y, int npen, int p
 }
 
 // Twiddle table held in registers between its load and its LDS store, so that its
-// loads are in flight together with the data loads (N <= 1024).
-template <int NT>
+// loads are in flight together with the data loads (N <= MaxN).
+template <int NT, int MaxN = 1024>
 struct Twiddles {
-  static constexpr int U = (1024 + NT - 1) / NT;
+  static constexpr int U = (MaxN + NT - 1) / NT;
   float2 v[U];
   __device__ __forceinline__ void load(const float2* src, int N) {
 #pragma unroll
@@ -129,12 +130,11 @@ __device__ __forceinline__ void slab_layout(const SlabArgs& a, float2* sm, float
 //   X_2c[k] = (Z[k] + conj Z[N-k]) / 2,  X_2c+1[k] = (Z[k] - conj Z[N-k]) / 2i.
 // src(y, z) gives the plane's real value at (y, z); the twiddles are in tz and ty
 // (stored to twz and twy before the first barrier); A and B hold max(npairs N_z,
-// H (N_y + 1)) complex values each.
-template <class Src>
+// H (N_y + 1)) complex values each; the workgroup has NT threads.
+template <int NT, class Src>
 __device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, float2* spec, const int x,
-                                             const Src& src,
-                                             const Twiddles<kSlabThreads>& tz,
-                                             const Twiddles<kSlabThreads>& ty, float2* twz,
+                                             const Src& src, const Twiddles<NT>& tz,
+                                             const Twiddles<NT>& ty, float2* twz,
                                              float2* twy, float2* A, float2* B) {
   const int Ny = a.ay.N, Nz = a.az.N, H = a.H;
   const int npairs = (Ny + 1) / 2;
@@ -225,12 +225,13 @@ __device__ __forceinline__ void slab_fwd_run(const SlabArgs& a, float2* spec, co
   }
 }
 
+template <int NT = kSlabThreads>
 __device__ __forceinline__ void slab_fwd_body(const SlabArgs& a, const float* real, float2* spec,
                                               const int x) {
   extern __shared__ float2 sm[];
   float2 *twz, *twy, *A, *B;
   slab_layout(a, sm, twz, twy, A, B);
-  Twiddles<kSlabThreads> tz, ty;
+  Twiddles<NT> tz, ty;
   tz.load(a.twz, a.az.N);
   ty.load(a.twy, a.ay.N);
   const int Nz = a.az.N;
@@ -242,6 +243,7 @@ __device__ __forceinline__ void slab_fwd_body(const SlabArgs& a, const float* re
 // from global memory (when one round covers it); the first z stage packs two
 // Hermitian rows into one complex pencil as it reads:
 //   P[m] = X_2c[m] + i X_2c+1[m], X[m] = conj X[N-m] for m >= H.
+template <int NT = kSlabThreads>
 __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const float2* spec, float* real,
                                               const int x) {
   extern __shared__ float2 sm[];
@@ -249,7 +251,7 @@ __device__ __forceinline__ void slab_inv_body(const SlabArgs& a, const float2* s
   const int npairs = (Ny + 1) / 2;
   float2 *twz, *twy, *A, *B;
   slab_layout(a, sm, twz, twy, A, B);
-  Twiddles<kSlabThreads> tz, ty;
+  Twiddles<NT> tz, ty;
   tz.load(a.twz, Nz);
   ty.load(a.twy, Ny);
   const int ps = Ny + 1;
@@ -396,7 +398,7 @@ struct XArgs {
 // sits between the last forward and the first inverse stage, in registers (x_middle).
 // MODE 0: the influence function of Eq. influence; 1: the same, also forming the
 // cell-gradient partials; 2: the optimal influence function (aliasing sums).
-template <int MODE = 0>
+template <int MODE = 0, int NT = kFFTThreads>
 __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const int blk,
                                           const double* box, double* epart) {
   extern __shared__ float2 sm[];
@@ -416,6 +418,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
   // the x and z deconvolution factors of the workgroup's points, loaded before the
   // lines (waiting for them does not wait for the lines) and put in LDS before the
   // g table is made
+  constexpr bool kSmall = NT < kFFTThreads;   // N_x <= kSmallN, N_x kt <= GU NT
   constexpr int DCU = 5;   // Nx + kt <= DCU blockDim (Nx <= 1024, kt <= 24)
   float dcv[DCU];
 #pragma unroll
@@ -467,7 +470,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
     }
     __syncthreads();
   };
-  Twiddles<kFFTThreads> twr;
+  Twiddles<NT, kSmall ? kSmallN : 1024> twr;
   twr.load(a.tw, Nx);
   const size_t xstride = size_t(Ny) * H;
   float2* base = f.spec + size_t(y) * H;
@@ -614,7 +617,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
     float2 lv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * kFFTThreads;
+      const int e = threadIdx.x + u * NT;
       if (e < Nx * kt) {
         const int xx = int(fdiv(uint32_t(e), a.ktd)), l = e - xx * kt;
         const int kz = kz0 + l;
@@ -625,7 +628,7 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
     gfill();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = threadIdx.x + u * kFFTThreads;
+      const int e = threadIdx.x + u * NT;
       if (e < Nx * kt) {
         const int xx = int(fdiv(uint32_t(e), a.ktd)), l = e - xx * kt;
         X[l * ps + xx] = lv[u];
@@ -681,10 +684,24 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
       add(fx, fy, fz, wv2);
     }
   };
+  auto sum_wave = [&](int t0) {
+    double v = double(e_acc);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[(t0 + int(threadIdx.x)) >> 6] = v;
+    e_acc = 0.0f;
+  };
   {
     const FFTStage& st = a.ax.st[last];
     const int NR = st.NR;
-    for (int t = threadIdx.x; t < kt * NR; t += blockDim.x) {
+    // The small workgroup takes the 256 threads' butterflies in turn and sums each 64 as
+    // their wavefront would, so that the energy is the same bit for bit.
+    for (int t0 = 0; t0 < kt * NR; t0 += NT) {
+      const int t = t0 + int(threadIdx.x);
+      if constexpr (kSmall) {
+        if (t0 > 0 && epart) sum_wave(t0 - NT);
+      }
+      if (t >= kt * NR) continue;
       const int pen = int(fdiv(uint32_t(t), st.nr));
       const int j = t - pen * NR;
       const float2* in = Z + pen * ps;
@@ -700,6 +717,9 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
         return gg;
       };
       with_radix(st.R, [&](auto rc) { x_middle<decltype(rc)::value>(in, out, j, NR, tw, gm); });
+    }
+    if constexpr (kSmall) {
+      if (epart) sum_wave((kt * NR - 1) / NT * NT);
     }
   }
   __syncthreads();
@@ -731,8 +751,17 @@ __device__ __forceinline__ void fftx_body(const XArgs& a, const XField f, const 
     }
   }
   if (epart) {
-    const double s = block_sum(double(e_acc), red);
-    if (threadIdx.x == 0) epart[blk] = s;
+    if constexpr (kSmall) {
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < (kt * a.ax.st[last].NR + 63) / 64; ++w) s += red[w];
+        epart[blk] = s;
+      }
+    } else {
+      const double s = block_sum(double(e_acc), red);
+      if (threadIdx.x == 0) epart[blk] = s;
+    }
   }
   if constexpr (VIR) {
     __shared__ double vred[16 * 6];
@@ -786,33 +815,40 @@ __global__ void __launch_bounds__(kFFTThreads) k_fftx_pair(XArgs a, XField f1) {
   fftx_body<MODE>(a, f, item >> 1, a.box, t ? nullptr : a.epart);
 }
 
-// Batched passes: work item (box, x-plane) or (box, x-pass workgroup); per-box
-// argument templates in device memory; workgroups loop over the items.
-__global__ void __launch_bounds__(kSlabThreads) k_slab_fwd_batch(const SlabArgs* args,
-                                                                 const int2* items, int n) {
+// Batched passes: work item (box, x-plane) or (box, x-pass workgroup); per-box argument
+// templates in device memory.  NT threads a plane: kBatchThreads where every box's planes
+// are small, so that all planes of a batch are in flight at once (64 boxes of 16^3 to
+// 48^3: an inverse pass 39 us in rounds of 512 workgroups of 1024, 13 so).
+template <int NT>
+__global__ void __launch_bounds__(NT) k_slab_fwd_batch(const SlabArgs* __restrict__ args,
+                                                       const int2* __restrict__ items, int n) {
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
-    slab_fwd_body(args[w.x], args[w.x].src, args[w.x].spec, w.y);
+    slab_fwd_body<NT>(args[w.x], args[w.x].src, args[w.x].spec, w.y);
     __syncthreads();
   }
 }
 
-__global__ void __launch_bounds__(kSlabThreads) k_slab_inv_batch(const SlabArgs* args,
-                                                                 const int2* items, int n) {
+template <int NT>
+__global__ void __launch_bounds__(NT) k_slab_inv_batch(const SlabArgs* __restrict__ args,
+                                                       const int2* __restrict__ items, int n) {
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
-    slab_inv_body(args[w.x], args[w.x].spec, args[w.x].dst, w.y);
+    slab_inv_body<NT>(args[w.x], args[w.x].spec, args[w.x].dst, w.y);
     __syncthreads();
   }
 }
 
-template <int MODE>
-__global__ void __launch_bounds__(kFFTThreads) k_fftx_batch(const XArgs* args, const int2* items,
+// The x pass of a batch, bound by the latency of a workgroup's few lines and so by how many
+// are resident: 27 us for 64 boxes of 16^3 to 48^3 in workgroups of 128, 43 of 256
+template <int MODE, int NT>
+__global__ void __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_fftx_batch(const XArgs* __restrict__ args, const int2* __restrict__ items,
                                                             int n, const double* box, int energy) {
   for (int it = blockIdx.x; it < n; it += gridDim.x) {
     const int2 w = items[it];
     const XArgs& a = args[w.x];
-    fftx_body<MODE>(a, a.f, w.y, box + 9 * w.x, energy ? a.epart : nullptr);
+    fftx_body<MODE, NT>(a, a.f, w.y, box + 9 * w.x, energy ? a.epart : nullptr);
     __syncthreads();
   }
 }
@@ -848,7 +884,7 @@ struct SpreadSlabArgs {
 // TREC: the records are tangent records (q, mu, v_q, v_r, v_mu) and the density is
 // the forward one (DEG 1): its coefficients q, J mu are formed from them as the
 // forward binning forms them.
-template <int P, int DEG, bool TREC>
+template <int P, int DEG, bool TREC, int NT = kSlabThreads>
 __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const unsigned* cmax,
                                                  float2* spec, const int X, const double* box) {
   static_assert(!TREC || DEG == 1, "tangent records serve the forward density");
@@ -867,8 +903,8 @@ __device__ __forceinline__ void spread_slab_body(const SpreadSlabArgs& a, const 
   uint32_t* s_rec = reinterpret_cast<uint32_t*>(A);
   __shared__ float s_J[(DEG == 2 || TREC) ? 9 : 1];
   __shared__ float s_cw[4 * P * P];           // whole-number spline pieces (x weights)
-  __shared__ int s_wsum[kSlabThreads / 64];   // per-wavefront sums of the scan
-  Twiddles<kSlabThreads> tz, ty;
+  __shared__ int s_wsum[NT / 64];   // per-wavefront sums of the scan
+  Twiddles<NT> tz, ty;
   constexpr int kTab = spline_offset(P);
   if (tid < 4 * P * P) s_cw[tid] = c_spline_whole.coef[kTab + tid];
   tz.load(a.sl.twz, Nz);
@@ -950,6 +986,17 @@ __global__ void __launch_bounds__(kSlabThreads) k_spread_slab(SpreadSlabArgs a, 
   spread_slab_body<P, DEG, TREC>(a, a.cmax, a.sl.spec, xcd_item(blockIdx.x, gridDim.x), box);
 }
 
+// The same over a batch, a workgroup per item (box, plane): 37 us for 64 boxes of 16^3 to
+// 48^3, where the tile spread took 49 (the tangent density's 61) and the transform 40
+template <int P, int DEG>
+__global__ void __launch_bounds__(kBatchThreads)
+k_spread_slab_batch(const SpreadSlabArgs* __restrict__ args, const int2* __restrict__ items,
+                    const double* __restrict__ box) {
+  const int2 w = items[xcd_item(blockIdx.x, gridDim.x)];
+  const SpreadSlabArgs& a = args[w.x];
+  spread_slab_body<P, DEG, false, kBatchThreads>(a, a.cmax, a.sl.spec, w.y, box + 9 * w.x);
+}
+
 // Both densities of a step from the one binning's (tangent) records, a plane each
 template <int P>
 __global__ void __launch_bounds__(kSlabThreads) k_spread_slab_pair(SpreadSlabArgs a,
@@ -993,6 +1040,23 @@ SlabArgs make_slab_args(const DevPlan& d, float* out) {
   return sa;
 }
 
+SpreadSlabArgs make_spread_slab_args(const DevPlan& d, const DevPlan& r, int set,
+                                     const unsigned* cmax) {
+  SpreadSlabArgs a;
+  a.sl = make_slab_args(d, nullptr);
+  for (int k = 0; k < 3; ++k) { a.N[k] = d.N[k]; a.B[k] = d.B[k]; a.nb[k] = d.nb[k]; }
+  // the bins (same geometry in both views of a plan) and the scale
+  a.cap = r.cap;
+  a.count = r.count[set]; a.ovf_count = r.ovf_count[set];
+  a.cmax = cmax;
+  a.rec = r.rec; a.ovf_base = r.ovf_base;
+  a.PY = d.N[1] + d.p - 1;
+  a.PZ = d.N[2] + d.p - 1;
+  a.abuf = d.fused_abuf;
+  a.map_cap = kFusedMap;
+  return a;
+}
+
 inline dim3 fft_batch_grid(int items, int cap) {
   return dim3(items < cap ? (items > 0 ? items : 1) : cap);
 }
@@ -1002,6 +1066,9 @@ inline dim3 fft_batch_grid(int items, int cap) {
 hipError_t fft_batch_build(const DevPlan* plans, int nbox, FFTBatch& t) {
   t = FFTBatch();
   std::vector<SlabArgs> s0(nbox), s1(nbox);
+  std::vector<SpreadSlabArgs> f[2];
+  t.p = nbox > 0 ? plans[0].p : 0;
+  t.small = t.fused = t.x_small = nbox > 0;
   std::vector<XArgs> xa(nbox);
   std::vector<int2> si, xi;
   t.opt = nbox > 0 && plans[0].opt;
@@ -1011,15 +1078,45 @@ hipError_t fft_batch_build(const DevPlan* plans, int nbox, FFTBatch& t) {
     s0[b] = make_slab_args(d, d.phi);
     s1[b] = make_slab_args(d, d.rho);
     xa[b] = make_x_args(d, nullptr, true);
-    for (int x = 0; x < d.N[0]; ++x) si.push_back(make_int2(b, x));
-    for (int k = 0; k < fftx_blocks(d); ++k) xi.push_back(make_int2(b, k));
+    t.small = t.small && d.N[1] * d.N[2] <= kBatchPlane;
+    // x pass in small workgroups: the loads of a thread cover its tables, and a butterfly
+    // of the middle stage is one of the 256 threads' (its energy sum then is too)
+    t.x_small = t.x_small && d.N[0] <= kSmallN && d.N[0] * d.ktile <= 14 * kSmallThreads &&
+                d.ktile * d.ax[0].st[d.ax[0].nst - 1].NR <= kFFTThreads;
+    // its spread fused with the transform: the listed records share the first buffer
+    t.fused = t.fused && d.fused && t.small;
+    if (d.fused) {
+      for (int set = 0; set < 2; ++set) {
+        f[set].push_back(make_spread_slab_args(d, d, set, d.cmax[set]));
+        SpreadSlabArgs& a = f[set].back();
+        const int buf = std::max((d.N[1] + 1) / 2 * d.N[2], d.H * (d.N[1] + 1));
+        a.map_cap = kBatchMap;
+        a.abuf = std::max(buf, kBatchMap / 2);
+        const size_t lds = sizeof(float2) * (d.N[1] + d.N[2] + a.abuf + std::max(buf, a.PY * a.PZ));
+        if (lds > t.fused_lds) t.fused_lds = lds;
+      }
+    }
     if (d.slab_lds > t.slab_lds) t.slab_lds = d.slab_lds;
     if (x_lds(d) > t.x_lds) t.x_lds = x_lds(d);
+  }
+  // planes of the largest boxes first: the last ones to start are then short
+  std::vector<int> by_size(nbox);
+  for (int b = 0; b < nbox; ++b) by_size[b] = b;
+  std::stable_sort(by_size.begin(), by_size.end(), [&](int i, int j) {
+    return plans[i].N[1] * plans[i].N[2] > plans[j].N[1] * plans[j].N[2];
+  });
+  for (int b : by_size) {
+    for (int x = 0; x < plans[b].N[0]; ++x) si.push_back(make_int2(b, x));
+    for (int k = 0; k < fftx_blocks(plans[b]); ++k) xi.push_back(make_int2(b, k));
   }
   hipError_t e = hipSuccess;
   auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
   ok(upload(&t.slab[0], s0.data(), sizeof(SlabArgs) * nbox));
   ok(upload(&t.slab[1], s1.data(), sizeof(SlabArgs) * nbox));
+  t.fused = t.fused && t.fused_lds <= 65536;   // long planes of a few rows need more
+  if (t.fused)
+    for (int set = 0; set < 2; ++set)
+      ok(upload(&t.spread[set], f[set].data(), sizeof(SpreadSlabArgs) * nbox));
   ok(upload(&t.x, xa.data(), sizeof(XArgs) * nbox));
   ok(upload(reinterpret_cast<void**>(&t.slab_items), si.data(), sizeof(int2) * si.size()));
   ok(upload(reinterpret_cast<void**>(&t.x_items), xi.data(), sizeof(int2) * xi.size()));
@@ -1030,30 +1127,63 @@ hipError_t fft_batch_build(const DevPlan* plans, int nbox, FFTBatch& t) {
 }
 
 void fft_batch_free(FFTBatch& t) {
-  void* ptrs[] = {t.slab[0], t.slab[1], t.x, t.slab_items, t.x_items};
+  void* ptrs[] = {t.slab[0], t.slab[1], t.spread[0], t.spread[1], t.x, t.slab_items, t.x_items};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   t = FFTBatch();
 }
 
+hipError_t launch_spread_slab_batch(const FFTBatch& t, hipStream_t s, int set, bool tangent,
+                                    const double* box) {
+  if (!t.fused || set < 0 || set > 1) return hipErrorInvalidValue;
+  const dim3 g(t.n_slab_items), b(kBatchThreads);
+  const SpreadSlabArgs* a = static_cast<const SpreadSlabArgs*>(t.spread[set]);
+#define PME_F(P)                                                                             \
+  case P:                                                                                    \
+    if (tangent)                                                                             \
+      hipLaunchKernelGGL((k_spread_slab_batch<P, 2>), g, b, t.fused_lds, s, a, t.slab_items, box); \
+    else                                                                                     \
+      hipLaunchKernelGGL((k_spread_slab_batch<P, 1>), g, b, t.fused_lds, s, a, t.slab_items, box); \
+    break;
+  switch (t.p) {
+    PME_F(1) PME_F(2) PME_F(3) PME_F(4) PME_F(5) PME_F(6) PME_F(7)
+    default: return hipErrorInvalidValue;
+  }
+#undef PME_F
+  return hipGetLastError();
+}
+
 hipError_t launch_convolve_batch(const FFTBatch& t, hipStream_t s, const double* box, bool to_phi,
                                  bool energy) {
   const SlabArgs* sa = static_cast<const SlabArgs*>(t.slab[to_phi ? 0 : 1]);
-  hipLaunchKernelGGL(k_slab_fwd_batch, fft_batch_grid(t.n_slab_items, 512), dim3(kSlabThreads),
-                     t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e;
+  if (!t.fused) {
+    if (t.small)
+      hipLaunchKernelGGL(k_slab_fwd_batch<kBatchThreads>, dim3(t.n_slab_items), dim3(kBatchThreads),
+                         t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
+    else
+      hipLaunchKernelGGL(k_slab_fwd_batch<kSlabThreads>, fft_batch_grid(t.n_slab_items, 512),
+                         dim3(kSlabThreads), t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const XArgs* xa = static_cast<const XArgs*>(t.x);
+  const int xe = energy ? 1 : 0;
   if (t.opt)
-    hipLaunchKernelGGL(k_fftx_batch<2>, fft_batch_grid(t.n_x_items, 2048), dim3(kFFTThreads),
-                       t.x_lds, s, static_cast<const XArgs*>(t.x), t.x_items, t.n_x_items, box,
-                       energy ? 1 : 0);
+    hipLaunchKernelGGL((k_fftx_batch<2, kFFTThreads>), fft_batch_grid(t.n_x_items, 2048),
+                       dim3(kFFTThreads), t.x_lds, s, xa, t.x_items, t.n_x_items, box, xe);
+  else if (t.x_small)
+    hipLaunchKernelGGL((k_fftx_batch<0, kSmallThreads>), dim3(t.n_x_items), dim3(kSmallThreads),
+                       t.x_lds, s, xa, t.x_items, t.n_x_items, box, xe);
   else
-    hipLaunchKernelGGL(k_fftx_batch<0>, fft_batch_grid(t.n_x_items, 2048), dim3(kFFTThreads),
-                       t.x_lds, s, static_cast<const XArgs*>(t.x), t.x_items, t.n_x_items, box,
-                       energy ? 1 : 0);
+    hipLaunchKernelGGL((k_fftx_batch<0, kFFTThreads>), fft_batch_grid(t.n_x_items, 2048),
+                       dim3(kFFTThreads), t.x_lds, s, xa, t.x_items, t.n_x_items, box, xe);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_slab_inv_batch, fft_batch_grid(t.n_slab_items, 512), dim3(kSlabThreads),
-                     t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
+  if (t.small)
+    hipLaunchKernelGGL(k_slab_inv_batch<kBatchThreads>, dim3(t.n_slab_items), dim3(kBatchThreads),
+                       t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
+  else
+    hipLaunchKernelGGL(k_slab_inv_batch<kSlabThreads>, fft_batch_grid(t.n_slab_items, 512),
+                       dim3(kSlabThreads), t.slab_lds, s, sa, t.slab_items, t.n_slab_items);
   return hipGetLastError();
 }
 
@@ -1102,27 +1232,6 @@ hipError_t launch_convolve_pair(const DevPlan& d, const DevPlan& dt, hipStream_t
   return hipGetLastError();
 }
 
-namespace {
-
-SpreadSlabArgs make_spread_slab_args(const DevPlan& d, const DevPlan& r, int set,
-                                     const unsigned* cmax) {
-  SpreadSlabArgs a;
-  a.sl = make_slab_args(d, nullptr);
-  for (int k = 0; k < 3; ++k) { a.N[k] = d.N[k]; a.B[k] = d.B[k]; a.nb[k] = d.nb[k]; }
-  // the bins (same geometry in both views of a plan) and the scale
-  a.cap = r.cap;
-  a.count = r.count[set]; a.ovf_count = r.ovf_count[set];
-  a.cmax = cmax;
-  a.rec = r.rec; a.ovf_base = r.ovf_base;
-  a.PY = d.N[1] + d.p - 1;
-  a.PZ = d.N[2] + d.p - 1;
-  a.abuf = d.fused_abuf;
-  a.map_cap = kFusedMap;
-  return a;
-}
-
-}  // namespace
-
 hipError_t launch_spread_slab(const DevPlan& d, hipStream_t s, int set, bool tangent,
                               const double* box, const LaunchEvents* ev, const RecordSource* from) {
   if (!d.fused || (from && (tangent || !from->d || !from->cmax))) return hipErrorInvalidValue;
@@ -1168,8 +1277,8 @@ hipError_t enable_slab_lds(size_t bytes) {
   if (bytes > size_t(kSlabLdsMax)) return hipErrorInvalidValue;
   const void* fns[] = {reinterpret_cast<const void*>(k_slab_fwd),
                        reinterpret_cast<const void*>(k_slab_inv),
-                       reinterpret_cast<const void*>(k_slab_fwd_batch),
-                       reinterpret_cast<const void*>(k_slab_inv_batch),
+                       reinterpret_cast<const void*>(k_slab_fwd_batch<kSlabThreads>),
+                       reinterpret_cast<const void*>(k_slab_inv_batch<kSlabThreads>),
                        reinterpret_cast<const void*>(k_slab_fwd_pair),
                        reinterpret_cast<const void*>(k_slab_inv_pair),
 #define PME_F(P)                                                   \

@@ -64,6 +64,11 @@ struct AxisPlan {          // 1D mixed-radix FFT of length N
 
 constexpr int kFFTThreads = 256;    // pencil-pass workgroup
 constexpr int kSlabThreads = 1024;  // slab-pass workgroup (one x-plane)
+constexpr int kBatchThreads = 256;  // the same in a batch of boxes with small planes
+constexpr int kBatchPlane = 4096;   // their most points
+constexpr int kSmallThreads = 128;  // x-pass workgroup there, lines of at most kSmallN
+constexpr int kSmallN = 128;
+constexpr int kBatchMap = 1024;     // records listed at a time there
 constexpr int kSlabLdsMax = 160 * 1024 - 2048;
 constexpr int kLineLdsTwo = 52 * 1024;         // two-stage pencil workgroup: three per CU
 constexpr int kLineLdsGeneral = 144 * 1024;    // general pencil workgroup (8 lines of 1024)
@@ -211,6 +216,12 @@ struct FFTBatch {
   int2* x_items = nullptr;
   int n_x_items = 0;
   size_t slab_lds = 0, x_lds = 0;
+  bool small = false;                   // planes of at most kBatchPlane points each
+  bool fused = false;                   // and each box's spread fused with its transform
+  bool x_small = false;                 // x pass in workgroups of kSmallThreads
+  int p = 0;
+  void* spread[2] = {nullptr, nullptr}; // [set]
+  size_t fused_lds = 0;
   bool opt = false;                     // every box with the optimal influence function
 };
 struct GatherBatch {
@@ -237,6 +248,9 @@ hipError_t launch_bin_batch(const SpreadBatch& t, hipStream_t s, int set, bool t
                             const BatchIO& io, bool self_sums);
 hipError_t launch_spread_batch(const SpreadBatch& t, hipStream_t s, int set, bool tangent,
                                const double* box);
+// Spread fused with the forward slab transform in each box (t.fused)
+hipError_t launch_spread_slab_batch(const FFTBatch& t, hipStream_t s, int set, bool tangent,
+                                    const double* box);
 hipError_t launch_convolve_batch(const FFTBatch& t, hipStream_t s, const double* box, bool to_phi,
                                  bool energy);
 hipError_t launch_gather_batch(const GatherBatch& t, hipStream_t s, int set, bool hvp,
