@@ -608,11 +608,11 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
     ok(hipEventCreateWithFlags(&pl->join, hipEventDisableTiming));
     ok(hipEventCreateWithFlags(&pl->binned, hipEventDisableTiming));
   }
-  if (d.slab) ok(pme::enable_slab_lds(d.slab_lds));
+  if (d.slab) ok(pme::enable_slab_lds(d.slab_lds, d.p));
   else ok(pme::enable_pencil_lds());
-  if (d.band) ok(pme::enable_band_lds());
-  ok(pme::enable_spread_lds());
-  ok(pme::enable_gather_lds());
+  if (d.band) ok(pme::enable_band_lds(d.p));
+  ok(pme::enable_spread_lds(d.p));
+  ok(pme::enable_gather_lds(d.p));
   ok(hipDeviceSynchronize());
   if (e != hipSuccess) {
     free_plan(pl);
@@ -1244,11 +1244,11 @@ int scratch_address(unsigned char** out) {
     void* p = nullptr;
     if ((e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch))) != hipSuccess) return hip_fail(e);
     if (!p) return PME_EHIP;
-    if ((e = pme::enable_slab_lds(pme::kSlabLdsMax)) != hipSuccess) return hip_fail(e);
+    if ((e = pme::enable_slab_lds(pme::kSlabLdsMax, 0)) != hipSuccess) return hip_fail(e);
     if ((e = pme::enable_pencil_lds()) != hipSuccess) return hip_fail(e);
-    if ((e = pme::enable_band_lds()) != hipSuccess) return hip_fail(e);
-    if ((e = pme::enable_spread_lds()) != hipSuccess) return hip_fail(e);
-    if ((e = pme::enable_gather_lds()) != hipSuccess) return hip_fail(e);
+    if ((e = pme::enable_band_lds(0)) != hipSuccess) return hip_fail(e);
+    if ((e = pme::enable_spread_lds(0)) != hipSuccess) return hip_fail(e);
+    if ((e = pme::enable_gather_lds(0)) != hipSuccess) return hip_fail(e);
     g_scratch[dev] = static_cast<unsigned char*>(p);
   }
   *out = g_scratch[dev];

@@ -236,21 +236,20 @@ hipError_t launch_spread_band_pair(const DevPlan& d, const DevPlan& dt, hipStrea
   return hipGetLastError();
 }
 
-hipError_t enable_band_lds() {
-  const void* fns[] = {
-#define PME_B(P)                                                   \
-  reinterpret_cast<const void*>(k_spread_band<P, 1, false>),       \
-      reinterpret_cast<const void*>(k_spread_band<P, 1, true>),    \
-      reinterpret_cast<const void*>(k_spread_band<P, 2, false>),   \
-      reinterpret_cast<const void*>(k_spread_band_pair<P>),
-      PME_B(1) PME_B(2) PME_B(3) PME_B(4) PME_B(5) PME_B(6) PME_B(7)
+hipError_t enable_band_lds(int order) {
+#define PME_B(P)                                                \
+  {reinterpret_cast<const void*>(k_spread_band<P, 1, false>),   \
+   reinterpret_cast<const void*>(k_spread_band<P, 1, true>),    \
+   reinterpret_cast<const void*>(k_spread_band<P, 2, false>),   \
+   reinterpret_cast<const void*>(k_spread_band_pair<P>)}
+  const void* fns[7][4] = {PME_B(1), PME_B(2), PME_B(3), PME_B(4), PME_B(5), PME_B(6), PME_B(7)};
 #undef PME_B
-  };
-  for (const void* f : fns) {
-    const hipError_t e =
-        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsMax);
-    if (e != hipSuccess) return e;
-  }
+  for (int k = order ? order - 1 : 0; k < (order ? order : 7); ++k)
+    for (const void* f : fns[k]) {
+      const hipError_t e =
+          hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsMax);
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 

@@ -1122,7 +1122,6 @@ hipError_t fft_batch_build(const DevPlan* plans, int nbox, FFTBatch& t) {
   ok(upload(reinterpret_cast<void**>(&t.x_items), xi.data(), sizeof(int2) * xi.size()));
   t.n_slab_items = int(si.size());
   t.n_x_items = int(xi.size());
-  if (e == hipSuccess) e = enable_slab_lds(t.slab_lds);
   return e;
 }
 
@@ -1271,29 +1270,34 @@ hipError_t launch_spread_slab_pair(const DevPlan& d, const DevPlan& dt, hipStrea
   return hipGetLastError();
 }
 
-hipError_t enable_slab_lds(size_t bytes) {
+hipError_t enable_slab_lds(size_t bytes, int order) {
   // The limit is per kernel, not per plan: raise it to the largest slab any plan
   // may use, so that a later plan with smaller planes does not lower it.
   if (bytes > size_t(kSlabLdsMax)) return hipErrorInvalidValue;
-  const void* fns[] = {reinterpret_cast<const void*>(k_slab_fwd),
-                       reinterpret_cast<const void*>(k_slab_inv),
-                       reinterpret_cast<const void*>(k_slab_fwd_batch<kSlabThreads>),
-                       reinterpret_cast<const void*>(k_slab_inv_batch<kSlabThreads>),
-                       reinterpret_cast<const void*>(k_slab_fwd_pair),
-                       reinterpret_cast<const void*>(k_slab_inv_pair),
-#define PME_F(P)                                                   \
-  reinterpret_cast<const void*>(k_spread_slab<P, 1, false>),       \
-      reinterpret_cast<const void*>(k_spread_slab<P, 1, true>),    \
-      reinterpret_cast<const void*>(k_spread_slab<P, 2, false>),   \
-      reinterpret_cast<const void*>(k_spread_slab_pair<P>),
-                       PME_F(1) PME_F(2) PME_F(3) PME_F(4) PME_F(5) PME_F(6) PME_F(7)
-#undef PME_F
-  };
-  for (const void* f : fns) {
+  const void* passes[] = {reinterpret_cast<const void*>(k_slab_fwd),
+                          reinterpret_cast<const void*>(k_slab_inv),
+                          reinterpret_cast<const void*>(k_slab_fwd_batch<kSlabThreads>),
+                          reinterpret_cast<const void*>(k_slab_inv_batch<kSlabThreads>),
+                          reinterpret_cast<const void*>(k_slab_fwd_pair),
+                          reinterpret_cast<const void*>(k_slab_inv_pair)};
+  for (const void* f : passes) {
     const hipError_t e =
         hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsMax);
     if (e != hipSuccess) return e;
   }
+#define PME_F(P)                                                \
+  {reinterpret_cast<const void*>(k_spread_slab<P, 1, false>),   \
+   reinterpret_cast<const void*>(k_spread_slab<P, 1, true>),    \
+   reinterpret_cast<const void*>(k_spread_slab<P, 2, false>),   \
+   reinterpret_cast<const void*>(k_spread_slab_pair<P>)}
+  const void* fns[7][4] = {PME_F(1), PME_F(2), PME_F(3), PME_F(4), PME_F(5), PME_F(6), PME_F(7)};
+#undef PME_F
+  for (int k = order ? order - 1 : 0; k < (order ? order : 7); ++k)
+    for (const void* f : fns[k]) {
+      const hipError_t e =
+          hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kSlabLdsMax);
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 

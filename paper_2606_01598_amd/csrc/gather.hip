@@ -977,23 +977,23 @@ hipError_t gather_batch_dispatch(int p, dim3 g, size_t sh, hipStream_t s, const 
 
 }  // namespace
 
-hipError_t enable_gather_lds() {
-  const void* fns[] = {
-#define PME_G(P)                                                                             \
-  reinterpret_cast<const void*>(k_gather<P, false>),                                         \
-      reinterpret_cast<const void*>(k_gather<P, true>),                                     \
-      reinterpret_cast<const void*>(k_gather_hvp<P, false>),                                \
-      reinterpret_cast<const void*>(k_gather_hvp<P, true>),                                 \
-      reinterpret_cast<const void*>(k_gather_quad<P>),                                      \
-      reinterpret_cast<const void*>(k_gather_batch<P, false>),                               \
-      reinterpret_cast<const void*>(k_gather_batch<P, true>),
-      PME_G(1) PME_G(2) PME_G(3) PME_G(4) PME_G(5) PME_G(6) PME_G(7)
+hipError_t enable_gather_lds(int order) {
+#define PME_G(P)                                                                                  \
+  {reinterpret_cast<const void*>(k_gather<P, false>),                                             \
+   reinterpret_cast<const void*>(k_gather<P, true>),                                              \
+   reinterpret_cast<const void*>(k_gather_hvp<P, false>),                                         \
+   reinterpret_cast<const void*>(k_gather_hvp<P, true>),                                          \
+   reinterpret_cast<const void*>(k_gather_quad<P>),                                               \
+   reinterpret_cast<const void*>(k_gather_batch<P, false>),                                       \
+   reinterpret_cast<const void*>(k_gather_batch<P, true>)}
+  const void* fns[7][7] = {PME_G(1), PME_G(2), PME_G(3), PME_G(4), PME_G(5), PME_G(6), PME_G(7)};
 #undef PME_G
-  };
-  for (const void* f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
-    if (e != hipSuccess) return e;
-  }
+  for (int k = order ? order - 1 : 0; k < (order ? order : 7); ++k)
+    for (const void* f : fns[k]) {
+      const hipError_t e =
+          hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGatherLds);
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 

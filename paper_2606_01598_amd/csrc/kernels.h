@@ -341,13 +341,15 @@ hipError_t launch_spread_band_pair(const DevPlan& d, const DevPlan& dt, hipStrea
 // spectra (from_spec) or the meshes
 hipError_t launch_convolve_pair(const DevPlan& d, const DevPlan& dt, hipStream_t s,
                                 const double* box, bool energy, bool from_spec);
-hipError_t enable_band_lds();
+// LDS limits of the band kernels.  Here and below, order 0: the kernels of every order; a
+// plan raises those of its own (raising all of them was a tenth of a small plan's creation).
+hipError_t enable_band_lds(int order);
 // Raise the dynamic LDS limit of the spread (kBigLds) and gather (kGatherLds) kernels.
-hipError_t enable_spread_lds();
-hipError_t enable_gather_lds();
+hipError_t enable_spread_lds(int order);
+hipError_t enable_gather_lds(int order);
 // Allow slab workgroups up to kSlabLdsMax of dynamic LDS (above the 64 KiB
 // default); `bytes`, the need of the calling plan, must not exceed it.
-hipError_t enable_slab_lds(size_t bytes);
+hipError_t enable_slab_lds(size_t bytes, int order);
 // Gradient gather (+ energy finalisation) over the atoms binned in counter set `set`.
 hipError_t launch_gather(const DevPlan& d, hipStream_t s, int set, int n, const float* pos,
                          const float* q, const float* mu, const double* box, double* energy,
