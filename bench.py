@@ -190,8 +190,8 @@ def _args(argv=None):
     ap.add_argument("--cpu-steps", type=int, default=8)
     ap.add_argument("--breakdown-steps", type=int, default=10)
     ap.add_argument("--sequential", type=int, default=0,
-                    help="1: pme_forward then pme_backward on one stream instead of pme_step "
-                         "with the cotangent chain on a second stream")
+                    help="1: pme_forward then pme_backward instead of pme_step, whose two "
+                         "chains run together")
     ap.add_argument("--graph", type=int, default=1,
                     help="1: the timed steps are captured into one HIP graph (pme_step_capture) "
                          "and replayed once, after one untimed replay; 0: eager calls")
@@ -399,7 +399,7 @@ def main(argv=None):
                                f"p={p}, alpha={alpha}, forward + Hessian-vector product",
                    "atoms": n, "mesh": list(mesh), "order": p, "alpha": alpha,
                    "call": "pme_forward; pme_backward" if args.sequential else
-                           "pme_step (cotangent chain on a second stream)",
+                           "pme_step (both chains together)",
                    "launch": ("the timed steps captured into one HIP graph (pme_step_capture), "
                               "replayed once" if args.graph else "eager calls")},
         "eager": {"ms_per_step": round(eager_ms, 6), "value": round(n / eager_ms / 1e3, 3),
@@ -1219,7 +1219,7 @@ def sweep_summary(logs) -> int:
     lines = [
         "# PME forward + Hessian-vector product across sizes (molten-salt boxes at the",
         "# density of molten NaCl, mesh ~1 A, p = 6, alpha = 0.30), one MI355X, pme_step",
-        "# with the cotangent chain on a second stream, the timed steps replayed from one",
+        "# with both chains together, the timed steps replayed from one",
         "# HIP graph (the bench default; ms/step and Matom-steps/s are of that replay)",
         "# commands (repository root):",
         "#   python -u bench.py --workload 8k   --batched 0 --learned 0 --cpu-baseline 0 "

@@ -246,12 +246,12 @@ int pme_backward(pme_plan_t plan, void* stream, int32_t n,
 /* pme_forward followed by pme_backward of the same (pos, q, mu, box) in one call
  * (arguments and outputs as there; the backward reuses the forward's phi).  The
  * forward gradient and H v of one evaluation, as a training step with a force
- * loss needs them (Sec. 2.4).  With PME_F_CONCURRENT the cotangent's binning,
- * spread and mesh transform run on the plan's second stream, forked from
- * `stream`, beside the forward chain on `stream`; the second stream is joined back
- * into `stream`, where one gather over the cotangent's records forms H v and the
- * forward outputs from both potentials, so all work is ordered before later work
- * on `stream`.
+ * loss needs them (Sec. 2.4).  With PME_F_CONCURRENT the cotangent's spread and
+ * mesh transform run beside the forward's: on slab meshes whose spread is by planes
+ * or bands in the same launches on `stream`, elsewhere on the plan's second stream,
+ * forked from `stream` and joined back into it.  One gather over the cotangent's
+ * records then forms H v and the forward outputs from both potentials on `stream`,
+ * so all work is ordered before later work on it.
  * Without the flag the two run in sequence on `stream`.  Calls on one plan must
  * not overlap (they share its workspaces). */
 int pme_step(pme_plan_t plan, void* stream, int32_t n,

@@ -81,3 +81,28 @@ def test_gather_orders(p):
     for k, w in want.items():
         assert rms_rel(host(both[k]), w) <= RMS_REL_TOL, ("step", k)
         assert rms_rel(host(apart[k]), w) <= RMS_REL_TOL, k
+
+
+@pytest.mark.parametrize("mesh,spread,opt", [((24, 20, 18), "fused", False), ((16, 30, 25), "fused", True),
+                                             ((20, 128, 125), "band", False)])
+def test_step_in_shared_launches_equals_two_streams(mesh, spread, opt):
+    """pme_step puts both chains' passes into the same launches; with the launch timer
+    armed for one of their kernels it runs them apart.  Every output is the same bit for
+    bit, in either order on one plan and without some inputs."""
+    from paper_2606_01598_amd.pme import Plan
+    f = synth.molten_box(150, 11, L=15.0)
+    plan = Plan(mesh, 6, 0.4, max_atoms=f.n, concurrent=True, optimal_influence=opt)
+    assert plan.spread_kind == spread
+    pos, q, mu, box = to_dev(f)
+    v = [torch.tensor(x, dtype=torch.float32, device=pos.device)
+         for x in synth.random_cotangents(f.n, 9, scale_r=0.1)]
+    for args in ((pos, q, mu, box, *v), (pos, q, None, box, v[0], None, None),
+                 (pos, None, mu, box, None, None, v[2])):
+        runs = []
+        for kind in (None, "spread", "fft_x", None, "gather_hvp"):
+            plan.timer(kind)
+            runs.append({k: x.clone() for k, x in plan.step(*args).items()})
+        plan.timer(None)
+        plan.status()
+        for r in runs[1:]:
+            assert all(torch.equal(r[k], runs[0][k]) for k in runs[0])
