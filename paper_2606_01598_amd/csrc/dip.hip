@@ -957,14 +957,33 @@ __global__ void __launch_bounds__(1024) k_loss(int n, const double* Us, const do
   const double cE = (n > 0) ? 2.0 * lE * dE / double(n) : 0.0;
   const double inv = (m > 0) ? 1.0 / double(m) : 0.0;
   double sF = 0.0, sM = 0.0;
-  for (int k = threadIdx.x; k < m; k += 1024) {
-    const float dF = ds[k] - dt[k];
-    const float dM = mut ? mu[k] - mut[k] : 0.0f;
-    sF += double(dF) * dF;
-    sM += double(dM) * dM;
-    vpos[k] = float(2.0 * lF * inv) * dF;
-    gmu[k] = float(cE) * dmu[k] + float(2.0 * lmu * inv) * dM;
-    if (gq && k < n) gq[k] = float(cE) * dq[k];
+  // kLossUnroll elements' loads in flight before their stores (which the compiler could
+  // not move them across): the loop is a chain of memory round trips, 11.3 us at 4096
+  // atoms one element at a time, 8.7 so.  The sums keep their order.
+  constexpr int kLossUnroll = 6;
+  for (int k0 = threadIdx.x; k0 < m; k0 += kLossUnroll * 1024) {
+    float dF[kLossUnroll], dM[kLossUnroll], gm[kLossUnroll], gc[kLossUnroll];
+#pragma unroll
+    for (int u = 0; u < kLossUnroll; ++u) {
+      const int k = k0 + u * 1024;
+      dF[u] = dM[u] = gm[u] = gc[u] = 0.0f;
+      if (k < m) {
+        dF[u] = ds[k] - dt[k];
+        if (mut) dM[u] = mu[k] - mut[k];
+        gm[u] = dmu[k];
+        if (gq && k < n) gc[u] = dq[k];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kLossUnroll; ++u) {
+      const int k = k0 + u * 1024;
+      if (k >= m) break;
+      sF += double(dF[u]) * dF[u];
+      sM += double(dM[u]) * dM[u];
+      vpos[k] = float(2.0 * lF * inv) * dF[u];
+      gmu[k] = float(cE) * gm[u] + float(2.0 * lmu * inv) * dM[u];
+      if (gq && k < n) gq[k] = float(cE) * gc[u];
+    }
   }
   rF[threadIdx.x] = sF;
   rM[threadIdx.x] = sM;
