@@ -1113,7 +1113,8 @@ hipError_t fft_batch_build(const DevPlan* plans, int nbox, FFTBatch& t) {
   auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
   ok(upload(&t.slab[0], s0.data(), sizeof(SlabArgs) * nbox));
   ok(upload(&t.slab[1], s1.data(), sizeof(SlabArgs) * nbox));
-  t.fused = t.fused && t.fused_lds <= 65536;   // long planes of a few rows need more
+  // long planes of a few rows need more than 64 KiB with the kernel's static LDS (< 1 KiB)
+  t.fused = t.fused && t.fused_lds + 1024 <= 65536;
   if (t.fused)
     for (int set = 0; set < 2; ++set)
       ok(upload(&t.spread[set], f[set].data(), sizeof(SpreadSlabArgs) * nbox));

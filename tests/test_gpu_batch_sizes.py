@@ -1,7 +1,7 @@
 """Batches at the edges of their dispatch: every box equals a plan of its own bit for
 bit.  Planes of 4096 points (the most that go in small workgroups, with the spread fused)
 and one box beyond; a mesh too small for a plane spread; long planes of few rows, whose
-fused workspace exceeds a small workgroup's; x lines of 128 points and beyond; one row of
+fused workspace exceeds a small workgroup's, or does with its static LDS; x lines of 128 points and beyond; one row of
 butterflies more than a small workgroup; a box with more atoms in a plane than are
 listed at a time."""
 import numpy as np
@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = {"most": [(64, 64, 64), (16, 16, 16)], "beyond": [(20, 80, 64), (16, 16, 16)],
          "tiny": [(8, 8, 8), (16, 18, 20)], "long": [(16, 10, 400), (16, 16, 16)],
+         "brim": [(12, 9, 450), (12, 9, 405)],
          "lines": [(128, 16, 20), (18, 16, 16)], "more_lines": [(135, 16, 20), (18, 16, 16)],
          "odd": [(45, 27, 25), (30, 36, 45), (50, 20, 50)], "crowded": [(12, 45, 48)]}
 
