@@ -12,6 +12,7 @@
 
 #include "../../include/pme.h"
 #include "fft_radix.h"
+#include "geometry.h"
 #include "kernels.h"
 
 using pme::DevPlan;
@@ -136,40 +137,6 @@ bool five_smooth(long m) {
   return m == 1;
 }
 
-int pick_bin(int N) {
-  for (int c : {4, 5, 3, 6, 2})
-    if (N % c == 0) return c;
-  return N;
-}
-
-// Default geometry of one axis: among atom-bin sizes B that divide N (in the
-// order of pick_bin) and tiles T = k B that divide N as well, the T closest to
-// the target within [target / 2, 2 target] (ties: the larger B, then the
-// smaller T).  Tiles that divide the mesh leave no partial tiles at the edge,
-// whose shorter work and uneven spread over the CUs cost the 100^3 mesh about 7 %
-// of a step (8 x 8 x 16 with 4-point bins against 10 x 10 x 20 with 5-point
-// bins).  Returns false when no such tile exists.
-bool pick_dividing_tile(int N, int target, int& B, int& T) {
-  int best = -1;
-  for (int c : {4, 5, 3, 6, 2}) {
-    if (N % c) continue;
-    for (int t = c; t <= 2 * target && t <= N; t += c) {
-      if (N % t || 2 * t < target) continue;
-      const int d = t > target ? t - target : target - t;
-      if (best < 0 || d < best || (d == best && c > B)) {
-        best = d;
-        B = c;
-        T = t;
-      }
-    }
-  }
-  return best >= 0;
-}
-
-
-
-
-
 // Descriptor checks shared by every entry point that takes one.
 int check_desc(const pme_desc_t& desc) {
   if (desc.order < 1 || desc.order > 7) return PME_EORDER;
@@ -202,67 +169,11 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cube
   d.opt = (desc.flags & PME_F_OPT_INFLUENCE) != 0;
   const long M = long(d.N[0]) * d.N[1] * d.N[2];
 
-  // mesh tiles of T = k B points: by default tiles near 8 x 8 x 16 that divide the mesh
-  // (pick_dividing_tile); a target the descriptor sets is rounded to the first B that
-  // divides N, as are axes with no dividing tile
-  int target[3] = {8, 8, 16};
-  const bool given = desc.tile[0] > 0 || desc.tile[1] > 0 || desc.tile[2] > 0;
-  for (int a = 0; a < 3; ++a)
-    if (desc.tile[a] > 0) target[a] = desc.tile[a];
-  for (int a = 0; a < 3; ++a) {
-    if (given || !pick_dividing_tile(d.N[a], target[a], d.B[a], d.T[a])) {
-      d.B[a] = pick_bin(d.N[a]);
-      int k = (target[a] + d.B[a] / 2) / d.B[a];
-      if (k < 1) k = 1;
-      if (k > d.N[a] / d.B[a]) k = d.N[a] / d.B[a];
-      d.T[a] = k * d.B[a];
-    }
-  }
-  // plane and band spreads need N >= p + B on every axis
-  bool roomy = true;
-  for (int a = 0; a < 3; ++a)
-    if (d.N[a] < p + d.B[a]) roomy = false;
-  // shrink tiles until the spread tile, the scanned bin range, the gather's own
-  // bins and its LDS field region fit their bounds
-  for (int a = 0; a < 3; ++a) d.nb[a] = d.N[a] / d.B[a];
-  for (;;) {
-    long range = 1, own = 1, region = 2;
-    for (int a = 0; a < 3; ++a) {
-      long k = (d.T[a] + p - 1 + d.B[a] - 1) / d.B[a] + 1;
-      range *= (k < d.nb[a] ? k : d.nb[a]);
-      own *= d.T[a] / d.B[a];
-      region *= d.T[a] + p - 1;
-    }
-    const long tpad = long(d.T[0]) * d.T[1] * (d.T[2] + 1);
-    // two field regions and their row and z tables
-    const long rows = long(d.T[0] + p - 1) * (d.T[1] + p - 1) + (d.T[2] + p - 1);
-    if (range <= pme::kMaxBinRange && own <= 256 && tpad <= pme::kTileLds &&
-        region * 4 + rows * 4 <= pme::kGatherLds &&
-        long(pme::spread_lds_bytes(int(tpad), int(range), 64, p, 2)) <= pme::kBigLds)
-      break;
-    int big = 0;
-    for (int a = 1; a < 3; ++a)
-      if (d.T[a] / d.B[a] > d.T[big] / d.B[big]) big = a;
-    if (d.T[big] == d.B[big]) return PME_EMESH;
-    d.T[big] -= d.B[big];
-  }
-  for (int a = 0; a < 3; ++a) d.nt[a] = (d.N[a] + d.T[a] - 1) / d.T[a];
-  // Where planes or bands are spread, the atom bins are 1 x B_y x T_z mesh cells instead:
-  // every atom of the p bin layers a plane takes reaches it, and a plane has few bins to
-  // count (100^3: 600 of 1 x 5 x 20 with 1920 atoms, all wanted, instead of 800 of
-  // 5 x 5 x 5 with 3200).  The tile spread, whose tiles test a halo in z as well, keeps
-  // cubes.
-  const bool spread_planes = roomy && p <= 7 && !(desc.flags & PME_F_SEPARATE_SPREAD);
-  const bool planes = spread_planes && !cubes;
-  if (planes) {
-    d.B[0] = 1;
-    if (d.N[2] % d.T[2] == 0) d.B[2] = d.T[2];
-  }
+  const pme::Bins bins = pme::plan_bins(desc, d, cubes);
+  if (!bins.fit) return PME_EMESH;
+  const bool spread_planes = bins.spread_planes, planes = bins.planes;
   long nbins = 1;
-  for (int a = 0; a < 3; ++a) {
-    d.nb[a] = d.N[a] / d.B[a];
-    nbins *= d.nb[a];
-  }
+  for (int a = 0; a < 3; ++a) nbins *= d.nb[a];
   {
     // spread staging: records per round such that five workgroups share a CU's
     // 160 KiB of LDS (all tiles of a 100^3 mesh resident at once; 1 KiB per

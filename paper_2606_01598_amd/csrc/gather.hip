@@ -272,7 +272,7 @@ __device__ __forceinline__ void gather_tile(const GArgs& a, const int tile) {
     nbo[ax] = T[ax] / a.B[ax];
     kb0[ax] = t0[ax] / a.B[ax];
   }
-  const int nown = nbo[0] * nbo[1] * nbo[2];   // at most 256 (one per thread)
+  const int nown = nbo[0] * nbo[1] * nbo[2];   // at most kGatherBins (one per thread)
   // 1. the atoms of the tile's bin tid (none past the last bin)
   int bcnt = 0, bfirst = 0;
   if (tid < nown) {

@@ -13,6 +13,7 @@ namespace pme {
 
 constexpr int kMaxStages = 16;
 constexpr int kMaxBinRange = 2048;   // bins a spread tile may scan (LDS count array)
+constexpr int kGatherBins = 256;      // own bins of a gather tile (one per thread)
 constexpr int kTileLds = 8192;       // max padded spread-tile points: T_x T_y (T_z + 1)
 constexpr int kBigLds = 150 * 1024;  // dynamic LDS limit of the spread kernels
 constexpr int kGatherQueue = 128;                      // atoms a gather queues at once
