@@ -139,7 +139,8 @@ __device__ __forceinline__ void visit_pairs(const CellGrid& g, const int* start,
     const float4 pj = sp[in ? k : 0];
     const float3 R = min_image(g, pi.x - pj.x, pi.y - pj.y, pi.z - pj.z);
     const float r2 = R.x * R.x + R.y * R.y + R.z * R.z;
-    const bool hit = in && r2 < rc2 && r2 > 0.0f && __float_as_int(pj.w) != i;
+    // a NaN distance is a pair too, so that it reaches the outputs
+    const bool hit = in && !(r2 >= rc2) && !(r2 <= 0.0f) && __float_as_int(pj.w) != i;
     const unsigned long long m = __ballot(hit);
     const int below = int(__builtin_amdgcn_mbcnt_hi(
         uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u)));

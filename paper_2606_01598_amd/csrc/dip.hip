@@ -71,7 +71,7 @@ __device__ __forceinline__ void radial(float r, float ir, float irc, float (&Rk)
 __global__ void __launch_bounds__(kFeatThreads) k_features(FeatArgs a) {
   __shared__ float4 s_pair[kFeatAtoms][64 + kFeatBatch];
   __shared__ float s_R[kFeatAtoms][kFeatBatch][NR];
-  __shared__ float4 s_w[kFeatAtoms][kFeatBatch][NS];   // (1, q_j u) at the neighbour's species
+  __shared__ float4 s_w[kFeatAtoms][kFeatBatch];       // (1, q_j u)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int at = blockIdx.x * kFeatAtoms + wave;
   if (at >= a.n) return;   // no workgroup barrier below
@@ -81,6 +81,7 @@ __global__ void __launch_bounds__(kFeatThreads) k_features(FeatArgs a) {
   float acc = 0.0f;
   visit_pairs<kFeatBatch, true>(
       a.g, a.start, a.sp, pi, i, a.rc * a.rc, s_pair[wave], [&](const float4* l, int nb) {
+        float qj = 0.0f;
         if (lane < nb) {
           const float4 p = l[lane];
           const float r = sqrtf(p.x * p.x + p.y * p.y + p.z * p.z), ir = 1.0f / r;
@@ -88,16 +89,18 @@ __global__ void __launch_bounds__(kFeatThreads) k_features(FeatArgs a) {
           radial(r, ir, 1.0f / a.rc, Rk, nullptr);
 #pragma unroll
           for (int m = 0; m < NR; ++m) s_R[wave][lane][m] = Rk[m];
-          const float qj = a.q[__float_as_int(p.w)];
-          const float4 w = make_float4(1.0f, qj * p.x * ir, qj * p.y * ir, qj * p.z * ir);
-          const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          s_w[wave][lane][0] = qj > 0.0f ? w : none;
-          s_w[wave][lane][1] = qj > 0.0f ? none : w;
+          qj = a.q[__float_as_int(p.w)];
+          s_w[wave][lane] = make_float4(1.0f, qj * p.x * ir, qj * p.y * ir, qj * p.z * ir);
         }
+        const unsigned long long other = __ballot(qj > 0.0f) ^ (s ? 0ull : ~0ull);
         wave_lds_fence();
         const float* R = &s_R[wave][0][k];
-        const float* w = reinterpret_cast<const float*>(&s_w[wave][0][s]) + comp;
-        for (int m = 0; m < nb; ++m) acc = fmaf(R[NR * m], w[4 * NS * m], acc);
+        const float* w = reinterpret_cast<const float*>(&s_w[wave][0]) + comp;
+        // left out, not multiplied by zero: a NaN stays in its species' channels
+        for (int m = 0; m < nb; ++m) {
+          const float sum = fmaf(R[NR * m], w[4 * m], acc);
+          acc = (other >> m) & 1 ? acc : sum;
+        }
         wave_lds_fence();
       });
   float v2 = acc * acc;   // |V|^2 of (species, k): the sum over the three components
@@ -866,7 +869,7 @@ struct FeatJvpArgs {
 __global__ void __launch_bounds__(kFeatThreads) k_features_jvp(FeatJvpArgs a) {
   __shared__ float4 s_pair[kFeatAtoms][64 + kFeatBatch];
   __shared__ float s_R[kFeatAtoms][kFeatBatch][2 * NR];         // R_k' r_dot, R_k / r
-  __shared__ float4 s_w[kFeatAtoms][kFeatBatch][2 * NS];        // their factors by species
+  __shared__ float4 s_w[kFeatAtoms][kFeatBatch][2];             // their factors
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int at = blockIdx.x * kFeatAtoms + wave;
   if (at >= a.n) return;   // no workgroup barrier below
@@ -877,6 +880,7 @@ __global__ void __launch_bounds__(kFeatThreads) k_features_jvp(FeatJvpArgs a) {
   float acc = 0.0f;
   visit_pairs<kFeatBatch, true>(
       a.g, a.start, a.sp, pi, i, a.rc * a.rc, s_pair[wave], [&](const float4* l, int nb) {
+        float qj = 0.0f;
         if (lane < nb) {
           const float4 p = l[lane];
           const int j = __float_as_int(p.w);
@@ -891,22 +895,19 @@ __global__ void __launch_bounds__(kFeatThreads) k_features_jvp(FeatJvpArgs a) {
             s_R[wave][lane][m] = dR[m] * rd;
             s_R[wave][lane][NR + m] = Rk[m] * ir;
           }
-          const float qj = a.q[j];
-          const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-          const float4 w0 = make_float4(1.0f, qj * ux, qj * uy, qj * uz);
-          const float4 w1 = make_float4(0.0f, qj * (wx - rd * ux), qj * (wy - rd * uy),
-                                        qj * (wz - rd * uz));
-          s_w[wave][lane][0] = qj > 0.0f ? w0 : none;
-          s_w[wave][lane][1] = qj > 0.0f ? none : w0;
-          s_w[wave][lane][2] = qj > 0.0f ? w1 : none;
-          s_w[wave][lane][3] = qj > 0.0f ? none : w1;
+          qj = a.q[j];
+          s_w[wave][lane][0] = make_float4(1.0f, qj * ux, qj * uy, qj * uz);
+          s_w[wave][lane][1] = make_float4(0.0f, qj * (wx - rd * ux), qj * (wy - rd * uy),
+                                           qj * (wz - rd * uz));
         }
+        const unsigned long long other = __ballot(qj > 0.0f) ^ (s ? 0ull : ~0ull);
         wave_lds_fence();
         const float* R = &s_R[wave][0][k];
-        const float* w = reinterpret_cast<const float*>(&s_w[wave][0][s]) + comp;
-        for (int m = 0; m < nb; ++m)
-          acc = fmaf(R[2 * NR * m], w[8 * NS * m],
-                     fmaf(R[2 * NR * m + NR], w[8 * NS * m + 4 * NS], acc));
+        const float* w = reinterpret_cast<const float*>(&s_w[wave][0][0]) + comp;
+        for (int m = 0; m < nb; ++m) {
+          const float sum = fmaf(R[2 * NR * m], w[8 * m], fmaf(R[2 * NR * m + NR], w[8 * m + 4], acc));
+          acc = (other >> m) & 1 ? acc : sum;
+        }
         wave_lds_fence();
       });
   // d|V|^2 = 2 V . V_dot of (species, k)
