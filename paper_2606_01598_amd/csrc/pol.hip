@@ -600,7 +600,7 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
     } else {
       double zz;
       if ((rc = wait_residual(plan, s, vb, plan->steps, zz)) != PME_OK) return rc;
-      rms = sqrt(fmax(zz, 0.0) / double(m));
+      rms = sqrt(zz / double(m));   // of squares: NaN where a residual is
       if (!isfinite(rms)) return PME_ENONFINITE;
       if (rms < tol || it >= max_iter) break;
     }

@@ -57,3 +57,21 @@ def test_feature_kernels(value):
         assert bool(torch.isnan(x[rest][:, 8 * own:8 * own + 8]).all()), k
         assert bool(torch.isfinite(x[rest][:, 8 - 8 * own:16 - 8 * own]).all()), k
     assert bool(torch.isfinite(feat[:, 32:]).all()) and bool((fd[:, 32:] == 0).all())
+
+
+@pytest.mark.parametrize("where", ["pos", "q", "mu"])
+def test_solve_reports_residuals_that_are_not_finite(where):
+    from paper_2606_01598_amd import _lib
+    from paper_2606_01598_amd.pme import Plan
+    from paper_2606_01598_amd.pol import PolPlan
+    pos, q, mu, pol, _, _ = _case(float("nan") if where == "pos" else 3.0)
+    if where == "q":
+        q[BAD] = float("nan")
+    if where == "mu":
+        mu[BAD, 0] = float("nan")
+    box = torch.tensor(np.eye(3) * SIDE, device=dev())
+    pme = Plan((18, 18, 18), 6, 0.35, max_atoms=N)
+    plan = PolPlan(box, 0.35, 7.0, max_atoms=N, warm_start=where == "mu")
+    with pytest.raises(_lib.PMEError) as err:
+        plan.scf(pme, pos, q, pol, box, tol=1e-6, max_iter=20, mu=mu)
+    assert err.value.code == _lib.PME_ENONFINITE
