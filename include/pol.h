@@ -24,8 +24,9 @@
  * - Per-atom arrays are device FP32; pos is [n][3], pol (the polarizabilities
  *   a_i, in Angstrom^3) is [n].
  * - Outputs are overwritten; a NULL output is skipped; a NULL q or mu means zero.
- * - Calls are asynchronous on `stream`, except pol_scf, which synchronises once
- *   per iteration to test convergence (unless POL_F_FIXED_ITERS).
+ * - Calls are asynchronous on `stream`, except pol_scf, which waits for the residual
+ *   of every iteration to test convergence and synchronises `stream` before it returns
+ *   (unless POL_F_FIXED_ITERS).
  * - A plan's workspaces are shared by its calls: calls on one plan must not
  *   overlap in time (one stream, or ordered by events).
  * - Every energy and gradient is multiplied by `prefactor`, including the
@@ -119,16 +120,19 @@ int pol_model_hvp(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, cons
 /* Self-consistent induced dipoles by preconditioned conjugate gradients.
  *
  * The system is (diag(1/a) + H_real + H_pme) mu = -(dE_lr/dmu + dE_real/dmu) at mu = 0.
- * - H_pme v is pme_backward with a dipole cotangent v.
+ * - H_pme v is the gradient in mu of the PME energy of the dipoles v alone (E_lr is
+ *   quadratic in them): one evaluation on the PME plan, which leaves the potential the
+ *   plan keeps (pme_plan_phi_id) as it is.  With the plan's launch timer it counts as a
+ *   forward evaluation.
  * - H_real v is pol_real with the dipoles v and no charges.
  * - The preconditioner is diag(a).
  *
  * Iterations stop when the RMS of the preconditioned residual, in e*Angstrom,
- * falls below `tol`, or after `max_iter` iterations.
+ * falls below `tol`, or after `max_iter` iterations.  A residual that is not finite
+ * ends the solve with PME_ENONFINITE.
  *
  * Arguments:
- * - pme: a plan with the same alpha and prefactor (PME_F_KEEP_PHI saves one
- *   potential per iteration).
+ * - pme: a plan with the same alpha and prefactor (PME_F_KEEP_PHI is not needed).
  * - box: the device copy of the cell, as for pme_forward.
  * - mu: the solution (device float[n*3]); also the initial guess under
  *   POL_F_WARM_START.

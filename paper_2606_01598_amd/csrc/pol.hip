@@ -601,8 +601,14 @@ int pol_scf(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const floa
       double zz;
       if ((rc = wait_residual(plan, s, vb, plan->steps, zz)) != PME_OK) return rc;
       rms = sqrt(zz / double(m));   // of squares: NaN where a residual is
-      if (!isfinite(rms)) return PME_ENONFINITE;
-      if (rms < tol || it >= max_iter) break;
+      if (!isfinite(rms) || rms < tol || it >= max_iter) {
+        // the residual arrives before its kernel ends and k_pcg_dir runs: the caller gets
+        // the solution with nothing in flight (a solve and its forces at 4096 ions: 791 us,
+        // 768 where the next call is queued behind them)
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return pol_hip_fail(e);
+        if (!isfinite(rms)) return PME_ENONFINITE;
+        break;
+      }
     }
     const double* old = part[it & 1];
     double* now = part[(it & 1) ^ 1];
