@@ -67,6 +67,7 @@ __host__ __device__ float deconv_factor(int t, int N, int p, double gamma) {
 struct pme_plan_s {
   pme_desc_t desc;
   DevPlan d;
+  DevPlan cubes;  // d with cubic atom bins, in the same workspaces: what the tile spread reads
   int64_t bytes;
   int max_atoms;
   bool phi_valid;
@@ -155,11 +156,11 @@ int check_desc(const pme_desc_t& desc) {
   return PME_OK;
 }
 
-// Geometry of a plan (host only, nothing allocated): mesh and order, atom bins and
-// their capacity, spread and gather tiles, spread staging, FFT layout.  `nbins`
-// receives the number of atom bins.  PME_EMESH when no tile or FFT layout fits.  cubes:
-// cubic atom bins whatever the spread (the smaller workspace of pme_forward_noalloc).
-int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cubes = false) {
+// Geometry of a plan (host only, nothing allocated): mesh and order, atom bins (d.ncount of
+// them) and their capacity, spread and gather tiles, spread staging, FFT layout.  PME_EMESH
+// when no tile or FFT layout fits.  cubes: cubic atom bins whatever the spread (for the tile
+// spread, and the smaller workspace of pme_forward_noalloc).
+int plan_geometry(const pme_desc_t& desc, DevPlan& d, bool cubes = false) {
   const int p = desc.order;
   for (int a = 0; a < 3; ++a) d.N[a] = desc.mesh[a];
   d.H = d.N[2] / 2 + 1;
@@ -172,8 +173,7 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cube
   const pme::Bins bins = pme::plan_bins(desc, d, cubes);
   if (!bins.fit) return PME_EMESH;
   const bool spread_planes = bins.spread_planes, planes = bins.planes;
-  long nbins = 1;
-  for (int a = 0; a < 3; ++a) nbins *= d.nb[a];
+  d.ncount = d.nb[0] * d.nb[1] * d.nb[2];
   {
     // spread staging: records per round such that five workgroups share a CU's
     // 160 KiB of LDS (all tiles of a 100^3 mesh resident at once; 1 KiB per
@@ -201,6 +201,7 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cube
     long cap = long(ceil((planes ? 4.0 : 2.0) * per_bin)) + 8;
     if (cap > 64) cap = 64;
     d.cap = int(cap);
+    d.ovf_base = (long long)d.ncount * d.cap;
   }
   // FFT layout
   for (int a = 0; a < 3; ++a)
@@ -277,7 +278,6 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, long& nbins_out, bool cube
       d.ktile = (d.H + nchunk - 1) / nchunk;
     }
   }
-  nbins_out = nbins;
   return PME_OK;
 }
 
@@ -389,29 +389,34 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
   pl->phi_valid = false;
   pl->set = 0;
   DevPlan& d = pl->d;
-  long nbins = 0;
   const int p = desc->order;
+  DevPlan cubes;
+  memset(&cubes, 0, sizeof(cubes));
   {
-    const int gc = plan_geometry(*desc, d, nbins);
+    int gc = plan_geometry(*desc, d);
+    if (gc == PME_OK) gc = plan_geometry(*desc, cubes, true);
     if (gc != PME_OK) {
       free_plan(pl);
       return gc;
     }
   }
+  // counters and records for either view
+  d.ncount = std::max(d.ncount, cubes.ncount);
+  const size_t ncount = size_t(d.ncount);
+  const size_t nrec = size_t(std::max(d.ovf_base, cubes.ovf_base)) + size_t(desc->max_atoms);
   const long M = long(d.N[0]) * d.N[1] * d.N[2];
 
   hipError_t e = hipSuccess;
   int64_t& by = pl->bytes;
   auto ok = [&](hipError_t r) { if (r != hipSuccess && e == hipSuccess) e = r; };
   for (int k = 0; k < 2; ++k) {
-    ok(dev_alloc(&d.count[k], size_t(nbins), by));
+    ok(dev_alloc(&d.count[k], ncount, by));
     ok(dev_alloc(&d.ovf_count[k], 1, by));
     ok(dev_alloc(&d.cmax[k], 1, by));
   }
   // one allocation for the bins and the overflow list, so that kernels select a
   // record by index from a single base pointer
-  d.ovf_base = (long long)nbins * d.cap;
-  ok(dev_alloc(&d.rec, (size_t(d.ovf_base) + size_t(desc->max_atoms)) * 16, by));
+  ok(dev_alloc(&d.rec, nrec * 16, by));
   for (int a = 0; a < 3; ++a) {
     ok(dev_alloc(&d.twiddle[a], size_t(d.N[a]), by));
     ok(dev_alloc(&d.deconv[a], size_t(d.N[a]), by));
@@ -473,13 +478,23 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
     delete[] dc;
   }
   for (int k = 0; k < 2; ++k) {
-    ok(hipMemset(d.count[k], 0, sizeof(int) * nbins));
+    ok(hipMemset(d.count[k], 0, sizeof(int) * ncount));
     ok(hipMemset(d.ovf_count[k], 0, sizeof(int)));
     ok(hipMemset(d.cmax[k], 0, sizeof(unsigned)));
   }
   ok(hipMemset(d.status, 0, sizeof(int)));
   if (d.gkey) ok(hipMemset(d.gkey, 0xff, sizeof(double) * 9 * xblocks));   // NaN: none made yet
   ok(hipMemset(d.phi, 0, sizeof(float) * M));
+  // the view with cubic bins (the same one where the plan's bins are cubes)
+  pl->cubes = d;
+  for (int a = 0; a < 3; ++a) {
+    pl->cubes.B[a] = cubes.B[a];
+    pl->cubes.nb[a] = cubes.nb[a];
+  }
+  pl->cubes.cap = cubes.cap;
+  pl->cubes.ovf_base = cubes.ovf_base;
+  pl->cubes.nbr_max = cubes.nbr_max;
+  for (int k = 0; k < 2; ++k) pl->cubes.spread_ch[k] = cubes.spread_ch[k];
   if (e == hipSuccess && (desc->flags & PME_F_CONCURRENT)) {
     pl->concurrent = true;
     DevPlan& t = pl->dt;
@@ -493,12 +508,12 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
     t.gcache = nullptr;
     t.gkey = nullptr;
     for (int k = 0; k < 2; ++k) {
-      ok(dev_alloc(&t.count[k], size_t(nbins), by));
+      ok(dev_alloc(&t.count[k], ncount, by));
       ok(dev_alloc(&t.ovf_count[k], 1, by));
       ok(dev_alloc(&t.cmax[k], 1, by));
       ok(dev_alloc(&t.cmax_fwd[k], 1, by));
     }
-    ok(dev_alloc(&t.rec, (size_t(t.ovf_base) + size_t(desc->max_atoms)) * 16, by));
+    ok(dev_alloc(&t.rec, nrec * 16, by));
     ok(dev_alloc(&t.rho, pme::mesh_floats(d), by));
     ok(dev_alloc(&t.spec, size_t(d.N[0]) * d.N[1] * d.H, by));
     // the cotangent chain's x passes keep their own g tables: the two chains' passes
@@ -509,7 +524,7 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
       if (e == hipSuccess) ok(hipMemset(t.gkey, 0xff, sizeof(double) * 9 * xblocks));
     }
     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-      ok(hipMemset(t.count[k], 0, sizeof(int) * nbins));
+      ok(hipMemset(t.count[k], 0, sizeof(int) * ncount));
       ok(hipMemset(t.ovf_count[k], 0, sizeof(int)));
       ok(hipMemset(t.cmax[k], 0, sizeof(unsigned)));
       ok(hipMemset(t.cmax_fwd[k], 0, sizeof(unsigned)));
@@ -652,7 +667,7 @@ int pme_forward_quad(pme_plan_t plan, void* stream, int32_t n, const float* pos,
   if (!plan || n < 0 || !box || (n > 0 && !pos) || plan->d.p < 4) return PME_EINVAL;
   if (n > plan->max_atoms) return PME_ECAPACITY;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const DevPlan& d = plan->d;
+  const DevPlan& d = plan->cubes;   // tiles are spread
   pme::KTimer& tm = plan->timer;
   hipError_t e;
   // phi of this call is not the one a following pme_backward may reuse
@@ -1040,8 +1055,11 @@ int pme_batch_plan(const pme_desc_t* descs, int32_t nbox, const int32_t* n_atoms
     }
     dp[b] = bt->plans[b]->d;
   }
-  hipError_t e = pme::spread_batch_build(dp.data(), bt->n.data(), bt->off.data(), nbox, bt->sp);
-  if (e == hipSuccess) e = pme::fft_batch_build(dp.data(), nbox, bt->ff);
+  hipError_t e = pme::fft_batch_build(dp.data(), nbox, bt->ff);
+  if (!bt->ff.fused)   // tiles are spread
+    for (int b = 0; b < nbox; ++b) dp[b] = bt->plans[b]->cubes;
+  if (e == hipSuccess)
+    e = pme::spread_batch_build(dp.data(), bt->n.data(), bt->off.data(), nbox, bt->sp);
   if (e == hipSuccess)
     e = pme::gather_batch_build(dp.data(), bt->n.data(), bt->off.data(), nbox, bt->ga);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&bt->cap, hipStreamNonBlocking);
@@ -1209,13 +1227,12 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
   if (dd.flags & PME_F_OPT_INFLUENCE) return PME_EINVAL;
   DevPlan d;
   memset(&d, 0, sizeof(d));
-  long nbins = 0;
   {
-    const int gc = plan_geometry(dd, d, nbins, true);
+    const int gc = plan_geometry(dd, d, true);
     if (gc != PME_OK) return gc;
   }
   const long M = long(d.N[0]) * d.N[1] * d.N[2];
-  d.ovf_base = (long long)nbins * d.cap;
+  const int nbins = d.ncount;
   // layout of the scratch array (256-byte aligned pieces)
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1223,7 +1240,7 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
     off += (bytes + 255) & ~size_t(255);
     return o;
   };
-  const int nzero = int(2 * nbins + 5);   // both counter sets, overflow counts, cmax, status
+  const int nzero = 2 * nbins + 5;   // both counter sets, overflow counts, cmax, status
   const size_t o_zero = take(sizeof(int) * size_t(nzero));
   const size_t o_rec = take(sizeof(float) * 16 * (size_t(d.ovf_base) + size_t(dd.max_atoms)));
   size_t o_tw[3], o_dc[3];

@@ -91,11 +91,12 @@ struct DevPlan {
   int spread_ch[2];        // records staged per round by the forward / tangent spread
   // two counter sets used alternately by successive binnings; a binning clears the
   // other set, so no kernel has to clear the set it reads
-  int* count[2];           // [nbins] atoms per bin
+  int* count[2];           // [ncount] atoms per bin
+  int ncount;              // counters of a set: the bins of the plan's view with most
   int* ovf_count[2];       // [1] atoms in the overflow list
   unsigned* cmax[2];       // [1] max over atoms of sum |assignment coefficients| (float bits)
-  float* rec;              // [(nbins * cap + max_atoms) * 16] records (16 words each):
-                           // the bins, then the overflow list
+  float* rec;              // [(ovf_base + max_atoms) * 16] records (16 words each), for the
+                           // view with most: the bins, then the overflow list
   long long ovf_base;      // record index of the overflow list (nbins * cap)
   // mesh tiles shared by the spread and the gathers (T[a] a multiple of B[a])
   int T[3];

@@ -766,7 +766,7 @@ BinArgs make_bin_args(const DevPlan& d, int set, int n, const float* pos, const 
   a.cmax_other = d.cmax[1 - set];
   a.cmax_fwd = nullptr;
   a.cmax_fwd_other = nullptr;
-  a.nbins = d.nb[0] * d.nb[1] * d.nb[2];
+  a.nbins = d.ncount;
   a.rec = d.rec; a.ovf_base = d.ovf_base;
   a.spart = self_sums ? d.spart : nullptr;
   a.status = d.status;
@@ -918,7 +918,7 @@ hipError_t spread_batch_build(const DevPlan* plans, const int* n, const int* off
       if (l > t.lds[tg]) t.lds[tg] = l;
     }
     ci[b].count = d.count[0];
-    ci[b].nbins = d.nb[0] * d.nb[1] * d.nb[2];
+    ci[b].nbins = d.ncount;
     ci[b].ovf_count = d.ovf_count[0];
     ci[b].cmax = d.cmax[0];
   }
