@@ -108,38 +108,30 @@ struct InfluenceLine {
 
   // the sum over the aliases f + m N of U^2 G, over the separable denominator; a partner
   // frequency s f (s = -1 on the flipped axes) takes the weight of alias -m of f, as sinc
-  // is even
+  // is even.  Loops, not straight-line code: the caller keeps its registers.
   __device__ __forceinline__ float optimal(const Influence& a, const int (&N)[3], int x) const {
     if ((x | y | kz) == 0) return 0.0f;
-    const float f[3] = {float(signed_freq(x, N[0])), float(fy), float(fz)};
-    const int at[3] = {x, y, kz};
-    float u[3][3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-      for (int m = 0; m < 3; ++m) u[d][m] = a.al[d][m * N[d] + at[d]];
-    auto sum = [&](int sx, int sy, int sz) {
-      float num = 0.0f;
-#pragma unroll
-      for (int mx = -1; mx <= 1; ++mx) {
-        const float ux = sx > 0 ? u[0][mx + 1] : u[0][1 - mx];
-#pragma unroll
-        for (int my = -1; my <= 1; ++my) {
-          const float uxy = ux * (sy > 0 ? u[1][my + 1] : u[1][1 - my]);
-#pragma unroll
-          for (int mz = -1; mz <= 1; ++mz) {
-            const float u2 = uxy * (sz > 0 ? u[2][mz + 1] : u[2][1 - mz]);
-            num = fmaf(u2, green(float(sx) * f[0] + float(mx * N[0]), float(sy) * f[1] + float(my * N[1]),
-                                 float(sz) * f[2] + float(mz * N[2])), num);
-          }
-        }
-      }
-      return num;
-    };
+    const float fx = float(signed_freq(x, N[0]));
     const bool nx = ((N[0] & 1) == 0) && (2 * x == N[0]);
-    float g = sum(1, 1, 1);
-    if (nx || ny || nz) g = 0.5f * (g + sum(nx ? 1 : -1, ny ? 1 : -1, nz ? 1 : -1));
-    return g * (a.dc[0][x] * dcy * dcz);
+    const int terms = nx || ny || nz ? 2 : 1;
+    float g = 0.0f;
+#pragma unroll 1
+    for (int t = 0; t < terms; ++t) {
+      const int sx = t && !nx ? -1 : 1, sy = t && !ny ? -1 : 1, sz = t && !nz ? -1 : 1;
+      float num = 0.0f;
+#pragma unroll 1
+      for (int m = 0; m < 9; ++m) {
+        const int mx = m / 3 - 1, my = m % 3 - 1;
+        const float uxy = a.al[0][(sx * mx + 1) * N[0] + x] * a.al[1][(sy * my + 1) * N[1] + y];
+#pragma unroll
+        for (int mz = -1; mz <= 1; ++mz)
+          num = fmaf(uxy * a.al[2][(sz * mz + 1) * N[2] + kz],
+                     green(float(sx) * fx + float(mx * N[0]), float(sy * fy) + float(my * N[1]),
+                           float(sz * fz) + float(mz * N[2])), num);
+      }
+      g += num;
+    }
+    return (terms == 2 ? 0.5f * g : g) * (a.dc[0][x] * dcy * dcz);
   }
 
   // cell gradient: w |v|^2 G(k) D(f) (1/k^2 + 1/(4 alpha^2)) k k^T with k = 2 pi C^-1 f,

@@ -304,7 +304,7 @@ struct XArgs {
 // 2: the optimal influence function (its alias sums kept in the plan's table by box).
 template <bool TWO, int MODE>
 __global__ void __launch_bounds__(TWO ? kTwoThreads : kStageThreads)
-__attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
+__attribute__((amdgpu_waves_per_eu(4))) k_pencil_x(XArgs a) {
   extern __shared__ float2 sm[];
   __shared__ double red[16 * 6];
   const int Nx = a.N[0], Ny = a.N[1], Nz = a.N[2];
@@ -324,24 +324,29 @@ __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
   float e_acc = 0.0f;
   float vacc[6] = {0, 0, 0, 0, 0, 0};
   const float wgt = (kz == 0 || (((Nz & 1) == 0) && 2 * kz == Nz)) ? 1.0f : 2.0f;
+  // MODE 2: the workgroup's table of g at [x][line].  Where it is another box's, each thread
+  // first makes the values that it will read (x0, x0 + stride, ..); the transform itself is
+  // then the same code either way, with the registers of one load a value.  (Made inside the
+  // butterfly the 27 aliases filled 256 registers: a step of 128k ions on 160^3 353 us with
+  // the table kept, 213 so; forward and product of 1M on 320^3 2584 and 1722; a forward at
+  // 160^3 whose cell changes at every call 239.)
   bool cached = false;
-  float* gblk = nullptr;
-  auto g_setup = [&]() {
-    gl.set(a.inf, a.box, a.N, y, live ? kz : 0);
+  float* table = nullptr;
+  auto g_setup = [&](int x0, int stride, bool act) {
     if constexpr (MODE == 2) {
-      gblk = a.gcache + size_t(blk) * Nx * a.lines;
+      table = a.gcache + size_t(blk) * Nx * a.lines + l;
       const double* key = a.gkey + size_t(blk) * 9;
       cached = true;
 #pragma unroll
       for (int k = 0; k < 9; ++k) cached = cached && key[k] == a.box[k];
+      if (!cached && act) {
+        gl.set(a.inf, a.box, a.N, y, kz);
+#pragma unroll 1
+        for (int x = x0; x < Nx; x += stride) table[x * a.lines] = gl.optimal(a.inf, a.N, x);
+      }
+    } else {
+      gl.set(a.inf, a.box, a.N, y, live ? kz : 0);
     }
-  };
-  // MODE 2: g of element x of the thread's line, from the table or made and kept
-  auto table = [&](int x) {
-    float* slot = gblk + x * a.lines + l;
-    const float gg = cached ? *slot : gl.optimal(a.inf, a.N, x);
-    if (!cached) *slot = gg;
-    return gg;
   };
   // v x g with its share of the energy and of the cell gradient
   auto scale = [&](int x, float gg, float2 v) {
@@ -354,6 +359,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
   if constexpr (TWO) {
     const int R0 = a.two.R0, R1 = a.two.R1, j = threadIdx.x >> shift;
     float2* rows = X + l * (two_stage_words(R0, R1) | 1);
+    if constexpr (MODE == 2) g_setup(j, R0, live && j < R0);
     with_wide_radix(R0, [&](auto rc) {
       constexpr int R = decltype(rc)::value;
       float2 v[R];
@@ -362,7 +368,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = line[size_t(j + r * R1) * w];
       load_twiddles(tw, a.tw, Nx);
-      g_setup();   // while the lines are in flight
+      if constexpr (MODE != 2) g_setup(0, 0, false);   // while the lines are in flight
       if (act) {
         Dft<R>::run(v, -1.0f);
 #pragma unroll
@@ -378,7 +384,7 @@ __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
       if (act) {
         if constexpr (MODE == 2) {
 #pragma unroll
-          for (int r = 0; r < R; ++r) gv[r] = table(j + r * R0);
+          for (int r = 0; r < R; ++r) gv[r] = table[(j + r * R0) * a.lines];
         } else {
           gl.values<R>(a.inf, a.N, j, R0, gv);
         }
@@ -407,12 +413,12 @@ __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 2 : 4))) k_pencil_x(XArgs a) {
     load_twiddles(tw, a.tw, Nx);
     if (live)
       for (int x = t0; x < Nx; x += step) X[l * ps + x] = line[size_t(x) * w];
-    g_setup();
+    g_setup(t0, step, live);
     __syncthreads();
     float2* Z = staged_fft(X, X + a.lines * ps, g.lines, ps, a.ax, tw, -1.0f);
     if (live)
       for (int x = t0; x < Nx; x += step) {
-        const float gg = MODE == 2 ? table(x) : gl.value(a.inf, a.N, x);
+        const float gg = MODE == 2 ? table[x * a.lines] : gl.value(a.inf, a.N, x);
         Z[l * ps + x] = scale(x, gg, Z[l * ps + x]);
       }
     __syncthreads();
