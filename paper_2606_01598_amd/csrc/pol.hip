@@ -316,6 +316,11 @@ __global__ void __launch_bounds__(256) k_pcg_dir(int m, const double* old, const
     p[k] = z[k] + be * p[k];
 }
 
+__global__ void __launch_bounds__(256) k_copy(int m, const float* from, float* to) {
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k < m) to[k] = from[k];
+}
+
 }  // namespace
 
 struct pol_plan_s {
@@ -405,6 +410,27 @@ int wait_residual(pol_plan_s* pl, hipStream_t s, int nb, unsigned long long step
   zz = 0.0;
   for (int b = 0; b < nb; ++b) zz += *static_cast<volatile double*>(&pl->host[b].zz);
   return PME_OK;
+}
+
+// Outputs of the model calls that lie in the place of inputs (an update of v_mu by H v, say):
+// both the long-range part and the pair kernel write outputs while inputs are still to be
+// read, so such calls work in the plan's vectors and copy.
+struct Range { const void* p; size_t floats; };
+
+bool overlap(const Range* out, int nout, const Range* in, int nin) {
+  for (int o = 0; o < nout; ++o)
+    for (int i = 0; i < nin; ++i) {
+      if (!out[o].p || !in[i].p) continue;
+      const uintptr_t a = reinterpret_cast<uintptr_t>(out[o].p), b = reinterpret_cast<uintptr_t>(in[i].p);
+      if (a < b + 4 * in[i].floats && b < a + 4 * out[o].floats) return true;
+    }
+  return false;
+}
+
+hipError_t copy_out(hipStream_t s, int m, const float* from, float* to) {
+  if (!to || m <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_copy, dim3(blocks_for(m, 256)), dim3(256), 0, s, m, from, to);
+  return hipGetLastError();
 }
 
 bool check_common(const pol_plan_s* pl, int n, const float* pos, const float* pol) {
@@ -502,14 +528,21 @@ int pol_model(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const fl
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the long-range gradients go straight into the outputs, to which the pair kernel adds
   // the real-space part and the polarization term
-  int rc = pme_forward(pme, stream, n, pos, q, mu, box, energy ? plan->scal : nullptr, dU_dpos,
-                       dU_dq, dU_dmu);
+  const size_t n1 = size_t(n), n3 = 3 * n1, stride = size_t(3) * plan->desc.max_atoms;
+  const Range outs[] = {{dU_dpos, n3}, {dU_dq, n1}, {dU_dmu, n3}};
+  const Range ins[] = {{pos, n3}, {q, n1}, {mu, n3}, {pol, n1}};
+  const bool apart = overlap(outs, 3, ins, 4);
+  float* o_pos = apart && dU_dpos ? plan->vec : dU_dpos;
+  float* o_q = apart && dU_dq ? plan->vec + stride : dU_dq;
+  float* o_mu = apart && dU_dmu ? plan->vec + 2 * stride : dU_dmu;
+  int rc = pme_forward(pme, stream, n, pos, q, mu, box, energy ? plan->scal : nullptr, o_pos, o_q,
+                       o_mu);
   if (rc != PME_OK) return rc;
   hipError_t e = build_cells(plan->cells, s, n, pos);
   if (e != hipSuccess) return pol_hip_fail(e);
   PairArgs a = pair_args(plan, n, pos, q, mu, pol);
-  a.o_pos = dU_dpos; a.o_q = dU_dq; a.o_mu = dU_dmu;
-  a.b_pos = dU_dpos; a.b_q = dU_dq; a.b_mu = dU_dmu;
+  a.o_pos = o_pos; a.o_q = o_q; a.o_mu = o_mu;
+  a.b_pos = o_pos; a.b_q = o_q; a.b_mu = o_mu;
   a.p_mu = mu;
   a.epart = energy ? plan->epart : nullptr;
   const int nb = n > 0 ? pair_blocks(n) : 0;
@@ -517,6 +550,10 @@ int pol_model(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, const fl
   if (energy)
     hipLaunchKernelGGL(k_energy_sum, dim3(1), dim3(256), 0, s, plan->epart, nb,
                        plan->desc.prefactor, plan->scal, energy);
+  if (apart && ((e = copy_out(s, 3 * n, o_pos, dU_dpos)) != hipSuccess ||
+                (e = copy_out(s, n, o_q, dU_dq)) != hipSuccess ||
+                (e = copy_out(s, 3 * n, o_mu, dU_dmu)) != hipSuccess))
+    return pol_hip_fail(e);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : pol_hip_fail(e);
 }
@@ -528,16 +565,25 @@ int pol_model_hvp(pol_plan_t plan, pme_plan_t pme, void* stream, int32_t n, cons
   if (!check_common(plan, n, pos, pol) || !pme || !box || !g_q || !g_mu) return PME_EINVAL;
   if (n == 0) return PME_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  int rc = pme_backward(pme, stream, n, pos, q, mu, box, v_pos, v_q, v_mu, nullptr, g_q, g_mu);
+  const size_t n1 = size_t(n), n3 = 3 * n1;
+  const Range outs[] = {{g_q, n1}, {g_mu, n3}};
+  const Range ins[] = {{pos, n3}, {q, n1}, {mu, n3}, {pol, n1}, {v_pos, n3}, {v_q, n1}, {v_mu, n3}};
+  const bool apart = overlap(outs, 2, ins, 7);
+  float* o_q = apart ? plan->vec : g_q;
+  float* o_mu = apart ? plan->vec + size_t(3) * plan->desc.max_atoms : g_mu;
+  int rc = pme_backward(pme, stream, n, pos, q, mu, box, v_pos, v_q, v_mu, nullptr, o_q, o_mu);
   if (rc != PME_OK) return rc;
   hipError_t e = build_cells(plan->cells, s, n, pos);
   if (e != hipSuccess) return pol_hip_fail(e);
   PairArgs a = pair_args(plan, n, pos, q, mu, pol);
   a.vpos = v_pos; a.vq = v_q; a.vmu = v_mu;
-  a.o_q = g_q; a.o_mu = g_mu;
-  a.b_q = g_q; a.b_mu = g_mu;
+  a.o_q = o_q; a.o_mu = o_mu;
+  a.b_q = o_q; a.b_mu = o_mu;
   a.p_mu = v_mu;   // the polarization term adds (pf / a) v_mu
   hipLaunchKernelGGL(k_pair<kHvp>, dim3(pair_blocks(n)), dim3(kPairThreads), 0, s, a);
+  if (apart && ((e = copy_out(s, n, o_q, g_q)) != hipSuccess ||
+                (e = copy_out(s, 3 * n, o_mu, g_mu)) != hipSuccess))
+    return pol_hip_fail(e);
   e = hipGetLastError();
   return e == hipSuccess ? PME_OK : pol_hip_fail(e);
 }
