@@ -528,7 +528,9 @@ hipError_t launch_pencil(const DevPlan& d, hipStream_t s, const double* box, flo
 
 // Lines per workgroup: 16 where a butterfly is a thread and three such workgroups fit a
 // CU's LDS, else 8 (a kz block; a step at 320^3 takes 1654 us with 16, whose far side is
-// whole 128-byte lines, and 1666 with 8); z lines so that a round fills 256 threads.
+// whole 128-byte lines, and 1666 with 8); z lines so that a round fills 256 threads, or 8
+// pairs in the general passes, and three workgroups fit as well (125 x 125 x 625, general: a
+// forward 379 us with 8 pairs, one workgroup a CU, and 333 with 4).
 void pencil_lines(DevPlan& d) {
   for (int a = 0; a < 2; ++a) {
     const TwoStage t = two_stage(d.N[a]);
@@ -536,12 +538,8 @@ void pencil_lines(DevPlan& d) {
         t.R0 && line_lds(d.N[a], t, kLineMax) <= size_t(kLineLdsTwo) ? kLineMax : 8;
   }
   const TwoStage t = two_stage(d.N[2]);
-  if (t.R0) {
-    d.zpairs = 256 / t.R0;
-    while (d.zpairs > 1 && line_lds(d.N[2], t, d.zpairs) > size_t(kLineLdsTwo)) --d.zpairs;
-  } else {
-    d.zpairs = 8;
-  }
+  d.zpairs = t.R0 ? 256 / t.R0 : 8;
+  while (d.zpairs > 1 && line_lds(d.N[2], t, d.zpairs) > size_t(kLineLdsTwo)) --d.zpairs;
 }
 
 hipError_t enable_pencil_lds() {
