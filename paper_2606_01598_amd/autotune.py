@@ -6,7 +6,7 @@ launch timer (the binning, spread, FFT and gather kernels of one forward +
 Hessian-vector product step) and keeps the fastest.  The search is by
 coordinates: first the spread/gather tile target (with the default FFT lines),
 then the FFT lines per workgroup of the x pass (pme_desc_t.fft_lines) for the
-best tile.  Results are cached in a JSON file so that later runs configure
+best tile, on the slab meshes where they have an effect.  Results are cached in a JSON file so that later runs configure
 plans without timing.
 """
 from __future__ import annotations
@@ -24,7 +24,8 @@ CANDIDATES = ((8, 8, 16), (8, 16, 16), (12, 12, 16), (16, 16, 16), (8, 8, 8), (1
 LINES = (4, 8, 16, 24, 32)
 TIMED = ("bin", "bin_tangent", "spread", "spread_tangent", "fft_r2c", "fft_x", "fft_c2r",
          "gather", "gather_hvp")
-VERSION = 2          # cache entries of other versions are timed again
+VERSION = 3          # cache entries of other versions (other kernels) are timed again
+SLAB_LDS_MAX = 160 * 1024 - 2048     # kSlabLdsMax of the library
 
 
 class Config(NamedTuple):
@@ -39,6 +40,14 @@ def default_cache() -> str:
 def _key(arch, mesh, order, n) -> str:
     bucket = 1 << max(0, int(round(math.log2(max(1, n)))))
     return f"v{VERSION}|{arch}|{mesh[0]}x{mesh[1]}x{mesh[2]}|p{order}|n{bucket}"
+
+
+def is_slab(mesh) -> bool:
+    """Whether the library transforms this mesh by y-z planes in LDS (its slab test)."""
+    ny, nz = mesh[1], mesh[2]
+    h = nz // 2 + 1
+    buf = max((ny + 1) // 2 * nz, h * (ny + 1))
+    return 8 * (2 * buf + ny + nz) <= SLAB_LDS_MAX
 
 
 def _time_candidate(cfg, mesh, order, alpha, pos, q, mu, box, v, steps):
@@ -82,7 +91,7 @@ def tune(boxes, order: int, alpha: float, cache_path: str | None = None, steps: 
                 t = _time_candidate(cfg, *args)
                 if best is None or t < best[0]:
                     best = (t, cfg)
-            for k in lines:
+            for k in (lines if is_slab(b["mesh"]) else ()):
                 cfg = Config(best[1].tile, int(k))
                 t = _time_candidate(cfg, *args)
                 if t < best[0]:
