@@ -1083,6 +1083,8 @@ def counter_summary(args) -> int:
         "# bank_conflict = SQ_LDS_BANK_CONFLICT / (SQ_LDS_IDX_ACTIVE - SQ_LDS_BANK_CONFLICT)",
         "#   (stall cycles per LDS access cycle);",
         "# occupancy = 400 SQ_WAVE_CYCLES / (GRBM_GUI_ACTIVE / 8 XCDs) / 256 CUs / 32 waves (%);",
+        "# valu = 400 SQ_ACTIVE_INST_VALU / (GRBM_GUI_ACTIVE / 8 XCDs) / 1024 SIMDs, lds = 100",
+        "#   SQ_LDS_IDX_ACTIVE / (GRBM_GUI_ACTIVE / 8 XCDs) / 256 CUs: share of the time busy (%);",
         "# hbm = FETCH_SIZE, WRITE_SIZE scaled by a 256 MiB device copy in the same run "
         f"(x {f_scale:.3f}, x {w_scale:.3f});",
         "# vgpr, lds_alloc: per workitem registers and LDS bytes per workgroup of the dispatch.",
@@ -1090,15 +1092,17 @@ def counter_summary(args) -> int:
         "",
         f"{'kernel':28s} {'grid':>8s} {'wg':>5s} {'vgpr':>5s} {'lds_alloc':>9s} {'waves':>7s} "
         f"{'valu/w':>7s} {'salu/w':>7s} {'lds/w':>6s} {'ldsat/w':>7s} {'vmem/w':>7s} "
-        f"{'lds_MB':>7s} {'bank_cf':>7s} {'occ%':>5s} {'hbm_MB':>7s}",
+        f"{'lds_MB':>7s} {'bank_cf':>7s} {'occ%':>5s} {'hbm_MB':>7s} {'valu%':>5s} {'lds%':>5s}",
     ]
     lds_lines = []
     order = [KERNEL_SYMBOL[k] for k in ("bin", "bin_tangent", "spread", "spread_tangent")]
     order += [FUSED_SYMBOL[k] for k in ("spread", "spread_tangent")]
     order += [BAND_SYMBOL[k] for k in ("spread", "spread_tangent")]
     order += [FUSED_STEP_SPREAD, BAND_STEP_SPREAD]
-    order += [KERNEL_SYMBOL[k] for k in ("fft_r2c", "fft_x", "fft_c2r", "gather", "gather_hvp")]
-    order += ["k_gather_hvp<6, true>"]
+    order += [KERNEL_SYMBOL[k] for k in ("fft_r2c", "fft_x", "fft_c2r")]
+    order += ["k_spread_slab_pair<6>", "k_fftx_pair<0>", "k_slab_inv_pair"]
+    order += dict.fromkeys("+".join(PENCIL_SYMBOL.values()).split("+"))
+    order += [KERNEL_SYMBOL["gather"], KERNEL_SYMBOL["gather_hvp"], "k_gather_hvp<6, true>"]
     for k in order:
         if k not in merged:
             continue
@@ -1114,12 +1118,14 @@ def counter_summary(args) -> int:
         bank = cf / (act - cf) if act > cf else float("nan")
         gui = c.get("GRBM_GUI_ACTIVE", 0.0) / 8.0
         occ = 400.0 * c.get("SQ_WAVE_CYCLES", 0.0) / gui / 256 / 32 if gui else float("nan")
+        busy = (lambda x, units: 100.0 * c.get(x, 0.0) / gui / units if gui else float("nan"))
         hbm = c.get("FETCH_SIZE", 0.0) * 1024 * f_scale + c.get("WRITE_SIZE", 0.0) * 1024 * w_scale
         lines.append(f"{k[:28]:28s} {grid:8d} {wg:5d} {vgpr:5d} {lds_alloc:9d} {int(waves):7d} "
                      f"{pw('SQ_INSTS_VALU'):7.0f} {pw('SQ_INSTS_SALU'):7.0f} "
                      f"{pw('SQ_INSTS_LDS'):6.0f} {pw('SQ_INSTS_LDS_ATOMIC'):7.1f} "
                      f"{pw('SQ_INSTS_VMEM_RD') + pw('SQ_INSTS_VMEM_WR'):7.1f} {lds_b / 1e6:7.2f} "
-                     f"{bank:7.3f} {occ:5.1f} {hbm / 1e6:7.2f}")
+                     f"{bank:7.3f} {occ:5.1f} {hbm / 1e6:7.2f} "
+                     f"{busy('SQ_ACTIVE_INST_VALU', 256):5.1f} {busy('SQ_LDS_IDX_ACTIVE', 256):5.1f}")
         lds_lines.append(f"lds_bytes_per_launch {k} {lds_b:.0f}")
     lines += ["", "# LDS bytes per launch (read by bench.py for the roofline's LDS figure):"]
     lines += lds_lines

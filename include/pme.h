@@ -262,8 +262,8 @@ int pme_step(pme_plan_t plan, void* stream, int32_t n,
 
 /* Capture `steps` consecutive pme_step calls with these arguments into a HIP
  * graph held by the plan (replacing any earlier one), without running them;
- * pme_step_replay launches it.  Replaying costs one launch instead of about ten
- * per step (the per-step launch overhead and the gaps between dependent kernels
+ * pme_step_replay launches it.  Replaying costs one launch instead of five or
+ * more per step (the per-step launch overhead and the gaps between dependent kernels
  * shrink), and gives the same results bit for bit as the eager calls.
  * The pointers are baked into the graph: the caller keeps those buffers alive
  * and updates their contents in place between replays.  Each binning alternates

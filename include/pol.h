@@ -24,6 +24,8 @@
  * - Per-atom arrays are device FP32; pos is [n][3], pol (the polarizabilities
  *   a_i, in Angstrom^3) is [n].
  * - Outputs are overwritten; a NULL output is skipped; a NULL q or mu means zero.
+ * - Outputs of pol_model and pol_model_hvp may lie in the place of inputs; those of the
+ *   other calls must not.
  * - Calls are asynchronous on `stream`, except pol_scf, which waits for the residual
  *   of every iteration to test convergence and synchronises `stream` before it returns
  *   (unless POL_F_FIXED_ITERS).

@@ -422,7 +422,7 @@ int pme_plan(const pme_desc_t* desc, pme_plan_t* out) {
     ok(dev_alloc(&d.deconv[a], size_t(d.N[a]), by));
     if (d.opt) ok(dev_alloc(&d.alias[a], size_t(3 * d.N[a]), by));
   }
-  // the x pass's g tables: where its workgroups fit in one round (at most four per
+  // the x pass's g tables, on slab meshes: where its workgroups fit in one round (at most four per
   // CU) the pass is latency-bound and loading a table beats making it; on larger
   // meshes the strided line traffic bounds it and the table's extra bytes cost more
   // than the arithmetic they save, except for the optimal influence function
@@ -768,8 +768,8 @@ int pme_step(pme_plan_t plan, void* stream, int32_t n, const float* pos, const f
     }
     // Otherwise the binning and the cotangent chain on the second stream; the forward
     // plane or band spread reads the records once they are written.  (Pencil passes fill
-    // the chip and overlap better with the other chain's spread: a step at 160^3 takes 228
-    // us either way, at 320^3 1513 so and 1533 in shared launches.)
+    // the chip and overlap better with the other chain's spread: in shared launches a step
+    // takes as long at 160^3 and 1.3 % longer at 320^3.)
     if ((e = hipEventRecord(plan->fork, s)) != hipSuccess) return hip_fail(e);
     if ((e = hipStreamWaitEvent(s2, plan->fork, 0)) != hipSuccess) return hip_fail(e);
     if ((e = pme::launch_bin(dt, s2, tset, n, pos, q, mu, box, v_pos, v_q, v_mu, true,

@@ -182,14 +182,14 @@ __device__ __forceinline__ FastDiv make_fastdiv(int d) {
 //  2. Those records are loaded into the queue together with the field region(s) over the
 //     tile plus the stencil halo, and processed with p lanes per atom; further windows of
 //     atoms follow.  (Loading every slot of the bins at once saves the wait for the
-//     counts but reads several times the records: 1M ions on 320^3, Hessian-vector
-//     product, 385 us so and 353 this way.)
-// Bound by vector issue, with the LDS reads of the stencils half as long beside it: what
-// a pass saves in instructions it gains, unless it pays for them in LDS.  (Sums round the
-// group without masks, outputs by different lanes and the cell by one wavefront: 1M ions,
-// forward 280 -> 235 us, Hessian-vector product 356 -> 344; 32,000 on 100^3 13.4 -> 12.4
-// and 18.1 -> 16.4.  The y and z weights of an atom made once and taken from its lanes:
-// 298 and 391.)
+//     counts but reads several times the records, more of them empty in bins one cell
+//     wide: 1M ions on 320^3, Hessian-vector product, 9 % longer.)
+// Bound by vector issue, with the LDS reads of the stencils half as long beside it (1M ions,
+// forward and Hessian-vector product: vector units busy 73 and 67 %, LDS 42 and 41 %).  Alone
+// at 1M 227 and 344 us (240 and 337 with cubic bins, masked sums and every slot loaded; the
+// step's product, which also forms the forward outputs, 411 and 398), 32,000 on 100^3 12.1
+// and 14.0 (12.4 and 15.1).  The y and z weights of an atom made once and taken from its
+// lanes cost more LDS than they save instructions: a quarter and an eighth longer.
 //  3. Overflow records whose anchor lies in the tile, compacted into the queue.
 // Queue entries: the anchor header and, forward: q, mu, atom; Hessian-vector
 // product: q, mu, v_q, v_r, v_mu, atom (the tangent record carries them).

@@ -63,10 +63,15 @@ struct AxisPlan {          // 1D mixed-radix FFT of length N
   FFTStage st[kMaxStages];
 };
 
-constexpr int kFFTThreads = 256;    // pencil-pass workgroup
+constexpr int kFFTThreads = 256;    // x-pass workgroup of the slab layout
 constexpr int kSlabThreads = 1024;  // slab-pass workgroup (one x-plane)
 constexpr int kBatchThreads = 256;  // the same in a batch of boxes with small planes
-constexpr int kBatchPlane = 4096;   // their most points
+constexpr int kBatchPlane = 4096;   // their most points: about where a plane, its padding and a
+                                    // transform buffer fill 64 KiB (p = 6: 56 KB at 64 x 64,
+                                    // 69 at 72 x 72), so that two and more share a CU.  32 boxes,
+                                    // forward and product, these workgroups against 1024 threads
+                                    // and the tile spread: 16^3 76 and 104 us, 32^3 128 and 206,
+                                    // 48^3 254 and 404, 64^3 553 and 759; one box 106 and 108.
 constexpr int kSmallThreads = 128;  // x-pass workgroup there, lines of at most kSmallN
 constexpr int kSmallN = 128;
 constexpr int kBatchMap = 1024;     // records listed at a time there

@@ -16,10 +16,11 @@
 // from memory, one LDS exchange, stage 1 to memory (fft_radix.h, two_stage).  Other
 // lengths go through LDS in the stages of radix_plan.
 //
-// Bound by memory traffic in the y passes (the 262 MB of one at 320^3 in 47 us, 5.5 TB/s)
-// and by vector issue in the others (x 105 us: g in double precision and four register
-// DFTs a value; z 70 and 84 us).  Through LDS stage by stage, from one [x][y][kz] array,
-// the same passes took 130, 139, 76 and 100 us.
+// Bound by memory traffic in the y passes (the 262 MB of one at 320^3 in 54 us on average,
+// 41 at best: 4.8 and 6.4 TB/s); the others issue vector instructions for about half of
+// their time and wait on memory for the rest (busy: x 55 %, which makes g in double
+// precision between four register DFTs; z 55 and 41).  Alone at 320^3 x 105 us, z 70 and 87;
+// through LDS stage by stage, from one [x][y][kz] array, y 130, x 151, z 76 and 99.
 #include "../../include/pme.h"
 #include "fft_radix.h"
 #include "influence.h"
@@ -298,8 +299,8 @@ struct XArgs {
 // x pass in place: forward transform, x g(k) with the energy partial, inverse.  The
 // inverse takes the radices in reverse, so the last forward and the first inverse stage
 // of a butterfly meet in registers with g between them.  g is made in registers before
-// the butterfly's column is read; 128 registers (a few spills of the widest radices) run
-// a step at 320^3 in 1654 us, 160 in 1713, 96 in 1675.
+// the butterfly's column is read; with 160 registers in the place of 128 (a few spills of
+// the widest radices) a step at 320^3 takes 3.6 % longer, with 96 1.3 %.
 // MODE 0: the influence function of Eq. influence; 1: also the cell-gradient partials;
 // 2: the optimal influence function (its alias sums kept in the plan's table by box).
 template <bool TWO, int MODE>
@@ -527,8 +528,8 @@ hipError_t launch_pencil(const DevPlan& d, hipStream_t s, const double* box, flo
 }
 
 // Lines per workgroup: 16 where a butterfly is a thread and three such workgroups fit a
-// CU's LDS, else 8 (a kz block; a step at 320^3 takes 1654 us with 16, whose far side is
-// whole 128-byte lines, and 1666 with 8); z lines so that a round fills 256 threads, or 8
+// CU's LDS, else 8 (a kz block; with 16 the far side is whole 128-byte lines, a step at
+// 320^3 takes 0.7 % longer with 8); z lines so that a round fills 256 threads, or 8
 // pairs in the general passes, and three workgroups fit as well (125 x 125 x 625, general: a
 // forward 379 us with 8 pairs, one workgroup a CU, and 333 with 4).
 void pencil_lines(DevPlan& d) {

@@ -12,13 +12,15 @@
 namespace pme {
 
 // body(record index) for every record of the scanned bins (bin_of(e) is the e-th of nscan:
-// its number and its counter's) and of the overflow list, by a whole workgroup of up to 1024 threads.  The slots
-// are numbered by a scan of the bins' counts and their records listed in LDS (s_rec, map_cap
-// of them at a time); a lane takes slots far from its neighbours', so that lanes do not
-// add to the same mesh points at once.  Bins are one mesh cell wide in x, so that apart
-// from the overflow list (and bands' edge rows) every listed record is wanted: testing
-// the anchors of wider bins, compacting the hits and scanning an item map took more
-// instructions than adding the atoms.  s_wsum: one int per wavefront.
+// its number and its counter's) and of the overflow list, by a whole workgroup of up to 1024
+// threads.  The slots are numbered by a scan of the bins' counts and their records listed in
+// LDS (s_rec, map_cap of them at a time); a lane takes slots far from its neighbours', so
+// that lanes do not add to the same mesh points at once.  Bins are one mesh cell wide in x
+// (but for tiles that would hold too many of them, see plan_bins), so that apart from the
+// overflow list and bands' edge rows every listed record is wanted: testing the anchors of
+// wider bins, compacting the hits and scanning an item map took more instructions than
+// adding the atoms.  At 1M ions on 320^3 a band spread keeps the vector units busy for 72 %
+// of its time (82 % for the tangent density) and LDS for half of it.  s_wsum: one int per wavefront.
 template <class BinOf, class Body>
 __device__ __forceinline__ void for_each_slot(int nscan, BinOf bin_of, const int* count, int cap,
                                               const int* ovf_count, long long ovf_base,
@@ -75,8 +77,8 @@ __device__ __forceinline__ void for_each_slot(int nscan, BinOf bin_of, const int
 }
 
 // One atom's footprint in x-plane X (nothing when its stencil misses the plane): record
-// ri's weights and coefficients with the tile spread's arithmetic, and its P x P words added at row rows(b_y, iy) (skipped from
-// row_limit on) and padded column b_z + iz of `plane` (rows of PZ words).  DEG 1 takes the
+// ri's weights and coefficients with the tile spread's arithmetic, and its P x P words
+// added at row rows(b_y, iy) (skipped from row_limit on) and padded column b_z + iz of `plane` (rows of PZ words).  DEG 1 takes the
 // forward coefficients from a forward record, or with TREC forms q and J mu from a
 // tangent record; DEG 2 forms the ten tangent coefficients.  s_J holds J (DEG 2 or
 // TREC), s_cw the whole-number spline pieces, scale the fixed-point unit; reaches(b_y):

@@ -1,7 +1,7 @@
 // Thole-damped polarizable point-charge model: cell list, real-space pair
 // kernels and the preconditioned-conjugate-gradient induced-dipole solve whose
-// matrix-vector product is the PME Hessian (pme_backward) plus the real-space
-// dipole tensor.  The model and its conventions are documented in pol.h.
+// matrix-vector product is the PME field of the dipoles (pme::dipole_response) plus the
+// real-space dipole tensor.  The model and its conventions are documented in pol.h.
 //
 // Pair kernels give a wavefront to an atom: the lanes test the atoms of the
 // neighbouring cells, compact the pairs within the cutoff into LDS, evaluate them 64 at
