@@ -156,6 +156,25 @@ int check_desc(const pme_desc_t& desc) {
   return PME_OK;
 }
 
+// Columns of the half spectrum that an x-pass workgroup takes in the [x][y][kz] layout.
+int x_columns(const pme_desc_t& desc, const DevPlan& d) {
+  const int nmax = d.N[0] > d.N[1] ? d.N[0] : d.N[1];
+  int kt = desc.fft_lines > 0 ? desc.fft_lines : (nmax <= 64 ? 16 : (nmax <= 160 ? 24 : 4));
+  // LDS of a line workgroup within 56 KB: twiddles, two line buffers, the kt N_x table
+  // of g and the deconvolution factors:
+  // 8 N + kt (16 (N + 1) + 4 N) + 4 (N + kt) bytes
+  // (optimal influence: 12 (N + kt) more bytes of aliasing weights)
+  const int extra = d.opt ? 3 * (nmax + 1) / 2 : 0;
+  const int lds_cap = (7000 - nmax - (nmax + 1) / 2 - extra) /
+                      (2 * (nmax + 1) + (nmax + 1) / 2 + 2 + (d.opt ? 2 : 0));
+  if (kt > lds_cap) kt = lds_cap;
+  if (kt < 1) kt = 1;
+  if (kt > d.H) kt = d.H;
+  // equal chunks of the H columns (no mostly-empty last chunk)
+  const int nchunk = (d.H + kt - 1) / kt;
+  return (d.H + nchunk - 1) / nchunk;
+}
+
 // Geometry of a plan (host only, nothing allocated): mesh and order, atom bins (d.ncount of
 // them) and their capacity, spread and gather tiles, spread staging, FFT layout.  PME_EMESH
 // when no tile or FFT layout fits.  cubes: cubic atom bins whatever the spread (for the tile
@@ -258,25 +277,8 @@ int plan_geometry(const pme_desc_t& desc, DevPlan& d, bool cubes = false) {
         d.band_lds = size_t(8 * rows * PZ + 4L * pme::kFusedMap);
       }
     }
-    if (!d.slab) {
-      pme::pencil_lines(d);
-    } else {
-      const int nmax = d.N[0] > d.N[1] ? d.N[0] : d.N[1];
-      int kt = desc.fft_lines > 0 ? desc.fft_lines : (nmax <= 64 ? 16 : (nmax <= 160 ? 24 : 4));
-      // LDS of a line workgroup within 56 KB: twiddles, two line buffers, the kt N_x table
-      // of g and the deconvolution factors:
-      // 8 N + kt (16 (N + 1) + 4 N) + 4 (N + kt) bytes
-      // (optimal influence: 12 (N + kt) more bytes of aliasing weights)
-      const int extra = d.opt ? 3 * (nmax + 1) / 2 : 0;
-      const int lds_cap = (7000 - nmax - (nmax + 1) / 2 - extra) /
-                          (2 * (nmax + 1) + (nmax + 1) / 2 + 2 + (d.opt ? 2 : 0));
-      if (kt > lds_cap) kt = lds_cap;
-      if (kt < 1) kt = 1;
-      if (kt > d.H) kt = d.H;
-      // equal chunks of the H columns (no mostly-empty last chunk)
-      const int nchunk = (d.H + kt - 1) / kt;
-      d.ktile = (d.H + nchunk - 1) / nchunk;
-    }
+    if (d.slab) d.ktile = x_columns(desc, d);
+    else pme::pencil_lines(d);
   }
   return PME_OK;
 }
@@ -1249,9 +1251,16 @@ int pme_forward_noalloc(const pme_desc_t* desc, void* stream, int32_t n, const f
     o_dc[a] = take(sizeof(float) * size_t(d.N[a]));
   }
   const size_t o_rho = take(sizeof(float) * size_t(M));
-  (void)take(sizeof(float) * size_t(M));
+  const size_t o_room = take(sizeof(float) * size_t(M));
   const size_t o_spec = take(sizeof(float2) * size_t(d.N[0]) * d.N[1] * d.H);
-  const size_t o_epart = take(sizeof(double) * size_t(pme::fftx_blocks(d)));
+  // energy partials: a workgroup's each in the [x][y][kz] layout.  Pencil passes have other
+  // workgroups; so that no call near the limit is decided by their number, theirs lie at the
+  // end of the room after the density, past the spectrum that is kept there
+  const int columns = x_columns(dd, d);
+  size_t o_epart = take(sizeof(double) * size_t(d.N[1]) * ((d.H + columns - 1) / columns));
+  if (!d.slab)
+    o_epart = ((o_room + sizeof(float) * size_t(M)) & ~size_t(7)) -
+              sizeof(double) * size_t(pme::fftx_blocks(d));
   const size_t o_spart = take(sizeof(double) * 4 * size_t(pme::bin_blocks(dd.max_atoms)));
   if (off > kScratchBytes) return PME_ESCRATCH;
 
